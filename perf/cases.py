@@ -71,7 +71,7 @@ def draw(rng):
                 "pick": rng.randrange(1 << 20), "precision": rng.choice(["fp32", "fp64"]), "sweeps": rng.randint(10, 50)}
     if kind == "flex":
         count = rng.choice([1, 1, _log_uniform(rng, 2, 64)])
-        return {"kind": kind, "body": rng.choice(sorted(BODIES)), "molecules": _log_uniform(rng, 60, 1300), "T": T,
+        return {"kind": kind, "body": rng.choice(sorted(BODIES)), "molecules": _log_uniform(rng, 120, 1300), "T": T,
                 "count": count, "sweeps": rng.randint(1, 12)}
     return {"kind": kind, "molecules": _log_uniform(rng, 60, 8000), "T": T, "precision": rng.choice(["fp32", "fp64"])}
 
