@@ -466,7 +466,7 @@ size_t fx_al(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct FxLayout {
     size_t dev, stats, pos, type, img, esamp, dsamp, gall, ginter, c2, c2s, fs, fscm, mom, u0, kref, r0, rcm0;
-    size_t cstart, clist, cid, ecell, part, total;
+    size_t cstart, clist, cid, ecell, part, nbr, total;
 };
 
 FxLayout fx_layout(const mcf_params* p, const FxGeom& g)
@@ -497,6 +497,8 @@ FxLayout fx_layout(const mcf_params* p, const FxGeom& g)
     l.cid = o;    o = fx_al(o + N * sizeof(uint32_t));
     l.ecell = o;  o = fx_al(o + size_t(g.ncell) * sizeof(double));
     l.part = o;   o = fx_al(o + kFxParts * sizeof(double));
+    l.nbr = o;    // neighbour lists, for systems whose atoms 16 bits can index
+    if (N <= kFxListed) o = fx_al(o + N * kFxNbr * sizeof(uint16_t));
     l.total = o;
     return l;
 }
@@ -837,6 +839,7 @@ int fx_init(mcf_system* s, const mcf_params* p, const FxGeom& g, const FxLayout&
     D.cell_id = (uint32_t*)(work + (lay.cid - work_off));
     D.ecell = (double*)(work + (lay.ecell - work_off));
     D.part = (double*)(work + (lay.part - work_off));
+    D.nbr = lay.total > lay.nbr ? (uint16_t*)(work + (lay.nbr - work_off)) : nullptr;
     s->dev = (FxDev*)(b + lay.dev);
     int rc;
     if (no_alloc) {
@@ -915,7 +918,9 @@ int mcf_init_system_noalloc(const mcf_params* p, const double* pos, const uint8_
 {
     FxGeom g;
     if (int rc = fx_check_request(p, pos, types, &g)) return rc;
-    const FxLayout lay = fx_layout(p, g);
+    FxLayout lay = fx_layout(p, g);
+    // a system whose neighbour lists do not fit the scratch runs without them
+    if (lay.total - lay.cstart > kFxScratchBytes) lay.total = lay.nbr;
     const size_t need = lay.cstart, work = lay.total - lay.cstart;
     if (state_bytes_needed) *state_bytes_needed = need;
     if (work > kFxScratchBytes)

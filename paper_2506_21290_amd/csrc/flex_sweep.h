@@ -14,17 +14,15 @@
 // Execution: one workgroup of 8 wave64s per system (several systems per
 // launch, a workgroup each), the positions, types and cell lists in LDS when
 // they fit.  Per sweep a random shift of a cubic cell grid over the atoms, a
-// counting sort into cells (ascending atom index inside each cell), then the
-// k^3 colours in order; the waves take the cells of a colour, and a wave runs
-// its cell's attempts one after another.  Same-colour cells are at least
-// (k - 1) w >= 2 D + r_c apart (D the largest distance two atoms of one
-// molecule can reach, r_c the largest cut-off), so no two attempts of a
-// colour touch the same pair term.  Per cell the wave lists the atoms of the
-// 27 cells around it and draws the proposals of the cell's atoms, a lane
-// each; per attempt the lanes take the intramolecular pairs and the listed
-// atoms, and a DPP reduction in FP64 gives dE in a fixed order.  A bond
-// stretched to 1.5 sigma_ij or beyond makes dE infinite: the move is
-// rejected.
+// counting sort into cells (ascending atom index inside each cell), the
+// neighbours of every atom, then the k^3 colours in order; the waves take the
+// cells of a colour, and a wave runs its cell's attempts in order, up to four
+// of them evaluated side by side, a row of 16 lanes per changed atom.
+// Same-colour cells are at least (k - 1) w >= 2 D + r_c apart (D the largest
+// distance two atoms of one molecule can reach, r_c the largest cut-off), so
+// no two attempts of a colour touch the same pair term.  A DPP reduction in
+// FP64 over each row gives dE in a fixed order.  A bond stretched to 1.5
+// sigma_ij or beyond makes dE infinite: the move is rejected.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -41,10 +39,13 @@ namespace {
 constexpr int kFxThreads = 512;
 constexpr int kFxWaves = kFxThreads / 64;
 constexpr int kFxSeg = 64;          // stencil row segments per attempt (radius <= 2: <= 50)
-constexpr int kFxCand = 384;        // atoms of a cell's 27-cell stencil listed per wave
-// static LDS of the sweep kernel: segments and candidate lists per wave, scan
+constexpr uint32_t kFxNbr = 48;     // neighbours listed per atom (three lanes' worth of a 16-lane row)
+constexpr uint32_t kFxListed = 65534;  // atoms a 16-bit list can index (0xFFFE, 0xFFFF are marks)
+constexpr uint32_t kFxNone = 0xFFFFu;  // no neighbour
+constexpr uint32_t kFxOver = 0xFFFEu;  // first entry of a list that did not fit
+// static LDS of the sweep kernel: segments per wave, pair tables, scan
 // scratch and the energy accumulator (with room to spare)
-constexpr size_t kFxStaticLds = (size_t)kFxWaves * (2 * kFxSeg + kFxCand) * 4 + 256;
+constexpr size_t kFxStaticLds = (size_t)kFxWaves * 2 * kFxSeg * 4 + 2 * 16 * 8 + 512;
 constexpr uint32_t kFxParts = 1024;  // workgroups of the event kernel
 constexpr uint32_t kFxMany = 256;    // systems of one sweep launch (a workgroup each)
 
@@ -89,6 +90,7 @@ struct FxDev {
     uint32_t* cell_id;    // [N]
     double* ecell;        // [ncell] accepted dE of each cell in the current sweep
     double* part;         // [kFxParts] partial energies of the event kernel
+    uint16_t* nbr;        // [N][kFxNbr] neighbours of each atom in the current sweep, or null
     MoveRecord* log;
     uint64_t log_sweep0, log_sweeps;
 };
@@ -108,8 +110,11 @@ struct FxK {
     double L, invL, w, T, p_flip, dmax, rc2f, sep, dyn_base;
     double sigma[4];
     int32_t* img;
+    uint16_t* nbr;
     MoveRecord* log;
     uint64_t log_sweep0;
+    uint32_t chg[4];    // bit s of word q: flip q changes the type of atom s
+    float list_r2;      // neighbour lists: squared radius, (r_c + 2 sqrt(3) d)^2 with a margin
 };
 
 __device__ __forceinline__ FxK fx_const(const FxDev& D)
@@ -124,8 +129,18 @@ __device__ __forceinline__ FxK fx_const(const FxDev& D)
     K.sep = D.sep; K.dyn_base = D.dyn_base; K.together = D.together;
     for (int t = 0; t < 4; ++t) K.sigma[t] = D.sigma[t];
     K.img = D.img;
+    K.nbr = D.nbr;
     K.log = D.log;
     K.log_sweep0 = D.log_sweep0;
+    for (int q = 0; q < 4; ++q) {
+        uint32_t c = 0;
+        for (uint32_t t = 0; t < 4; ++t) c |= (t < D.n && D.flips[q][t] != t ? 1u : 0u) << t;
+        K.chg[q] = c;
+    }
+    // the FP32 distances of the list build are within 1e-5 of the FP64 ones
+    const double smax = fmax(fmax(D.sigma[0], D.sigma[1]), fmax(D.sigma[2], D.n > 3u ? D.sigma[3] : 0.0));
+    const float r = (float)(sqrt(D.rc2f) * smax + 2.0 * 1.7320508075688772 * D.dmax) + 1e-3f;
+    K.list_r2 = r * r;
     return K;
 }
 
@@ -144,16 +159,6 @@ __device__ __forceinline__ uint32_t fx_cell(double x, double y, double z, const 
     const uint32_t nc = D.nc;
     return (uint32_t)fx_axis(x, h[0], D) +
            nc * ((uint32_t)fx_axis(y, h[1], D) + nc * (uint32_t)fx_axis(z, h[2], D));
-}
-
-// Whether every atom within distance m of coordinate x (one axis, grid shift
-// h) was sorted into the three cells c - 1, c, c + 1 of that axis: x lies at
-// least m inside the outer faces of the three
-__device__ __forceinline__ bool fx_in_stencil(double x, double h, uint32_t c, const FxK& D, double m)
-{
-    if (D.nc <= 3u) return true;  // the three cells are the whole axis
-    const double t = fx_mi(fx_wrap(x - h, D.L) - (double)c * D.w, D.L, D.invL);
-    return t >= m - D.w && t <= 2.0 * D.w - m;
 }
 
 // Eq. (1) as (2 (s/r)^6 - 1)^2 below the cut-off, FP64.  1 / r^2 is the
@@ -180,15 +185,17 @@ __device__ __forceinline__ double fx_fene(double sig, double r2)
 
 struct FxCount {
     uint32_t att_t, att_f, acc_t, acc_f, exits;
-    uint64_t terms;
+    uint32_t terms;  // interacting pairs, this lane's share
     double e;  // accepted dE of the current cell, in attempt order
 };
 
-// Per-wave LDS: the stencil's row segments.
+// Per-wave LDS: the stencil's row segments.  Per workgroup: the pair
+// diameters sigma_ij and their squares by 4 t_i + t_j.
 struct FxWaveLds {
     uint32_t* seglo;
     uint32_t* segoff;
-    uint32_t* cand;  // [kFxCand] atoms of the current cell's stencil
+    const double* sij;
+    const double* s2ij;
 };
 
 // Where the sweep kernel reads and writes the state and the cell lists: the
@@ -318,242 +325,387 @@ __device__ __forceinline__ FxProp fx_propose(const FxK& D, const FxView& V, uint
     return pr;
 }
 
-__device__ __forceinline__ double rl_dbl(double v, int l)
+// Sum over each row of 16 lanes (the row's last lane gets it) in the order of
+// wave_sum_dpp's first steps.
+__device__ __forceinline__ double fx_row_sum(double v)
 {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+    v += dpp_move<0x111, 0xf>(v);
+    v += dpp_move<0x112, 0xf>(v);
+    v += dpp_move<0x114, 0xf>(v);
+    v += dpp_move<0x118, 0xf>(v);
+    return v;
+}
+__device__ __forceinline__ uint32_t fx_row_sum_u(uint32_t v)
+{
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);
+    return v;
 }
 
-__device__ __forceinline__ FxProp fx_prop_of_lane(const FxProp& p, int l)
+// Eq. (1) given whether the pair is inside the cut-off (the reciprocal as in
+// fx_wca).
+__device__ __forceinline__ double fx_wca_in(double s2, double r2, bool in)
 {
-    FxProp r;
-    r.thr = rl_dbl(p.thr, l);
-    r.tx = rl_dbl(p.tx, l);
-    r.ty = rl_dbl(p.ty, l);
-    r.tz = rl_dbl(p.tz, l);
-    r.kind = (uint32_t)__builtin_amdgcn_readlane((int)p.kind, l);
-    r.flip = (uint32_t)__builtin_amdgcn_readlane((int)p.flip, l);
-    r.exited = (uint32_t)__builtin_amdgcn_readlane((int)p.exited, l);
-    return r;
+    double y = __builtin_amdgcn_rcp(r2);
+    y = fma(fma(-r2, y, 1.0), y, y);
+    y = fma(fma(-r2, y, 1.0), y, y);
+    const double x = s2 * y;
+    const double t = fma(2.0, x * x * x, -1.0);
+    return in ? t * t : 0.0;
 }
 
-// The atoms of the 27-cell stencil around `cell` into the wave's candidate
-// list, in the order fx_stencil_atom gives them.  Returns their count, or
-// 0xFFFFFFFF when they exceed the list (attempts then walk the stencil).
-__device__ __forceinline__ uint32_t fx_gather_candidates(const FxK& D, const FxView& V, uint32_t cell,
-                                                         const FxWaveLds& W)
+// The neighbours of every atom in the current sweep: the atoms of other
+// molecules within r_c + 2 sqrt(3) d of it at the sort (each of two atoms
+// moves at most sqrt(3) d in the sweep, so every pair that comes within its
+// cut-off is listed).  A wave per cell: the atoms of the 27 cells around it a
+// lane each (relative to the cell's centre, FP32), tested against the cell's
+// atoms one after another; the list keeps the order of the cell list.  Built
+// once per sweep by all waves side by side, it takes the search (158 atoms of
+// the 27 cells for about 18 within reach) out of the serial attempts: an
+// attempt then needs a row of 16 lanes instead of the whole wave.
+__device__ __forceinline__ void fx_build_lists(const FxK& K, const FxView& V, const double h[3], int wave,
+                                               uint32_t ncell, const FxWaveLds& W)
 {
-    const uint32_t nc = D.nc;
-    uint32_t total;
-    const int nseg = fx_segments(D, V, (int)(cell % nc), (int)((cell / nc) % nc), (int)(cell / (nc * nc)), 1,
-                                 W, &total);
-    if (total > (uint32_t)kFxCand) return 0xFFFFFFFFu;
-    for (uint32_t b = 0; b < total; b += 64u) {
-        const uint32_t idx = b + (uint32_t)__lane_id();
-        if (idx < total) W.cand[idx] = fx_stencil_atom(V, W, nseg, idx);
+    const uint32_t lane = (uint32_t)__lane_id();
+    const uint32_t nc = K.nc, N = K.N, n = K.n;
+    const bool fold = nc <= 3u;  // the 27 cells span the box: nearest image per pair
+    const float Lf = (float)K.L, iLf = (float)K.invL;
+    for (uint32_t cell = (uint32_t)wave; cell < ncell; cell += kFxWaves) {
+        const uint32_t b = V.cell_start[cell], e = V.cell_start[cell + 1];
+        if (b >= e) continue;
+        const uint32_t ix = cell % nc, iy = (cell / nc) % nc, iz = cell / (nc * nc);
+        const double ox = h[0] + ((double)ix + 0.5) * K.w, oy = h[1] + ((double)iy + 0.5) * K.w,
+                     oz = h[2] + ((double)iz + 0.5) * K.w;
+        uint32_t total;
+        const int nseg = fx_segments(K, V, (int)ix, (int)iy, (int)iz, 1, W, &total);
+        for (uint32_t q0 = b; q0 < e; q0 += 64u) {
+            const uint32_t cnt = min(64u, e - q0);
+            uint32_t at = 0, mol = 0, have = 0;  // lane q: atom q, its molecule, neighbours found
+            float ax = 0.f, ay = 0.f, az = 0.f;
+            if (lane < cnt) {
+                at = V.cell_list[q0 + lane];
+                mol = at / n;
+                ax = (float)fx_mi(V.pos[at] - ox, K.L, K.invL);
+                ay = (float)fx_mi(V.pos[N + at] - oy, K.L, K.invL);
+                az = (float)fx_mi(V.pos[2 * N + at] - oz, K.L, K.invL);
+            }
+            for (uint32_t c0 = 0; c0 < total; c0 += 192u) {
+                uint32_t id[3], mj[3];
+                float x[3], y[3], z[3];
+#pragma unroll
+                for (int u = 0; u < 3; ++u) {
+                    const uint32_t idx = c0 + 64u * (uint32_t)u + lane;
+                    id[u] = kFxNone;
+                    mj[u] = 0xFFFFFFFFu;
+                    x[u] = y[u] = z[u] = 1e9f;
+                    if (idx < total) {
+                        const uint32_t j = fx_stencil_atom(V, W, nseg, idx);
+                        id[u] = j;
+                        mj[u] = j / n;
+                        x[u] = (float)fx_mi(V.pos[j] - ox, K.L, K.invL);
+                        y[u] = (float)fx_mi(V.pos[N + j] - oy, K.L, K.invL);
+                        z[u] = (float)fx_mi(V.pos[2 * N + j] - oz, K.L, K.invL);
+                    }
+                }
+                for (uint32_t q = 0; q < cnt; ++q) {
+                    const float qx = rl_f(ax, (int)q), qy = rl_f(ay, (int)q), qz = rl_f(az, (int)q);
+                    const uint32_t qm = rl_u(mol, (int)q);
+                    uint16_t* out = K.nbr + (size_t)rl_u(at, (int)q) * kFxNbr;
+                    uint32_t k = rl_u(have, (int)q);
+#pragma unroll
+                    for (int u = 0; u < 3; ++u) {
+                        float dx = x[u] - qx, dy = y[u] - qy, dz = z[u] - qz;
+                        if (fold) {
+                            dx = fmaf(-Lf, rintf(dx * iLf), dx);
+                            dy = fmaf(-Lf, rintf(dy * iLf), dy);
+                            dz = fmaf(-Lf, rintf(dz * iLf), dz);
+                        }
+                        const bool keep = fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < K.list_r2 && mj[u] != qm;
+                        const uint64_t bm = __ballot(keep);
+                        const uint32_t at_k = k + rank_below(bm);
+                        if (keep && at_k < kFxNbr) out[at_k] = (uint16_t)id[u];
+                        k += (uint32_t)__popcll(bm);
+                    }
+                    if (lane == q) have = k;
+                }
+            }
+            // pad the lists; mark those that did not fit
+            for (uint32_t q = 0; q < cnt; ++q) {
+                uint16_t* out = K.nbr + (size_t)rl_u(at, (int)q) * kFxNbr;
+                const uint32_t k = rl_u(have, (int)q);
+                if (k <= kFxNbr) {
+                    if (lane >= k && lane < kFxNbr) out[lane] = (uint16_t)kFxNone;
+                } else if (lane == 0) {
+                    out[0] = (uint16_t)kFxOver;
+                }
+            }
+        }
     }
-    wave_lds_sync();
-    return total;
 }
 
-// One attempt on atom a (Sec. II.B) by a whole wave, with its proposal pr
-// (wave-uniform).  `cell` is the atom's cell for the sweep's shift h: a
-// translation that leaves it is rejected.  ncand: the size of the wave's
-// candidate list of this cell's stencil (0xFFFFFFFF: no list).
-__device__ __forceinline__ void fx_attempt(const FxK& D, const FxView& V, uint32_t a, const FxProp& pr,
-                                           uint64_t sweep, const double h[3], uint32_t cell, uint32_t ncand,
-                                           bool logging, const FxWaveLds& W, FxCount& wc)
+// The attempts on up to 64 atoms of one cell (lane q holds atom q and its
+// proposal), in order, by one wave.
+//
+// Up to four attempts are evaluated side by side against the present state, a
+// row of 16 lanes for each atom that changes (one for a translation, two to
+// four for a flip; a flip's rows stay together): a lane per listed neighbour,
+// and on the first row of an attempt a lane per pair inside the molecule.
+// They are then decided in order.  An accepted attempt voids those after it in
+// the group that have a changed atom among their neighbours or in their own
+// molecule; the next group starts from the first void one, so every decision
+// is taken on the state its predecessors left, and dE does not depend on how
+// the attempts were grouped.  With 7 - 30 % accepted about three of four
+// stand.  The serial chain of a cell's attempts bounds the kernel (a system
+// runs on one compute unit); a group costs little more than one attempt by
+// the whole wave over the 27 cells' atoms did: a sweep of 1000 triangles at
+// T = 0.75 went from 2.80 to 1.22 ms, of 333 tetrahedra from 7.4 to 2.2 ms.
+__device__ __forceinline__ void fx_run_rows(const FxK& K, const FxView& V, uint32_t cnt,
+                                            uint32_t at, const FxProp& pr, uint64_t sweep, bool logging,
+                                            const FxWaveLds& W, FxCount& wc)
 {
-    const int lane = __lane_id();
-    const uint32_t n = D.n, N = D.N;
-    const bool flip = pr.flip != 0u;
-    const uint32_t base = n * (a / n), sa = a - base;
-    const double sig[4] = {D.sigma[0], D.sigma[1], D.sigma[2], D.sigma[3]};
-
-    // the molecule's atoms before and after (wave-uniform)
-    double ox[4], oy[4], oz[4], nx[4], ny[4], nz[4];
-    uint32_t ot[4], nt[4];
-#pragma unroll
-    for (uint32_t s = 0; s < 4; ++s) {
-        const uint32_t at = base + (s < n ? s : 0u);
-        ox[s] = nx[s] = V.pos[at];
-        oy[s] = ny[s] = V.pos[N + at];
-        oz[s] = nz[s] = V.pos[2 * N + at];
-        ot[s] = nt[s] = V.type[at];
+    const uint32_t lane = (uint32_t)__lane_id(), row = lane >> 4, rl = lane & 15u;
+    const uint32_t n = K.n, N = K.N;
+    const uint32_t base = n * (at / n);
+    const bool mine = lane < cnt;
+    const uint64_t flips = __ballot(mine && pr.flip != 0u);
+    const uint64_t exits = __ballot(mine && pr.exited != 0u);
+    wc.att_f += (uint32_t)__popcll(flips);
+    wc.att_t += cnt - (uint32_t)__popcll(flips);
+    wc.exits += (uint32_t)__popcll(exits);
+    if (logging && mine && pr.exited) {
+        MoveRecord rec;
+        rec.delta_e = 0.0; rec.scale = 0.0; rec.t_log_u = pr.thr; rec.sweep = sweep;
+        rec.molecule = at; rec.move = MC_TRANSLATE; rec.accepted = 0; rec.exited = 1;
+        rec.axis = 255; rec.pair_terms = 0; rec.pad = 0;
+        K.log[(sweep - K.log_sweep0) * N + at] = rec;
     }
-    uint32_t changed = 0;  // bit s: atom base + s moves or changes type
-    double wx = 0.0, wy = 0.0, wz = 0.0;
-    if (flip) {
+    uint64_t live = (cnt >= 64u ? ~0ull : (1ull << cnt) - 1ull) & ~exits;
+    // pair (i, j) inside the molecule on row lane 0 .. 5
+    const uint32_t pi = rl < 3u ? 0u : (rl < 5u ? 1u : 2u);
+    const uint32_t pj = rl < 3u ? rl + 1u : (rl < 5u ? rl - 1u : 3u);
+    const bool pair_lane = rl < 6u && pj < n;
+    while (live) {
+        // ---- form a group: byte r of rows = attempt | atom of the molecule << 6
+        uint32_t rows = 0, nrow = 0, natt = 0;
+        uint32_t qa[4] = {0, 0, 0, 0}, r0[5] = {0, 0, 0, 0, 0};
+        {
+            uint64_t left = live;
 #pragma unroll
-        for (uint32_t s = 0; s < 4; ++s) {
-            if (s >= n) continue;
-            nt[s] = fx_pick(ot, (fx_pick(D.flipw, pr.kind) >> (8 * s)) & 0xFFu);
-            if (nt[s] != ot[s]) changed |= 1u << s;
-        }
-    } else {
-        wx = fx_wrap(pr.tx, D.L);
-        wy = fx_wrap(pr.ty, D.L);
-        wz = fx_wrap(pr.tz, D.L);
+            for (int g = 0; g < 4; ++g) {
+                if (!left || natt != (uint32_t)g) continue;
+                const uint32_t q = (uint32_t)__builtin_ctzll(left);
+                uint32_t chg, need;
+                if ((flips >> q) & 1u) {
+                    chg = fx_pick(K.chg, rl_u(pr.kind, (int)q));
+                    need = (uint32_t)__popc(chg);
+                } else {
+                    chg = 1u << (rl_u(at, (int)q) - rl_u(base, (int)q));
+                    need = 1u;
+                }
+                if (nrow + need > 4u) continue;
+                qa[g] = q;
+                r0[g] = nrow;
 #pragma unroll
-        for (uint32_t s = 0; s < 4; ++s)
-            if (s == sa) {
-                nx[s] = wx;
-                ny[s] = wy;
-                nz[s] = wz;
-            }
-        changed = 1u << sa;
-    }
-    if (flip) wc.att_f += 1; else wc.att_t += 1;
-    if (pr.exited) {
-        wc.exits += 1;
-        if (logging && lane == 0) {
-            MoveRecord rec;
-            rec.delta_e = 0.0; rec.scale = 0.0; rec.t_log_u = pr.thr; rec.sweep = sweep;
-            rec.molecule = a; rec.move = MC_TRANSLATE; rec.accepted = 0; rec.exited = 1;
-            rec.axis = 255; rec.pair_terms = 0; rec.pad = 0;
-            D.log[(sweep - D.log_sweep0) * N + a] = rec;
-        }
-        return;
-    }
-
-    double de = 0.0, sc = 0.0;
-    uint32_t terms = 0;  // wave totals (popcounts of ballots)
-    // intramolecular pairs touching a changed atom: pair (i, j), i < j, on
-    // lane 0 .. 5 in the order (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
-    {
-        const uint32_t i = lane < 3 ? 0u : (lane < 5 ? 1u : 2u);
-        const uint32_t j = lane < 3 ? (uint32_t)lane + 1u : (lane < 5 ? (uint32_t)lane - 1u : 3u);
-        const bool on = lane < 6 && j < n && (((changed >> i) | (changed >> j)) & 1u);
-        bool ino = false, inn = false, fino = false, finn = false;
-        if (on) {
-            const double xi = fx_pick(ox, i), yi = fx_pick(oy, i), zi = fx_pick(oz, i);
-            const double xj = fx_pick(ox, j), yj = fx_pick(oy, j), zj = fx_pick(oz, j);
-            const double xin = fx_pick(nx, i), yin = fx_pick(ny, i), zin = fx_pick(nz, i);
-            const double xjn = fx_pick(nx, j), yjn = fx_pick(ny, j), zjn = fx_pick(nz, j);
-            const double dxo = fx_mi(xi - xj, D.L, D.invL), dyo = fx_mi(yi - yj, D.L, D.invL),
-                         dzo = fx_mi(zi - zj, D.L, D.invL);
-            const double dxn = fx_mi(xin - xjn, D.L, D.invL), dyn = fx_mi(yin - yjn, D.L, D.invL),
-                         dzn = fx_mi(zin - zjn, D.L, D.invL);
-            const double r2o = dxo * dxo + dyo * dyo + dzo * dzo;
-            const double r2n = dxn * dxn + dyn * dyn + dzn * dzn;
-            const double so = 0.5 * (fx_pick(sig, fx_pick(ot, i)) + fx_pick(sig, fx_pick(ot, j)));
-            const double sn = 0.5 * (fx_pick(sig, fx_pick(nt, i)) + fx_pick(sig, fx_pick(nt, j)));
-            const double uo = fx_wca(so * so, r2o, D.rc2f), un = fx_wca(sn * sn, r2n, D.rc2f);
-            ino = r2o < D.rc2f * so * so;
-            inn = r2n < D.rc2f * sn * sn;
-            de = un - uo;
-            sc = un + uo;
-            if ((D.bonded >> (4 * i + j)) & 1u) {
-                // the change of Eq. (2) in one logarithm: the ratio of the
-                // arguments before and after; +inf at or beyond the limit
-                const double lo2 = 2.25 * so * so, ln2 = 2.25 * sn * sn;
-                fino = r2o < lo2;
-                finn = r2n < ln2;
-                if (fino && finn)
-                    de += -33.75 * log((1.0 - r2n / ln2) / (1.0 - r2o / lo2));
-                else
-                    de += (finn ? 0.0 : __builtin_inf()) - (fino ? 0.0 : __builtin_inf());
-                if (logging) sc += fx_fene(so, r2o) + fx_fene(sn, r2n);
+                for (uint32_t t = 0; t < 4; ++t)
+                    if ((chg >> t) & 1u) {
+                        rows |= (q | (t << 6)) << (8u * nrow);
+                        ++nrow;
+                    }
+                r0[g + 1] = nrow;
+                natt = (uint32_t)g + 1u;
+                left &= left - 1ull;
             }
         }
-        terms += (uint32_t)__popcll(__ballot(ino)) + (uint32_t)__popcll(__ballot(inn)) +
-                 (uint32_t)__popcll(__ballot(fino)) + (uint32_t)__popcll(__ballot(finn));
-    }
-    // intermolecular pairs: for each changed atom, the atoms of the 27 cells
-    // around the cell it was sorted into this sweep, a lane each (cells are at
-    // least r_c + 2 sqrt(3) d wide, and either atom has moved at most
-    // sqrt(3) d since the sort, so every partner within r_c is there)
+        // ---- the lanes' atoms and neighbours
+        const bool act = row < nrow;
+        const uint32_t info = act ? (rows >> (8u * row)) & 0xFFu : qa[0];
+        const int ql = (int)(info & 63u);
+        const uint32_t bl = (uint32_t)__shfl((int)base, ql), al = (uint32_t)__shfl((int)at, ql);
+        const uint32_t kl = (uint32_t)__shfl((int)pr.kind, ql);
+        const bool fl = kl != 255u;
+        const uint32_t cl = fl ? bl + (info >> 6) : al;
+        uint32_t j[3] = {kFxNone, kFxNone, kFxNone};
+        if (K.nbr != nullptr && act) {
+            const uint16_t* list = K.nbr + (size_t)cl * kFxNbr;
 #pragma unroll
-    for (uint32_t s = 0; s < 4; ++s) {
-        if (!((changed >> s) & 1u)) continue;  // wave-uniform
-        const uint32_t cy_id = V.cell_id[base + s];
-        bool listed = ncand != 0xFFFFFFFFu && cy_id == cell;  // wave-uniform
-        if (!listed && ncand != 0xFFFFFFFFu && flip) {
-            // an atom of another cell whose type changes (its position does
-            // not) is served by the list too when every atom that can reach
-            // it was sorted into the list's 27 cells: those within the largest
-            // cut-off now were within it plus sqrt(3) d at the sort
-            const double m = sqrt(D.rc2f) * fmax(fmax(sig[0], sig[1]), fmax(sig[2], sig[3])) +
-                             1.7320508075688772 * D.dmax + 1e-9;
-            const uint32_t nc = D.nc;
-            listed = fx_in_stencil(ox[s], h[0], cell % nc, D, m) &&
-                     fx_in_stencil(oy[s], h[1], (cell / nc) % nc, D, m) &&
-                     fx_in_stencil(oz[s], h[2], cell / (nc * nc), D, m);
+            for (int u = 0; u < 3; ++u) j[u] = list[16u * (uint32_t)u + rl];
         }
-        uint32_t total = ncand;
-        int nseg = 0;
-        if (!listed) {
-            const uint32_t ux = cy_id % D.nc, uy = (cy_id / D.nc) % D.nc, uz = cy_id / (D.nc * D.nc);
-            nseg = fx_segments(D, V, (int)ux, (int)uy, (int)uz, 1, W, &total);
-        }
-        const double sos = fx_pick(sig, ot[s]), sns = fx_pick(sig, nt[s]);
-        for (uint32_t b = 0; b < total; b += 64u) {
-            const uint32_t idx = b + (uint32_t)lane;
-            uint32_t j = 0xFFFFFFFFu;
-            if (idx < total) j = listed ? W.cand[idx] : fx_stencil_atom(V, W, nseg, idx);
-            const bool valid = j != 0xFFFFFFFFu && j - base >= n;  // not an atom of the molecule
-            double xj = 0.0, yj = 0.0, zj = 0.0;
-            uint32_t tj = 0;
-            if (valid) {
-                xj = V.pos[j]; yj = V.pos[N + j]; zj = V.pos[2 * N + j];
-                tj = V.type[j];
-            }
-            const double sj = fx_pick(sig, tj);
-            const double dxo = fx_mi(ox[s] - xj, D.L, D.invL), dyo = fx_mi(oy[s] - yj, D.L, D.invL),
-                         dzo = fx_mi(oz[s] - zj, D.L, D.invL);
-            const double r2o = valid ? dxo * dxo + dyo * dyo + dzo * dzo : 1e30;
-            double r2n = r2o;
-            if (!flip) {
-                const double dxn = fx_mi(nx[s] - xj, D.L, D.invL), dyn = fx_mi(ny[s] - yj, D.L, D.invL),
-                             dzn = fx_mi(nz[s] - zj, D.L, D.invL);
-                r2n = valid ? dxn * dxn + dyn * dyn + dzn * dzn : 1e30;
-            }
-            const double so = 0.5 * (sos + sj);
-            const double sn = 0.5 * (sns + sj);
-            const double uo = fx_wca(so * so, r2o, D.rc2f), un = fx_wca(sn * sn, r2n, D.rc2f);
+        // rows without a list (it did not fit, or the system has none)
+        const uint32_t head = K.nbr != nullptr ? (uint32_t)__shfl((int)j[0], (int)(lane & 48u)) : kFxOver;
+        const bool over = act && head == kFxOver;
+        const double xo = V.pos[cl], yo = V.pos[N + cl], zo = V.pos[2 * N + cl];
+        const double tx = __shfl(pr.tx, ql), ty = __shfl(pr.ty, ql), tz = __shfl(pr.tz, ql);
+        const double mx = fl ? 0.0 : tx - xo, my = fl ? 0.0 : ty - yo, mz = fl ? 0.0 : tz - zo;
+        const uint32_t perm = fx_pick(K.flipw, kl);
+        const uint32_t to = V.type[cl];
+        const uint32_t tn = fl ? (uint32_t)V.type[bl + ((perm >> (8u * (cl - bl))) & 0xFFu)] : to;
+        double de = 0.0, sc = 0.0;
+        uint32_t terms = 0;
+        // ---- pairs with other molecules: separations after a translation are
+        // those before it plus the displacement
+        auto eval = [&](uint32_t jn, bool valid) __attribute__((always_inline)) {
+            const uint32_t jj = valid ? jn : cl;
+            const double xj = V.pos[jj], yj = V.pos[N + jj], zj = V.pos[2 * N + jj];
+            const uint32_t tj = V.type[jj];
+            const double s2o = W.s2ij[4u * to + tj], s2n = W.s2ij[4u * tn + tj];
+            const double dx = fx_mi(xo - xj, K.L, K.invL), dy = fx_mi(yo - yj, K.L, K.invL),
+                         dz = fx_mi(zo - zj, K.L, K.invL);
+            const double ex = dx + mx, ey = dy + my, ez = dz + mz;
+            const double r2o = dx * dx + dy * dy + dz * dz;
+            const double r2n = ex * ex + ey * ey + ez * ez;
+            const bool io = valid && r2o < K.rc2f * s2o, in = valid && r2n < K.rc2f * s2n;
+            const double uo = fx_wca_in(s2o, r2o, io), un = fx_wca_in(s2n, r2n, in);
             de += un - uo;
-            sc += un + uo;
-            terms += (uint32_t)__popcll(__ballot(r2o < D.rc2f * so * so)) +
-                     (uint32_t)__popcll(__ballot(r2n < D.rc2f * sn * sn));
-        }
-    }
-    const double dE = wave_sum_dpp(de);
-    const double S = logging ? wave_sum_dpp(sc) : 0.0;
-    const bool accept = (dE <= 0.0) || (pr.thr < -dE);
-    wc.terms += terms;
-    if (accept) {
-        if (flip) wc.acc_f += 1; else wc.acc_t += 1;
-        wc.e += dE;
-    }
-    if (lane == 0) {
-        if (accept) {
-            if (flip) {
+            if (logging) sc += un + uo;
+            terms += (io ? 1u : 0u) + (in ? 1u : 0u);
+        };
+        if (!__ballot(over)) {
 #pragma unroll
-                for (uint32_t s = 0; s < 4; ++s)
-                    if ((changed >> s) & 1u) V.type[base + s] = (uint8_t)nt[s];
-            } else {
-                V.pos[a] = wx;
-                V.pos[N + a] = wy;
-                V.pos[2 * N + a] = wz;
-                // periodic images crossed (the shifts the wrap took off)
-                const int ix = (int)floor(pr.tx / D.L), iy = (int)floor(pr.ty / D.L),
-                          iz = (int)floor(pr.tz / D.L);
-                if (ix) D.img[a] += ix;
-                if (iy) D.img[N + a] += iy;
-                if (iz) D.img[2 * N + a] += iz;
+            for (int u = 0; u < 3; ++u) {
+                const bool valid = j[u] < kFxOver;
+                if (u && !__ballot(valid)) break;  // wave-uniform
+                eval(j[u], valid);
+            }
+        } else {
+            // the 27 cells around the cell the atom was sorted into (every
+            // cell once where they span the axis), a lane per atom
+            const uint32_t nc = K.nc, span = min(nc, 3u);
+            const uint32_t cid = V.cell_id[cl];
+            const uint32_t ix = cid % nc, iy = (cid / nc) % nc, iz = cid / (nc * nc);
+            const uint32_t listed = over ? 3u : 0u;
+            for (uint32_t u = 0; u < 3u; ++u) {
+                const uint32_t ju = u == 0 ? j[0] : (u == 1 ? j[1] : j[2]);
+                eval(ju, !listed && ju < kFxOver);
+            }
+            for (uint32_t o = 0; o < span * span * span; ++o) {
+                const uint32_t x = (ix + nc - 1u + o % span) % nc, y = (iy + nc - 1u + (o / span) % span) % nc,
+                               z = (iz + nc - 1u + o / (span * span)) % nc;
+                const uint32_t c = x + nc * (y + nc * z);
+                const uint32_t cb = V.cell_start[c], ce = over ? V.cell_start[c + 1] : cb;
+                for (uint32_t q = cb + rl; __ballot(q < ce); q += 16u) {
+                    const uint32_t ja = q < ce ? V.cell_list[q] : cl;
+                    eval(ja, q < ce && ja - bl >= n);
+                }
             }
         }
-        if (logging) {
-            MoveRecord rec;
-            rec.delta_e = dE; rec.scale = S; rec.t_log_u = pr.thr; rec.sweep = sweep;
-            rec.molecule = a; rec.move = flip ? MC_FLIP : MC_TRANSLATE; rec.accepted = accept ? 1 : 0;
-            rec.exited = 0; rec.axis = (uint8_t)pr.kind; rec.pair_terms = terms; rec.pad = 0;
-            D.log[(sweep - D.log_sweep0) * N + a] = rec;
+        // ---- pairs inside the molecule that touch a changed atom, on the
+        // attempt's first row
+        {
+            bool first = false;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) first = first || ((uint32_t)g < natt && row == r0[g]);
+            const uint32_t chg = fl ? fx_pick(K.chg, kl) : 1u << (cl - bl);
+            const bool on = first && pair_lane && (((chg >> pi) | (chg >> pj)) & 1u);
+            if (on) {
+                const uint32_t ai = bl + pi, aj = bl + pj;
+                const double dx = fx_mi(V.pos[ai] - V.pos[aj], K.L, K.invL),
+                             dy = fx_mi(V.pos[N + ai] - V.pos[N + aj], K.L, K.invL),
+                             dz = fx_mi(V.pos[2 * N + ai] - V.pos[2 * N + aj], K.L, K.invL);
+                const double sg = ai == cl ? 1.0 : (aj == cl ? -1.0 : 0.0);  // m is 0 for a flip
+                const double ex = fma(sg, mx, dx), ey = fma(sg, my, dy), ez = fma(sg, mz, dz);
+                const double r2o = dx * dx + dy * dy + dz * dz;
+                const double r2n = ex * ex + ey * ey + ez * ez;
+                const uint32_t oi = V.type[ai], oj = V.type[aj];
+                uint32_t ni = oi, nj = oj;
+                if (fl) {
+                    ni = V.type[bl + ((perm >> (8u * pi)) & 0xFFu)];
+                    nj = V.type[bl + ((perm >> (8u * pj)) & 0xFFu)];
+                }
+                const double so = W.s2ij[4u * oi + oj], sn = W.s2ij[4u * ni + nj];
+                const bool io = r2o < K.rc2f * so, in = r2n < K.rc2f * sn;
+                const double uo = fx_wca_in(so, r2o, io), un = fx_wca_in(sn, r2n, in);
+                de += un - uo;
+                if (logging) sc += un + uo;
+                terms += (io ? 1u : 0u) + (in ? 1u : 0u);
+                if ((K.bonded >> (4u * pi + pj)) & 1u) {
+                    // the change of Eq. (2) in one logarithm: the ratio of the
+                    // arguments before and after; +inf at or beyond the limit
+                    const double lo2 = 2.25 * so, ln2 = 2.25 * sn;
+                    const bool fo = r2o < lo2, fn = r2n < ln2;
+                    if (fo && fn)
+                        de += -33.75 * log(((ln2 - r2n) * lo2) / ((lo2 - r2o) * ln2));
+                    else
+                        de += (fn ? 0.0 : __builtin_inf()) - (fo ? 0.0 : __builtin_inf());
+                    terms += (fo ? 1u : 0u) + (fn ? 1u : 0u);
+                    if (logging)
+                        sc += fx_fene(W.sij[4u * oi + oj], r2o) + fx_fene(W.sij[4u * ni + nj], r2n);
+                }
+            }
         }
+        // ---- decide in order
+        const double rs = fx_row_sum(de);
+        double ss = 0.0;
+        uint32_t ts = 0;
+        if (logging) {
+            ss = fx_row_sum(sc);
+            ts = fx_row_sum_u(terms);
+        }
+        uint32_t void_rows = 0, done_rows = 0;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            if ((uint32_t)g >= natt) break;
+            const uint32_t rb = r0[g], re = r0[g + 1];
+            const uint32_t rmask = ((1u << re) - 1u) & ~((1u << rb) - 1u);
+            if (void_rows & rmask) break;  // evaluated on a state that has changed since
+            double dE = 0.0;
+            for (uint32_t r = rb; r < re; ++r) dE += rl_d(rs, (int)(16u * r + 15u));
+            const int q = (int)qa[g];
+            const bool flip = (flips >> q) & 1u;
+            const double thr = rl_d(pr.thr, q);
+            const bool accept = (dE <= 0.0) || (thr < -dE);
+            done_rows |= rmask;
+            live &= live - 1ull;
+            if (logging) {
+                double S = 0.0;
+                uint32_t tt = 0;
+                for (uint32_t r = rb; r < re; ++r) {
+                    S += rl_d(ss, (int)(16u * r + 15u));
+                    tt += rl_u(ts, (int)(16u * r + 15u));
+                }
+                if ((int)lane == q) {
+                    MoveRecord rec;
+                    rec.delta_e = dE; rec.scale = S; rec.t_log_u = thr; rec.sweep = sweep;
+                    rec.molecule = at; rec.move = flip ? MC_FLIP : MC_TRANSLATE; rec.accepted = accept ? 1 : 0;
+                    rec.exited = 0; rec.axis = (uint8_t)pr.kind; rec.pair_terms = tt; rec.pad = 0;
+                    K.log[(sweep - K.log_sweep0) * N + at] = rec;
+                }
+            }
+            if (!accept) continue;
+            wc.e += dE;
+            if (flip) wc.acc_f += 1; else wc.acc_t += 1;
+            if (rl == 0u && row >= rb && row < re) {
+                if (flip) {
+                    V.type[cl] = (uint8_t)tn;
+                } else {
+                    // wrapped as fx_wrap does; the shifts are the periodic
+                    // images crossed
+                    const double fx = floor(tx / K.L), fy = floor(ty / K.L), fz = floor(tz / K.L);
+                    V.pos[cl] = tx - K.L * fx;
+                    V.pos[N + cl] = ty - K.L * fy;
+                    V.pos[2 * N + cl] = tz - K.L * fz;
+                    if ((int)fx) K.img[cl] += (int)fx;
+                    if ((int)fy) K.img[N + cl] += (int)fy;
+                    if ((int)fz) K.img[2 * N + cl] += (int)fz;
+                }
+            }
+            if ((uint32_t)g + 1u < natt) {
+                // attempts after this one that a changed atom reaches
+                bool hit = over || bl == rl_u(base, q);
+                for (uint32_t r = rb; r < re; ++r) {
+                    const uint32_t c = rl_u(cl, (int)(16u * r));
+                    hit = hit || j[0] == c || j[1] == c || j[2] == c;
+                }
+                const uint64_t hb = __ballot(hit && row >= re && act);
+#pragma unroll
+                for (uint32_t r = 0; r < 4; ++r)
+                    if ((hb >> (16u * r)) & 0xFFFFull) void_rows |= 1u << r;
+            }
+        }
+        if ((done_rows >> row) & 1u) wc.terms += terms;
+        wave_lds_sync();
     }
-    wave_lds_sync();
 }
 
 // Ascending atom index inside every cell of c0, c0 + cstep, ...: one wave per
@@ -596,7 +748,7 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
 {
     FxDev* __restrict__ Dp = list.d[blockIdx.x];
     __shared__ uint32_t seg[kFxWaves][2][kFxSeg];
-    __shared__ uint32_t cand[kFxWaves][kFxCand];
+    __shared__ double pair_s[16], pair_s2[16];
     __shared__ uint32_t scratch[kFxWaves];
     __shared__ double misc[2];
     __shared__ double dmax2[kFxWaves];
@@ -604,7 +756,7 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
     const FxDev& D = *Dp;
     const FxK K = fx_const(D);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    FxWaveLds W{seg[wave][0], seg[wave][1], cand[wave]};
+    FxWaveLds W{seg[wave][0], seg[wave][1], pair_s, pair_s2};
     Stats* st = D.stats;
     const uint32_t N = D.N, ncell = D.ncell, nc = D.nc, k = D.k;
     FxView V{D.pos, D.type, D.cell_start, D.cell_list, D.cell_id, D.ecell};
@@ -620,6 +772,11 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
     uint64_t sweep = st->sweep;
     const uint64_t origin = st->obs_origin;
     if (tid == 0) misc[0] = st->e_acc;
+    if (tid < 16) {
+        const double sg = 0.5 * (fx_pick(K.sigma, (uint32_t)tid >> 2) + fx_pick(K.sigma, (uint32_t)tid & 3u));
+        pair_s[tid] = sg;
+        pair_s2[tid] = sg * sg;
+    }
     FxCount wc{};
     for (uint64_t it = 0; it < n_sweeps; ++it) {
         const U4 g = philox10(0xFFFFFFFFu, (uint32_t)sweep, (uint32_t)(sweep >> 32), 3u, K.seed_lo, K.seed_hi);
@@ -639,6 +796,10 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
         __syncthreads();
         fx_sort_cells(V.cell_list, V.cell_start, (uint32_t)wave, kFxWaves, ncell);
         __syncthreads();
+        if (K.nbr != nullptr) {
+            fx_build_lists(K, V, h, wave, ncell, W);
+            __syncthreads();
+        }
         const bool logging = D.log != nullptr && sweep - D.log_sweep0 < D.log_sweeps;
         // The cells of a colour are attempted in ascending index; they run
         // side by side when no attempt in one can reach an atom another
@@ -686,7 +847,6 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
             wc.e = 0.0;
             const uint32_t b = V.cell_start[cell], e = V.cell_start[cell + 1];
             if (b < e) {
-                const uint32_t ncand = fx_gather_candidates(K, V, cell, W);
                 for (uint32_t q0 = b; q0 < e; q0 += 64u) {
                     const uint32_t cnt = min(64u, e - q0);
                     uint32_t at = 0;
@@ -695,9 +855,7 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
                         at = V.cell_list[q0 + lane];
                         pr = fx_propose(K, V, at, sweep, h, cell);
                     }
-                    for (uint32_t q = 0; q < cnt; ++q)
-                        fx_attempt(K, V, (uint32_t)__builtin_amdgcn_readlane((int)at, (int)q),
-                                   fx_prop_of_lane(pr, (int)q), sweep, h, cell, ncand, logging, W, wc);
+                    fx_run_rows(K, V, cnt, at, pr, sweep, logging, W, wc);
                 }
             }
             if (lane == 0) V.ecell[cell] = wc.e;
@@ -738,7 +896,12 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
         if (wc.acc_t) atomicAdd((unsigned long long*)&st->accepts[MC_TRANSLATE], (unsigned long long)wc.acc_t);
         if (wc.acc_f) atomicAdd((unsigned long long*)&st->accepts[MC_FLIP], (unsigned long long)wc.acc_f);
         if (wc.exits) atomicAdd((unsigned long long*)&st->exits, (unsigned long long)wc.exits);
-        if (wc.terms) atomicAdd((unsigned long long*)&st->pair_terms, (unsigned long long)wc.terms);
+    }
+    {
+        uint64_t t = wc.terms;
+#pragma unroll
+        for (int o = 32; o; o >>= 1) t += (uint64_t)__shfl_xor((unsigned long long)t, o);
+        if (lane == 0 && t) atomicAdd((unsigned long long*)&st->pair_terms, (unsigned long long)t);
     }
     __syncthreads();
     if (kRes) {
