@@ -402,9 +402,10 @@ int mcf_init_system(const mcf_params* p, const double* pos, const uint8_t* types
  * serving loops, harnesses that forbid it): mcf_init_system without any
  * allocation by the library.  The caller's device_state (256-byte aligned,
  * at least *state_bytes_needed bytes, must outlive the system) holds the
- * state and the observables; the work arrays of the sweeps and events (cell
- * lists, per-cell energies, partial sums) live in one static per-device array
- * of 4 MiB, so MC_ENOMEM when they would exceed it.  Clearing is done by a
+ * state, the observables and the sweeps' proposals and neighbour lists; the
+ * other work arrays of the sweeps and events (cell lists, per-cell energies,
+ * partial sums) live in one static per-device array of 4 MiB, so MC_ENOMEM
+ * when they would exceed it.  Clearing is done by a
  * kernel (no memset), host positions are staged through the state buffer, and
  * the handle comes from a static pool of 16 (MC_EBUSY when all are alive).
  * With device_state NULL the call only stores *state_bytes_needed (and the

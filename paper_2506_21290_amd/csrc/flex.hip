@@ -466,8 +466,11 @@ size_t fx_al(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct FxLayout {
     size_t dev, stats, pos, type, img, esamp, dsamp, gall, ginter, c2, c2s, fs, fscm, mom, u0, kref, r0, rcm0;
-    size_t cstart, clist, cid, ecell, part, nbr, total;
+    size_t atom, props, nbr;  // of the sweep kernel, in the state's part
+    size_t cstart, clist, ecell, part, total;
 };
+
+size_t fx_resident_lds(const mcf_params* p, const FxGeom& g);
 
 FxLayout fx_layout(const mcf_params* p, const FxGeom& g)
 {
@@ -492,13 +495,14 @@ FxLayout fx_layout(const mcf_params* p, const FxGeom& g)
     l.kref = o;   o = fx_al(o + M);
     l.r0 = o;     o = fx_al(o + 3 * N * sizeof(double));
     l.rcm0 = o;   o = fx_al(o + 3 * M * sizeof(double));
+    l.atom = o;
+    if (!fx_resident_lds(p, g)) o = fx_al(o + N * sizeof(FxAtom));
+    l.props = o;  o = fx_al(o + N * sizeof(FxProp));
+    l.nbr = o;    o = fx_al(o + N * kFxNbr * (fx_resident_lds(p, g) ? sizeof(FxNbr<true>) : sizeof(FxNbr<false>)));
     l.cstart = o; o = fx_al(o + (size_t(g.ncell) + 1) * sizeof(uint32_t));
     l.clist = o;  o = fx_al(o + N * sizeof(uint32_t));
-    l.cid = o;    o = fx_al(o + N * sizeof(uint32_t));
     l.ecell = o;  o = fx_al(o + size_t(g.ncell) * sizeof(double));
     l.part = o;   o = fx_al(o + kFxParts * sizeof(double));
-    l.nbr = o;    // neighbour lists, for systems whose atoms 16 bits can index
-    if (N <= kFxListed) o = fx_al(o + N * kFxNbr * sizeof(uint16_t));
     l.total = o;
     return l;
 }
@@ -770,8 +774,10 @@ int fx_init(mcf_system* s, const mcf_params* p, const FxGeom& g, const FxLayout&
         static size_t configured = 0;
         std::lock_guard<std::mutex> lk(mu);
         if (s->lds > configured) {
-            FXCHK(hipFuncSetAttribute((const void*)&k_fx_sweeps<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      (int)s->lds));
+            FXCHK(hipFuncSetAttribute((const void*)&k_fx_sweeps<true, false>,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)s->lds));
+            FXCHK(hipFuncSetAttribute((const void*)&k_fx_sweeps<true, true>,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)s->lds));
             configured = s->lds;
         }
     }
@@ -836,10 +842,11 @@ int fx_init(mcf_system* s, const mcf_params* p, const FxGeom& g, const FxLayout&
     D.rcm0 = (double*)(b + lay.rcm0);
     D.cell_start = (uint32_t*)(work + (lay.cstart - work_off));
     D.cell_list = (uint32_t*)(work + (lay.clist - work_off));
-    D.cell_id = (uint32_t*)(work + (lay.cid - work_off));
     D.ecell = (double*)(work + (lay.ecell - work_off));
     D.part = (double*)(work + (lay.part - work_off));
-    D.nbr = lay.total > lay.nbr ? (uint16_t*)(work + (lay.nbr - work_off)) : nullptr;
+    D.atom = s->lds ? nullptr : (FxAtom*)(b + lay.atom);
+    D.props = (FxProp*)(b + lay.props);
+    D.nbr = b + lay.nbr;
     s->dev = (FxDev*)(b + lay.dev);
     int rc;
     if (no_alloc) {
@@ -918,9 +925,7 @@ int mcf_init_system_noalloc(const mcf_params* p, const double* pos, const uint8_
 {
     FxGeom g;
     if (int rc = fx_check_request(p, pos, types, &g)) return rc;
-    FxLayout lay = fx_layout(p, g);
-    // a system whose neighbour lists do not fit the scratch runs without them
-    if (lay.total - lay.cstart > kFxScratchBytes) lay.total = lay.nbr;
+    const FxLayout lay = fx_layout(p, g);
     const size_t need = lay.cstart, work = lay.total - lay.cstart;
     if (state_bytes_needed) *state_bytes_needed = need;
     if (work > kFxScratchBytes)
@@ -964,7 +969,9 @@ int fx_launch_sweeps(mcf_system* const* s, uint32_t n, uint64_t chunk, hipStream
     FxList res{}, buf{};
     uint32_t nr = 0, nb = 0;
     size_t lds = 0;
+    bool log = false;
     for (uint32_t i = 0; i < n; ++i) {
+        log = log || s[i]->host.log != nullptr;
         if (s[i]->lds) {
             res.d[nr++] = s[i]->dev;
             lds = std::max(lds, s[i]->lds);
@@ -973,11 +980,17 @@ int fx_launch_sweeps(mcf_system* const* s, uint32_t n, uint64_t chunk, hipStream
         }
     }
     if (nr) {
-        hipLaunchKernelGGL(k_fx_sweeps<true>, dim3(nr), dim3(kFxThreads), lds, stream, res, chunk);
+        if (log)
+            hipLaunchKernelGGL((k_fx_sweeps<true, true>), dim3(nr), dim3(kFxThreads), lds, stream, res, chunk);
+        else
+            hipLaunchKernelGGL((k_fx_sweeps<true, false>), dim3(nr), dim3(kFxThreads), lds, stream, res, chunk);
         FXCHK(hipGetLastError());
     }
     if (nb) {
-        hipLaunchKernelGGL(k_fx_sweeps<false>, dim3(nb), dim3(kFxThreads), 0, stream, buf, chunk);
+        if (log)
+            hipLaunchKernelGGL((k_fx_sweeps<false, true>), dim3(nb), dim3(kFxThreads), 0, stream, buf, chunk);
+        else
+            hipLaunchKernelGGL((k_fx_sweeps<false, false>), dim3(nb), dim3(kFxThreads), 0, stream, buf, chunk);
         FXCHK(hipGetLastError());
     }
     return MC_OK;

@@ -15,9 +15,10 @@
 // launch, a workgroup each), the positions, types and cell lists in LDS when
 // they fit.  Per sweep a random shift of a cubic cell grid over the atoms, a
 // counting sort into cells (ascending atom index inside each cell), the
-// neighbours of every atom, then the k^3 colours in order; the waves take the
-// cells of a colour, and a wave runs its cell's attempts in order, up to four
-// of them evaluated side by side, a row of 16 lanes per changed atom.
+// proposals and the neighbours of every atom, then the k^3 colours in order;
+// the waves take the cells of a colour, and a wave runs its cell's attempts in
+// order, several of them evaluated side by side, a row of 16 lanes per changed
+// atom.
 // Same-colour cells are at least (k - 1) w >= 2 D + r_c apart (D the largest
 // distance two atoms of one molecule can reach, r_c the largest cut-off), so
 // no two attempts of a colour touch the same pair term.  A DPP reduction in
@@ -29,6 +30,7 @@
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "engine.h"
 #include "flipmc.h"
@@ -38,16 +40,39 @@ namespace flipmc {
 namespace {
 constexpr int kFxThreads = 512;
 constexpr int kFxWaves = kFxThreads / 64;
-constexpr int kFxSeg = 64;          // stencil row segments per attempt (radius <= 2: <= 50)
-constexpr uint32_t kFxNbr = 48;     // neighbours listed per atom (three lanes' worth of a 16-lane row)
-constexpr uint32_t kFxListed = 65534;  // atoms a 16-bit list can index (0xFFFE, 0xFFFF are marks)
-constexpr uint32_t kFxNone = 0xFFFFu;  // no neighbour
-constexpr uint32_t kFxOver = 0xFFFEu;  // first entry of a list that did not fit
-// static LDS of the sweep kernel: segments per wave, pair tables, scan
-// scratch and the energy accumulator (with room to spare)
-constexpr size_t kFxStaticLds = (size_t)kFxWaves * 2 * kFxSeg * 4 + 2 * 16 * 8 + 512;
+// Neighbour lists: kFxNbr entries per atom, three for each lane of a row of
+// 16.  The first kFxPartners are the other atoms of its own molecule, the rest
+// atoms of other molecules.  The entries have 16 bits in systems that fit LDS
+// (the marks sign-extended), 32 bits in the others.
+constexpr uint32_t kFxNbr = 48, kFxPartners = 3;
+constexpr int kFxSlots = 6;  // atoms of the 27 cells per lane of a list build
+template <bool kRes>
+using FxNbr = std::conditional_t<kRes, int16_t, uint32_t>;
+constexpr uint32_t kFxBuild = 8;  // atoms whose lists are put together at a time
+constexpr uint32_t kFxNone = 0xFFFFFFFFu;  // no neighbour
+constexpr uint32_t kFxOver = 0xFFFFFFFEu;  // entry kFxPartners of a list that did not fit
+constexpr uint32_t kFxRows = 8;  // rows of one evaluation: two per 16 lanes
+// static LDS of the sweep kernel: pair tables, the waves' row tasks and sums,
+// scan scratch and the energy accumulator (with room to spare)
+constexpr size_t kFxStaticLds = 2 * 16 * 8 + (size_t)kFxWaves * (kFxRows * (40 + 8 + 8 + 4) + kFxBuild * 64 * 2) + 512;
 constexpr uint32_t kFxParts = 1024;  // workgroups of the event kernel
 constexpr uint32_t kFxMany = 256;    // systems of one sweep launch (a workgroup each)
+
+// An atom as the sweep kernel holds it: position, type, cell of the sweep.
+struct alignas(16) FxAtom {
+    double x, y, z;
+    uint32_t type, cell;
+};
+static_assert(sizeof(FxAtom) == 32, "two 16-byte words");
+
+// The proposal of an attempt (Sec. II.B).
+struct alignas(8) FxProp {
+    double thr;         // T ln u
+    double tx, ty, tz;  // translation target before the wrap
+    uint32_t kind;      // flip: rotation index; translation: kFxMove
+    uint32_t cross;     // translation: bits 2 a, 2 a + 1 = periodic image crossed along axis a plus 1; kFxExit
+};
+constexpr uint32_t kFxMove = 255, kFxExit = 64;
 
 // Everything a workgroup needs about one system; in the system's buffer.
 struct FxDev {
@@ -87,10 +112,11 @@ struct FxDev {
     double* rcm0;         // [3][M] unwrapped centres at the origin
     uint32_t* cell_start; // [ncell + 1]
     uint32_t* cell_list;  // [N] atoms sorted by cell, ascending inside a cell
-    uint32_t* cell_id;    // [N]
     double* ecell;        // [ncell] accepted dE of each cell in the current sweep
     double* part;         // [kFxParts] partial energies of the event kernel
-    uint16_t* nbr;        // [N][kFxNbr] neighbours of each atom in the current sweep, or null
+    FxAtom* atom;         // [N] the sweep kernel's copy of the state, or null (in LDS)
+    FxProp* props;        // [N] proposals of the current sweep, in cell-list order
+    void* nbr;            // [N][kFxNbr] neighbours of each atom in the current sweep
     MoveRecord* log;
     uint64_t log_sweep0, log_sweeps;
 };
@@ -107,14 +133,12 @@ struct FxList {
 struct FxK {
     uint32_t n, N, nc, nflip, bonded, seed_lo, seed_hi, together;
     uint32_t flipw[4];  // byte s of word q: flips[q][s]
-    double L, invL, w, T, p_flip, dmax, rc2f, sep, dyn_base;
-    double sigma[4];
-    int32_t* img;
-    uint16_t* nbr;
-    MoveRecord* log;
-    uint64_t log_sweep0;
-    uint32_t chg[4];    // bit s of word q: flip q changes the type of atom s
-    float list_r2;      // neighbour lists: squared radius, (r_c + 2 sqrt(3) d)^2 with a margin
+    uint32_t chgw;      // bits 4 q + s: flip q changes the type of atom s
+    double L, invL, w, invw, T, p_flip, dmax, rc2f, sep, dyn_base;
+    Global<int32_t>* img;
+    Global<FxProp>* props;
+    Global<void>* nbr;  // FxNbr [N][kFxNbr]
+    float list_r2;  // neighbour lists: squared radius, (r_c + 2 sqrt(3) d)^2 with a margin
 };
 
 __device__ __forceinline__ FxK fx_const(const FxDev& D)
@@ -122,21 +146,16 @@ __device__ __forceinline__ FxK fx_const(const FxDev& D)
     FxK K;
     K.n = D.n; K.N = D.N; K.nc = D.nc; K.nflip = D.nflip; K.bonded = D.bonded;
     K.seed_lo = D.seed_lo; K.seed_hi = D.seed_hi;
-    for (int q = 0; q < 4; ++q)
+    K.chgw = 0;
+    for (int q = 0; q < 4; ++q) {
         K.flipw[q] = (uint32_t)D.flips[q][0] | ((uint32_t)D.flips[q][1] << 8) | ((uint32_t)D.flips[q][2] << 16) |
                      ((uint32_t)D.flips[q][3] << 24);
-    K.L = D.L; K.invL = D.invL; K.w = D.w; K.T = D.T; K.p_flip = D.p_flip; K.dmax = D.dmax; K.rc2f = D.rc2f;
-    K.sep = D.sep; K.dyn_base = D.dyn_base; K.together = D.together;
-    for (int t = 0; t < 4; ++t) K.sigma[t] = D.sigma[t];
-    K.img = D.img;
-    K.nbr = D.nbr;
-    K.log = D.log;
-    K.log_sweep0 = D.log_sweep0;
-    for (int q = 0; q < 4; ++q) {
-        uint32_t c = 0;
-        for (uint32_t t = 0; t < 4; ++t) c |= (t < D.n && D.flips[q][t] != t ? 1u : 0u) << t;
-        K.chg[q] = c;
+        for (uint32_t t = 0; t < 4; ++t) K.chgw |= (t < D.n && D.flips[q][t] != t ? 1u : 0u) << (4 * q + t);
     }
+    K.L = D.L; K.invL = D.invL; K.w = D.w; K.invw = 1.0 / D.w;
+    K.T = D.T; K.p_flip = D.p_flip; K.dmax = D.dmax; K.rc2f = D.rc2f;
+    K.sep = D.sep; K.dyn_base = D.dyn_base; K.together = D.together;
+    K.img = (Global<int32_t>*)D.img; K.props = (Global<FxProp>*)D.props; K.nbr = (Global<void>*)D.nbr;
     // the FP32 distances of the list build are within 1e-5 of the FP64 ones
     const double smax = fmax(fmax(D.sigma[0], D.sigma[1]), fmax(D.sigma[2], D.n > 3u ? D.sigma[3] : 0.0));
     const float r = (float)(sqrt(D.rc2f) * smax + 2.0 * 1.7320508075688772 * D.dmax) + 1e-3f;
@@ -144,12 +163,35 @@ __device__ __forceinline__ FxK fx_const(const FxDev& D)
     return K;
 }
 
-__device__ __forceinline__ double fx_wrap(double x, double L) { return x - L * floor(x / L); }
+// Molecule of atom j.
+__device__ __forceinline__ uint32_t fx_mol(uint32_t n, uint32_t j)
+{
+    return n == 3u ? __umulhi(j, 0x55555556u) : j >> 2;  // N <= 2^24
+}
+
 __device__ __forceinline__ double fx_mi(double d, double L, double invL) { return d - L * rint(d * invL); }
+// the same with one rounding fewer (the events keep the plain form, whose
+// bits the g(r) bins are defined by)
+__device__ __forceinline__ double fx_mif(double d, double L, double invL) { return fma(-L, rint(d * invL), d); }
+
+// floor(x / y), iy = 1 / y: the product is within an ulp or two of the
+// quotient (below 1e3 here), so the floors agree unless it lies next to a
+// whole number; only then the division is taken.
+__device__ __forceinline__ double fx_floor_div(double x, double y, double iy)
+{
+    const double q = x * iy;
+    double f = floor(q);
+    if (fabs(q - rint(q)) < 1e-9) f = floor(x / y);
+    return f;
+}
+
+__device__ __forceinline__ double fx_wrap(double x, double L) { return x - L * floor(x / L); }
 
 __device__ __forceinline__ int fx_axis(double x, double h, const FxK& D)
 {
-    int c = (int)floor(fx_wrap(x - h, D.L) / D.w);
+    const double d = x - h;
+    const double g = d - D.L * fx_floor_div(d, D.L, D.invL);
+    int c = (int)fx_floor_div(g, D.w, D.invw);
     c = c < 0 ? 0 : c;
     return c >= (int)D.nc ? (int)D.nc - 1 : c;
 }
@@ -183,34 +225,51 @@ __device__ __forceinline__ double fx_fene(double sig, double r2)
     return -33.75 * log(1.0 - r2 / lim2);
 }
 
+// This lane's share of the counters, and the accepted dE of the wave's
+// current cell in attempt order (wave-uniform, as the accepted counts).
 struct FxCount {
     uint32_t att_t, att_f, acc_t, acc_f, exits;
-    uint32_t terms;  // interacting pairs, this lane's share
-    double e;  // accepted dE of the current cell, in attempt order
+    uint64_t terms;
+    double e;
 };
 
-// Per-wave LDS: the stencil's row segments.  Per workgroup: the pair
-// diameters sigma_ij and their squares by 4 t_i + t_j.
+// A row of an evaluation: one changed atom of an attempt.
+struct alignas(8) FxRow {
+    double tx, ty, tz;  // target of a translation
+    uint32_t atom, base, kind, pad;
+};
+
+// LDS of one wave: the rows of an evaluation and what they sum; of the workgroup: the pair diameters sigma_ij and
+// their squares by 4 t_i + t_j.
 struct FxWaveLds {
-    uint32_t* seglo;
-    uint32_t* segoff;
+    FxRow* row;      // [kFxRows]
+    double* sum;     // [kFxRows] dE
+    double* scale;   // [kFxRows] u_new + u_old (logged sweeps)
+    uint32_t* terms; // [kFxRows] pairs inside the cut-off
+    void* list;      // FxNbr [kFxBuild][64] lists being built
     const double* sij;
     const double* s2ij;
 };
 
-// Where the sweep kernel reads and writes the state and the cell lists: the
-// workgroup's LDS for systems that fit there, the system's buffer otherwise.
+// Where the sweep kernel keeps the state and the cell lists: the workgroup's
+// LDS for systems that fit there, the system's buffer otherwise.
+template <bool kRes>
 struct FxView {
-    double* pos;          // SoA [3][N]
-    uint8_t* type;        // [N]
-    uint32_t* cell_start; // [ncell + 1]
-    uint32_t* cell_list;  // [N]
-    uint32_t* cell_id;    // [N]
-    double* ecell;        // [ncell]
+    template <typename T>
+    using Ptr = std::conditional_t<kRes, Lds<T>, Global<T>>*;
+    Ptr<FxAtom> atom;         // [N]
+    Ptr<uint32_t> cell_start; // [ncell + 1]
+    Ptr<uint32_t> cell_list;  // [N]
+    Ptr<double> ecell;        // [ncell]
+    __device__ __forceinline__ FxAtom at(uint32_t i) const
+    {
+        const auto* p = atom + i;
+        return FxAtom{p->x, p->y, p->z, p->type, p->cell};
+    }
 };
 
 struct FxLds {
-    size_t pos, type, cstart, clist, cid, ecell, total;
+    size_t atom, cstart, clist, ecell, total;
 };
 
 __host__ __device__ inline FxLds fx_lds_layout(uint32_t N, uint32_t ncell)
@@ -218,66 +277,53 @@ __host__ __device__ inline FxLds fx_lds_layout(uint32_t N, uint32_t ncell)
     FxLds l{};
     size_t o = 0;
     auto a16 = [](size_t x) { return (x + 15) & ~size_t(15); };
-    l.pos = o;    o = a16(o + 3 * size_t(N) * sizeof(double));
+    l.atom = o;   o = a16(o + size_t(N) * sizeof(FxAtom));
     l.ecell = o;  o = a16(o + size_t(ncell) * sizeof(double));
-    l.type = o;   o = a16(o + size_t(N));
     l.cstart = o; o = a16(o + (size_t(ncell) + 1) * sizeof(uint32_t));
     l.clist = o;  o = a16(o + size_t(N) * sizeof(uint32_t));
-    l.cid = o;    o = a16(o + size_t(N) * sizeof(uint32_t));
     l.total = o;
     return l;
 }
 
-// Row segments of the cells within radius r of cell (cx, cy, cz): rows along
-// x of one or two contiguous cell ranges (every cell once when the stencil
-// covers the whole axis).  Returns the number of segments; *total = atoms.
-__device__ __forceinline__ int fx_segments(const FxK& D, const FxView& V, int cx, int cy, int cz, int r,
-                                           const FxWaveLds& W,
-                           uint32_t* total)
+// The 27 cells around cell (cx, cy, cz) (every cell once where they span an
+// axis) as row segments along x of one or two contiguous cell ranges: lane s
+// gets segment s's first place in the cell list (*lo) and the atoms before it
+// in the stencil (*off).  Returns the number of segments; *total = atoms.
+template <bool kRes>
+__device__ __forceinline__ int fx_segments(const FxK& D, const FxView<kRes>& V, int cx, int cy, int cz, uint32_t* lo,
+                                           uint32_t* off, uint32_t* total)
 {
     const int lane = __lane_id();
     const int nc = (int)D.nc;
-    const bool full = 2 * r + 1 >= nc;
-    const int nrow = full ? nc : 2 * r + 1;
+    const bool full = 3 >= nc;
+    const int nrow = full ? nc : 3;
     int xa0, xb0, xa1 = 0, xb1 = -1;
     if (full) {
         xa0 = 0; xb0 = nc - 1;
-    } else if (cx - r < 0) {
-        xa0 = cx - r + nc; xb0 = nc - 1; xa1 = 0; xb1 = cx + r;
-    } else if (cx + r >= nc) {
-        xa0 = cx - r; xb0 = nc - 1; xa1 = 0; xb1 = cx + r - nc;
+    } else if (cx < 1) {
+        xa0 = cx - 1 + nc; xb0 = nc - 1; xa1 = 0; xb1 = cx + 1;
+    } else if (cx + 1 >= nc) {
+        xa0 = cx - 1; xb0 = nc - 1; xa1 = 0; xb1 = cx + 1 - nc;
     } else {
-        xa0 = cx - r; xb0 = cx + r;
+        xa0 = cx - 1; xb0 = cx + 1;
     }
     const int nxr = xb1 >= xa1 ? 2 : 1;
     const int nseg = nrow * nrow * nxr;
-    uint32_t cnt = 0, lo = 0;
+    uint32_t cnt = 0;
+    *lo = 0;
     if (lane < nseg) {
-        const int ixr = lane % nxr, iy = (lane / nxr) % nrow, iz = lane / (nxr * nrow);
-        const int y = full ? iy : (cy - r + iy + nc) % nc;
-        const int z = full ? iz : (cz - r + iz + nc) % nc;
+        const int r = nxr == 2 ? lane >> 1 : lane, ixr = nxr == 2 ? lane & 1 : 0;
+        const int iz = nrow == 3 ? r / 3 : r >> 1, iy = r - nrow * iz;  // nrow is 2 or 3
+        int y = full ? iy : cy - 1 + iy, z = full ? iz : cz - 1 + iz;
+        y += y < 0 ? nc : (y >= nc ? -nc : 0);
+        z += z < 0 ? nc : (z >= nc ? -nc : 0);
         const int xa = ixr ? xa1 : xa0, xb = ixr ? xb1 : xb0;
         const uint32_t row = (uint32_t)(nc * (y + nc * z));
-        lo = V.cell_start[row + xa];
-        cnt = V.cell_start[row + xb + 1] - lo;
+        *lo = V.cell_start[row + xa];
+        cnt = V.cell_start[row + xb + 1] - *lo;
     }
-    const uint32_t off = wave_excl_scan(cnt, total);
-    if (lane < nseg) {
-        W.seglo[lane] = lo;
-        W.segoff[lane] = off;
-    }
-    wave_lds_sync();
+    *off = wave_excl_scan(cnt, total);
     return nseg;
-}
-
-__device__ __forceinline__ uint32_t fx_stencil_atom(const FxView& V, const FxWaveLds& W, int nseg, uint32_t idx)
-{
-    int lo = 0, hi = nseg;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (W.segoff[mid] <= idx) lo = mid; else hi = mid;
-    }
-    return V.cell_list[W.seglo[lo] + (idx - W.segoff[lo])];
 }
 
 template <typename T>
@@ -286,44 +332,60 @@ __device__ __forceinline__ T fx_pick(const T v[4], uint32_t i)
     return i == 0 ? v[0] : (i == 1 ? v[1] : (i == 2 ? v[2] : v[3]));
 }
 
-// The proposal of the attempt on atom a (Sec. II.B): move kind, flip
-// rotation or translation target, the cell-exit test and T ln u.  Drawn for
-// the atoms of a cell by one lane each before the cell's attempts (an atom's
-// position changes only in its own attempt, so the draws do not depend on
-// the attempts before it).
-struct FxProp {
-    double thr;         // T ln u
-    double tx, ty, tz;  // translation target before the wrap
-    uint32_t kind;      // flip: rotation index; translation: 255
-    uint32_t flip, exited;
-};
-
-__device__ __forceinline__ FxProp fx_propose(const FxK& D, const FxView& V, uint32_t a, uint64_t sweep,
-                                             const double h[3], uint32_t cell)
+// The proposals of every atom's attempt in this sweep, at the atom's place in
+// the cell list: move kind, flip rotation or translation target, the cell-exit
+// test and T ln u (an atom's position changes only in its own attempt, so the
+// draws do not depend on the attempts before it).  A thread per atom, before
+// the first colour: drawn by the cell's wave, they were a tenth of its chain.
+template <bool kRes>
+__device__ __forceinline__ void fx_propose_all(const FxDev& Dv, const FxK& D, const FxView<kRes>& V, uint64_t sweep,
+                                               const double h[3], bool logging, FxCount& wc)
 {
-    const uint32_t N = D.N;
     const uint32_t slo = (uint32_t)sweep, shi = (uint32_t)(sweep >> 32);
-    const U4 b0 = philox10(a, slo, shi, 0u, D.seed_lo, D.seed_hi);
-    const U4 b1 = philox10(a, slo, shi, 1u, D.seed_lo, D.seed_hi);
-    const double uacc = unit_53(b0.x, b0.y), ut = unit_open(b0.z);
-    const double p0 = unit_open(b1.x), p1 = unit_open(b1.y), p2 = unit_open(b1.z);
-    FxProp pr;
-    pr.thr = D.T * log(uacc);
-    pr.flip = ut < D.p_flip ? 1u : 0u;
-    pr.kind = 255;
-    pr.exited = 0;
-    pr.tx = pr.ty = pr.tz = 0.0;
-    if (pr.flip) {
-        uint32_t q = (uint32_t)((double)D.nflip * p0);
-        pr.kind = q >= D.nflip ? D.nflip - 1 : q;
-    } else {
-        pr.tx = V.pos[a] + D.dmax * (2.0 * p0 - 1.0);
-        pr.ty = V.pos[N + a] + D.dmax * (2.0 * p1 - 1.0);
-        pr.tz = V.pos[2 * N + a] + D.dmax * (2.0 * p2 - 1.0);
-        pr.exited = fx_cell(fx_wrap(pr.tx, D.L), fx_wrap(pr.ty, D.L), fx_wrap(pr.tz, D.L), h, D) != cell;
+    for (uint32_t p = threadIdx.x; p < D.N; p += kFxThreads) {
+        const uint32_t a = V.cell_list[p];
+        const FxAtom at = V.at(a);
+        const U4 b0 = philox10(a, slo, shi, 0u, D.seed_lo, D.seed_hi);
+        const U4 b1 = philox10(a, slo, shi, 1u, D.seed_lo, D.seed_hi);
+        const double uacc = unit_53(b0.x, b0.y), ut = unit_open(b0.z);
+        const double p0 = unit_open(b1.x), p1 = unit_open(b1.y), p2 = unit_open(b1.z);
+        FxProp pr;
+        pr.thr = D.T * log(uacc);
+        pr.kind = kFxMove;
+        pr.cross = 0;
+        pr.tx = pr.ty = pr.tz = 0.0;
+        if (ut < D.p_flip) {
+            const uint32_t q = (uint32_t)((double)D.nflip * p0);
+            pr.kind = q >= D.nflip ? D.nflip - 1 : q;
+            wc.att_f += 1;
+        } else {
+            pr.tx = at.x + D.dmax * (2.0 * p0 - 1.0);
+            pr.ty = at.y + D.dmax * (2.0 * p1 - 1.0);
+            pr.tz = at.z + D.dmax * (2.0 * p2 - 1.0);
+            // d < L / 4: at most one image
+            const double fx = fx_floor_div(pr.tx, D.L, D.invL), fy = fx_floor_div(pr.ty, D.L, D.invL),
+                         fz = fx_floor_div(pr.tz, D.L, D.invL);
+            pr.cross = (uint32_t)((int)fx + 1) | (uint32_t)((int)fy + 1) << 2 | (uint32_t)((int)fz + 1) << 4;
+            wc.att_t += 1;
+            if (fx_cell(pr.tx - D.L * fx, pr.ty - D.L * fy, pr.tz - D.L * fz, h, D) != at.cell) {
+                pr.cross |= kFxExit;
+                wc.exits += 1;
+                if (logging) {
+                    MoveRecord rec;
+                    rec.delta_e = 0.0; rec.scale = 0.0; rec.t_log_u = pr.thr; rec.sweep = sweep;
+                    rec.molecule = a; rec.move = MC_TRANSLATE; rec.accepted = 0; rec.exited = 1;
+                    rec.axis = 255; rec.pair_terms = 0; rec.pad = 0;
+                    Dv.log[(sweep - Dv.log_sweep0) * D.N + a] = rec;
+                }
+            }
+        }
+        Global<FxProp>* out = D.props + p;
+        out->thr = pr.thr; out->tx = pr.tx; out->ty = pr.ty; out->tz = pr.tz;
+        out->kind = pr.kind; out->cross = pr.cross;
     }
-    return pr;
 }
+
+using W4 = uint32_t __attribute__((ext_vector_type(4)));
 
 // Sum over each row of 16 lanes (the row's last lane gets it) in the order of
 // wave_sum_dpp's first steps.
@@ -337,10 +399,10 @@ __device__ __forceinline__ double fx_row_sum(double v)
 }
 __device__ __forceinline__ uint32_t fx_row_sum_u(uint32_t v)
 {
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);
+    v += dpp_move_u<0x111, 0xf>(v);
+    v += dpp_move_u<0x112, 0xf>(v);
+    v += dpp_move_u<0x114, 0xf>(v);
+    v += dpp_move_u<0x118, 0xf>(v);
     return v;
 }
 
@@ -356,91 +418,348 @@ __device__ __forceinline__ double fx_wca_in(double s2, double r2, bool in)
     return in ? t * t : 0.0;
 }
 
-// The neighbours of every atom in the current sweep: the atoms of other
-// molecules within r_c + 2 sqrt(3) d of it at the sort (each of two atoms
-// moves at most sqrt(3) d in the sweep, so every pair that comes within its
-// cut-off is listed).  A wave per cell: the atoms of the 27 cells around it a
-// lane each (relative to the cell's centre, FP32), tested against the cell's
-// atoms one after another; the list keeps the order of the cell list.  Built
-// once per sweep by all waves side by side, it takes the search (158 atoms of
-// the 27 cells for about 18 within reach) out of the serial attempts: an
-// attempt then needs a row of 16 lanes instead of the whole wave.
-__device__ __forceinline__ void fx_build_lists(const FxK& K, const FxView& V, const double h[3], int wave,
+// The lists of one cell's atoms (list places q0 .. q0 + cnt, cnt <= 64) from
+// the atoms of the 27 cells around it, S of them per lane.  fold: nearest
+// image per pair.
+template <int S, bool kFold, bool kRes>
+__device__ __forceinline__ void fx_cell_lists(const FxK& K, const FxView<kRes>& V, uint32_t q0, uint32_t cnt, double ox,
+                                              double oy, double oz, int nseg, uint32_t delta, uint32_t off,
+                                              uint32_t total, const FxWaveLds& W)
+{
+    const uint32_t lane = (uint32_t)__lane_id(), n = K.n;
+    const float Lf = (float)K.L, iLf = (float)K.invL;
+    uint32_t id[S], mj[S], sg[S];
+    uint64_t have[S];  // lanes with an atom
+    float x[S], y[S], z[S];
+#pragma unroll
+    for (int u = 0; u < S; ++u) sg[u] = 0;
+    for (int t = 1; t < nseg; ++t) {  // the segment each place lies in
+        const uint32_t o = rl_u(off, t);
+#pragma unroll
+        for (int u = 0; u < S; ++u) sg[u] += 64u * (uint32_t)u + lane >= o ? 1u : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+        const uint32_t idx = 64u * (uint32_t)u + lane;
+        have[u] = __builtin_amdgcn_ballot_w64(idx < total);
+        const uint32_t d = (uint32_t)__shfl((int)delta, (int)sg[u]);
+        id[u] = V.cell_list[idx < total ? idx + d : q0];
+    }
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+        const FxAtom A = V.at(id[u]);
+        mj[u] = fx_mol(n, id[u]);
+        x[u] = (float)fx_mif(A.x - ox, K.L, K.invL);
+        y[u] = (float)fx_mif(A.y - oy, K.L, K.invL);
+        z[u] = (float)fx_mif(A.z - oz, K.L, K.invL);
+    }
+    uint32_t at = 0, mol = 0;  // lane q: the cell's atom q
+    float ax = 0.f, ay = 0.f, az = 0.f;
+    if (lane < cnt) {
+        at = V.cell_list[q0 + lane];
+        const FxAtom A = V.at(at);
+        mol = fx_mol(n, at);
+        ax = (float)fx_mif(A.x - ox, K.L, K.invL);
+        ay = (float)fx_mif(A.y - oy, K.L, K.invL);
+        az = (float)fx_mif(A.z - oz, K.L, K.invL);
+    }
+    using T = FxNbr<kRes>;
+    T* list = (T*)W.list;
+    constexpr uint32_t kWords = kFxNbr * sizeof(T) / 4u, kLdsWords = 64u * sizeof(T) / 4u;  // of a list
+    for (uint32_t qb = 0; qb < cnt; qb += kFxBuild) {
+        // the lists in LDS: no neighbour, the partners, then the neighbours
+        // compacted by ballots (those past the end share the last, spare entry)
+#pragma unroll
+        for (uint32_t t = 0; t < kFxBuild * kLdsWords; t += 256u)
+            ((W4*)W.list)[t / 4u + lane] = W4{~0u, ~0u, ~0u, ~0u};
+        wave_lds_sync();
+        {
+            const int q = (int)((qb + (lane >> 2)) & 63u);
+            const uint32_t p = lane & 3u, a = (uint32_t)__shfl((int)at, q), m = (uint32_t)__shfl((int)mol, q);
+            if (lane < 4u * kFxBuild && p + 1u < n)
+                list[64u * (lane >> 2) + p] = (T)(n * m + p + (p >= a - n * m ? 1u : 0u));
+        }
+        wave_lds_sync();
+        const uint32_t nq = min(kFxBuild, cnt - qb);
+#pragma unroll 2
+        for (uint32_t i = 0; i < nq; ++i) {
+            const int q = (int)(qb + i);
+            const float qx = rl_f(ax, q), qy = rl_f(ay, q), qz = rl_f(az, q);
+            const uint32_t qm = rl_u(mol, q);
+            uint32_t k = kFxPartners;
+#pragma unroll
+            for (int u = 0; u < S; ++u) {
+                float dx = x[u] - qx, dy = y[u] - qy, dz = z[u] - qz;
+                if (kFold) {
+                    dx = fmaf(-Lf, rintf(dx * iLf), dx);
+                    dy = fmaf(-Lf, rintf(dy * iLf), dy);
+                    dz = fmaf(-Lf, rintf(dz * iLf), dz);
+                }
+                const uint64_t bm = __builtin_amdgcn_ballot_w64(fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < K.list_r2) &
+                                    __builtin_amdgcn_ballot_w64(mj[u] != qm) & have[u];
+                const uint32_t kk = __builtin_amdgcn_mbcnt_hi((uint32_t)(bm >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)bm, k));
+                if (__builtin_amdgcn_inverse_ballot_w64(bm)) list[64u * i + min(kk, 63u)] = (T)id[u];
+                k += (uint32_t)__popcll(bm);
+            }
+            if (k > kFxNbr && lane == 0u) list[64u * i + kFxPartners] = (T)kFxOver;
+        }
+        wave_lds_sync();
+        // out, coalesced
+#pragma unroll
+        for (uint32_t t0 = 0; t0 < kFxBuild * kWords; t0 += 64u) {
+            const uint32_t r = (t0 + lane) / kWords, e = t0 + lane - kWords * r;
+            const uint32_t a = (uint32_t)__shfl((int)at, (int)((qb + r) & 63u));
+            const uint32_t v = ((const uint32_t*)W.list)[kLdsWords * r + e];
+            if (r < nq) ((Global<uint32_t>*)K.nbr)[(size_t)a * kWords + e] = v;
+        }
+        wave_lds_sync();
+    }
+}
+
+// The neighbours of every atom in the current sweep: the other atoms of its
+// molecule, and the atoms of other molecules within r_c + 2 sqrt(3) d of it at
+// the sort (each of two atoms moves at most sqrt(3) d in the sweep, so every
+// pair that comes within its cut-off is listed).  A wave per cell: the atoms
+// of the 27 cells around it up to kFxSlots to a lane (relative to the cell's
+// centre, FP32), tested against the cell's atoms one after another; a list
+// keeps the order of the cell list.  Built once per sweep by all waves side by
+// side, it takes the search (158 atoms of the 27 cells for about 18 within
+// reach) out of the serial attempts: an attempt then needs a row of 16 lanes
+// instead of the whole wave.  The lists are put together in LDS: stored from
+// the lanes that found them, 2 bytes at a time under a branch each, the build
+// of 3000 atoms' lists took 0.37 ms instead of 0.25.
+template <bool kRes>
+__device__ __forceinline__ void fx_build_lists(const FxK& K, const FxView<kRes>& V, const double h[3], int wave,
                                                uint32_t ncell, const FxWaveLds& W)
 {
-    const uint32_t lane = (uint32_t)__lane_id();
-    const uint32_t nc = K.nc, N = K.N, n = K.n;
-    const bool fold = nc <= 3u;  // the 27 cells span the box: nearest image per pair
-    const float Lf = (float)K.L, iLf = (float)K.invL;
+    const uint32_t nc = K.nc;
+    const bool fold = nc <= 3u;  // the 27 cells span the box
     for (uint32_t cell = (uint32_t)wave; cell < ncell; cell += kFxWaves) {
-        const uint32_t b = V.cell_start[cell], e = V.cell_start[cell + 1];
+        const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane((int)V.cell_start[cell]),
+                       e = (uint32_t)__builtin_amdgcn_readfirstlane((int)V.cell_start[cell + 1]);
         if (b >= e) continue;
         const uint32_t ix = cell % nc, iy = (cell / nc) % nc, iz = cell / (nc * nc);
         const double ox = h[0] + ((double)ix + 0.5) * K.w, oy = h[1] + ((double)iy + 0.5) * K.w,
                      oz = h[2] + ((double)iz + 0.5) * K.w;
-        uint32_t total;
-        const int nseg = fx_segments(K, V, (int)ix, (int)iy, (int)iz, 1, W, &total);
+        uint32_t lo, off, total;
+        const int nseg = fx_segments(K, V, (int)ix, (int)iy, (int)iz, &lo, &off, &total);
+        total = (uint32_t)__builtin_amdgcn_readfirstlane((int)total);
         for (uint32_t q0 = b; q0 < e; q0 += 64u) {
             const uint32_t cnt = min(64u, e - q0);
-            uint32_t at = 0, mol = 0, have = 0;  // lane q: atom q, its molecule, neighbours found
-            float ax = 0.f, ay = 0.f, az = 0.f;
-            if (lane < cnt) {
-                at = V.cell_list[q0 + lane];
-                mol = at / n;
-                ax = (float)fx_mi(V.pos[at] - ox, K.L, K.invL);
-                ay = (float)fx_mi(V.pos[N + at] - oy, K.L, K.invL);
-                az = (float)fx_mi(V.pos[2 * N + at] - oz, K.L, K.invL);
-            }
-            for (uint32_t c0 = 0; c0 < total; c0 += 192u) {
-                uint32_t id[3], mj[3];
-                float x[3], y[3], z[3];
-#pragma unroll
-                for (int u = 0; u < 3; ++u) {
-                    const uint32_t idx = c0 + 64u * (uint32_t)u + lane;
-                    id[u] = kFxNone;
-                    mj[u] = 0xFFFFFFFFu;
-                    x[u] = y[u] = z[u] = 1e9f;
-                    if (idx < total) {
-                        const uint32_t j = fx_stencil_atom(V, W, nseg, idx);
-                        id[u] = j;
-                        mj[u] = j / n;
-                        x[u] = (float)fx_mi(V.pos[j] - ox, K.L, K.invL);
-                        y[u] = (float)fx_mi(V.pos[N + j] - oy, K.L, K.invL);
-                        z[u] = (float)fx_mi(V.pos[2 * N + j] - oz, K.L, K.invL);
+            if (total > 64u * kFxSlots) {
+                // too many for the lanes: the rows of these atoms walk the cells
+                const uint32_t lane = (uint32_t)__lane_id();
+                if (lane < cnt) {
+                    const uint32_t a = V.cell_list[q0 + lane], m = fx_mol(K.n, a), sa = a - K.n * m;
+                    for (uint32_t p = 0; p < kFxNbr; ++p) {
+                        const uint32_t v = p + 1u < K.n ? K.n * m + p + (p >= sa ? 1u : 0u)
+                                                        : (p == kFxPartners ? kFxOver : kFxNone);
+                        ((Global<FxNbr<kRes>>*)K.nbr)[(size_t)a * kFxNbr + p] = (FxNbr<kRes>)v;
                     }
                 }
-                for (uint32_t q = 0; q < cnt; ++q) {
-                    const float qx = rl_f(ax, (int)q), qy = rl_f(ay, (int)q), qz = rl_f(az, (int)q);
-                    const uint32_t qm = rl_u(mol, (int)q);
-                    uint16_t* out = K.nbr + (size_t)rl_u(at, (int)q) * kFxNbr;
-                    uint32_t k = rl_u(have, (int)q);
+            } else if (fold) {
+                fx_cell_lists<kFxSlots, true>(K, V, q0, cnt, ox, oy, oz, nseg, lo - off, off, total, W);
+            } else if (total <= 192u) {
+                fx_cell_lists<3, false>(K, V, q0, cnt, ox, oy, oz, nseg, lo - off, off, total, W);
+            } else if (total <= 256u) {
+                fx_cell_lists<4, false>(K, V, q0, cnt, ox, oy, oz, nseg, lo - off, off, total, W);
+            } else {
+                fx_cell_lists<kFxSlots, false>(K, V, q0, cnt, ox, oy, oz, nseg, lo - off, off, total, W);
+            }
+        }
+    }
+}
+
+// dE of the rows W.row[0 .. nrow), nrow <= 4 G, against the present state into
+// W.sum: row r = 4 g + (lane / 16) is one changed atom of an attempt, a lane
+// per listed neighbour and per partner in its molecule (three passes of 16,
+// the third rarely filled).  The G evaluations of a lane are independent
+// chains side by side.
+template <int G, bool kLog, bool kRes>
+__device__ __forceinline__ void fx_eval_rows(const FxK& K, const FxView<kRes>& V, uint32_t nrow, bool logging,
+                                             const FxWaveLds& W)
+{
+    const uint32_t lane = (uint32_t)__lane_id(), row = lane >> 4, rl = lane & 15u;
+    bool act[G], fl[G];
+    uint32_t cl[G], bl[G], kl[G], perm[G], to[G], tn[G], j[G][3];
+    double xo[G], yo[G], zo[G], mx[G], my[G], mz[G], de[G], sc[G];
+    uint32_t terms[G];
 #pragma unroll
-                    for (int u = 0; u < 3; ++u) {
-                        float dx = x[u] - qx, dy = y[u] - qy, dz = z[u] - qz;
-                        if (fold) {
-                            dx = fmaf(-Lf, rintf(dx * iLf), dx);
-                            dy = fmaf(-Lf, rintf(dy * iLf), dy);
-                            dz = fmaf(-Lf, rintf(dz * iLf), dz);
+    for (int g = 0; g < G; ++g) {
+        const uint32_t r = 4u * (uint32_t)g + row;
+        act[g] = r < nrow;
+        const FxRow* R = W.row + (act[g] ? r : 0u);
+        mx[g] = R->tx; my[g] = R->ty; mz[g] = R->tz;
+        cl[g] = R->atom; bl[g] = R->base; kl[g] = R->kind;
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const Global<FxNbr<kRes>>* list = (Global<FxNbr<kRes>>*)K.nbr + (size_t)cl[g] * kFxNbr + rl;
+#pragma unroll
+        for (uint32_t u = 0; u < 3; ++u) j[g][u] = (uint32_t)(int32_t)list[16u * u];
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const FxAtom A = V.at(cl[g]);
+        xo[g] = A.x; yo[g] = A.y; zo[g] = A.z; to[g] = A.type;
+        fl[g] = kl[g] != kFxMove;
+        perm[g] = fx_pick(K.flipw, kl[g]);
+        const uint32_t tp = V.atom[bl[g] + ((perm[g] >> (8u * (cl[g] - bl[g]))) & 3u)].type;
+        tn[g] = fl[g] ? tp : to[g];
+        // the displacement of a translation; none for a flip
+        mx[g] = fl[g] ? 0.0 : mx[g] - xo[g];
+        my[g] = fl[g] ? 0.0 : my[g] - yo[g];
+        mz[g] = fl[g] ? 0.0 : mz[g] - zo[g];
+        de[g] = 0.0;
+        sc[g] = 0.0;
+        terms[g] = 0;
+        if (!act[g]) j[g][0] = j[g][1] = j[g][2] = kFxNone;
+    }
+    // the pairs of lane's neighbours (one per g): separations after the move
+    // are those before it plus the displacement; partner lanes (bond) hold
+    // atoms of the own molecule, whose type a flip may change too
+    auto pass = [&](const uint32_t (&jn)[G], const bool (&valid)[G], bool inner) __attribute__((always_inline)) {
+        uint32_t tj[G], tm[G];
+        double dx[G], dy[G], dz[G], num[G], den[G];
+        bool bond[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const FxAtom A = V.at(valid[g] ? jn[g] : cl[g]);
+            dx[g] = xo[g] - A.x; dy[g] = yo[g] - A.y; dz[g] = zo[g] - A.z;
+            tj[g] = tm[g] = A.type;
+            bond[g] = false;
+        }
+        if (inner) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                bond[g] = valid[g] && jn[g] - bl[g] < K.n;
+                const uint32_t sj = bond[g] ? jn[g] - bl[g] : 0u;
+                const uint32_t tp = V.atom[bl[g] + ((perm[g] >> (8u * sj)) & 3u)].type;
+                if (bond[g] && fl[g]) tm[g] = tp;
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            bool ok = valid[g];
+            if (inner) {
+                // a pair of two changed atoms counts in the row of the lower
+                const uint32_t sj = jn[g] - bl[g];
+                ok = ok && !(bond[g] && fl[g] && jn[g] < cl[g] && ((K.chgw >> (4u * (kl[g] & 3u) + (sj & 3u))) & 1u));
+            }
+            const double s2o = W.s2ij[4u * to[g] + tj[g]], s2n = W.s2ij[4u * tn[g] + tm[g]];
+            const double ux = fx_mif(dx[g], K.L, K.invL), uy = fx_mif(dy[g], K.L, K.invL),
+                         uz = fx_mif(dz[g], K.L, K.invL);
+            const double vx = ux + mx[g], vy = uy + my[g], vz = uz + mz[g];
+            const double r2o = fma(ux, ux, fma(uy, uy, uz * uz));
+            const double r2n = fma(vx, vx, fma(vy, vy, vz * vz));
+            const bool io = ok && r2o < K.rc2f * s2o, in = ok && r2n < K.rc2f * s2n;
+            const double uo = fx_wca_in(s2o, r2o, io), un = fx_wca_in(s2n, r2n, in);
+            de[g] += un - uo;
+            if (kLog) sc[g] += un + uo;
+            terms[g] += (io ? 1u : 0u) + (in ? 1u : 0u);
+            if (inner) {
+                const uint32_t sc0 = min(jn[g], cl[g]) - bl[g], sc1 = max(jn[g], cl[g]) - bl[g];
+                const bool fene = ok && bond[g] && ((K.bonded >> ((4u * sc0 + sc1) & 31u)) & 1u);
+                // Eq. (2): +inf at or beyond the limit, else the ratio of its
+                // arguments after and before the move
+                const double lo2 = 2.25 * s2o, ln2 = 2.25 * s2n;
+                const bool fo = r2o < lo2, fn = r2n < ln2, fin = fene && fo && fn;
+                num[g] = fin ? (ln2 - r2n) * lo2 : 1.0;
+                den[g] = fin ? (lo2 - r2o) * ln2 : 1.0;
+                if (fene) {
+                    if (!fin) de[g] += (fn ? 0.0 : __builtin_inf()) - (fo ? 0.0 : __builtin_inf());
+                    terms[g] += (fo ? 1u : 0u) + (fn ? 1u : 0u);
+                    if (kLog && logging)
+                        sc[g] += fx_fene(W.sij[4u * to[g] + tj[g]], r2o) + fx_fene(W.sij[4u * tn[g] + tm[g]], r2n);
+                }
+            }
+        }
+        if (inner) {
+            // the change of Eq. (2) in one logarithm; the partners sit on the
+            // first lanes of a row, so the second evaluation's go to lanes 8 ..
+            // and one division and one logarithm serve both
+            double nu = num[0], dn = den[0];
+            if (G == 2) {
+                const double n1 = dpp_move<0x128, 0xf>(num[G - 1]), d1 = dpp_move<0x128, 0xf>(den[G - 1]);  // row_ror:8
+                nu = rl < 8u ? nu : n1;
+                dn = rl < 8u ? dn : d1;
+            }
+            const double dl = -33.75 * log(nu / dn);
+            if (G == 2) {
+                de[0] += rl < 8u ? dl : 0.0;
+                de[G - 1] += rl < 8u ? 0.0 : dl;
+            } else {
+                de[0] += dl;
+            }
+        }
+    };
+    // a list that did not fit: its row walks the 27 cells instead
+    bool over[G];
+    bool any_over = false, any_third = false;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        over[g] = act[g] && (uint32_t)__shfl((int)j[g][0], (int)((lane & 48u) + kFxPartners)) == kFxOver;
+        any_over = any_over || over[g];
+        any_third = any_third || j[g][2] < kFxOver;
+    }
+    {
+        uint32_t jn[G];
+        bool ok[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            jn[g] = j[g][0];
+            ok[g] = j[g][0] < kFxOver && (!over[g] || rl < kFxPartners);
+        }
+        pass(jn, ok, true);
+#pragma unroll
+        for (int g = 0; g < G; ++g) { jn[g] = j[g][1]; ok[g] = j[g][1] < kFxOver && !over[g]; }
+        pass(jn, ok, false);
+        if (__ballot(any_third || any_over)) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) { jn[g] = j[g][2]; ok[g] = j[g][2] < kFxOver && !over[g]; }
+            pass(jn, ok, false);
+            if (__ballot(any_over)) {
+                const uint32_t nc = K.nc, span = min(nc, 3u);
+                for (uint32_t o = 0; o < span * span * span; ++o) {
+                    uint32_t q[G], ce[G];
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        const uint32_t cid = V.atom[cl[g]].cell;
+                        const uint32_t ix = cid % nc, iy = (cid / nc) % nc, iz = cid / (nc * nc);
+                        const uint32_t x = (ix + nc - 1u + o % span) % nc, y = (iy + nc - 1u + (o / span) % span) % nc,
+                                       z = (iz + nc - 1u + o / (span * span)) % nc;
+                        const uint32_t c = x + nc * (y + nc * z);
+                        q[g] = V.cell_start[c] + rl;
+                        ce[g] = over[g] ? V.cell_start[c + 1] : 0u;
+                    }
+                    for (;;) {
+                        bool more = false;
+#pragma unroll
+                        for (int g = 0; g < G; ++g) {
+                            const bool in = q[g] < ce[g];
+                            more = more || in;
+                            jn[g] = in ? V.cell_list[q[g]] : cl[g];
+                            ok[g] = in && jn[g] - bl[g] >= K.n;
+                            q[g] += 16u;
                         }
-                        const bool keep = fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < K.list_r2 && mj[u] != qm;
-                        const uint64_t bm = __ballot(keep);
-                        const uint32_t at_k = k + rank_below(bm);
-                        if (keep && at_k < kFxNbr) out[at_k] = (uint16_t)id[u];
-                        k += (uint32_t)__popcll(bm);
+                        if (!__ballot(more)) break;
+                        pass(jn, ok, false);
                     }
-                    if (lane == q) have = k;
                 }
             }
-            // pad the lists; mark those that did not fit
-            for (uint32_t q = 0; q < cnt; ++q) {
-                uint16_t* out = K.nbr + (size_t)rl_u(at, (int)q) * kFxNbr;
-                const uint32_t k = rl_u(have, (int)q);
-                if (k <= kFxNbr) {
-                    if (lane >= k && lane < kFxNbr) out[lane] = (uint16_t)kFxNone;
-                } else if (lane == 0) {
-                    out[0] = (uint16_t)kFxOver;
-                }
-            }
+        }
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const double rs = fx_row_sum(de[g]);
+        const uint32_t ts = fx_row_sum_u(terms[g]);
+        double ss = 0.0;
+        if (kLog) ss = fx_row_sum(sc[g]);
+        if (rl == 15u) {
+            W.sum[4u * (uint32_t)g + row] = rs;
+            W.terms[4u * (uint32_t)g + row] = ts;
+            if (kLog) W.scale[4u * (uint32_t)g + row] = ss;
         }
     }
 }
@@ -448,262 +767,101 @@ __device__ __forceinline__ void fx_build_lists(const FxK& K, const FxView& V, co
 // The attempts on up to 64 atoms of one cell (lane q holds atom q and its
 // proposal), in order, by one wave.
 //
-// Up to four attempts are evaluated side by side against the present state, a
-// row of 16 lanes for each atom that changes (one for a translation, two to
-// four for a flip; a flip's rows stay together): a lane per listed neighbour,
-// and on the first row of an attempt a lane per pair inside the molecule.
-// They are then decided in order.  An accepted attempt voids those after it in
-// the group that have a changed atom among their neighbours or in their own
-// molecule; the next group starts from the first void one, so every decision
-// is taken on the state its predecessors left, and dE does not depend on how
-// the attempts were grouped.  With 7 - 30 % accepted about three of four
-// stand.  The serial chain of a cell's attempts bounds the kernel (a system
-// runs on one compute unit); a group costs little more than one attempt by
-// the whole wave over the 27 cells' atoms did: a sweep of 1000 triangles at
-// T = 0.75 went from 2.80 to 1.22 ms, of 333 tetrahedra from 7.4 to 2.2 ms.
-__device__ __forceinline__ void fx_run_rows(const FxK& K, const FxView& V, uint32_t cnt,
-                                            uint32_t at, const FxProp& pr, uint64_t sweep, bool logging,
-                                            const FxWaveLds& W, FxCount& wc)
+// The next attempts, up to kFxRows changed atoms of them (one for a
+// translation, two to four for a flip), are evaluated side by side against the
+// present state, a row of 16 lanes per changed atom.  They are decided in
+// order: everything up to the first accepted one stands; those after it are
+// evaluated again on the state it leaves (in a cell nearly every pair of atoms
+// is within reach), so every decision is taken on its predecessors' state and
+// dE does not depend on how the attempts were grouped.  With 7 - 30 % accepted
+// a cell of 6 atoms takes one to three evaluations of 2 us.  The chain of
+// evaluations bounds the kernel (a system runs on one compute unit): a sweep
+// of 1000 triangles at T = 0.75 takes 0.78 ms, of 333 tetrahedra 1.37 ms (by
+// the whole wave, one attempt after another over the 27 cells' atoms, 2.80 and
+// 7.4 ms; two rows per 16 lanes against one 0.78 and 1.22 ms).
+template <bool kLog, bool kRes>
+__device__ __forceinline__ void fx_run_rows(const FxDev& Dv, const FxK& K, const FxView<kRes>& V, uint32_t cnt, uint32_t at,
+                                            const FxProp& pr, uint64_t sweep, bool logging, const FxWaveLds& W,
+                                            FxCount& wc)
 {
-    const uint32_t lane = (uint32_t)__lane_id(), row = lane >> 4, rl = lane & 15u;
-    const uint32_t n = K.n, N = K.N;
-    const uint32_t base = n * (at / n);
-    const bool mine = lane < cnt;
-    const uint64_t flips = __ballot(mine && pr.flip != 0u);
-    const uint64_t exits = __ballot(mine && pr.exited != 0u);
-    wc.att_f += (uint32_t)__popcll(flips);
-    wc.att_t += cnt - (uint32_t)__popcll(flips);
-    wc.exits += (uint32_t)__popcll(exits);
-    if (logging && mine && pr.exited) {
-        MoveRecord rec;
-        rec.delta_e = 0.0; rec.scale = 0.0; rec.t_log_u = pr.thr; rec.sweep = sweep;
-        rec.molecule = at; rec.move = MC_TRANSLATE; rec.accepted = 0; rec.exited = 1;
-        rec.axis = 255; rec.pair_terms = 0; rec.pad = 0;
-        K.log[(sweep - K.log_sweep0) * N + at] = rec;
-    }
-    uint64_t live = (cnt >= 64u ? ~0ull : (1ull << cnt) - 1ull) & ~exits;
-    // pair (i, j) inside the molecule on row lane 0 .. 5
-    const uint32_t pi = rl < 3u ? 0u : (rl < 5u ? 1u : 2u);
-    const uint32_t pj = rl < 3u ? rl + 1u : (rl < 5u ? rl - 1u : 3u);
-    const bool pair_lane = rl < 6u && pj < n;
+    const uint32_t lane = (uint32_t)__lane_id();
+    const uint32_t n = K.n;
+    const uint32_t base = n * fx_mol(n, at);
+    const bool flip = pr.kind != kFxMove;
+    const uint32_t chg = flip ? (K.chgw >> (4u * (pr.kind & 3u))) & 15u : 1u << (at - base);
+    uint64_t live = __ballot(lane < cnt && !(pr.cross & kFxExit));
     while (live) {
-        // ---- form a group: byte r of rows = attempt | atom of the molecule << 6
-        uint32_t rows = 0, nrow = 0, natt = 0;
-        uint32_t qa[4] = {0, 0, 0, 0}, r0[5] = {0, 0, 0, 0, 0};
-        {
-            uint64_t left = live;
+        // the rows: first row of each attempt by a prefix sum
+        uint32_t need = (live >> lane) & 1u ? (uint32_t)__popc(chg) : 0u;
+        const uint32_t end = wave_incl_scan(need);
+        const bool in = need != 0u && end <= kFxRows;
+        const uint64_t win = __ballot(in);
+        const uint32_t nrow = rl_u(end, 63 - __builtin_clzll(win));
+        if (in) {
+            uint32_t r = end - need;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                if (!left || natt != (uint32_t)g) continue;
-                const uint32_t q = (uint32_t)__builtin_ctzll(left);
-                uint32_t chg, need;
-                if ((flips >> q) & 1u) {
-                    chg = fx_pick(K.chg, rl_u(pr.kind, (int)q));
-                    need = (uint32_t)__popc(chg);
-                } else {
-                    chg = 1u << (rl_u(at, (int)q) - rl_u(base, (int)q));
-                    need = 1u;
-                }
-                if (nrow + need > 4u) continue;
-                qa[g] = q;
-                r0[g] = nrow;
+            for (uint32_t t = 0; t < 4; ++t)
+                if ((chg >> t) & 1u) W.row[r++] = FxRow{pr.tx, pr.ty, pr.tz, base + t, base, pr.kind, 0u};
+        }
+        wave_lds_sync();
+        if (nrow > 4u)
+            fx_eval_rows<2, kLog>(K, V, nrow, logging, W);
+        else
+            fx_eval_rows<1, kLog>(K, V, nrow, logging, W);
+        wave_lds_sync();
+        double dE = 0.0;
+        const uint32_t r0 = in ? end - need : 0u;
 #pragma unroll
-                for (uint32_t t = 0; t < 4; ++t)
-                    if ((chg >> t) & 1u) {
-                        rows |= (q | (t << 6)) << (8u * nrow);
-                        ++nrow;
-                    }
-                r0[g + 1] = nrow;
-                natt = (uint32_t)g + 1u;
-                left &= left - 1ull;
+        for (uint32_t t = 0; t < 4; ++t) {
+            const double v = W.sum[(r0 + t) & (kFxRows - 1u)];
+            if (t < need) dE += v;
+        }
+        const bool accept = in && ((dE <= 0.0) || (pr.thr < -dE));
+        const uint64_t acc = __ballot(accept);
+        const uint64_t done = acc ? win & ((acc & (0ull - acc)) * 2ull - 1ull) : win;
+        if ((done >> lane) & 1u) {
+            uint32_t tt = 0;
+            double S = 0.0;
+            for (uint32_t t = 0; t < need; ++t) {
+                tt += W.terms[r0 + t];
+                if (kLog) S += W.scale[r0 + t];
+            }
+            wc.terms += tt;
+            if (kLog && logging) {
+                MoveRecord rec;
+                rec.delta_e = dE; rec.scale = S; rec.t_log_u = pr.thr; rec.sweep = sweep;
+                rec.molecule = at; rec.move = flip ? MC_FLIP : MC_TRANSLATE; rec.accepted = accept ? 1 : 0;
+                rec.exited = 0; rec.axis = (uint8_t)pr.kind; rec.pair_terms = tt; rec.pad = 0;
+                Dv.log[(sweep - Dv.log_sweep0) * K.N + at] = rec;
             }
         }
-        // ---- the lanes' atoms and neighbours
-        const bool act = row < nrow;
-        const uint32_t info = act ? (rows >> (8u * row)) & 0xFFu : qa[0];
-        const int ql = (int)(info & 63u);
-        const uint32_t bl = (uint32_t)__shfl((int)base, ql), al = (uint32_t)__shfl((int)at, ql);
-        const uint32_t kl = (uint32_t)__shfl((int)pr.kind, ql);
-        const bool fl = kl != 255u;
-        const uint32_t cl = fl ? bl + (info >> 6) : al;
-        uint32_t j[3] = {kFxNone, kFxNone, kFxNone};
-        if (K.nbr != nullptr && act) {
-            const uint16_t* list = K.nbr + (size_t)cl * kFxNbr;
-#pragma unroll
-            for (int u = 0; u < 3; ++u) j[u] = list[16u * (uint32_t)u + rl];
-        }
-        // rows without a list (it did not fit, or the system has none)
-        const uint32_t head = K.nbr != nullptr ? (uint32_t)__shfl((int)j[0], (int)(lane & 48u)) : kFxOver;
-        const bool over = act && head == kFxOver;
-        const double xo = V.pos[cl], yo = V.pos[N + cl], zo = V.pos[2 * N + cl];
-        const double tx = __shfl(pr.tx, ql), ty = __shfl(pr.ty, ql), tz = __shfl(pr.tz, ql);
-        const double mx = fl ? 0.0 : tx - xo, my = fl ? 0.0 : ty - yo, mz = fl ? 0.0 : tz - zo;
-        const uint32_t perm = fx_pick(K.flipw, kl);
-        const uint32_t to = V.type[cl];
-        const uint32_t tn = fl ? (uint32_t)V.type[bl + ((perm >> (8u * (cl - bl))) & 0xFFu)] : to;
-        double de = 0.0, sc = 0.0;
-        uint32_t terms = 0;
-        // ---- pairs with other molecules: separations after a translation are
-        // those before it plus the displacement
-        auto eval = [&](uint32_t jn, bool valid) __attribute__((always_inline)) {
-            const uint32_t jj = valid ? jn : cl;
-            const double xj = V.pos[jj], yj = V.pos[N + jj], zj = V.pos[2 * N + jj];
-            const uint32_t tj = V.type[jj];
-            const double s2o = W.s2ij[4u * to + tj], s2n = W.s2ij[4u * tn + tj];
-            const double dx = fx_mi(xo - xj, K.L, K.invL), dy = fx_mi(yo - yj, K.L, K.invL),
-                         dz = fx_mi(zo - zj, K.L, K.invL);
-            const double ex = dx + mx, ey = dy + my, ez = dz + mz;
-            const double r2o = dx * dx + dy * dy + dz * dz;
-            const double r2n = ex * ex + ey * ey + ez * ez;
-            const bool io = valid && r2o < K.rc2f * s2o, in = valid && r2n < K.rc2f * s2n;
-            const double uo = fx_wca_in(s2o, r2o, io), un = fx_wca_in(s2n, r2n, in);
-            de += un - uo;
-            if (logging) sc += un + uo;
-            terms += (io ? 1u : 0u) + (in ? 1u : 0u);
-        };
-        if (!__ballot(over)) {
-#pragma unroll
-            for (int u = 0; u < 3; ++u) {
-                const bool valid = j[u] < kFxOver;
-                if (u && !__ballot(valid)) break;  // wave-uniform
-                eval(j[u], valid);
-            }
-        } else {
-            // the 27 cells around the cell the atom was sorted into (every
-            // cell once where they span the axis), a lane per atom
-            const uint32_t nc = K.nc, span = min(nc, 3u);
-            const uint32_t cid = V.cell_id[cl];
-            const uint32_t ix = cid % nc, iy = (cid / nc) % nc, iz = cid / (nc * nc);
-            const uint32_t listed = over ? 3u : 0u;
-            for (uint32_t u = 0; u < 3u; ++u) {
-                const uint32_t ju = u == 0 ? j[0] : (u == 1 ? j[1] : j[2]);
-                eval(ju, !listed && ju < kFxOver);
-            }
-            for (uint32_t o = 0; o < span * span * span; ++o) {
-                const uint32_t x = (ix + nc - 1u + o % span) % nc, y = (iy + nc - 1u + (o / span) % span) % nc,
-                               z = (iz + nc - 1u + o / (span * span)) % nc;
-                const uint32_t c = x + nc * (y + nc * z);
-                const uint32_t cb = V.cell_start[c], ce = over ? V.cell_start[c + 1] : cb;
-                for (uint32_t q = cb + rl; __ballot(q < ce); q += 16u) {
-                    const uint32_t ja = q < ce ? V.cell_list[q] : cl;
-                    eval(ja, q < ce && ja - bl >= n);
-                }
-            }
-        }
-        // ---- pairs inside the molecule that touch a changed atom, on the
-        // attempt's first row
-        {
-            bool first = false;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) first = first || ((uint32_t)g < natt && row == r0[g]);
-            const uint32_t chg = fl ? fx_pick(K.chg, kl) : 1u << (cl - bl);
-            const bool on = first && pair_lane && (((chg >> pi) | (chg >> pj)) & 1u);
-            if (on) {
-                const uint32_t ai = bl + pi, aj = bl + pj;
-                const double dx = fx_mi(V.pos[ai] - V.pos[aj], K.L, K.invL),
-                             dy = fx_mi(V.pos[N + ai] - V.pos[N + aj], K.L, K.invL),
-                             dz = fx_mi(V.pos[2 * N + ai] - V.pos[2 * N + aj], K.L, K.invL);
-                const double sg = ai == cl ? 1.0 : (aj == cl ? -1.0 : 0.0);  // m is 0 for a flip
-                const double ex = fma(sg, mx, dx), ey = fma(sg, my, dy), ez = fma(sg, mz, dz);
-                const double r2o = dx * dx + dy * dy + dz * dz;
-                const double r2n = ex * ex + ey * ey + ez * ez;
-                const uint32_t oi = V.type[ai], oj = V.type[aj];
-                uint32_t ni = oi, nj = oj;
-                if (fl) {
-                    ni = V.type[bl + ((perm >> (8u * pi)) & 0xFFu)];
-                    nj = V.type[bl + ((perm >> (8u * pj)) & 0xFFu)];
-                }
-                const double so = W.s2ij[4u * oi + oj], sn = W.s2ij[4u * ni + nj];
-                const bool io = r2o < K.rc2f * so, in = r2n < K.rc2f * sn;
-                const double uo = fx_wca_in(so, r2o, io), un = fx_wca_in(sn, r2n, in);
-                de += un - uo;
-                if (logging) sc += un + uo;
-                terms += (io ? 1u : 0u) + (in ? 1u : 0u);
-                if ((K.bonded >> (4u * pi + pj)) & 1u) {
-                    // the change of Eq. (2) in one logarithm: the ratio of the
-                    // arguments before and after; +inf at or beyond the limit
-                    const double lo2 = 2.25 * so, ln2 = 2.25 * sn;
-                    const bool fo = r2o < lo2, fn = r2n < ln2;
-                    if (fo && fn)
-                        de += -33.75 * log(((ln2 - r2n) * lo2) / ((lo2 - r2o) * ln2));
-                    else
-                        de += (fn ? 0.0 : __builtin_inf()) - (fo ? 0.0 : __builtin_inf());
-                    terms += (fo ? 1u : 0u) + (fn ? 1u : 0u);
-                    if (logging)
-                        sc += fx_fene(W.sij[4u * oi + oj], r2o) + fx_fene(W.sij[4u * ni + nj], r2n);
-                }
-            }
-        }
-        // ---- decide in order
-        const double rs = fx_row_sum(de);
-        double ss = 0.0;
-        uint32_t ts = 0;
-        if (logging) {
-            ss = fx_row_sum(sc);
-            ts = fx_row_sum_u(terms);
-        }
-        uint32_t void_rows = 0, done_rows = 0;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            if ((uint32_t)g >= natt) break;
-            const uint32_t rb = r0[g], re = r0[g + 1];
-            const uint32_t rmask = ((1u << re) - 1u) & ~((1u << rb) - 1u);
-            if (void_rows & rmask) break;  // evaluated on a state that has changed since
-            double dE = 0.0;
-            for (uint32_t r = rb; r < re; ++r) dE += rl_d(rs, (int)(16u * r + 15u));
-            const int q = (int)qa[g];
-            const bool flip = (flips >> q) & 1u;
-            const double thr = rl_d(pr.thr, q);
-            const bool accept = (dE <= 0.0) || (thr < -dE);
-            done_rows |= rmask;
-            live &= live - 1ull;
-            if (logging) {
-                double S = 0.0;
-                uint32_t tt = 0;
-                for (uint32_t r = rb; r < re; ++r) {
-                    S += rl_d(ss, (int)(16u * r + 15u));
-                    tt += rl_u(ts, (int)(16u * r + 15u));
-                }
-                if ((int)lane == q) {
-                    MoveRecord rec;
-                    rec.delta_e = dE; rec.scale = S; rec.t_log_u = thr; rec.sweep = sweep;
-                    rec.molecule = at; rec.move = flip ? MC_FLIP : MC_TRANSLATE; rec.accepted = accept ? 1 : 0;
-                    rec.exited = 0; rec.axis = (uint8_t)pr.kind; rec.pair_terms = tt; rec.pad = 0;
-                    K.log[(sweep - K.log_sweep0) * N + at] = rec;
-                }
-            }
-            if (!accept) continue;
-            wc.e += dE;
-            if (flip) wc.acc_f += 1; else wc.acc_t += 1;
-            if (rl == 0u && row >= rb && row < re) {
+        live &= ~done;
+        if (acc) {
+            const int q = (int)__builtin_ctzll(acc);
+            wc.e += rl_d(dE, q);
+            if (rl_u(pr.kind, q) != kFxMove) wc.acc_f += 1; else wc.acc_t += 1;
+            if ((int)lane == q) {
                 if (flip) {
-                    V.type[cl] = (uint8_t)tn;
-                } else {
-                    // wrapped as fx_wrap does; the shifts are the periodic
-                    // images crossed
-                    const double fx = floor(tx / K.L), fy = floor(ty / K.L), fz = floor(tz / K.L);
-                    V.pos[cl] = tx - K.L * fx;
-                    V.pos[N + cl] = ty - K.L * fy;
-                    V.pos[2 * N + cl] = tz - K.L * fz;
-                    if ((int)fx) K.img[cl] += (int)fx;
-                    if ((int)fy) K.img[N + cl] += (int)fy;
-                    if ((int)fz) K.img[2 * N + cl] += (int)fz;
-                }
-            }
-            if ((uint32_t)g + 1u < natt) {
-                // attempts after this one that a changed atom reaches
-                bool hit = over || bl == rl_u(base, q);
-                for (uint32_t r = rb; r < re; ++r) {
-                    const uint32_t c = rl_u(cl, (int)(16u * r));
-                    hit = hit || j[0] == c || j[1] == c || j[2] == c;
-                }
-                const uint64_t hb = __ballot(hit && row >= re && act);
+                    const uint32_t perm = fx_pick(K.flipw, pr.kind);
+                    uint32_t t[4];
 #pragma unroll
-                for (uint32_t r = 0; r < 4; ++r)
-                    if ((hb >> (16u * r)) & 0xFFFFull) void_rows |= 1u << r;
+                    for (uint32_t u = 0; u < 4; ++u) t[u] = V.atom[base + (u < n ? (perm >> (8u * u)) & 3u : 0u)].type;
+#pragma unroll
+                    for (uint32_t u = 0; u < 4; ++u)
+                        if ((chg >> u) & 1u) V.atom[base + u].type = t[u];
+                } else {
+                    // wrapped; the shifts are the periodic images crossed
+                    const int fx = (int)(pr.cross & 3u) - 1, fy = (int)((pr.cross >> 2) & 3u) - 1,
+                              fz = (int)((pr.cross >> 4) & 3u) - 1;
+                    V.atom[at].x = pr.tx - K.L * (double)fx;
+                    V.atom[at].y = pr.ty - K.L * (double)fy;
+                    V.atom[at].z = pr.tz - K.L * (double)fz;
+                    if (fx) K.img[at] += fx;
+                    if (fy) K.img[K.N + at] += fy;
+                    if (fz) K.img[2 * K.N + at] += fz;
+                }
             }
         }
-        if ((done_rows >> row) & 1u) wc.terms += terms;
         wave_lds_sync();
     }
 }
@@ -740,15 +898,19 @@ __device__ void fx_sort_cells(uint32_t* list, const uint32_t* start, uint32_t c0
 }
 
 // The hot kernel: n sweeps of one system on one workgroup.  With kRes the
-// positions, types and cell lists live in LDS for the whole launch (copied in
-// at the start, positions and types written back at the end); otherwise the
-// same code runs on the arrays in the system's buffer.
-template <bool kRes>
+// atoms and cell lists live in LDS for the whole launch; otherwise the same
+// code runs on arrays in the system's buffer.  Positions and types are copied
+// in at the start and written back at the end.  kLog: some system of the
+// launch has a decision log.
+template <bool kRes, bool kLog>
 __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t n_sweeps)
 {
     FxDev* __restrict__ Dp = list.d[blockIdx.x];
-    __shared__ uint32_t seg[kFxWaves][2][kFxSeg];
     __shared__ double pair_s[16], pair_s2[16];
+    __shared__ FxRow rows[kFxWaves][kFxRows];
+    __shared__ uint32_t rterms[kFxWaves][kFxRows];
+    __shared__ double rsum[kFxWaves][kFxRows], rscale[kLog ? kFxWaves : 1][kFxRows];
+    __shared__ __align__(16) FxNbr<kRes> lists[kFxWaves][kFxBuild * 64];
     __shared__ uint32_t scratch[kFxWaves];
     __shared__ double misc[2];
     __shared__ double dmax2[kFxWaves];
@@ -756,27 +918,34 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
     const FxDev& D = *Dp;
     const FxK K = fx_const(D);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    FxWaveLds W{seg[wave][0], seg[wave][1], pair_s, pair_s2};
+    FxWaveLds W{rows[wave], rsum[wave], rscale[kLog ? wave : 0], rterms[wave], lists[wave], pair_s, pair_s2};
     Stats* st = D.stats;
     const uint32_t N = D.N, ncell = D.ncell, nc = D.nc, k = D.k;
-    FxView V{D.pos, D.type, D.cell_start, D.cell_list, D.cell_id, D.ecell};
-    if (kRes) {
+    FxView<kRes> V;
+    if constexpr (kRes) {
         const FxLds l = fx_lds_layout(N, ncell);
-        V = FxView{(double*)(fx_smem + l.pos), (uint8_t*)(fx_smem + l.type), (uint32_t*)(fx_smem + l.cstart),
-                   (uint32_t*)(fx_smem + l.clist), (uint32_t*)(fx_smem + l.cid), (double*)(fx_smem + l.ecell)};
-        for (uint32_t i = tid; i < 3 * N; i += kFxThreads) V.pos[i] = D.pos[i];
-        for (uint32_t i = tid; i < N; i += kFxThreads) V.type[i] = D.type[i];
-        __syncthreads();
+        V = FxView<kRes>{(Lds<FxAtom>*)(fx_smem + l.atom), (Lds<uint32_t>*)(fx_smem + l.cstart),
+                         (Lds<uint32_t>*)(fx_smem + l.clist), (Lds<double>*)(fx_smem + l.ecell)};
+    } else {
+        V = FxView<kRes>{(Global<FxAtom>*)D.atom, (Global<uint32_t>*)D.cell_start, (Global<uint32_t>*)D.cell_list,
+                         (Global<double>*)D.ecell};
+    }
+    for (uint32_t i = tid; i < N; i += kFxThreads)
+    {
+        auto* a = V.atom + i;
+        a->x = D.pos[i]; a->y = D.pos[N + i]; a->z = D.pos[2 * N + i];
+        a->type = D.type[i]; a->cell = 0u;
     }
     const uint32_t na = nc / k, nact = na * na * na;
     uint64_t sweep = st->sweep;
     const uint64_t origin = st->obs_origin;
     if (tid == 0) misc[0] = st->e_acc;
     if (tid < 16) {
-        const double sg = 0.5 * (fx_pick(K.sigma, (uint32_t)tid >> 2) + fx_pick(K.sigma, (uint32_t)tid & 3u));
+        const double sg = 0.5 * (D.sigma[tid >> 2] + D.sigma[tid & 3]);
         pair_s[tid] = sg;
         pair_s2[tid] = sg * sg;
     }
+    __syncthreads();
     FxCount wc{};
     for (uint64_t it = 0; it < n_sweeps; ++it) {
         const U4 g = philox10(0xFFFFFFFFu, (uint32_t)sweep, (uint32_t)(sweep >> 32), 3u, K.seed_lo, K.seed_hi);
@@ -785,22 +954,21 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
         for (uint32_t c = tid; c <= ncell; c += kFxThreads) V.cell_start[c] = 0;
         __syncthreads();
         for (uint32_t i = tid; i < N; i += kFxThreads) {
-            const uint32_t c = fx_cell(V.pos[i], V.pos[N + i], V.pos[2 * N + i], h, K);
-            V.cell_id[i] = c;
-            atomicAdd(&V.cell_start[c + 1], 1u);
+            const uint32_t c = fx_cell(V.atom[i].x, V.atom[i].y, V.atom[i].z, h, K);
+            V.atom[i].cell = c;
+            atomicAdd((uint32_t*)&V.cell_start[c + 1], 1u);
         }
         __syncthreads();
-        block_excl_scan_t<kFxThreads>(V.cell_start + 1, ncell, scratch);
+        block_excl_scan_t<kFxThreads>((uint32_t*)(V.cell_start + 1), ncell, scratch);
         for (uint32_t i = tid; i < N; i += kFxThreads)
-            V.cell_list[atomicAdd(&V.cell_start[V.cell_id[i] + 1], 1u)] = i;
+            V.cell_list[atomicAdd((uint32_t*)&V.cell_start[V.atom[i].cell + 1], 1u)] = i;
         __syncthreads();
-        fx_sort_cells(V.cell_list, V.cell_start, (uint32_t)wave, kFxWaves, ncell);
+        fx_sort_cells((uint32_t*)V.cell_list, (const uint32_t*)V.cell_start, (uint32_t)wave, kFxWaves, ncell);
         __syncthreads();
-        if (K.nbr != nullptr) {
-            fx_build_lists(K, V, h, wave, ncell, W);
-            __syncthreads();
-        }
-        const bool logging = D.log != nullptr && sweep - D.log_sweep0 < D.log_sweeps;
+        const bool logging = kLog && D.log != nullptr && sweep - D.log_sweep0 < D.log_sweeps;
+        fx_propose_all(D, K, V, sweep, h, logging, wc);
+        fx_build_lists(K, V, h, wave, ncell, W);
+        __syncthreads();
         // The cells of a colour are attempted in ascending index; they run
         // side by side when no attempt in one can reach an atom another
         // reads or writes.  Two attempted atoms of different cells are at
@@ -820,13 +988,12 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
                                                                   nc * (kz + k * (ci / (na * na))));
                 const uint32_t b = V.cell_start[cell], e = V.cell_start[cell + 1];
                 for (uint32_t q = b + (uint32_t)lane; q < e; q += 64u) {
-                    const uint32_t base = n * (V.cell_list[q] / n);
+                    const uint32_t base = n * fx_mol(n, V.cell_list[q]);
                     for (uint32_t i = 0; i + 1 < n; ++i)
                         for (uint32_t j = i + 1; j < n; ++j) {
-                            const double dx = fx_mi(V.pos[base + i] - V.pos[base + j], K.L, K.invL);
-                            const double dy = fx_mi(V.pos[N + base + i] - V.pos[N + base + j], K.L, K.invL);
-                            const double dz =
-                                fx_mi(V.pos[2 * N + base + i] - V.pos[2 * N + base + j], K.L, K.invL);
+                            const double dx = fx_mif(V.atom[base + i].x - V.atom[base + j].x, K.L, K.invL);
+                            const double dy = fx_mif(V.atom[base + i].y - V.atom[base + j].y, K.L, K.invL);
+                            const double dz = fx_mif(V.atom[base + i].z - V.atom[base + j].z, K.L, K.invL);
                             d2 = fmax(d2, dx * dx + dy * dy + dz * dz);
                         }
                 }
@@ -840,34 +1007,57 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
             __syncthreads();
             return K.sep >= 2.0 * sqrt(dm) + K.dyn_base;
         };
-        // the attempts of cell `ci` of a colour by this wave
-        auto run_cell = [&](uint32_t kx, uint32_t ky, uint32_t kz, uint32_t ci) __attribute__((always_inline)) {
-            const uint32_t cell = (kx + k * (ci % na)) + nc * ((ky + k * ((ci / na) % na)) +
-                                                              nc * (kz + k * (ci / (na * na))));
-            wc.e = 0.0;
+        // Cell number i of the colours in order; a wave takes number `wave` of
+        // each colour and every kFxWaves-th after it.
+        auto cell_of = [&](uint32_t col, uint32_t ci) __attribute__((always_inline)) {
+            const uint32_t kx = col % k, ky = (col / k) % k, kz = col / (k * k);
+            return (kx + k * (ci % na)) + nc * ((ky + k * ((ci / na) % na)) + nc * (kz + k * (ci / (na * na))));
+        };
+        const uint32_t ncol = k * k * k;
+        // The lines of the wave's next cell (its proposals and the lists of its
+        // molecules' atoms) are brought near while the present cell is attempted.
+        uint32_t touched = 0;
+        auto touch = [&](uint32_t cell) __attribute__((always_inline)) {
             const uint32_t b = V.cell_start[cell], e = V.cell_start[cell + 1];
-            if (b < e) {
-                for (uint32_t q0 = b; q0 < e; q0 += 64u) {
-                    const uint32_t cnt = min(64u, e - q0);
-                    uint32_t at = 0;
-                    FxProp pr{};
-                    if ((uint32_t)lane < cnt) {
-                        at = V.cell_list[q0 + lane];
-                        pr = fx_propose(K, V, at, sweep, h, cell);
-                    }
-                    fx_run_rows(K, V, cnt, at, pr, sweep, logging, W, wc);
+            const uint32_t q = b + (uint32_t)(lane >> 3), s = (uint32_t)(lane >> 1) & 3u;
+            if (q < e) {
+                const uint32_t c = K.n * fx_mol(K.n, V.cell_list[q]) + s;
+                if (s < K.n)
+                    touched = (uint32_t)((Global<FxNbr<kRes>>*)K.nbr)[(size_t)c * kFxNbr + (lane & 1 ? kFxNbr - 1u : 0u)];
+                else
+                    touched = K.props[q].kind;
+            }
+        };
+        // the attempts of cell `ci` of colour `col` by this wave
+        auto run_cell = [&](uint32_t col, uint32_t ci) __attribute__((always_inline)) {
+            const uint32_t cell = cell_of(col, ci);
+            const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane((int)V.cell_start[cell]),
+                           e = (uint32_t)__builtin_amdgcn_readfirstlane((int)V.cell_start[cell + 1]);
+            wc.e = 0.0;
+            for (uint32_t q0 = b; q0 < e; q0 += 64u) {
+                const uint32_t cnt = min(64u, e - q0);
+                uint32_t at = 0;
+                FxProp pr{};
+                if ((uint32_t)lane < cnt) {
+                    at = V.cell_list[q0 + lane];
+                    const Global<FxProp>* in = K.props + (q0 + (uint32_t)lane);
+                    pr = FxProp{in->thr, in->tx, in->ty, in->tz, in->kind, in->cross};
                 }
+                asm volatile("" ::"v"(touched));
+                const bool last = ci + kFxWaves >= nact;
+                if (!last || col + 1u < ncol) touch(last ? cell_of(col + 1u, (uint32_t)wave) : cell_of(col, ci + kFxWaves));
+                fx_run_rows<kLog>(D, K, V, cnt, at, pr, sweep, logging, W, wc);
             }
             if (lane == 0) V.ecell[cell] = wc.e;
         };
-        for (uint32_t col = 0; col < k * k * k; ++col) {
+        for (uint32_t col = 0; col < ncol; ++col) {
             const uint32_t kx = col % k, ky = (col / k) % k, kz = col / (k * k);
             if (colour_together(kx, ky, kz)) {
-                for (uint32_t ci = (uint32_t)wave; ci < nact; ci += kFxWaves) run_cell(kx, ky, kz, ci);
+                for (uint32_t ci = (uint32_t)wave; ci < nact; ci += kFxWaves) run_cell(col, ci);
                 __syncthreads();
             } else {
                 for (uint32_t ci = 0; ci < nact; ++ci) {
-                    if (ci % kFxWaves == (uint32_t)wave) run_cell(kx, ky, kz, ci);
+                    if (ci % kFxWaves == (uint32_t)wave) run_cell(col, ci);
                     __syncthreads();
                 }
             }
@@ -875,7 +1065,7 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
         ++sweep;
         // E_acc += the sweep's dE, the cells in a fixed order; E/M samples
         if (wave == 0) {
-            const double e = misc[0] + sweep_energy(V.ecell, ncell);
+            const double e = misc[0] + sweep_energy((const double*)V.ecell, ncell);
             if (lane == 0) misc[0] = e;
         }
         if (tid == 0) {
@@ -890,23 +1080,27 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
         }
         __syncthreads();
     }
-    if (lane == 0) {
-        if (wc.att_t) atomicAdd((unsigned long long*)&st->attempts[MC_TRANSLATE], (unsigned long long)wc.att_t);
-        if (wc.att_f) atomicAdd((unsigned long long*)&st->attempts[MC_FLIP], (unsigned long long)wc.att_f);
-        if (wc.acc_t) atomicAdd((unsigned long long*)&st->accepts[MC_TRANSLATE], (unsigned long long)wc.acc_t);
-        if (wc.acc_f) atomicAdd((unsigned long long*)&st->accepts[MC_FLIP], (unsigned long long)wc.acc_f);
-        if (wc.exits) atomicAdd((unsigned long long*)&st->exits, (unsigned long long)wc.exits);
-    }
     {
-        uint64_t t = wc.terms;
+        const uint32_t att_t = wave_sum_u(wc.att_t), att_f = wave_sum_u(wc.att_f), exits = wave_sum_u(wc.exits);
+        unsigned long long terms = wc.terms;
 #pragma unroll
-        for (int o = 32; o; o >>= 1) t += (uint64_t)__shfl_xor((unsigned long long)t, o);
-        if (lane == 0 && t) atomicAdd((unsigned long long*)&st->pair_terms, (unsigned long long)t);
+        for (int o = 32; o; o >>= 1) terms += __shfl_xor(terms, o);
+        if (lane == 0) {
+            if (att_t) atomicAdd((unsigned long long*)&st->attempts[MC_TRANSLATE], (unsigned long long)att_t);
+            if (att_f) atomicAdd((unsigned long long*)&st->attempts[MC_FLIP], (unsigned long long)att_f);
+            if (wc.acc_t) atomicAdd((unsigned long long*)&st->accepts[MC_TRANSLATE], (unsigned long long)wc.acc_t);
+            if (wc.acc_f) atomicAdd((unsigned long long*)&st->accepts[MC_FLIP], (unsigned long long)wc.acc_f);
+            if (exits) atomicAdd((unsigned long long*)&st->exits, (unsigned long long)exits);
+            if (terms) atomicAdd((unsigned long long*)&st->pair_terms, terms);
+        }
     }
     __syncthreads();
-    if (kRes) {
-        for (uint32_t i = tid; i < 3 * N; i += kFxThreads) D.pos[i] = V.pos[i];
-        for (uint32_t i = tid; i < N; i += kFxThreads) D.type[i] = V.type[i];
+    for (uint32_t i = tid; i < N; i += kFxThreads) {
+        const FxAtom A = V.at(i);
+        D.pos[i] = A.x;
+        D.pos[N + i] = A.y;
+        D.pos[2 * N + i] = A.z;
+        D.type[i] = (uint8_t)A.type;
     }
     if (tid == 0) {
         st->sweep = sweep;

@@ -14,6 +14,14 @@ namespace {
 
 constexpr double kTwoPi = 6.283185307179586;
 
+// Pointers whose address space the type states.  Through a plain pointer read
+// from a descriptor the compiler can only use FLAT instructions, which count as
+// LDS operations too, so every wait for LDS also waits for them.
+template <typename T>
+using Global = __attribute__((address_space(1))) T;
+template <typename T>
+using Lds = __attribute__((address_space(3))) T;
+
 struct U4 {
     uint32_t x, y, z, w;
 };
@@ -118,16 +126,29 @@ __device__ __forceinline__ double sweep_energy(const double* ecell, uint32_t nce
 }
 
 // Exclusive prefix sum over the wave; *total gets the wave total.
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ uint32_t dpp_move_u(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, kRowMask, 0xf, true);
+}
+
+// Inclusive prefix sum over the wave, in the steps of wave_sum_dpp (six adds;
+// as lane shuffles it was six LDS round trips).
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
+{
+    v += dpp_move_u<0x111, 0xf>(v);
+    v += dpp_move_u<0x112, 0xf>(v);
+    v += dpp_move_u<0x114, 0xf>(v);
+    v += dpp_move_u<0x118, 0xf>(v);
+    v += dpp_move_u<0x142, 0xa>(v);
+    v += dpp_move_u<0x143, 0xc>(v);
+    return v;
+}
+
 __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t* total)
 {
-    const int lane = __lane_id();
-    uint32_t inc = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = __shfl_up(inc, o);
-        if (lane >= o) inc += t;
-    }
-    *total = __shfl(inc, 63);
+    const uint32_t inc = wave_incl_scan(v);
+    *total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
     return inc - v;
 }
 
