@@ -66,8 +66,8 @@ enum { MC_FLAG_HBM_STATE = 1, MC_FLAG_SINGLE_WORKGROUP = 2 };
 enum { MC_FLAG_SERIAL_CELLS = 4 };
 
 /* Engines (mc_engine): one workgroup with the state in LDS, one workgroup
- * with the state in HBM, many workgroups in one cooperative launch with the
- * state in HBM and each cell's neighbourhood staged in LDS. */
+ * with the state in HBM, many workgroups that share a system, with the state in
+ * HBM and each cell's neighbourhood staged in LDS. */
 enum { MC_ENGINE_LDS = 0, MC_ENGINE_HBM = 1, MC_ENGINE_SPREAD = 2 };
 
 #define MC_GOFR_MAX_BINS 256
@@ -112,10 +112,11 @@ typedef struct {
     uint32_t workgroups;       /* workgroups of mc_sweep's launches: 0 = the engine's
                                   cost model; 1 = one workgroup (as
                                   MC_FLAG_SINGLE_WORKGROUP); n >= 2 = the
-                                  multi-workgroup engine on min(n, cells of a colour
-                                  / 4 rounded up, device limit) workgroups, also the
-                                  most a batch gives the system.  Every choice gives
-                                  bitwise the same chain (an autotuner's knob)       */
+                                  multi-workgroup engine on n workgroups, also the
+                                  most a batch gives the system, or from a quarter of
+                                  the cells of a colour on (rounded up) on one per
+                                  cell.  Every choice gives bitwise the same chain (an
+                                  autotuner's knob)                                   */
     double   fs_q;             /* |q| of F_s(q, t) over the sites (Sec. III.B: 7.4,
                                   the first peak of the structure factor)             */
     double   fs_q_cm;          /* |q| of F_s^cm(q, t) over the centres (5.1)         */
@@ -213,13 +214,16 @@ int mc_geometry(const mc_params* p, double* box, uint32_t* colours_per_axis,
 int mc_placement(const mc_params* p, int* resident, size_t* lds_bytes);
 
 /* The engine mc_sweep uses for a system with these parameters (MC_ENGINE_*)
- * and, for MC_ENGINE_SPREAD, the number of workgroups of its launches
- * (*workgroups = 1 otherwise).  A system beyond one workgroup's LDS runs on
- * the multi-workgroup engine; one within it runs there too when a wave per
- * cell of a colour gives it enough workgroups to be modelled 25 % faster
- * (FP32 systems of 1114 - 1728 molecules with k = 2, n_c = 6), else on its
- * LDS workgroup.  Inside a batch the engine is chosen per run (see
- * mc_batch_run).  Either output may be NULL. */
+ * and, for MC_ENGINE_SPREAD, the number of its workgroups, counted as one for
+ * four cells of a colour (*workgroups = 1 otherwise).  A system beyond one
+ * workgroup's LDS runs on the multi-workgroup engine, and so does one within it
+ * that has more than 16 cells per colour.  A system alone in its launch gets a
+ * workgroup per cell of a colour, up to the compute units of the device; one
+ * named MC_ENGINE_LDS runs that way too when that is modelled 25 % faster than
+ * its one workgroup, without other workgroups to ask for it (flags or
+ * workgroups = 1 keep it on one).  Workgroups that find no room beside other
+ * work take no part: any number gives the same results.  Inside a batch the
+ * engine is chosen per run (see mc_batch_run).  Either output may be NULL. */
 int mc_engine(const mc_params* p, int* engine, uint32_t* workgroups);
 
 /* Bytes of device memory mc_init_system needs for these parameters (state of
@@ -510,15 +514,15 @@ int mcf_dynamics(const mc_obs* runs, size_t n_runs, uint32_t n_molecules, uint32
  * A batch holds up to max_slots systems of one precision.  Each
  * mc_batch_run gives every system one workgroup; the workgroups left over
  * (up to the batch's workgroup limit, one per compute unit by default) go to
- * the systems with the most remaining work that can use several (those
- * beyond one workgroup's LDS, and those within it when enough workgroups are
- * idle to make them modelled 25 % faster), which then run on the
- * multi-workgroup engine, each on up to the workgroups its cells allow.
+ * the systems that are modelled to finish last and can use several (those
+ * beyond one workgroup's LDS, and those within it when that is modelled 25 %
+ * faster), which then run on the multi-workgroup engine, each on up to one
+ * workgroup per cell of a colour.
  * Systems on one workgroup share one persistent launch per
  * placement class (state in LDS / in HBM; the HBM class beside the LDS
  * class on a third caller stream when mc_batch_set_hbm_stream gives one);
- * systems on the multi-workgroup engine share one cooperative launch on the
- * caller's second stream (hip_stream_aux of mc_batch_create).
+ * systems on the multi-workgroup engine share one launch on the caller's
+ * second stream (hip_stream_aux of mc_batch_create).
  * All engines make the same decisions and sum the energy in the same order,
  * so a system gives bitwise the same results in a batch as alone, whichever
  * engines its runs used. */
@@ -551,8 +555,7 @@ int mc_batch_add(mc_batch* b, mc_system* s, uint64_t n_sweeps, uint32_t* slot);
  * round of workgroups.  Every launch of the run is sized to
  * the time a 1000-molecule system (k = 2, n_c = 4) takes for
  * max_moves_per_slot moves on one workgroup: each system's slice is that time
- * over its modelled sweep time (one-workgroup cost model, divided by its
- * workgroups on the multi-workgroup engine), scaled per engine by the time
+ * over its modelled sweep time on its workgroups, scaled per engine by the time
  * per modelled cycle measured on the batch's earlier launches; at least one
  * sweep.  Slices also stop at each system's re-sum / g(r) / C_2 sweeps, whose
  * work follows in a second launch.  *n_launched = number of sweep launches

@@ -103,17 +103,28 @@ struct Geometry {
     double L, bond, radius, reach;
     uint32_t k, nc, ncell;
     bool resident;
-    bool spread;          // standalone sweeps on the multi-workgroup engine
-    uint32_t spread_blocks;  // its workgroups (also of an LDS system a batch may move there)
-    size_t lds;
+    uint32_t near_cap;    // molecules listed near a cell
+    bool spread;          // standalone sweeps are the multi-workgroup engine's (mc_engine)
+    bool team;            // standalone sweeps run on its workgroups
+    uint32_t spread_blocks;  // its workgroups in units of four cells of a colour (mc_engine)
+    uint32_t team_blocks;    // the workgroups it launches alone, the most it takes in a batch
+    bool lists;              // the multi-workgroup engine has the cell lists in LDS
+    uint32_t wave_fit;       // cells that its workgroups have room for with one per wave
+    uint32_t team_waves;     // waves with a cell each when it runs alone
+    size_t lds;              // LDS of the one-workgroup engine
     double sweep_cost;    // modelled cycles of one sweep on one workgroup
-    double spread_cost;   // the same with the state in HBM (the multi-workgroup engine's unit)
+    // Modelled cycles of a sweep on nb workgroups with a cell per wave (waves) or
+    // per workgroup.
+    double spread_cycles(uint32_t M, uint32_t nb, bool waves) const;
+    // Whether the buffer has the multi-workgroup engine's arrays.
+    bool team_arrays() const { return !resident || team || team_blocks >= 2; }
 };
 
-// Critical path of one sweep of the resident kernel in cycles (a model fitted
-// to measured per-cell and per-trial costs): k^3 colour phases; in each, the
-// busiest wave builds the neighbour list of each of its cells and runs the
-// cell's trials one after another.
+// The critical path of one sweep of the resident kernel, as the choice of the
+// decomposition has always taken it (the same parameters keep the same cells,
+// and with them the same chain): k^3 colour phases; in each, the busiest wave
+// builds the neighbour list of each of its cells and runs the cell's trials one
+// after another.
 double cost_estimate(uint32_t M, double L, double reach, uint32_t k, uint32_t nc)
 {
     const double ncell = (double)nc * nc * nc;
@@ -130,21 +141,56 @@ double cost_estimate(uint32_t M, double L, double reach, uint32_t k, uint32_t nc
     return (double)k * k * k * (cells_per_wave * (t_list + std::max(1.0, per_cell) * t_trial) + 300.0);
 }
 
+// Cycles of a sweep on one workgroup, for the sizes of time slices and the
+// choice of the engine.  Fitted to 216 (k = 3, n_c = 6), 512 and 1000 (k = 2,
+// n_c = 4) and 1728 (n_c = 6) molecules in LDS: 195, 180, 313 and 565 us.
+double sweep_cycles(uint32_t M, uint32_t k, uint32_t nc)
+{
+    const double per_cell = std::max(1.0, (double)M / ((double)nc * nc * nc));
+    const double cells_per_wave = std::ceil(std::pow((double)(nc / k), 3.0) / kWaves);
+    return (double)k * k * k * (cells_per_wave * (6000.0 + 4800.0 * per_cell) + 6000.0);
+}
+
+// The same for the multi-workgroup engine on nb workgroups with a cell each:
+// a workgroup's waves list the neighbourhood together and evaluate kWaves trials
+// at once, of which the decisions use those up to the first accepted one
+// (measured: 3.5 rounds for 16 trials at T = 0.75, 2.3 for 8 at T = 1.1); cells
+// wait for their neighbours at every colour and all workgroups three times a
+// sweep.
+double team_cycles(uint32_t M, uint32_t k, uint32_t nc, uint32_t nb)
+{
+    const double per_cell = std::max(1.0, (double)M / ((double)nc * nc * nc));
+    const double rounds = std::ceil(std::pow((double)(nc / k), 3.0) / nb), colours = (double)k * k * k;
+    return colours * rounds * (9000.0 + 4750.0 * (1.0 + per_cell / 6.2)) + (nb > 1 ? colours * 9000.0 + 45000.0 : 10000.0);
+}
+
+// With a cell per wave on nb workgroups of `waves` such waves: longer, but at a
+// quarter of the work, so a full device moves more molecules.
+double waves_cycles(uint32_t M, uint32_t k, uint32_t nc, uint32_t nb, uint32_t waves)
+{
+    const double per_cell = std::max(1.0, (double)M / ((double)nc * nc * nc));
+    const double rounds = std::ceil(std::pow((double)(nc / k), 3.0) / (nb * waves)), colours = (double)k * k * k;
+    return colours * (rounds * (9000.0 + 4800.0 * per_cell) + 8000.0) + 45000.0;
+}
+
 // Initial milliseconds per modelled cycle of the engine classes (one
-// workgroup with the state in LDS, in HBM; the multi-workgroup engine per
-// workgroup), relative to the LDS class; a batch then measures its own.
-// The multi-workgroup engine moves about 2.9 times fewer molecules per
-// workgroup than an LDS workgroup (1728 molecules on 7 workgroups, 8000 on
-// 32), 2.2 per modelled cycle of its HBM cost; 2.5 keeps a margin.
-constexpr double kCycleRatio[3] = {1.0, 1.3, 2.5};
+// workgroup with the state in LDS, in HBM; the multi-workgroup engine with a cell
+// per workgroup, with a cell per wave), relative to the LDS class; a batch then
+// measures its own.
+constexpr double kCycleRatio[4] = {1.0, 1.0, 1.1, 1.1};
+
+double Geometry::spread_cycles(uint32_t M, uint32_t nb, bool waves) const
+{
+    return waves ? waves_cycles(M, k, nc, nb, wave_fit) : team_cycles(M, k, nc, nb);
+}
 
 // Whether the multi-workgroup engine on nb workgroups is modelled at least
 // 25 % faster than the system's own engine on one workgroup, with ms_one and
-// ms_multi the milliseconds per modelled cycle of the two (always, for a
-// system beyond one workgroup's LDS).
-bool spread_pays(const Geometry& g, uint32_t nb, double ms_one, double ms_multi)
+// ms_multi the milliseconds per modelled cycle of the two (always on several,
+// for a system beyond one workgroup's LDS).
+bool spread_pays(const Geometry& g, uint32_t M, uint32_t nb, bool waves, double ms_one, double ms_multi)
 {
-    return !g.resident || (double)nb * g.sweep_cost * ms_one >= 1.25 * g.spread_cost * ms_multi;
+    return (!g.resident && nb > 1) || g.sweep_cost * ms_one >= 1.25 * g.spread_cycles(M, nb, waves) * ms_multi;
 }
 
 int geometry(const mc_params* p, Geometry* g)
@@ -207,41 +253,66 @@ int geometry(const mc_params* p, Geometry* g)
     g->ncell = nc * nc * nc;
     const bool fp64 = p->precision == MC_FP64;
     const size_t limit = device_lds_limit();
-    const LdsLayout res = lds_layout(fp64, true, p->n_molecules, g->ncell);
+    // the near list: what a cell of this width meets at this density with a
+    // fifth to spare, in steps of 64; fewer where that keeps the state in LDS
+    {
+        const double w = g->L / nc, R = g->reach;
+        const double region = w * w * w + 6.0 * w * w * R + 3.0 * M_PI * w * R * R + 4.0 / 3.0 * M_PI * R * R * R;
+        const double need = std::min((double)p->n_molecules, 1.2 * region * p->density / 3.0 + 16.0);
+        g->near_cap = kNearMin;
+        while (g->near_cap < kNearMax && g->near_cap < need) g->near_cap += 64;
+        while (g->near_cap > kNearMin &&
+               lds_layout(fp64, true, p->n_molecules, g->ncell, g->near_cap).total > limit &&
+               lds_layout(fp64, true, p->n_molecules, g->ncell, kNearMin).total <= limit)
+            g->near_cap -= 64;
+    }
+    const LdsLayout res = lds_layout(fp64, true, p->n_molecules, g->ncell, g->near_cap);
     g->resident = res.total <= limit && !(p->flags & MC_FLAG_HBM_STATE);
-    g->lds = g->resident ? res.total : lds_layout(fp64, false, p->n_molecules, g->ncell).total;
+    g->lds = g->resident ? res.total : lds_layout(fp64, false, p->n_molecules, g->ncell, g->near_cap).total;
     const bool one_wg = (p->flags & MC_FLAG_SINGLE_WORKGROUP) || p->workgroups == 1;
+    g->lists = spread_layout(fp64, true, p->n_molecules, g->ncell, g->near_cap, 0).total <= limit;
+    g->wave_fit = 0;
+    while (g->lists && g->wave_fit < (uint32_t)kWaves &&
+           spread_layout(fp64, true, p->n_molecules, g->ncell, g->near_cap, g->wave_fit + 1).total <= limit)
+        ++g->wave_fit;
+    g->team_waves = 0;
     g->spread = !g->resident && !one_wg;
-    g->spread_blocks = 1;
+    g->team = false;
+    g->spread_blocks = g->team_blocks = 1;
     // the model is fitted to the LDS state; with the state in HBM a sweep on
     // one workgroup takes about 1.3 times as long (measured 1.1 - 1.4 over
     // 2197 - 27000 molecules)
-    const double cost = cost_estimate(p->n_molecules, g->L, g->reach, k, nc);
-    g->sweep_cost = cost * (g->resident ? 1.0 : 1.3);
-    g->spread_cost = cost * 1.3;
+    g->sweep_cost = sweep_cycles(p->n_molecules, k, nc) * (g->resident ? 1.0 : 1.3);
     if (!one_wg) {
-        // one wave per cell of a colour, within one cooperative wave of the
-        // device.  A system whose state fits one workgroup's LDS runs alone on
-        // the multi-workgroup engine too when that is modelled faster (many
-        // cells per colour) or when the caller asks for a workgroup count;
-        // otherwise it keeps the count for a batch, which may move it there
-        // when compute units are idle
+        // one workgroup per cell of a colour, as many as the device holds.  A
+        // system whose state fits one workgroup's LDS runs alone on the
+        // multi-workgroup engine too when that is modelled faster or when the
+        // caller asks for a workgroup count; otherwise it keeps the count for a
+        // batch, which may move it there when compute units are idle
         uint32_t maxb = 0;
-        const hipError_t e = spread_max_blocks(fp64, &maxb);
+        const hipError_t e = spread_max_blocks(&maxb);
         if (e != hipSuccess || maxb == 0) {
             (void)hipGetLastError();
             g->spread = false;
         } else {
-            const uint32_t na = nc / k;
-            const uint32_t want = (na * na * na + kSpreadWaves - 1) / kSpreadWaves;
-            g->spread_blocks = std::max(1u, std::min({want, maxb, (uint32_t)(kMaxParts / kSpreadWaves)}));
-            if (p->workgroups >= 2) {
-                g->spread_blocks = std::min(g->spread_blocks, p->workgroups);
-                if (g->spread_blocks >= 2) g->spread = true;
-            } else if (g->resident && g->spread_blocks >= 2 &&
-                       spread_pays(*g, g->spread_blocks, kCycleRatio[0], kCycleRatio[2])) {
-                g->spread = true;
+            constexpr uint32_t kUnit = 4, kMaxUnits = 256;
+            const uint32_t na = nc / k, nact = na * na * na;
+            const uint32_t units = std::max(1u, std::min({(nact + kUnit - 1) / kUnit, maxb, kMaxUnits}));
+            g->spread_blocks = units;
+            g->team_blocks = std::min(nact, maxb);
+            if (p->workgroups >= 2 && units >= 2) {
+                if (p->workgroups < units) g->spread_blocks = g->team_blocks = p->workgroups;
+                g->spread = g->team = true;
+            } else if (g->resident) {
+                // many cells per colour are the multi-workgroup engine's by name
+                // as well
+                g->spread = units >= 5;
+                g->team = g->spread || spread_pays(*g, p->n_molecules, g->team_blocks, false, kCycleRatio[0], kCycleRatio[2]);
             }
+            if (!g->resident) g->team = true;
+            if (g->wave_fit && g->spread_cycles(p->n_molecules, g->team_blocks, true) <
+                                   g->spread_cycles(p->n_molecules, g->team_blocks, false))
+                g->team_waves = std::min(g->wave_fit, (nact + g->team_blocks - 1) / g->team_blocks);
         }
     }
     return MC_OK;
@@ -251,11 +322,7 @@ int geometry(const mc_params* p, Geometry* g)
 // reference system (k = 2, n_c = 4) on one workgroup.
 double slice_time(uint64_t max_moves)
 {
-    static const double ref = [] {
-        const double L = std::cbrt(3.0 * 1000.0 / 1.2);
-        const double reach = std::pow(2.0, 1.0 / 6.0) * 1.1 + 2.0 * bond_star() / std::sqrt(3.0);
-        return cost_estimate(1000, L, reach, 2, 4);
-    }();
+    static const double ref = sweep_cycles(1000, 2, 4);
     return (double)max_moves / 1000.0 * ref;
 }
 
@@ -309,15 +376,15 @@ BufLayout buf_layout(const mc_params* p, const Geometry& g)
     b.mom = o;    o = al(o + 4 * kC2Max * sizeof(double));
     b.props = o;  o = al(o + M * 48);
     b.gpart = o;  o = al(o + kMaxParts * sizeof(double));
-    if (!g.resident || g.spread_blocks >= 2) {
+    if (g.team_arrays()) {
         const bool fp64 = p->precision == MC_FP64;
-        b.gsite = o;   o = al(o + 3 * M * site_bytes(fp64));
+        b.gsite = o;   o = al(o + M * std::max(3 * site_bytes(fp64), mol_bytes(fp64)));
         b.gcell = o;   o = al(o + (size_t(g.ncell) + 1) * sizeof(uint32_t));
         b.gcellid = o; o = al(o + M * sizeof(uint16_t));
         b.glist = o;   o = al(o + M * sizeof(uint16_t));
         b.gcnt = o;    o = al(o + 2 * size_t(g.ncell) * sizeof(uint32_t));
         b.gecell = o;  o = al(o + size_t(g.ncell) * sizeof(double));
-        b.gbar = o;    o = al(o + sizeof(uint32_t));
+        b.gbar = o;    o = al(o + kBarWords * sizeof(uint32_t));
     }
     b.total = o;
     return b;
@@ -342,6 +409,10 @@ struct mc_system {
     std::vector<std::pair<hipEvent_t, hipEvent_t>> ev_sweep, ev_event;
 };
 
+// Slices of the systems on the multi-workgroup engine that one run of all
+// remaining sweeps enqueues (they end at event sweeps).
+constexpr uint32_t kRounds = 16;
+
 struct mc_batch {
     uint32_t max_slots;
     uint32_t precision;
@@ -353,8 +424,8 @@ struct mc_batch {
     hipEvent_t copied[2];
     bool pending[2];
     int parity;
-    // systems on the multi-workgroup engine: one cooperative launch per run on
-    // stream2, overlapping the batch stream's launches
+    // systems on the multi-workgroup engine: one launch per run on stream2,
+    // overlapping the batch stream's launches
     hipStream_t stream2;              // caller's second stream (or the batch stream)
     hipEvent_t go, done;              // stream2 waits for go (stream), stream for done (stream2)
     // systems on one workgroup with the state in HBM: their launch on stream3
@@ -363,22 +434,23 @@ struct mc_batch {
     hipStream_t stream3;
     hipEvent_t go3, done3;            // stream3 waits for go3 (stream), stream for done3 (stream3)
     SpreadSlot* dev_spread[2];        // per parity: [systems | (events as Slot)] x max_slots
-    SpreadSlot* host_spread[2];
+    SpreadSlot* host_spread[2];       // staging of kRounds tables of ncu systems
     Slot* dev_ev2[2];
     Slot* host_ev2[2];
     hipEvent_t copied2[2];
     bool pending2[2];
-    uint32_t spread_max;              // co-resident workgroups of the cooperative launch
+    uint32_t spread_max;              // workgroups of one launch of it that the device holds
     uint32_t ncu;                     // compute units of the device
     uint32_t wg_limit;                // compute units the batch's runs use at once
     uint32_t turn;                    // where the next run starts taking systems when
                                       // there are more than wg_limit
     // slice calibration per engine class (one workgroup with the state in LDS,
-    // one workgroup with the state in HBM, multi-workgroup): milliseconds per
+    // one workgroup with the state in HBM, multi-workgroup with a cell per
+    // workgroup, with a cell per wave): milliseconds per
     // modelled cycle, learnt from the timed launches of earlier runs
-    double ms_per_cycle[3];
-    double pred[3];                   // modelled cycles of the class's last launch (0: none)
-    hipEvent_t t_beg[3], t_end[3];
+    double ms_per_cycle[4];
+    double pred[4];                   // modelled cycles of the class's last launch (0: none)
+    hipEvent_t t_beg[4], t_end[4];
 };
 
 namespace {
@@ -500,11 +572,11 @@ uint64_t next_event(const mc_system* s, bool gofr_only = false)
 
 constexpr uint64_t kMaxSweepsPerLaunch = 1u << 16;
 
-// Zero a system's barrier counter with a kernel, not a memset: mc_sweep stays
+// Zero a system's barrier words with a kernel, not a memset: mc_sweep stays
 // free of memset nodes for callers that capture it into a graph.
 __global__ void k_zero_counter(uint32_t* c)
 {
-    if (threadIdx.x == 0) *c = 0u;
+    for (int i = threadIdx.x; i < kBarWords; i += blockDim.x) c[i] = 0u;
 }
 
 // Enqueue n sweeps of one system, split at event sweeps.
@@ -517,20 +589,24 @@ int advance(mc_system* s, uint64_t n)
         const uint64_t chunk = std::min<uint64_t>({n, next_event(s) - s->sweep, kMaxSweepsPerLaunch});
         one.n_sweeps = chunk;
         one.flags = 0;
-        TraceRange tr(s->g.spread ? "flipmc sweeps: multi-workgroup launch" : "flipmc sweeps: one-workgroup launch");
-        if (s->g.spread) {
+        TraceRange tr(s->g.team ? "flipmc sweeps: multi-workgroup launch" : "flipmc sweeps: one-workgroup launch");
+        if (s->g.team && s->g.team_blocks >= 2) {
             hipLaunchKernelGGL(k_zero_counter, dim3(1), dim3(64), 0, s->stream, s->host.g_bar);
             HIPCHK(hipGetLastError());
         }
         hipEvent_t t0 = timing_start(s);
-        if (s->g.spread) {
+        if (s->g.team) {
             SpreadSlot sl{};
             sl.sys = s->dev;
             sl.n_sweeps = chunk;
             sl.first_block = 0;
-            sl.n_blocks = s->g.spread_blocks;
-            HIPCHK(launch_spread(s->p.precision == MC_FP64, nullptr, 1, sl, s->g.spread_blocks,
-                                 s->stream));
+            sl.n_blocks = s->g.team_blocks;
+            sl.waves = s->g.team_waves;
+            const size_t lds = spread_layout(s->p.precision == MC_FP64, s->g.lists, s->p.n_molecules, s->g.ncell,
+                                             s->g.near_cap, sl.waves).total;
+            HIPCHK(launch_spread(s->p.precision == MC_FP64,
+                                 sl.waves ? kSpreadWaves : (s->g.lists ? kSpreadTeam : kSpreadCrew), nullptr, 1, sl,
+                                 s->g.team_blocks, lds, s->stream));
         }
         else
             HIPCHK(launch_sweeps(s->p.precision == MC_FP64, s->g.resident, nullptr, one, 1,
@@ -755,6 +831,7 @@ int mc_init_system(const mc_params* p, const double* com, const double* quat, co
     D.gofr_nbins = nb;
     D.gofr_dr = p->gofr_dr;
     D.barrier_polls = p->barrier_polls ? p->barrier_polls : (1u << 23);
+    D.near_cap = g.near_cap;
     D.gofr_rmax = rmax;
     D.lds_bytes = (uint32_t)g.lds;
     D.com = (double*)(b + lay.com);
@@ -779,7 +856,7 @@ int mc_init_system(const mc_params* p, const double* com, const double* quat, co
     D.fs_q_cm = p->fs_q_cm;
     D.props = (void*)(b + lay.props);
     D.g_part = (double*)(b + lay.gpart);
-    if (!g.resident || g.spread_blocks >= 2) {
+    if (g.team_arrays()) {
         D.g_site = (void*)(b + lay.gsite);
         D.g_cell = (uint32_t*)(b + lay.gcell);
         D.g_cellid = (uint16_t*)(b + lay.gcellid);
@@ -1200,7 +1277,7 @@ int mc_batch_create(uint32_t max_slots, uint32_t precision, void* device_buf, si
     b->ncu = 1;
     b->wg_limit = 0;
     b->turn = 0;
-    for (int c = 0; c < 3; ++c) {
+    for (int c = 0; c < 4; ++c) {
         b->ms_per_cycle[c] = ms_per_model_cycle() * kCycleRatio[c];
         b->pred[c] = 0.0;
         b->t_beg[c] = b->t_end[c] = nullptr;
@@ -1217,6 +1294,13 @@ int mc_batch_create(uint32_t max_slots, uint32_t precision, void* device_buf, si
         b->copied2[i] = nullptr;
         b->pending2[i] = false;
     }
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+        mc_batch_destroy(b);
+        return fail(MC_EDEVICE, "could not query the device");
+    }
+    const size_t table = std::min(max_slots, (uint32_t)std::max(1, ncu));  // systems on several workgroups
     uint8_t* dbuf = (uint8_t*)device_buf;
     for (int i = 0; i < 2; ++i) {
         // slot tables: one per residency class, double-buffered; the device
@@ -1226,14 +1310,14 @@ int mc_batch_create(uint32_t max_slots, uint32_t precision, void* device_buf, si
         b->dev_ev2[i] = (Slot*)(dbuf + lay.ev2[i]);
         if (hipHostMalloc((void**)&b->host_slots[i], 3 * sizeof(Slot) * max_slots, hipHostMallocDefault) != hipSuccess ||
             hipEventCreateWithFlags(&b->copied[i], hipEventDisableTiming) != hipSuccess ||
-            hipHostMalloc((void**)&b->host_spread[i], sizeof(SpreadSlot) * max_slots, hipHostMallocDefault) != hipSuccess ||
-            hipHostMalloc((void**)&b->host_ev2[i], sizeof(Slot) * max_slots, hipHostMallocDefault) != hipSuccess ||
+            hipHostMalloc((void**)&b->host_spread[i], sizeof(SpreadSlot) * kRounds * table, hipHostMallocDefault) != hipSuccess ||
+            hipHostMalloc((void**)&b->host_ev2[i], sizeof(Slot) * kRounds * table, hipHostMallocDefault) != hipSuccess ||
             hipEventCreateWithFlags(&b->copied2[i], hipEventDisableTiming) != hipSuccess) {
             mc_batch_destroy(b);
             return fail(MC_EDEVICE, "could not allocate the host staging of the slot tables");
         }
     }
-    for (int c = 0; c < 3; ++c)
+    for (int c = 0; c < 4; ++c)
         if (hipEventCreate(&b->t_beg[c]) != hipSuccess || hipEventCreate(&b->t_end[c]) != hipSuccess) {
             mc_batch_destroy(b);
             return fail(MC_EDEVICE, "could not create the timing events");
@@ -1246,15 +1330,9 @@ int mc_batch_create(uint32_t max_slots, uint32_t precision, void* device_buf, si
         mc_batch_destroy(b);
         return fail(MC_EDEVICE, "could not create the stream events");
     }
-    if (spread_max_blocks(precision == MC_FP64, &b->spread_max) != hipSuccess) {
+    if (spread_max_blocks(&b->spread_max) != hipSuccess) {
         (void)hipGetLastError();
         b->spread_max = 0;
-    }
-    int dev = 0, ncu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
-        mc_batch_destroy(b);
-        return fail(MC_EDEVICE, "could not query the device");
     }
     b->ncu = (uint32_t)ncu;
     b->wg_limit = (uint32_t)ncu;
@@ -1267,7 +1345,8 @@ int mc_batch_create(uint32_t max_slots, uint32_t precision, void* device_buf, si
         SpreadSlot snone{};
         hipError_t e = launch_sweeps(fp64, true, nullptr, none, 1, 0, b->stream, true);
         if (e == hipSuccess) e = launch_sweeps(fp64, false, nullptr, none, 1, 0, b->stream, true);
-        if (e == hipSuccess && b->spread_max >= 2) e = launch_spread(fp64, nullptr, 0, snone, 1, b->stream);
+        for (const SpreadMode m : {kSpreadTeam, kSpreadWaves, kSpreadCrew})
+            if (e == hipSuccess && b->spread_max >= 2) e = launch_spread(fp64, m, nullptr, 0, snone, 1, 0, b->stream);
         if (e != hipSuccess) {
             mc_batch_destroy(b);
             return fail(MC_EDEVICE, "warm-up launch: %s", hipGetErrorString(e));
@@ -1329,7 +1408,7 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
     const bool fp64 = b->precision == MC_FP64;
 
     // calibration from the launches of the last run that have finished
-    for (int c = 0; c < 3; ++c) {
+    for (int c = 0; c < 4; ++c) {
         if (b->pred[c] <= 0.0) continue;
         if (hipEventQuery(b->t_end[c]) != hipSuccess) {
             (void)hipGetLastError();  // not finished: no sample
@@ -1347,15 +1426,12 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
     // every launch of a run is sized to the time the reference system takes
     // for max_moves_per_slot moves
     const double t_slice = slice_time(max_moves_per_slot) * ms_per_model_cycle();
-    double pred[3] = {0.0, 0.0, 0.0};
+    double pred[4] = {0.0, 0.0, 0.0, 0.0};
 
     // Engine of every system for this run.  Each system needs one workgroup;
-    // the workgroups left over (up to the batch's limit) go to the systems
-    // that can run on the multi-workgroup engine, most remaining work first,
-    // each up to its own workgroup count; a system whose state fits in LDS
-    // moves there only with enough workgroups to be modelled 25 % faster than
-    // on its own one.  The engines make the same decisions, so a system may
-    // change engine from run to run.
+    // the workgroups left over (up to the batch's limit) go to systems that can
+    // run on the multi-workgroup engine (below).  The engines make the same
+    // decisions, so a system may change engine from run to run.
     std::vector<uint32_t> active;
     for (uint32_t i = 0; i < S; ++i)
         if (b->sys[i] && b->remaining[i] != 0) active.push_back(i);
@@ -1371,59 +1447,78 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
         std::sort(chosen.begin(), chosen.end());
         active.swap(chosen);
     }
-    std::vector<std::pair<double, uint32_t>> cand;  // (-remaining moves, slot)
-    for (uint32_t i : active) {
-        const mc_system* s = b->sys[i];
-        if (s->g.spread_blocks >= 2 && b->spread_max >= 2)
-            cand.emplace_back(-(double)b->remaining[i] * (double)s->p.n_molecules, i);
-    }
-    std::sort(cand.begin(), cand.end());
+    // The spare compute units go to the systems that would otherwise finish
+    // last: the one with the longest modelled time for its remaining sweeps
+    // takes workgroups until one of its rounds of cells per colour is saved, and
+    // so on while any are left.  (In proportion to the remaining work, a share
+    // that saves no round is lost, and one slow system holds up the run.)  With
+    // its workgroups a system has a cell per workgroup or a cell per wave,
+    // whichever is modelled faster.
     std::vector<uint32_t> nblk(S, 0);
-    {
-        // the spare compute units shared in proportion to the remaining work,
-        // each system up to its own workgroup count (bpc workgroups of the
-        // multi-workgroup engine fit on one compute unit), the cooperative
-        // launch up to what the device holds at once; what the caps and the
-        // rounding leave goes to the systems with the most work, in order
-        const uint32_t spare = b->wg_limit > active.size() ? b->wg_limit - (uint32_t)active.size() : 0u;
-        const uint32_t bpc = std::max(1u, b->spread_max / std::max(1u, b->ncu));
-        double total = 0.0;
-        for (const auto& c : cand) total -= c.first;
-        uint32_t left = spare, coop = 0;
-        auto cus = [&](uint32_t nb) { return (nb + bpc - 1) / bpc; };
-        auto pays = [&](const mc_system* s, uint32_t nb) {
-            return spread_pays(s->g, nb, b->ms_per_cycle[0], b->ms_per_cycle[2]);
+    std::vector<char> by_wave(S, 0);
+    if (b->spread_max >= 2) {
+        struct Cand {
+            double time;  // of the remaining sweeps on nb workgroups (0: its own engine's one)
+            uint32_t slot, nb;
         };
-        for (const auto& c : cand) {
-            const mc_system* s = b->sys[c.second];
-            const uint32_t share = total > 0.0 ? (uint32_t)((double)spare * (-c.first) / total) : 0u;
-            const uint32_t nb = std::min({s->g.spread_blocks, (1u + std::min(share, left)) * bpc,
-                                          b->spread_max - coop});
-            if (nb < 2 || !pays(s, nb)) continue;
-            nblk[c.second] = nb;
-            left -= cus(nb) - 1;
-            coop += nb;
+        auto later = [](const Cand& a, const Cand& b) {
+            return a.time < b.time || (a.time == b.time && a.slot > b.slot);
+        };
+        std::vector<Cand> heap;
+        uint32_t left = b->wg_limit > active.size() ? b->wg_limit - (uint32_t)active.size() : 0u;
+        uint32_t held = 0;
+        for (uint32_t i : active) {
+            const mc_system* s = b->sys[i];
+            const double one = s->g.sweep_cost * b->ms_per_cycle[s->g.resident ? 0 : 1];
+            if (s->g.team_arrays()) heap.push_back(Cand{(double)b->remaining[i] * one, i, 0u});
         }
-        for (const auto& c : cand) {
-            if (left == 0 || coop >= b->spread_max) break;
-            const mc_system* s = b->sys[c.second];
-            const uint32_t have = nblk[c.second];
-            const uint32_t want = std::min({s->g.spread_blocks, (cus(std::max(have, 1u)) + left) * bpc,
-                                            b->spread_max - coop + have});
-            if (want <= std::max(have, 1u) || want < 2 || !pays(s, want)) continue;
-            left -= cus(want) - (have ? cus(have) : 1u);
-            coop += want - have;
-            nblk[c.second] = want;
+        std::make_heap(heap.begin(), heap.end(), later);
+        while (!heap.empty()) {
+            std::pop_heap(heap.begin(), heap.end(), later);
+            Cand c = heap.back();
+            heap.pop_back();
+            const mc_system* s = b->sys[c.slot];
+            const uint32_t na = s->g.nc / s->g.k, nact = na * na * na, M = s->p.n_molecules, most = s->g.team_blocks;
+            const double ms_one = b->ms_per_cycle[s->g.resident ? 0 : 1];
+            // the fewest workgroups that save a round of one of the ways, and pay
+            uint32_t want = 0;
+            char wave = 0;
+            double time = c.time;
+            for (uint32_t nb = c.nb; nb < most && !want;) {
+                uint32_t next = most;
+                for (const uint32_t cells : {1u, s->g.wave_fit}) {  // of a workgroup at once
+                    if (cells == 0u) continue;
+                    const uint32_t rounds = nb ? (nact + cells * nb - 1) / (cells * nb) : nact + 1u;
+                    if (rounds > 1) next = std::min(next, (nact + cells * (rounds - 1) - 1) / (cells * (rounds - 1)));
+                }
+                nb = std::min(most, std::max(nb + 1, next));
+                for (const char w : {0, 1}) {
+                    if (w && s->g.wave_fit < 2) continue;
+                    const double ms = b->ms_per_cycle[w ? 3 : 2];
+                    const double t = (double)b->remaining[c.slot] * s->g.spread_cycles(M, nb, w) * ms;
+                    if (t < time && (c.nb || spread_pays(s->g, M, nb, w, ms_one, ms))) {
+                        want = nb;
+                        wave = w;
+                        time = t;
+                    }
+                }
+            }
+            const uint32_t more = want - std::max(c.nb, 1u);
+            if (!want || more > left || held + want - c.nb > b->spread_max) continue;  // as fast as it gets
+            left -= more;
+            held += want - c.nb;
+            nblk[c.slot] = c.nb = want;
+            by_wave[c.slot] = wave;
+            c.time = time;
+            heap.push_back(c);
+            std::push_heap(heap.begin(), heap.end(), later);
         }
     }
     uint32_t n[3] = {0, 0, 0};
     size_t lds[2] = {0, 0};
-    uint32_t ns = 0, ne = 0, blocks = 0;
-    SpreadSlot* hsp = b->host_spread[par];
-    Slot* hev = b->host_ev2[par];
     // the O(M^2) event work of large systems goes to the event kernel over
     // many workgroups, whatever engine ran the sweeps
-    std::vector<std::pair<mc_system*, uint32_t>> parts1, parts2;
+    std::vector<std::pair<mc_system*, uint32_t>> parts1;
     auto event_slot = [&](mc_system* s, uint32_t f, std::vector<std::pair<mc_system*, uint32_t>>& parts) {
         Slot ev{};
         ev.sys = s->dev;
@@ -1437,73 +1532,122 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
         return ev;
     };
     for (uint32_t i : active) {
+        if (nblk[i]) continue;
         mc_system* s = b->sys[i];
         // a system on one workgroup whose events fit the one-workgroup event
         // kernel takes its scheduled re-sums and C_2 samples inside the sweep
         // kernel: its slice stops only at g(r) frames
-        const bool inl = !nblk[i] && event_blocks(s->p.n_molecules) == 1;
+        const bool inl = event_blocks(s->p.n_molecules) == 1;
         uint64_t k = std::min<uint64_t>(b->remaining[i], next_event(s, inl) - s->sweep);
-        if (nblk[i]) {
-            // modelled cycles of a sweep: the one-workgroup model over the
-            // workgroups (the class calibration absorbs the engine's overheads)
-            const double unit = s->g.spread_cost / nblk[i];
-            if (max_moves_per_slot) {
-                const double q = t_slice / (b->ms_per_cycle[2] * unit);
-                k = std::min<uint64_t>(k, std::max<uint64_t>(1, (uint64_t)q));
-            }
-            pred[2] = std::max(pred[2], (double)k * unit);
-            SpreadSlot sl{};
-            sl.sys = s->dev;
-            sl.n_sweeps = k;
-            sl.first_block = blocks;
-            sl.n_blocks = nblk[i];
-            hsp[ns++] = sl;
-            blocks += nblk[i];
-        } else {
-            const int cls = s->g.resident ? 0 : 1;
-            if (max_moves_per_slot) {
-                // equal time slices: the time of max_moves_per_slot moves of the
-                // 1000-molecule reference, in sweeps of this system
-                const double cap = t_slice / (b->ms_per_cycle[cls] * s->g.sweep_cost);
-                k = std::min<uint64_t>(k, std::max<uint64_t>(1, (uint64_t)cap));
-            }
-            pred[cls] = std::max(pred[cls], (double)k * s->g.sweep_cost);
-            Slot sl{};
-            sl.sys = s->dev;
-            sl.n_sweeps = k;
-            sl.flags = inl ? kFlagInline : 0u;
-            hs[cls * S + n[cls]++] = sl;
-            lds[cls] = std::max(lds[cls], s->g.lds);
+        const int cls = s->g.resident ? 0 : 1;
+        if (max_moves_per_slot) {
+            // equal time slices: the time of max_moves_per_slot moves of the
+            // 1000-molecule reference, in sweeps of this system
+            const double cap = t_slice / (b->ms_per_cycle[cls] * s->g.sweep_cost);
+            k = std::min<uint64_t>(k, std::max<uint64_t>(1, (uint64_t)cap));
         }
+        pred[cls] = std::max(pred[cls], (double)k * s->g.sweep_cost);
+        Slot sl{};
+        sl.sys = s->dev;
+        sl.n_sweeps = k;
+        sl.flags = inl ? kFlagInline : 0u;
+        hs[cls * S + n[cls]++] = sl;
+        lds[cls] = std::max(lds[cls], s->g.lds);
         b->remaining[i] -= k;
         s->sweep += k;
         const uint32_t f = events_at(s, s->sweep) & (inl ? ~(kFlagResumPeriodic | kFlagC2) : ~0u);
-        if (f) {
-            if (nblk[i]) hev[ne++] = event_slot(s, f, parts2);
-            else hs[2 * S + n[2]++] = event_slot(s, f, parts1);
-        }
+        if (f) hs[2 * S + n[2]++] = event_slot(s, f, parts1);
     }
 
-    if (ns) {
+    // A slice of every system on the multi-workgroup engine: those with a cell
+    // per workgroup in one launch, those with a cell per wave in another, beside
+    // it on the third stream where that is free, then the event work of both.
+    std::vector<uint32_t> several;
+    for (uint32_t i : active)
+        if (nblk[i]) several.push_back(i);
+    const size_t table = std::min(S, b->ncu);
+    bool team_runs = false, wave_runs = false;
+    auto spread_round = [&](uint32_t round) -> int {
+        SpreadSlot* hsp = b->host_spread[par] + round * table;
+        Slot* hev = b->host_ev2[par] + round * table;
+        std::vector<std::pair<mc_system*, uint32_t>> parts;
+        std::vector<SpreadSlot> by[2];
+        uint32_t blocks[2] = {0, 0}, ne = 0;
+        size_t need[2] = {0, 0}, crew_need = 0;
+        double cycles[2] = {0.0, 0.0};
+        bool lists = true;  // the cell lists of all systems with a cell per workgroup fit its LDS
+        for (uint32_t i : several) {
+            mc_system* s = b->sys[i];
+            uint64_t k = std::min<uint64_t>(b->remaining[i], next_event(s) - s->sweep);
+            if (k == 0) continue;
+            const int w = by_wave[i];
+            const double unit = s->g.spread_cycles(s->p.n_molecules, nblk[i], w);  // modelled cycles of a sweep
+            if (max_moves_per_slot) {
+                const double q = t_slice / (b->ms_per_cycle[2 + w] * unit);
+                k = std::min<uint64_t>(k, std::max<uint64_t>(1, (uint64_t)q));
+            }
+            cycles[w] = std::max(cycles[w], (double)k * unit);
+            SpreadSlot sl{};
+            sl.sys = s->dev;
+            sl.n_sweeps = k;
+            sl.first_block = blocks[w];
+            sl.n_blocks = nblk[i];
+            sl.waves = w ? s->g.wave_fit : 0u;
+            by[w].push_back(sl);
+            blocks[w] += nblk[i];
+            need[w] = std::max(need[w], spread_layout(fp64, s->g.lists, s->p.n_molecules, s->g.ncell, s->g.near_cap,
+                                                      sl.waves).total);
+            if (!w) {
+                lists = lists && s->g.lists;
+                crew_need = std::max(crew_need, spread_layout(fp64, false, s->p.n_molecules, s->g.ncell,
+                                                              s->g.near_cap, 0).total);
+            }
+            b->remaining[i] -= k;
+            s->sweep += k;
+            if (const uint32_t f = events_at(s, s->sweep)) hev[ne++] = event_slot(s, f, parts);
+        }
+        const uint32_t nt = (uint32_t)by[0].size(), nw = (uint32_t)by[1].size();
+        if (nt + nw == 0) return MC_OK;
+        team_runs = team_runs || nt;
+        wave_runs = wave_runs || nw;
+        std::copy(by[0].begin(), by[0].end(), hsp);
+        std::copy(by[1].begin(), by[1].end(), hsp + nt);
+        const hipStream_t st = b->stream2;
+        HIPCHK(hipMemcpyAsync(b->dev_spread[par], hsp, sizeof(SpreadSlot) * (nt + nw), hipMemcpyHostToDevice, st));
+        if (ne) HIPCHK(hipMemcpyAsync(b->dev_ev2[par], hev, sizeof(Slot) * ne, hipMemcpyHostToDevice, st));
+        HIPCHK(hipEventRecord(b->copied2[par], st));
+        b->pending2[par] = true;
+        const SpreadSlot none{};
+        HIPCHK(launch_zero_barriers(b->dev_spread[par], nt + nw, st));
+        const bool beside = nt && nw && b->stream3 && !n[1];
+        const hipStream_t st_of[2] = {st, beside ? b->stream3 : st};
+        if (beside) {
+            HIPCHK(hipEventRecord(b->go3, st));
+            HIPCHK(hipStreamWaitEvent(b->stream3, b->go3, 0));
+        }
+        for (int w = 1; w >= 0; --w) {
+            if (by[w].empty()) continue;
+            const SpreadMode mode = w ? kSpreadWaves : (lists ? kSpreadTeam : kSpreadCrew);
+            const bool sample = cycles[w] > pred[2 + w];  // the longest slice is the run's sample
+            if (sample) HIPCHK(hipEventRecord(b->t_beg[2 + w], st_of[w]));
+            HIPCHK(launch_spread(fp64, mode, b->dev_spread[par] + (w ? nt : 0u), (uint32_t)by[w].size(), none, blocks[w],
+                                 mode == kSpreadCrew ? crew_need : need[w], st_of[w]));
+            if (sample) {
+                HIPCHK(hipEventRecord(b->t_end[2 + w], st_of[w]));
+                b->pred[2 + w] = pred[2 + w] = cycles[w];
+            }
+            if (w && beside) HIPCHK(hipEventRecord(b->done3, st_of[w]));
+        }
+        if (beside) HIPCHK(hipStreamWaitEvent(st, b->done3, 0));
+        HIPCHK(launch_parts_of(parts, st));
+        const Slot none2{};
+        if (ne) HIPCHK(launch_events(b->dev_ev2[par], none2, ne, st));
+        return MC_OK;
+    };
+    if (!several.empty()) {
         HIPCHK(hipEventRecord(b->go, b->stream));
         HIPCHK(hipStreamWaitEvent(b->stream2, b->go, 0));
-        HIPCHK(hipMemcpyAsync(b->dev_spread[par], hsp, sizeof(SpreadSlot) * ns, hipMemcpyHostToDevice,
-                              b->stream2));
-        if (ne)
-            HIPCHK(hipMemcpyAsync(b->dev_ev2[par], hev, sizeof(Slot) * ne, hipMemcpyHostToDevice,
-                                  b->stream2));
-        HIPCHK(hipEventRecord(b->copied2[par], b->stream2));
-        b->pending2[par] = true;
-        SpreadSlot none{};
-        HIPCHK(launch_zero_barriers(b->dev_spread[par], ns, b->stream2));
-        HIPCHK(hipEventRecord(b->t_beg[2], b->stream2));
-        HIPCHK(launch_spread(fp64, b->dev_spread[par], ns, none, blocks, b->stream2));
-        HIPCHK(hipEventRecord(b->t_end[2], b->stream2));
-        b->pred[2] = pred[2];
-        HIPCHK(launch_parts_of(parts2, b->stream2));
-        Slot none2{};
-        if (ne) HIPCHK(launch_events(b->dev_ev2[par], none2, ne, b->stream2));
-        HIPCHK(hipEventRecord(b->done, b->stream2));
+        if (const int rc = spread_round(0)) return rc;
     }
 
     if (n[0] + n[1] + n[2]) {
@@ -1538,8 +1682,15 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
     }
     // later work on the batch stream (the next run, poll, reads) follows the
     // multi-workgroup launch
-    if (ns) HIPCHK(hipStreamWaitEvent(b->stream, b->done, 0));
-    if (n_launched) *n_launched = (n[0] ? 1u : 0u) + (n[1] ? 1u : 0u) + (ns ? 1u : 0u);
+    if (!several.empty()) {
+        // all remaining sweeps: the slices between these systems' event sweeps
+        // one after another, beside the others' launch
+        for (uint32_t r = 1; r < kRounds && !max_moves_per_slot && b->stream2 != b->stream; ++r)
+            if (const int rc = spread_round(r)) return rc;
+        HIPCHK(hipEventRecord(b->done, b->stream2));
+        HIPCHK(hipStreamWaitEvent(b->stream, b->done, 0));
+    }
+    if (n_launched) *n_launched = (n[0] ? 1u : 0u) + (n[1] ? 1u : 0u) + (team_runs ? 1u : 0u) + (wave_runs ? 1u : 0u);
     return MC_OK;
 }
 
@@ -1586,7 +1737,7 @@ void mc_batch_destroy(mc_batch* b)
         if (b->host_ev2[i]) (void)hipHostFree(b->host_ev2[i]);
         if (b->copied2[i]) (void)hipEventDestroy(b->copied2[i]);
     }
-    for (int c = 0; c < 3; ++c) {
+    for (int c = 0; c < 4; ++c) {
         if (b->t_beg[c]) (void)hipEventDestroy(b->t_beg[c]);
         if (b->t_end[c]) (void)hipEventDestroy(b->t_end[c]);
     }

@@ -1,9 +1,10 @@
 // engine.h -- device-side data layout of the flip Monte Carlo engine.
 //
-// One system = one workgroup of 512 threads (8 wave64s).  A system whose
-// state fits in the workgroup's LDS ("resident") keeps centres of mass, site
-// offsets and cell lists there for the whole launch; larger systems keep them
-// in HBM and the same code reads them through global pointers.
+// A system either has one workgroup of 512 threads (8 wave64s) -- when its state
+// fits the workgroup's LDS ("resident") centres of mass, site offsets and cell
+// lists stay there for the whole launch, else in HBM, where the same code reads
+// them through global pointers -- or shares several workgroups, each with the
+// neighbourhood of the cell it works on in LDS and the state in HBM.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -19,7 +20,11 @@ constexpr int kGofrBins = 256;
 constexpr int kGofrQueue = 128;  // per-wave queue of molecule pairs of a g(r) frame
 constexpr int kC2Max = 32;
 constexpr int kMaxMolecules = 65535;  // indices are stored as u16 in cell lists
-constexpr int kCellListCap = 192;     // per-wave list of molecules near the current cell
+// Molecules near a cell that an engine lists: a system has as many places as
+// its cells need (near_cap, set by the host), the same in every engine, so that
+// all take the same cells for too full.
+constexpr uint32_t kNearMin = 192, kNearMax = 320;
+constexpr int kNearSlots = kNearMin / 64;  // list entries per lane in registers
 // The single-workgroup event kernel copies centres, quaternions and types of
 // systems up to this size into LDS for its O(M^2) loops (larger systems use
 // the multi-workgroup event kernel).
@@ -78,6 +83,7 @@ struct SysDev {
     double sigma[3];     // diameters of types A, B, C
     uint32_t resum_interval, obs_interval, gofr_interval, obs_start;
     uint32_t max_samples, gofr_nbins, lds_bytes, barrier_polls;
+    uint32_t near_cap, pad1;
     double gofr_dr, gofr_rmax;
     double fs_q, fs_q_cm;  // wavenumbers of F_s (sites) and F_s^cm (centres)
     // state
@@ -100,7 +106,7 @@ struct SysDev {
     double* fs_cm;       // [kC2Max] F_s^cm(q, t) at the same sweeps
     double* mom;         // [4][kC2Max] per-particle moments at the same sweeps
     // HBM copies of the work arrays of non-resident systems
-    void* g_site;        // Real4 [3M]: offset xyz + sigma of the site's type
+    void* g_site;        // Real4 [3M]: offset xyz + sigma of the site's type, or molecule records [M]
     uint32_t* g_cell;    // [ncell + 1] cell starts
     uint16_t* g_cellid;  // [M]
     uint16_t* g_list;    // [M] molecules sorted by cell, ascending inside a cell
@@ -108,7 +114,7 @@ struct SysDev {
     uint32_t* g_cnt;     // [2 * ncell] cell counts and fill cursors (multi-workgroup engine)
     double* g_part;      // [kMaxParts] per-workgroup partial sums of the event kernel
     double* g_ecell;     // [ncell] accepted dE of each cell in the current sweep (HBM state)
-    uint32_t* g_bar;     // barrier counter of the system's workgroups (multi-workgroup engine)
+    uint32_t* g_bar;     // [kBarWords] barrier counter and crew of the system's workgroups (multi-workgroup engine)
     // decision log
     void* log;
     uint64_t log_sweep0;
@@ -137,7 +143,11 @@ static_assert(sizeof(MoveRecord) == 48, "record layout");
 // Per-wave LDS work areas: the molecules near the current cell, the
 // survivors of a trial's prune, the trial in flight.
 __host__ __device__ constexpr size_t site_bytes(bool fp64) { return fp64 ? 32 : 16; }
+__host__ __device__ constexpr size_t mol_bytes(bool fp64) { return fp64 ? 128 : 64; }  // record of a molecule (multi-workgroup engine)
 __host__ __device__ constexpr size_t trial_bytes(bool fp64) { return fp64 ? 272 : 160; }
+__host__ __device__ constexpr size_t record_bytes(bool fp64) { return fp64 ? 304 : 208; }  // a trial with its proposal
+constexpr size_t kSumBytes = 24;  // an evaluated trial
+constexpr size_t kPropBytes = 48;  // a proposal
 
 __host__ __device__ inline size_t align16(size_t x) { return (x + 15) & ~size_t(15); }
 
@@ -148,14 +158,14 @@ struct LdsLayout {
 };
 
 __host__ __device__ inline LdsLayout lds_layout(bool fp64, bool resident, uint32_t M,
-                                                 uint32_t ncell)
+                                                 uint32_t ncell, uint32_t near_cap)
 {
     LdsLayout l{};
     size_t o = 0;
-    l.surv = o;   o = align16(o + kWaves * kCellListCap * sizeof(uint16_t));
+    l.surv = o;   o = align16(o + kWaves * size_t(near_cap) * sizeof(uint16_t));
     l.seglo = o;  o = align16(o + kWaves * kMaxSeg * sizeof(uint16_t));
     l.segoff = o; o = align16(o + kWaves * kMaxSeg * sizeof(uint16_t));
-    l.near = o;   o = align16(o + kWaves * kCellListCap * 8);
+    l.near = o;   o = align16(o + kWaves * size_t(near_cap) * 8);
     l.misc = o;   o = align16(o + 16 * sizeof(double));
     l.trial = o;  o = align16(o + kWaves * trial_bytes(fp64));
     if (resident) {
@@ -170,31 +180,48 @@ __host__ __device__ inline LdsLayout lds_layout(bool fp64, bool resident, uint32
     return l;
 }
 
-// Multi-workgroup ("spread") engine for systems larger than one workgroup's
-// LDS: 4 waves per workgroup, every wave takes cells of the current colour and
-// stages each cell's neighbourhood (up to kCellListCap molecules, from a
-// stencil of up to kSpreadPerLane * 64 molecules) in its LDS.
-constexpr int kSpreadThreads = 256;
-constexpr int kSpreadWaves = kSpreadThreads / 64;
-constexpr int kSpreadPerLane = 8;
-constexpr int kMaxParts = 1024;  // workgroups of the event kernel, waves of the spread kernel
+// Multi-workgroup ("spread") engine: a workgroup takes a cell of the current
+// colour, stages the cell's neighbourhood (up to near_cap molecules) in its LDS
+// and its waves share the cell's trials; or each of the first `waves` waves of a
+// workgroup takes and stages a cell of its own.
+constexpr int kMaxParts = 1024;  // workgroups of the event kernel
+constexpr int kBarWords = 272;   // words of SysDev::g_bar
 
-__host__ __device__ inline size_t spread_wave_bytes(bool fp64)
+// LDS of one of its workgroups: the lists of the system's cells too where they
+// fit (lists), which are put together over the place of the staged cells.
+struct SpreadLayout {
+    size_t com, site, own, near, surv, seg, trial;  // from the start, or from each wave's
+    size_t wave;                                    // bytes of a wave that has a cell
+    size_t sums, cnt, misc, cell, list, total;
+};
+
+__host__ __device__ inline SpreadLayout spread_layout(bool fp64, bool lists, uint32_t M, uint32_t ncell,
+                                                      uint32_t near_cap, uint32_t waves)
 {
+    SpreadLayout l{};
+    const size_t N = near_cap;
     size_t o = 0;
-    o = align16(o + 3 * size_t(kCellListCap) * sizeof(double));  // staged centres
-    o = align16(o + 3 * size_t(kCellListCap) * site_bytes(fp64));  // staged sites
-    o = align16(o + size_t(kCellListCap) * sizeof(uint16_t));      // molecule of each slot
-    o = align16(o + size_t(kCellListCap) * sizeof(uint16_t));      // slot of each cell molecule
-    o = align16(o + size_t(kCellListCap) * 8);                     // near list
-    o = align16(o + size_t(kCellListCap) * sizeof(uint16_t));      // survivors
-    o = align16(o + 2 * size_t(kMaxSeg) * sizeof(uint16_t));       // stencil segments
-    o = align16(o + trial_bytes(fp64));
-    return o;
-}
-__host__ __device__ inline size_t spread_lds_bytes(bool fp64)
-{
-    return kSpreadWaves * spread_wave_bytes(fp64) + 16 * sizeof(double);
+    l.com = o;   o = align16(o + 3 * N * sizeof(double));     // staged centres
+    l.site = o;  o = align16(o + 3 * N * site_bytes(fp64));   // staged sites
+    l.own = o;   o = align16(o + N * sizeof(uint16_t));       // slot of each cell molecule
+    l.near = o;  o = align16(o + N * 8);                      // near list
+    l.surv = o;  o = align16(o + (waves ? 1 : kWaves) * N * sizeof(uint16_t));  // survivors, per wave
+    l.seg = o;   o = align16(o + 2 * size_t(kMaxSeg) * sizeof(uint16_t));       // stencil segments
+    l.trial = o; o = align16(o + (waves ? 1 : 64) * record_bytes(fp64));  // the trial, or the next of the cell
+    l.wave = o;
+    if (waves) o = waves * l.wave;
+    l.sums = o;  o = align16(o + 2 * kWaves * kSumBytes);  // evaluated trials, by turns
+    l.cnt = o;   o = align16(o + 2 * kWaves * sizeof(uint32_t));
+    if (lists && o < size_t(M) * sizeof(uint16_t)) o = align16(size_t(M) * sizeof(uint16_t));
+    // (the proposals of 512 molecules leave from there too)
+    if (o < kThreads * kPropBytes) o = kThreads * kPropBytes;
+    l.misc = o;  o = align16(o + 16 * sizeof(double));
+    if (lists) {
+        l.cell = o; o = align16(o + (size_t(ncell) + 1) * sizeof(uint32_t));
+        l.list = o; o = align16(o + size_t(M) * sizeof(uint16_t));
+    }
+    l.total = o;
+    return l;
 }
 
 // Kernel launchers (kernels.hip).  inline_events: the sweep kernel takes the
@@ -210,18 +237,23 @@ struct SpreadSlot {
     SysDev* sys;
     uint64_t n_sweeps;
     uint32_t first_block, n_blocks;
+    uint32_t waves, pad;  // waves of a workgroup with a cell each, 0: a cell per workgroup
 };
 
-// Cooperative launch of the multi-workgroup engine over n_blocks workgroups:
-// the systems of dev_slots[0 .. n_slots) (device array), or `one` when
-// dev_slots is null.  The workgroups of each system synchronise among
-// themselves only (each system's g_bar must be zero at launch).
-hipError_t launch_spread(bool fp64, const SpreadSlot* dev_slots, uint32_t n_slots,
-                         const SpreadSlot& one, uint32_t n_blocks, hipStream_t stream);
-// Zero the barrier counters of the systems of dev_slots[0 .. n_slots).
+// Launch of the multi-workgroup engine over n_blocks workgroups: the systems of
+// dev_slots[0 .. n_slots) (device array), or `one` when dev_slots is null, with
+// a cell per workgroup and the cell lists in LDS or in the systems' buffers, or
+// with a cell per wave (SpreadSlot::waves, lists in LDS), and the LDS that the
+// largest needs (spread_layout).  The workgroups of each system synchronise
+// among themselves only (each system's g_bar must be zero at launch; one
+// workgroup alone does not use it).
+enum SpreadMode { kSpreadTeam, kSpreadWaves, kSpreadCrew };
+hipError_t launch_spread(bool fp64, SpreadMode mode, const SpreadSlot* dev_slots, uint32_t n_slots,
+                         const SpreadSlot& one, uint32_t n_blocks, size_t lds, hipStream_t stream);
+// Zero the barrier words of the systems of dev_slots[0 .. n_slots).
 hipError_t launch_zero_barriers(const SpreadSlot* dev_slots, uint32_t n_slots, hipStream_t stream);
-// Largest cooperative grid of the spread kernel on the current device.
-hipError_t spread_max_blocks(bool fp64, uint32_t* n_blocks);
+// Workgroups of the spread kernel that the current device holds at once.
+hipError_t spread_max_blocks(uint32_t* n_blocks);
 // The systems of one launch of the event work over many workgroups, passed by
 // value (no table in memory): system i owns workgroups [first, first + count)
 // and splits its work over them as a launch of count workgroups of its own

@@ -63,7 +63,7 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_event_parts(FxList list, uint
             }
         }
         // fixed-order sum over the workgroup
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        const int lane = threadIdx.x & 63, wave = wave_index();
         e = wave_sum_dpp(e);
         if (lane == 0) red[wave] = e;
         __syncthreads();
@@ -122,7 +122,7 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_events(FxList list, uint32_t 
     const uint32_t nparts = (D.N + kFxThreads - 1) / kFxThreads;
     Stats* st = D.stats;
     const uint32_t N = D.N, M = D.M, n = D.n;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
     auto block_sum = [&](double v) {
         v = wave_sum_dpp(v);
         __syncthreads();

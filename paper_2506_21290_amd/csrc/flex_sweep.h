@@ -387,25 +387,6 @@ __device__ __forceinline__ void fx_propose_all(const FxDev& Dv, const FxK& D, co
 
 using W4 = uint32_t __attribute__((ext_vector_type(4)));
 
-// Sum over each row of 16 lanes (the row's last lane gets it) in the order of
-// wave_sum_dpp's first steps.
-__device__ __forceinline__ double fx_row_sum(double v)
-{
-    v += dpp_move<0x111, 0xf>(v);
-    v += dpp_move<0x112, 0xf>(v);
-    v += dpp_move<0x114, 0xf>(v);
-    v += dpp_move<0x118, 0xf>(v);
-    return v;
-}
-__device__ __forceinline__ uint32_t fx_row_sum_u(uint32_t v)
-{
-    v += dpp_move_u<0x111, 0xf>(v);
-    v += dpp_move_u<0x112, 0xf>(v);
-    v += dpp_move_u<0x114, 0xf>(v);
-    v += dpp_move_u<0x118, 0xf>(v);
-    return v;
-}
-
 // Eq. (1) given whether the pair is inside the cut-off (the reciprocal as in
 // fx_wca).
 __device__ __forceinline__ double fx_wca_in(double s2, double r2, bool in)
@@ -536,15 +517,15 @@ __device__ __forceinline__ void fx_build_lists(const FxK& K, const FxView<kRes>&
     const uint32_t nc = K.nc;
     const bool fold = nc <= 3u;  // the 27 cells span the box
     for (uint32_t cell = (uint32_t)wave; cell < ncell; cell += kFxWaves) {
-        const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane((int)V.cell_start[cell]),
-                       e = (uint32_t)__builtin_amdgcn_readfirstlane((int)V.cell_start[cell + 1]);
+        const uint32_t b = uniform(V.cell_start[cell]),
+                       e = uniform(V.cell_start[cell + 1]);
         if (b >= e) continue;
         const uint32_t ix = cell % nc, iy = (cell / nc) % nc, iz = cell / (nc * nc);
         const double ox = h[0] + ((double)ix + 0.5) * K.w, oy = h[1] + ((double)iy + 0.5) * K.w,
                      oz = h[2] + ((double)iz + 0.5) * K.w;
         uint32_t lo, off, total;
         const int nseg = fx_segments(K, V, (int)ix, (int)iy, (int)iz, &lo, &off, &total);
-        total = (uint32_t)__builtin_amdgcn_readfirstlane((int)total);
+        total = uniform(total);
         for (uint32_t q0 = b; q0 < e; q0 += 64u) {
             const uint32_t cnt = min(64u, e - q0);
             if (total > 64u * kFxSlots) {
@@ -752,10 +733,10 @@ __device__ __forceinline__ void fx_eval_rows(const FxK& K, const FxView<kRes>& V
     }
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        const double rs = fx_row_sum(de[g]);
-        const uint32_t ts = fx_row_sum_u(terms[g]);
+        const double rs = row_sum_dpp(de[g]);
+        const uint32_t ts = row_sum_dpp_u(terms[g]);
         double ss = 0.0;
-        if (kLog) ss = fx_row_sum(sc[g]);
+        if (kLog) ss = row_sum_dpp(sc[g]);
         if (rl == 15u) {
             W.sum[4u * (uint32_t)g + row] = rs;
             W.terms[4u * (uint32_t)g + row] = ts;
@@ -874,7 +855,7 @@ __device__ void fx_sort_cells(uint32_t* list, const uint32_t* start, uint32_t c0
 {
     const uint32_t lane = (uint32_t)__lane_id();
     for (uint32_t c = c0; c < ncell; c += cstep) {
-        const uint32_t b = start[c], cnt = start[c + 1] - b;
+        const uint32_t b = uniform(start[c]), cnt = uniform(start[c + 1]) - b;
         if (cnt <= 1u) continue;
         if (cnt <= 64u) {
             const uint32_t v = lane < cnt ? list[b + lane] : 0xFFFFFFFFu;
@@ -917,7 +898,7 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
     extern __shared__ __align__(16) unsigned char fx_smem[];
     const FxDev& D = *Dp;
     const FxK K = fx_const(D);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
     FxWaveLds W{rows[wave], rsum[wave], rscale[kLog ? wave : 0], rterms[wave], lists[wave], pair_s, pair_s2};
     Stats* st = D.stats;
     const uint32_t N = D.N, ncell = D.ncell, nc = D.nc, k = D.k;
@@ -1031,8 +1012,8 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
         // the attempts of cell `ci` of colour `col` by this wave
         auto run_cell = [&](uint32_t col, uint32_t ci) __attribute__((always_inline)) {
             const uint32_t cell = cell_of(col, ci);
-            const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane((int)V.cell_start[cell]),
-                           e = (uint32_t)__builtin_amdgcn_readfirstlane((int)V.cell_start[cell + 1]);
+            const uint32_t b = uniform(V.cell_start[cell]),
+                           e = uniform(V.cell_start[cell + 1]);
             wc.e = 0.0;
             for (uint32_t q0 = b; q0 < e; q0 += 64u) {
                 const uint32_t cnt = min(64u, e - q0);
@@ -1065,7 +1046,7 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
         ++sweep;
         // E_acc += the sweep's dE, the cells in a fixed order; E/M samples
         if (wave == 0) {
-            const double e = misc[0] + sweep_energy((const double*)V.ecell, ncell);
+            const double e = misc[0] + sweep_energy([&](uint32_t c) { return (double)V.ecell[c]; }, ncell);
             if (lane == 0) misc[0] = e;
         }
         if (tid == 0) {

@@ -22,6 +22,15 @@ using Global = __attribute__((address_space(1))) T;
 template <typename T>
 using Lds = __attribute__((address_space(3))) T;
 
+// A value every lane of the wave holds, in a scalar register: the compiler takes
+// what comes from memory, LDS or threadIdx for different in every lane, and
+// then branches on it with execution masks.
+__device__ __forceinline__ uint32_t uniform(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+__device__ __forceinline__ int wave_index() { return (int)uniform(threadIdx.x >> 6); }
+
 struct U4 {
     uint32_t x, y, z, w;
 };
@@ -90,6 +99,13 @@ __device__ __forceinline__ uint32_t wave_sum_u(uint32_t v)
     return v;
 }
 
+__device__ __forceinline__ unsigned long long wave_sum_ull(unsigned long long v)
+{
+#pragma unroll
+    for (int o = 32; o; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
+
 // Wave-wide sum with DPP row shifts and row broadcasts (a fixed addition
 // order, so the result does not depend on timing); every lane gets it.
 template <int kCtrl, int kRowMask>
@@ -114,14 +130,26 @@ __device__ __forceinline__ double wave_sum_dpp(double v)
     return __longlong_as_double((long long)((hi << 32) | lo));
 }
 
+// Sum over each row of 16 lanes (the row's last lane gets it), in the order of
+// wave_sum_dpp's first steps.
+__device__ __forceinline__ double row_sum_dpp(double v)
+{
+    v += dpp_move<0x111, 0xf>(v);
+    v += dpp_move<0x112, 0xf>(v);
+    v += dpp_move<0x114, 0xf>(v);
+    v += dpp_move<0x118, 0xf>(v);
+    return v;
+}
+
 // The accepted dE of a sweep from the per-cell sums (each in its cell's trial
 // order): lane l adds cells l, l + 64, ... in turn, then the DPP sum.  Every
 // engine reduces the same way, so E_acc does not depend on how the cells were
 // spread over waves and workgroups.  Call with a whole wave.
-__device__ __forceinline__ double sweep_energy(const double* ecell, uint32_t ncell)
+template <class At>
+__device__ __forceinline__ double sweep_energy(At at, uint32_t ncell)
 {
     double a = 0.0;
-    for (uint32_t c = (uint32_t)__lane_id(); c < ncell; c += 64u) a += ecell[c];
+    for (uint32_t c = (uint32_t)__lane_id(); c < ncell; c += 64u) a += at(c);
     return wave_sum_dpp(a);
 }
 
@@ -130,6 +158,38 @@ template <int kCtrl, int kRowMask>
 __device__ __forceinline__ uint32_t dpp_move_u(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, kRowMask, 0xf, true);
+}
+
+// Wave-wide OR and maximum in the same steps; every lane gets them.
+__device__ __forceinline__ uint32_t wave_or_dpp(uint32_t v)
+{
+    v |= dpp_move_u<0x111, 0xf>(v);
+    v |= dpp_move_u<0x112, 0xf>(v);
+    v |= dpp_move_u<0x114, 0xf>(v);
+    v |= dpp_move_u<0x118, 0xf>(v);
+    v |= dpp_move_u<0x142, 0xa>(v);
+    v |= dpp_move_u<0x143, 0xc>(v);
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+__device__ __forceinline__ uint32_t wave_max_dpp(uint32_t v)
+{
+    v = max(v, dpp_move_u<0x111, 0xf>(v));
+    v = max(v, dpp_move_u<0x112, 0xf>(v));
+    v = max(v, dpp_move_u<0x114, 0xf>(v));
+    v = max(v, dpp_move_u<0x118, 0xf>(v));
+    v = max(v, dpp_move_u<0x142, 0xa>(v));
+    v = max(v, dpp_move_u<0x143, 0xc>(v));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+__device__ __forceinline__ uint32_t row_sum_dpp_u(uint32_t v)
+{
+    v += dpp_move_u<0x111, 0xf>(v);
+    v += dpp_move_u<0x112, 0xf>(v);
+    v += dpp_move_u<0x114, 0xf>(v);
+    v += dpp_move_u<0x118, 0xf>(v);
+    return v;
 }
 
 // Inclusive prefix sum over the wave, in the steps of wave_sum_dpp (six adds;
@@ -169,7 +229,7 @@ __device__ __forceinline__ void wave_lds_sync()
 template <int kT>
 __device__ void block_excl_scan_t(uint32_t* a, uint32_t n, uint32_t* scratch)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
     const uint32_t per = (n + kT - 1) / kT;
     const uint32_t beg = min(n, tid * per), end = min(n, beg + per);
     uint32_t s = 0;

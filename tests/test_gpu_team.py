@@ -1,0 +1,65 @@
+"""Workgroups that share a system's sweeps: bitwise what one workgroup does, at
+the edges of the multi-workgroup engine's layouts."""
+import numpy as np
+import pytest
+
+from paper_2506_21290_amd import flipmc
+
+pytestmark = pytest.mark.gpu
+
+
+def chain(M, T, k, nc, seed, fp32, sweeps, workgroups):
+    rng = np.random.default_rng(seed)
+    n = int(np.ceil(M ** (1 / 3)))
+    side = (3.0 * M / 1.2) ** (1 / 3)
+    at = np.sort(rng.permutation(n ** 3)[:M])
+    com = (np.stack([at % n, (at // n) % n, at // (n * n)], axis=1) + 0.5) * (side / n)
+    q = rng.normal(size=(M, 4))
+    q /= np.linalg.norm(q, axis=1, keepdims=True)
+    types = np.argsort(rng.random((M, 3)), axis=1).astype(np.uint8)
+    p = flipmc.mc_params_default(n_molecules=M, temperature=T, colours_per_axis=k, cells_per_side=nc, seed=seed,
+                                 precision=flipmc.MC_FP32_DE if fp32 else flipmc.MC_FP64, workgroups=workgroups,
+                                 gofr_interval=0, resum_interval=2)
+    s = flipmc.System(p, com=com, quat=q, types=types)
+    s.decision_log(sweeps)
+    s.sweep(sweeps)
+    out = s.read_log(), s.get_state(), s.observables()
+    s.close()
+    return out
+
+
+@pytest.mark.parametrize("M,k,nc,workgroups", [
+    (64, 2, 2, 0),       # one cell per colour: one workgroup's waves share it
+    (83, 2, 2, 0),       # no whole groups of eight molecules
+    (1000, 2, 2, 0),     # 125 molecules a cell, neighbourhoods too large to stage
+    (217, 3, 6, 0),      # 27 colours of 8 cells
+    (1001, 2, 4, 0),     # 8 workgroups, each ranking all molecules
+    (2048, 2, 6, 0),     # the largest that each ranks alone
+    (2049, 2, 6, 0),     # the smallest whose ranks are shared out
+    (2197, 2, 6, 3),     # fewer workgroups than cells of a colour: a cell per wave
+    (8000, 2, 10, 4),    # the same with several cells a wave
+    (2747, 2, 8, 0),     # 64 workgroups: barriers in groups
+    (6001, 3, 18, 0),    # 216 workgroups, 125 cells in the stencil
+])
+@pytest.mark.parametrize("fp32", [False, True])
+def test_team_equals_one_workgroup(M, k, nc, workgroups, fp32):
+    n = 4
+    l0, s0, o0 = chain(M, 1.1, k, nc, 7, fp32, n, 1)
+    l1, s1, o1 = chain(M, 1.1, k, nc, 7, fp32, n, workgroups)
+    for f in ("delta_e", "scale", "accepted", "exited", "move", "pair_terms"):
+        assert np.array_equal(l0[f], l1[f]), f
+    for f in ("com", "quat", "types", "e_acc", "sweep"):
+        assert np.array_equal(s0[f], s1[f]), f
+    for f in ("attempts", "accepts", "exits", "pair_terms", "pair_tests", "near_overflows"):
+        assert np.array_equal(o0[f], o1[f]), f
+    assert np.sum(o1["accepts"]) > 0 and (nc > 2 or M < 1000 or o1["near_overflows"] > 0)
+
+
+def test_lists_beyond_lds():
+    # 40000 molecules: the cell lists do not fit a workgroup's LDS, and the
+    # workgroups build them together in the system's buffer
+    l0, s0, _ = chain(40000, 1.1, 2, 18, 5, True, 2, 1)
+    l1, s1, _ = chain(40000, 1.1, 2, 18, 5, True, 2, 0)
+    assert np.array_equal(l0["delta_e"], l1["delta_e"]) and np.array_equal(l0["accepted"], l1["accepted"])
+    for f in ("com", "quat", "types", "e_acc"):
+        assert np.array_equal(s0[f], s1[f]), f
