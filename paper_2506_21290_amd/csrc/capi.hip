@@ -356,7 +356,16 @@ BufLayout buf_layout(const mc_params* p, const Geometry& g)
     const size_t M = p->n_molecules;
     size_t o = 0;
     b.sys = o;    o = al(o + sizeof(SysDev));
+    // what the reading calls want lies together, so that each takes one copy:
+    // the observables, and on to the configuration
     b.stats = o;  o = al(o + sizeof(Stats));
+    b.gall = o;   o = al(o + kGofrBins * sizeof(uint64_t));
+    b.ginter = o; o = al(o + kGofrBins * sizeof(uint64_t));
+    b.c2 = o;     o = al(o + kC2Max * sizeof(double));
+    b.c2s = o;    o = al(o + kC2Max * sizeof(uint64_t));
+    b.fs = o;     o = al(o + kC2Max * sizeof(double));
+    b.fscm = o;   o = al(o + kC2Max * sizeof(double));
+    b.mom = o;    o = al(o + 4 * kC2Max * sizeof(double));
     b.com = o;    o = al(o + 3 * M * sizeof(double));
     b.quat = o;   o = al(o + 4 * M * sizeof(double));
     b.types = o;  o = al(o + M * sizeof(uint32_t));
@@ -364,16 +373,9 @@ BufLayout buf_layout(const mc_params* p, const Geometry& g)
     b.kref = o;   o = al(o + M);
     b.esamp = o;  o = al(o + size_t(p->max_samples) * sizeof(double));
     b.dsamp = o;  o = al(o + size_t(p->max_samples) * sizeof(double));
-    b.gall = o;   o = al(o + kGofrBins * sizeof(uint64_t));
-    b.ginter = o; o = al(o + kGofrBins * sizeof(uint64_t));
-    b.c2 = o;     o = al(o + kC2Max * sizeof(double));
-    b.c2s = o;    o = al(o + kC2Max * sizeof(uint64_t));
     b.img = o;    o = al(o + 3 * M * sizeof(int32_t));
     b.r0 = o;     o = al(o + 3 * M * sizeof(double));
     b.o0 = o;     o = al(o + 9 * M * sizeof(double));
-    b.fs = o;     o = al(o + kC2Max * sizeof(double));
-    b.fscm = o;   o = al(o + kC2Max * sizeof(double));
-    b.mom = o;    o = al(o + 4 * kC2Max * sizeof(double));
     b.props = o;  o = al(o + M * 48);
     b.gpart = o;  o = al(o + kMaxParts * sizeof(double));
     if (g.team_arrays()) {
@@ -623,15 +625,25 @@ int advance(mc_system* s, uint64_t n)
     return MC_OK;
 }
 
-int read_stats(mc_system* s, Stats* st)
+// A copy of the system's buffer from its statistics up to byte `to` (a system of 1000 molecules took 70 us for its configuration in
+// four copies, each with a wait of its own).
+int read_block(mc_system* s, size_t to, std::vector<uint8_t>* out, Stats* st)
 {
     if (int rc = sync_owner(s)) return rc;
-    HIPCHK(hipMemcpyAsync(st, s->host.stats, sizeof(Stats), hipMemcpyDeviceToHost, s->stream));
+    out->resize(to - s->lay.stats);
+    HIPCHK(hipMemcpyAsync(out->data(), s->buf + s->lay.stats, out->size(), hipMemcpyDeviceToHost, s->stream));
     HIPCHK(hipStreamSynchronize(s->stream));
+    std::memcpy(st, out->data(), sizeof(Stats));
     if (st->fault)
         return fail(MC_EDEVICE, "a workgroup barrier of the multi-workgroup engine timed out: "
                                 "the system's state is invalid");
     return MC_OK;
+}
+
+int read_stats(mc_system* s, Stats* st)
+{
+    std::vector<uint8_t> raw;
+    return read_block(s, s->lay.stats + sizeof(Stats), &raw, st);
 }
 
 int write_stats(mc_system* s, const Stats* st)
@@ -939,8 +951,9 @@ int mc_observables(mc_system* s, mc_obs* o)
 {
     if (!s || !o) return fail(MC_EINVAL, "null argument");
     Stats st;
-    int rc = read_stats(s, &st);
-    if (rc) return rc;
+    std::vector<uint8_t> raw;
+    if (int rc = read_block(s, s->lay.com, &raw, &st)) return rc;
+    const uint8_t* at = raw.data() - s->lay.stats;
     std::memset(o, 0, sizeof *o);
     o->sweep = st.sweep;
     for (int i = 0; i < 3; ++i) {
@@ -965,17 +978,17 @@ int mc_observables(mc_system* s, mc_obs* o)
     o->gofr_dr = s->host.gofr_dr;
     o->gofr_rmax = s->host.gofr_rmax;
     o->n_c2 = st.n_c2;
-    HIPCHK(hipMemcpyAsync(o->gofr_all, s->host.gofr_all, sizeof o->gofr_all, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipMemcpyAsync(o->gofr_inter, s->host.gofr_inter, sizeof o->gofr_inter, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipMemcpyAsync(o->c2, s->host.c2, sizeof o->c2, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipMemcpyAsync(o->fs, s->host.fs, sizeof o->fs, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipMemcpyAsync(o->fs_cm, s->host.fs_cm, sizeof o->fs_cm, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipMemcpyAsync(o->c2_sq, s->host.mom, sizeof o->c2_sq, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipMemcpyAsync(o->fs_cm_sq, s->host.mom + kC2Max, sizeof o->fs_cm_sq, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipMemcpyAsync(o->c2_fs_cm, s->host.mom + 2 * kC2Max, sizeof o->c2_fs_cm, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipMemcpyAsync(o->fs_sq, s->host.mom + 3 * kC2Max, sizeof o->fs_sq, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipMemcpyAsync(o->c2_sweep, s->host.c2_sweep, sizeof o->c2_sweep, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipStreamSynchronize(s->stream));
+    const BufLayout& l = s->lay;
+    std::memcpy(o->gofr_all, at + l.gall, sizeof o->gofr_all);
+    std::memcpy(o->gofr_inter, at + l.ginter, sizeof o->gofr_inter);
+    std::memcpy(o->c2, at + l.c2, sizeof o->c2);
+    std::memcpy(o->fs, at + l.fs, sizeof o->fs);
+    std::memcpy(o->fs_cm, at + l.fscm, sizeof o->fs_cm);
+    std::memcpy(o->c2_sq, at + l.mom, sizeof o->c2_sq);
+    std::memcpy(o->fs_cm_sq, at + l.mom + kC2Max * sizeof(double), sizeof o->fs_cm_sq);
+    std::memcpy(o->c2_fs_cm, at + l.mom + 2 * kC2Max * sizeof(double), sizeof o->c2_fs_cm);
+    std::memcpy(o->fs_sq, at + l.mom + 3 * kC2Max * sizeof(double), sizeof o->fs_sq);
+    std::memcpy(o->c2_sweep, at + l.c2s, sizeof o->c2_sweep);
     gofr_normalise(s, o);
     return MC_OK;
 }
@@ -1012,15 +1025,13 @@ int mc_get_state(mc_system* s, double* com, double* quat, uint8_t* types, uint64
 {
     if (!s) return fail(MC_EINVAL, "null system");
     const size_t M = s->p.n_molecules;
-    std::vector<double> c(3 * M), q(4 * M);
-    std::vector<uint32_t> t(M);
     Stats st;
-    if (int rc0 = sync_owner(s)) return rc0;
-    HIPCHK(hipMemcpyAsync(c.data(), s->host.com, c.size() * sizeof(double), hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipMemcpyAsync(q.data(), s->host.quat, q.size() * sizeof(double), hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipMemcpyAsync(t.data(), s->host.types, t.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, s->stream));
-    int rc = read_stats(s, &st);
-    if (rc) return rc;
+    std::vector<uint8_t> raw;
+    if (int rc = read_block(s, s->lay.types + M * sizeof(uint32_t), &raw, &st)) return rc;
+    const uint8_t* at = raw.data() - s->lay.stats;
+    const double* c = (const double*)(at + s->lay.com);
+    const double* q = (const double*)(at + s->lay.quat);
+    const uint32_t* t = (const uint32_t*)(at + s->lay.types);
     for (size_t m = 0; m < M; ++m) {
         if (com)
             for (int a = 0; a < 3; ++a) com[3 * m + a] = c[a * M + m];

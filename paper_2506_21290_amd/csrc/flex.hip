@@ -1132,11 +1132,15 @@ int mcf_get_state(mcf_system* s, double* pos, uint8_t* types, uint64_t* sweep, d
 {
     if (!s) return fx_fail(MC_EINVAL, "null system");
     const uint32_t N = s->g.N;
-    std::vector<double> x(3 * (size_t)N);
-    FXCHK(hipMemcpyAsync(x.data(), s->host.pos, x.size() * sizeof(double), hipMemcpyDeviceToHost, s->stream));
-    if (types) FXCHK(hipMemcpyAsync(types, s->host.type, N, hipMemcpyDeviceToHost, s->stream));
+    // statistics, positions and types lie together: one copy
+    std::vector<uint8_t> raw(s->lay.type + N - s->lay.stats);
+    FXCHK(hipMemcpyAsync(raw.data(), s->host.stats, raw.size(), hipMemcpyDeviceToHost, s->stream));
+    FXCHK(hipStreamSynchronize(s->stream));
+    const uint8_t* at = raw.data() - s->lay.stats;
     Stats st;
-    if (int rc = fx_read_stats(s, &st)) return rc;
+    std::memcpy(&st, raw.data(), sizeof st);
+    const double* x = (const double*)(at + s->lay.pos);
+    if (types) std::memcpy(types, at + s->lay.type, N);
     if (pos)
         for (uint32_t i = 0; i < N; ++i)
             for (int d = 0; d < 3; ++d) pos[3 * i + d] = x[(size_t)d * N + i];
