@@ -334,13 +334,18 @@ double ms_per_model_cycle()
     return 0.31 / slice_time(1000);
 }
 
-// Workgroups of the multi-workgroup event kernel for M molecules (one
-// molecule per thread of the O(M^2) loops), 1 = single-workgroup events.
+// Workgroups of the multi-workgroup event kernel for M molecules, 1 =
+// single-workgroup events.  256 molecules are 20 units: below that the extra
+// launch takes longer than it saves.
 uint32_t event_blocks(uint32_t M)
 {
-    if (M < 2048) return 1;
-    return std::min((uint32_t)kMaxParts, (M + kThreads - 1) / kThreads);
+    if (M < 256) return 1;
+    return std::min(256u, (event_units(M).count() + kWaves - 1) / kWaves);
 }
+
+// Systems below this size take scheduled re-sums and C_2 samples inside a
+// batch's sweep kernel.
+constexpr uint32_t kInlineBelow = 2048;
 
 struct BufLayout {
     size_t sys, stats, com, quat, types, u0, kref, esamp, dsamp, gall, ginter, c2, c2s;
@@ -377,7 +382,7 @@ BufLayout buf_layout(const mc_params* p, const Geometry& g)
     b.r0 = o;     o = al(o + 3 * M * sizeof(double));
     b.o0 = o;     o = al(o + 9 * M * sizeof(double));
     b.props = o;  o = al(o + M * 48);
-    b.gpart = o;  o = al(o + kMaxParts * sizeof(double));
+    b.gpart = o;  o = al(o + max_units((uint32_t)M) * sizeof(double));
     if (g.team_arrays()) {
         const bool fp64 = p->precision == MC_FP64;
         b.gsite = o;   o = al(o + M * std::max(3 * site_bytes(fp64), mol_bytes(fp64)));
@@ -501,6 +506,27 @@ void timing_stop(mc_system* s, hipEvent_t a, bool sweep_kernel)
     (sweep_kernel ? s->ev_sweep : s->ev_event).emplace_back(a, b);
 }
 
+constexpr uint32_t kOverPairs = kFlagResumSet | kFlagResumReport | kFlagResumPeriodic | kFlagGofr;
+
+// The part of event work `flags` of a system that goes to the multi-workgroup
+// event kernel, and in *units the energies it leaves.  A scheduled re-sum
+// follows sweeps, whose cell lists are still there (but not the LDS engine's):
+// above 8192 molecules they save more than the shorter ranges of a wave cost
+// (27000 molecules: 0.5 ms over all pairs).
+PartSlot part_slot(const mc_system* s, uint32_t flags, uint32_t first, uint32_t* units)
+{
+    const uint32_t M = s->p.n_molecules;
+    PartSlot p{s->dev, flags, first, event_blocks(M), 0u};
+    const int span = (int)std::ceil((std::sqrt(s->host.reach2) + 2.0 * 1.7320508075688772 * s->host.dmax + 1e-9) /
+                                    s->host.w);
+    const uint32_t planes = 2u * (uint32_t)span + 1u;
+    if (M > 8192 && !(flags & (kFlagResumSet | kFlagResumReport)) && s->host.g_cell && planes <= s->host.nc &&
+        planes <= kMaxPlanes)
+        p.span = (uint32_t)span;
+    *units = p.span ? (M + 63u) / 64u * planes : event_units(M).count();
+    return p;
+}
+
 int launch_events_one(mc_system* s, uint32_t flags)
 {
     TraceRange tr((flags & (kFlagResumSet | kFlagResumReport | kFlagResumPeriodic)) ? "flipmc events: FP64 re-sum"
@@ -509,15 +535,13 @@ int launch_events_one(mc_system* s, uint32_t flags)
     one.sys = s->dev;
     one.flags = flags;
     hipEvent_t t0 = timing_start(s);
-    const uint32_t nb = event_blocks(s->p.n_molecules);
-    if (nb > 1 && (flags & (kFlagResumSet | kFlagResumReport | kFlagResumPeriodic | kFlagGofr))) {
-        // the O(M^2) re-sum and g(r) frame on many workgroups, then the rest
+    if (event_blocks(s->p.n_molecules) > 1 && (flags & kOverPairs)) {
+        // the re-sum and g(r) frame over all pairs on many workgroups, then the rest
         PartList pl{};
-        pl.s[0] = PartSlot{s->dev, flags, 0u, nb, 0u};
+        pl.s[0] = part_slot(s, flags, 0u, &one.pad);
         pl.n = 1;
-        HIPCHK(launch_event_parts(pl, nb, s->stream));
+        HIPCHK(launch_event_parts(pl, pl.s[0].count, s->stream));
         one.flags = flags | kFlagParts;
-        one.pad = nb;
     }
     HIPCHK(launch_events(nullptr, one, 1, s->stream));
     timing_stop(s, t0, false);
@@ -686,9 +710,9 @@ hipError_t launch_parts_of(const std::vector<std::pair<mc_system*, uint32_t>>& p
         PartList pl{};
         uint32_t blocks = 0;
         for (size_t i = i0; i < std::min(parts.size(), i0 + kPartSlots); ++i) {
-            const uint32_t nb = event_blocks(parts[i].first->p.n_molecules);
-            pl.s[pl.n++] = PartSlot{parts[i].first->dev, parts[i].second, blocks, nb, 0u};
-            blocks += nb;
+            uint32_t units;
+            pl.s[pl.n] = part_slot(parts[i].first, parts[i].second, blocks, &units);
+            blocks += pl.s[pl.n++].count;
         }
         const hipError_t e = launch_event_parts(pl, blocks, stream);
         if (e != hipSuccess) return e;
@@ -1534,11 +1558,12 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
         Slot ev{};
         ev.sys = s->dev;
         ev.flags = f;
-        const uint32_t nbp = event_blocks(s->p.n_molecules);
-        if (nbp > 1 && (f & (kFlagResumSet | kFlagResumReport | kFlagResumPeriodic | kFlagGofr))) {
+        // (many small systems fill the device with a workgroup each)
+        const uint32_t M = s->p.n_molecules;
+        if ((M >= kInlineBelow || active.size() <= 32) && event_blocks(M) > 1 && (f & kOverPairs)) {
             parts.emplace_back(s, f);
+            (void)part_slot(s, f, 0u, &ev.pad);
             ev.flags = f | kFlagParts;
-            ev.pad = nbp;
         }
         return ev;
     };
@@ -1548,7 +1573,7 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
         // a system on one workgroup whose events fit the one-workgroup event
         // kernel takes its scheduled re-sums and C_2 samples inside the sweep
         // kernel: its slice stops only at g(r) frames
-        const bool inl = event_blocks(s->p.n_molecules) == 1;
+        const bool inl = s->p.n_molecules < kInlineBelow;
         uint64_t k = std::min<uint64_t>(b->remaining[i], next_event(s, inl) - s->sweep);
         const int cls = s->g.resident ? 0 : 1;
         if (max_moves_per_slot) {

@@ -31,6 +31,30 @@ constexpr int kNearSlots = kNearMin / 64;  // list entries per lane in registers
 constexpr uint32_t kEventStage = 2047;
 constexpr size_t kEventStageBytes = size_t(kEventStage) * (7 * sizeof(double) + sizeof(uint32_t));
 
+// The units of the event work over all pairs of M molecules (a wave's each):
+// blocks of 64 molecules, each against `splits` ranges of the other half.  About
+// 2048 in all, a wave for every two SIMDs of the device, and ranges of 32 pairs
+// or more.
+struct EventUnits {
+    uint32_t blocks, splits;
+    __host__ __device__ uint32_t count() const { return blocks * splits; }
+};
+__host__ __device__ inline EventUnits event_units(uint32_t M)
+{
+    EventUnits u;
+    u.blocks = (M + 63u) / 64u;
+    const uint32_t most = M / 64u ? M / 64u : 1u, want = 2048u / u.blocks ? 2048u / u.blocks : 1u;
+    u.splits = want < most ? want : most;
+    return u;
+}
+// Planes of cells that a re-sum from the cell lists may take as units.
+constexpr uint32_t kMaxPlanes = 5;
+__host__ __device__ inline uint32_t max_units(uint32_t M)
+{
+    const uint32_t a = event_units(M).count(), b = (M + 63u) / 64u * kMaxPlanes;
+    return a > b ? a : b;
+}
+
 // Work of the event kernel (Slot::flags).
 enum : uint32_t {
     kFlagResumSet = 1u,       // re-sum E and take it as the accumulated energy
@@ -40,7 +64,7 @@ enum : uint32_t {
     kFlagGofr = 16u,          // accumulate one g(r) frame
     kFlagC2 = 32u,            // record one C_2 sample
     kFlagParts = 64u,         // the re-sum and the g(r) frame were done by the
-                              // multi-workgroup event kernel: sum its partial
+                              // multi-workgroup event kernel: sum its unit
                               // energies (Slot::pad of them), count the frame
     kFlagInline = 128u,       // (a sweep slot) the scheduled re-sums and C_2
                               // samples of its sweeps are taken by the sweep
@@ -112,7 +136,7 @@ struct SysDev {
     uint16_t* g_list;    // [M] molecules sorted by cell, ascending inside a cell
     void* props;         // [M] proposals of the current sweep (48 bytes each)
     uint32_t* g_cnt;     // [2 * ncell] cell counts and fill cursors (multi-workgroup engine)
-    double* g_part;      // [kMaxParts] per-workgroup partial sums of the event kernel
+    double* g_part;      // [max_units(M)] unit energies of a re-sum
     double* g_ecell;     // [ncell] accepted dE of each cell in the current sweep (HBM state)
     uint32_t* g_bar;     // [kBarWords] barrier counter and crew of the system's workgroups (multi-workgroup engine)
     // decision log
@@ -184,7 +208,6 @@ __host__ __device__ inline LdsLayout lds_layout(bool fp64, bool resident, uint32
 // colour, stages the cell's neighbourhood (up to near_cap molecules) in its LDS
 // and its waves share the cell's trials; or each of the first `waves` waves of a
 // workgroup takes and stages a cell of its own.
-constexpr int kMaxParts = 1024;  // workgroups of the event kernel
 constexpr int kBarWords = 272;   // words of SysDev::g_bar
 
 // LDS of one of its workgroups: the lists of the system's cells too where they
@@ -255,21 +278,21 @@ hipError_t launch_zero_barriers(const SpreadSlot* dev_slots, uint32_t n_slots, h
 // Workgroups of the spread kernel that the current device holds at once.
 hipError_t spread_max_blocks(uint32_t* n_blocks);
 // The systems of one launch of the event work over many workgroups, passed by
-// value (no table in memory): system i owns workgroups [first, first + count)
-// and splits its work over them as a launch of count workgroups of its own
-// would, so its partial sums do not depend on the systems beside it.
+// value (no table in memory): system i owns workgroups [first, first + count),
+// whose waves take its units in turn.
 struct PartSlot {
     SysDev* sys;
-    uint32_t flags, first, count, pad;
+    uint32_t flags, first, count;
+    uint32_t span;  // re-sum from the cell lists, so many cells each way (0: all pairs)
 };
 constexpr uint32_t kPartSlots = 128;
 struct PartList {
     PartSlot s[kPartSlots];
     uint32_t n;
 };
-// The O(M^2) part of the events of list.s[0 .. n) (re-sum partial energies
+// The part over all pairs of the events of list.s[0 .. n) (re-sum unit energies
 // into g_part, g(r) frame into the histograms), n_blocks = the sum of their
-// counts; follow with launch_events(flags | kFlagParts, pad = count).
+// counts; follow with launch_events(flags | kFlagParts, pad = units).
 hipError_t launch_event_parts(const PartList& list, uint32_t n_blocks, hipStream_t stream);
 
 // Record msg as the calling thread's last error (mc_last_error) and return code.

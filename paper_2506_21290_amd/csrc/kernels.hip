@@ -419,91 +419,168 @@ __device__ __forceinline__ void offsets_f64(const Ctx<Real, kMem>& C, uint32_t m
     for (int s = 0; s < 3; ++s) sg[s] = sigma_of(C, (ty >> (8 * s)) & 0xFFu);
 }
 
-// Total inter-molecular energy in FP64 over balanced molecule pairs.
-template <typename Real, int kMem>
-__device__ double resum_energy(const Ctx<Real, kMem>& C, uint32_t m0, uint32_t mstep)
+// The event work over all pairs of molecules is cut into units that a wave
+// takes: 64 molecules, one a lane, against a range of the others (EventUnits).
+// Whoever takes a unit adds it up in the same order, so one workgroup and many
+// give the same bits.
+//
+// Almost all pairs end at the distance of their centres, so the few that go on
+// are queued and evaluated 64 at a time with every lane busy: evaluated where
+// they were found, one of 64 lanes having one kept the others waiting in most
+// iterations.  A total energy of 8000 molecules took 858 us on 16 workgroups,
+// a thread per molecule.
+
+// Pairs of a wave that passed the distance test, its `each` called with 64 of
+// them (or the rest, at the end).
+template <typename Each>
+struct PairQueue {
+    uint32_t* q;  // kGofrQueue words of LDS
+    Each each;
+    uint32_t n;
+    __device__ __forceinline__ void drain(uint32_t upto)
+    {
+        while (n >= upto && n > 0u) {
+            const uint32_t take = min(n, 64u), base = n - take, lane = (uint32_t)__lane_id();
+            if (lane < take) each(q[base + lane] & 0xFFFFu, q[base + lane] >> 16);
+            n = base;
+        }
+    }
+    // keep: whether this lane has the pair (m, j)
+    __device__ __forceinline__ void push(bool keep, uint32_t m, uint32_t j)
+    {
+        const uint64_t bm = __ballot(keep);
+        if (bm == 0ull) return;
+        if (keep) q[n + rank_below(bm)] = m | (j << 16);
+        n += (uint32_t)__popcll(bm);
+        wave_lds_sync();
+        drain(64u);
+        wave_lds_sync();
+    }
+};
+
+// The pairs of unit u whose centres are nearer than the root of cut2.
+template <typename Cx, typename Queue>
+__device__ __forceinline__ void unit_pairs(const Cx& C, const EventUnits& U, uint32_t u, double cut2, Queue& Q)
 {
     const uint32_t M = C.M, half = M / 2;
-    double e = 0.0;
-    for (uint32_t m = m0; m < M; m += mstep) {
-        double om[9], sm[3];
-        offsets_f64(C, m, om, sm);
-        const double cx = C.com[m], cy = C.com[M + m], cz = C.com[2 * M + m];
-        for (uint32_t dj = 1; dj <= half; ++dj) {
-            if ((M & 1u) == 0u && dj == half && m >= half) break;
-            uint32_t j = m + dj;
-            if (j >= M) j -= M;
+    const uint32_t blk = u / U.splits, part = u - blk * U.splits;
+    const uint32_t m = 64u * blk + (uint32_t)__lane_id();
+    const uint32_t d0 = 1u + (uint32_t)((uint64_t)half * part / U.splits),
+                   d1 = 1u + (uint32_t)((uint64_t)half * (part + 1u) / U.splits);
+    const bool mine = m < M;
+    const double cx = mine ? C.com[m] : 0.0, cy = mine ? C.com[M + m] : 0.0, cz = mine ? C.com[2 * M + m] : 0.0;
+    for (uint32_t dj = d0; dj < d1; ++dj) {
+        // (half way round an even number each pair comes twice)
+        bool keep = mine && !((M & 1u) == 0u && dj == half && m >= half);
+        uint32_t j = m + dj;
+        if (j >= M) j -= M;
+        if (keep) {
             const double dx = min_image(C.com[j] - cx, C.L, C.invL);
             const double dy = min_image(C.com[M + j] - cy, C.L, C.invL);
             const double dz = min_image(C.com[2 * M + j] - cz, C.L, C.invL);
-            if (dx * dx + dy * dy + dz * dz >= C.reach2) continue;
-            double oj[9], sj[3];
-            offsets_f64(C, j, oj, sj);
-#pragma unroll
-            for (int s = 0; s < 3; ++s)
-#pragma unroll
-                for (int t = 0; t < 3; ++t) {
-                    const double rx = dx + oj[3 * t] - om[3 * s];
-                    const double ry = dy + oj[3 * t + 1] - om[3 * s + 1];
-                    const double rz = dz + oj[3 * t + 2] - om[3 * s + 2];
-                    const double r2 = rx * rx + ry * ry + rz * rz;
-                    const double sg = 0.5 * (sm[s] + sj[t]);
-                    const double s2 = sg * sg;
-                    if (r2 < C.rc2_factor * s2) e += pair_u(s2, r2);
-                }
+            keep = dx * dx + dy * dy + dz * dz < cut2;
         }
+        Q.push(keep, m, j);
     }
-    return block_sum(e, C.red);
 }
 
-// The same total from the cell lists of the last sweep (HBM state): a
-// molecule has moved at most sqrt(3) d_max since they were built, so every
-// pair within reach lies within `span` cells per axis of the cell it was
-// sorted into.  Each pair is counted by its lower index, the neighbour cells
-// in a fixed order and the molecules of a cell in ascending index.
-// Requires 2 span + 1 <= n_c.
-template <typename Real, int kMem>
-__device__ double resum_energy_cells(const Ctx<Real, kMem>& C, uint32_t m0, uint32_t mstep, int span)
+// Energy of the nine site pairs of two molecules.
+template <typename Cx>
+__device__ __forceinline__ double pair_energy(const Cx& C, uint32_t m, uint32_t j)
 {
     const uint32_t M = C.M;
-    const int nc = (int)C.nc;
+    double om[9], sm[3], oj[9], sj[3];
+    offsets_f64(C, m, om, sm);
+    offsets_f64(C, j, oj, sj);
+    const double dx = min_image(C.com[j] - C.com[m], C.L, C.invL);
+    const double dy = min_image(C.com[M + j] - C.com[M + m], C.L, C.invL);
+    const double dz = min_image(C.com[2 * M + j] - C.com[2 * M + m], C.L, C.invL);
     double e = 0.0;
-    for (uint32_t m = m0; m < M; m += mstep) {
-        double om[9], sm[3];
-        offsets_f64(C, m, om, sm);
-        const double cx = C.com[m], cy = C.com[M + m], cz = C.com[2 * M + m];
-        const int cid = (int)C.cellid[m];
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const double rx = dx + oj[3 * t] - om[3 * s];
+            const double ry = dy + oj[3 * t + 1] - om[3 * s + 1];
+            const double rz = dz + oj[3 * t + 2] - om[3 * s + 2];
+            const double r2 = rx * rx + ry * ry + rz * rz;
+            const double sg = 0.5 * (sm[s] + sj[t]);
+            const double s2 = sg * sg;
+            if (r2 < C.rc2_factor * s2) e += pair_u(s2, r2);
+        }
+    return e;
+}
+
+// Eq. (1) over all pairs of sites of different molecules in FP64, unit by unit
+// into C.gpart: units wave, wave + nwaves, ...  queue: the wave's words of LDS.
+template <typename Real, int kMem>
+__device__ __forceinline__ void resum_units(const Ctx<Real, kMem>& C, const EventUnits& U, uint32_t wave,
+                                            uint32_t nwaves, uint32_t* queue)
+{
+    for (uint32_t u = wave; u < U.count(); u += nwaves) {
+        double e = 0.0;
+        auto each = [&](uint32_t m, uint32_t j) __attribute__((always_inline)) { e += pair_energy(C, m, j); };
+        PairQueue<decltype(each)> Q{queue, each, 0u};
+        unit_pairs(C, U, u, C.reach2, Q);
+        Q.drain(1u);
+        e = wave_sum_dpp(e);
+        if (__lane_id() == 0) C.gpart[u] = e;
+    }
+}
+
+// The same from the cell lists of the sweep that ended (positions that moved at
+// most one step since they were made, `span` cells each way): unit u takes 64
+// molecules against one plane of cells.  Requires 2 span + 1 <= n_c.
+template <typename Real, int kMem>
+__device__ __forceinline__ void resum_units_cells(const Ctx<Real, kMem>& C, uint32_t wave, uint32_t nwaves, int span,
+                                                  uint32_t* queue)
+{
+    const uint32_t M = C.M, planes = 2u * (uint32_t)span + 1u;
+    const int nc = (int)C.nc;
+    for (uint32_t u = wave; u < (M + 63u) / 64u * planes; u += nwaves) {
+        double e = 0.0;
+        auto each = [&](uint32_t m, uint32_t j) __attribute__((always_inline)) { e += pair_energy(C, m, j); };
+        PairQueue<decltype(each)> Q{queue, each, 0u};
+        const uint32_t blk = u / planes;
+        const int oz = (int)(u - blk * planes) - span;
+        const uint32_t m = 64u * blk + (uint32_t)__lane_id();
+        const bool mine = m < M;
+        const double cx = mine ? C.com[m] : 0.0, cy = mine ? C.com[M + m] : 0.0, cz = mine ? C.com[2 * M + m] : 0.0;
+        const int cid = mine ? (int)C.cellid[m] : 0;
         const int ix = cid % nc, iy = (cid / nc) % nc, iz = cid / (nc * nc);
-        for (int oz = -span; oz <= span; ++oz)
-            for (int oy = -span; oy <= span; ++oy)
-                for (int ox = -span; ox <= span; ++ox) {
-                    const int x = (ix + ox + nc) % nc, y = (iy + oy + nc) % nc, z = (iz + oz + nc) % nc;
-                    const uint32_t c = (uint32_t)(x + nc * (y + nc * z));
-                    const uint32_t pe = C.cellb[c + 1];
-                    for (uint32_t p = C.cellb[c]; p < pe; ++p) {
-                        const uint32_t j = C.list[p];
-                        if (j <= m) continue;
+        auto wrapped = [&](int v) { return v + (v < 0 ? nc : (v >= nc ? -nc : 0)); };
+        const int z = wrapped(iz + oz);
+        for (int oy = -span; oy <= span; ++oy)
+            for (int ox = -span; ox <= span; ++ox) {
+                const uint32_t c = (uint32_t)(wrapped(ix + ox) + nc * (wrapped(iy + oy) + nc * z));
+                uint32_t p = mine ? (uint32_t)C.cellb[c] : 0u;
+                const uint32_t pe = mine ? (uint32_t)C.cellb[c + 1] : 0u;
+                while (__ballot(p < pe) != 0ull) {
+                    bool keep = p < pe;
+                    uint32_t j = 0;
+                    if (keep) {
+                        j = C.list[p];
                         const double dx = min_image(C.com[j] - cx, C.L, C.invL);
                         const double dy = min_image(C.com[M + j] - cy, C.L, C.invL);
                         const double dz = min_image(C.com[2 * M + j] - cz, C.L, C.invL);
-                        if (dx * dx + dy * dy + dz * dz >= C.reach2) continue;
-                        double oj[9], sj[3];
-                        offsets_f64(C, j, oj, sj);
-#pragma unroll
-                        for (int a = 0; a < 3; ++a)
-#pragma unroll
-                            for (int t = 0; t < 3; ++t) {
-                                const double rx = dx + oj[3 * t] - om[3 * a];
-                                const double ry = dy + oj[3 * t + 1] - om[3 * a + 1];
-                                const double rz = dz + oj[3 * t + 2] - om[3 * a + 2];
-                                const double r2 = rx * rx + ry * ry + rz * rz;
-                                const double sg = 0.5 * (sm[a] + sj[t]);
-                                const double s2 = sg * sg;
-                                if (r2 < C.rc2_factor * s2) e += pair_u(s2, r2);
-                            }
+                        keep = j > m && dx * dx + dy * dy + dz * dz < C.reach2;
                     }
+                    Q.push(keep, m, j);
+                    ++p;
                 }
+            }
+        Q.drain(1u);
+        e = wave_sum_dpp(e);
+        if (__lane_id() == 0) C.gpart[u] = e;
     }
+}
+
+// Sum of the first n unit energies by the workgroup, in a fixed order.
+template <typename Cx>
+__device__ double sum_units(const Cx& C, uint32_t n)
+{
+    double e = 0.0;
+    for (uint32_t u = threadIdx.x; u < n; u += kThreads) e += C.gpart[u];
     return block_sum(e, C.red);
 }
 
@@ -629,14 +706,12 @@ __device__ void reset_observables(const Ctx<Real, kMem>& C)
 
 // One g(r) frame (Eq. 3 numerator): every ordered pair of distinct sites.
 template <typename Real, int kMem>
-__device__ void gofr_frame(const Ctx<Real, kMem>& C, uint32_t m0, uint32_t mstep, bool shared_out,
-                           uint32_t* queue)
+__device__ void gofr_frame(const Ctx<Real, kMem>& C, const EventUnits& U, uint32_t wave, uint32_t nwaves,
+                           bool shared_out, uint32_t* queue)
 {
-    const uint32_t M = C.M, half = M / 2, nb = C.gofr_nbins;
+    const uint32_t M = C.M, nb = C.gofr_nbins;
     uint32_t* bintra = C.bins;  // intramolecular pairs; all = intra + inter at the end
     uint32_t* binter = C.bins + kGofrBins;
-    uint32_t* q = queue + (threadIdx.x >> 6) * kGofrQueue;  // this wave's molecule pairs
-    const uint32_t lane = (uint32_t)__lane_id();
     for (uint32_t b = threadIdx.x; b < 2 * kGofrBins; b += kThreads) C.bins[b] = 0;
     __syncthreads();
     const double dr = C.gofr_dr, rmax = C.gofr_rmax;
@@ -674,26 +749,11 @@ __device__ void gofr_frame(const Ctx<Real, kMem>& C, uint32_t m0, uint32_t mstep
             }
         }
     };
-    // the pairs within reach of the bins are queued per wave and binned 64 at
-    // a time (the counts do not depend on the order)
-    uint32_t qn = 0;
-    auto drain = [&](uint32_t upto) __attribute__((always_inline)) {
-        while (qn >= upto && qn > 0) {
-            const uint32_t take = min(qn, 64u);
-            const uint32_t base = qn - take;
-            if (lane < take) {
-                const uint32_t e = q[base + lane];
-                site_pairs(e & 0xFFFFu, e >> 16);
-            }
-            qn = base;
-        }
-    };
-    // rounds of the wave's first lane (the most of any lane): wave-uniform
-    const uint32_t nrounds = (M + mstep - 1 - min(m0 - lane, M)) / mstep;
-    for (uint32_t r = 0; r < nrounds; ++r) {
-        const uint32_t m = m0 + r * mstep;
-        const bool mine = m < M;
-        if (mine) {
+    // (the counts do not depend on the order)
+    PairQueue<decltype(site_pairs)> Q{queue, site_pairs, 0u};
+    for (uint32_t u = wave; u < U.count(); u += nwaves) {
+        const uint32_t m = 64u * (u / U.splits) + (uint32_t)__lane_id();
+        if (u % U.splits == 0u && m < M) {
             double om[9], sm[3];
             offsets_f64(C, m, om, sm);
 #pragma unroll
@@ -706,27 +766,9 @@ __device__ void gofr_frame(const Ctx<Real, kMem>& C, uint32_t m0, uint32_t mstep
                     if (b >= 0 && b < (int)nb) atomicAdd(&bintra[b], 2u);
                 }
         }
-        const double cx = mine ? C.com[m] : 0.0, cy = mine ? C.com[M + m] : 0.0,
-                     cz = mine ? C.com[2 * M + m] : 0.0;
-        for (uint32_t dj = 1; dj <= half; ++dj) {
-            bool keep = mine && !((M & 1u) == 0u && dj == half && m >= half);
-            uint32_t j = m + dj;
-            if (j >= M) j -= M;
-            if (keep) {
-                const double dx = min_image(C.com[j] - cx, C.L, C.invL);
-                const double dy = min_image(C.com[M + j] - cy, C.L, C.invL);
-                const double dz = min_image(C.com[2 * M + j] - cz, C.L, C.invL);
-                keep = dx * dx + dy * dy + dz * dz < cut2;
-            }
-            const uint64_t bm = __ballot(keep);
-            if (keep) q[qn + rank_below(bm)] = m | (j << 16);
-            qn += (uint32_t)__popcll(bm);
-            wave_lds_sync();
-            drain(64u);
-            wave_lds_sync();
-        }
+        unit_pairs(C, U, u, cut2, Q);
     }
-    drain(1u);
+    Q.drain(1u);
     __syncthreads();
     for (uint32_t b = threadIdx.x; b < nb; b += kThreads) {
         const uint32_t all = bintra[b] + binter[b];
@@ -1995,7 +2037,12 @@ __device__ __attribute__((noinline)) void inline_events(const SysDev* __restrict
     Stats* st = E.stats;
     __syncthreads();
     if (resum) {
-        const double e = resum_energy(E, tid, kThreads);
+        // (the wave's near list is free between sweeps)
+        uint32_t* queue = (uint32_t*)(smem + L.near) + (size_t)wave_index() * Dp->near_cap * 2u;
+        const EventUnits U = event_units(E.M);
+        resum_units(E, U, (uint32_t)wave_index(), kWaves, queue);
+        __syncthreads();
+        const double e = sum_units(E, U.count());
         if (tid == 0) {
             // re-anchor the accumulated energy: each drift sample is the
             // error of one window
@@ -2156,6 +2203,7 @@ __global__ void __launch_bounds__(kThreads) k_events(const Slot* __restrict__ sl
     C.cellid = nullptr;
     C.list = nullptr;
     const int tid = threadIdx.x;
+    uint32_t* queue = gqueue + wave_index() * kGofrQueue;
     Stats* st = C.stats;
     if (tid == 0) {
         misc[1] = C.sig0;
@@ -2200,12 +2248,15 @@ __global__ void __launch_bounds__(kThreads) k_events(const Slot* __restrict__ sl
     }
     if (f & (kFlagResumSet | kFlagResumReport | kFlagResumPeriodic)) {
         double e;
-        if (f & kFlagParts) {  // partial energies of the multi-workgroup kernel, in order
-            e = 0.0;
-            for (uint32_t b = 0; b < sl.pad; ++b) e += C.gpart[b];
-        } else {
-            e = resum_energy(C, threadIdx.x, kThreads);
+        // (kFlagParts: the units were added up by the multi-workgroup kernel)
+        uint32_t n = sl.pad;
+        if (!(f & kFlagParts)) {
+            const EventUnits U = event_units(M);
+            resum_units(C, U, (uint32_t)wave_index(), kWaves, queue);
+            n = U.count();
+            __syncthreads();
         }
+        e = sum_units(C, n);
         if (tid == 0) {
             const double acc = (f & kFlagResumSet) ? e : e_acc;
             // a set or a scheduled re-sum re-anchors the accumulated energy, so
@@ -2229,7 +2280,7 @@ __global__ void __launch_bounds__(kThreads) k_events(const Slot* __restrict__ sl
         if (f & kFlagParts) {
             if (tid == 0) st->n_gofr += 1;
         } else {
-            gofr_frame(C, threadIdx.x, kThreads, false, gqueue);
+            gofr_frame(C, event_units(M), (uint32_t)wave_index(), kWaves, false, queue);
         }
         __syncthreads();
     }
@@ -2889,8 +2940,9 @@ __global__ void __launch_bounds__(kThreads) k_spread(const SpreadSlot* __restric
     }
 }
 
-// The O(M^2) work of an event on many workgroups: the re-sum's partial energy
-// of each workgroup into g_part, the g(r) frame into the histograms.
+// The event work over all pairs on many workgroups: the waves of a system's
+// workgroups take its units in turn, the energies go to g_part for k_events to
+// sum, the g(r) counts into the histograms.
 __global__ void __launch_bounds__(kThreads) k_event_parts(PartList list)
 {
     // this workgroup's system: the last slot whose first workgroup is at or
@@ -2925,17 +2977,15 @@ __global__ void __launch_bounds__(kThreads) k_event_parts(PartList list)
     }
     __syncthreads();
     const uint32_t f = one.flags;
-    const uint32_t m0 = bid * kThreads + threadIdx.x, step = one.count * kThreads;
+    const EventUnits U = event_units(C.M);
+    const uint32_t wave = bid * kWaves + (uint32_t)wave_index(), nwaves = one.count * kWaves;
+    uint32_t* queue = gqueue + wave_index() * kGofrQueue;
     if (f & (kFlagResumSet | kFlagResumReport | kFlagResumPeriodic)) {
-        // a scheduled re-sum follows sweeps, whose cell lists are still there
-        const int span = (int)ceil((sqrt(C.reach2) + 2.0 * 1.7320508075688772 * C.dmax + 1e-9) / C.w);
-        const bool cells = (f & (kFlagResumSet | kFlagResumReport)) == 0 && C.cellb != nullptr &&
-                           2 * span + 1 <= (int)C.nc;
-        const double e = cells ? resum_energy_cells(C, m0, step, span) : resum_energy(C, m0, step);
-        if (threadIdx.x == 0) C.gpart[bid] = e;
-        __syncthreads();
+        const int span = one.span;
+        if (span) resum_units_cells(C, wave, nwaves, span, queue);
+        else resum_units(C, U, wave, nwaves, queue);
     }
-    if (f & kFlagGofr) gofr_frame(C, m0, step, true, gqueue);
+    if (f & kFlagGofr) gofr_frame(C, U, wave, nwaves, true, queue);
 }
 
 __global__ void k_init_lattice(SysDev* Dp, uint32_t n)

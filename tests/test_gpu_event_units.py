@@ -1,0 +1,91 @@
+"""The event work over all pairs, cut into units: total energy and g(r) counts
+against a plain FP64 sum, at the edges of the units."""
+import numpy as np
+import pytest
+
+from paper_2506_21290_amd import flipmc
+
+pytestmark = pytest.mark.gpu
+
+
+def start(M, seed):
+    rng = np.random.default_rng(seed)
+    n = int(np.ceil(M ** (1 / 3)))
+    side = (3.0 * M / 1.2) ** (1 / 3)
+    at = np.sort(rng.permutation(n ** 3)[:M])
+    com = (np.stack([at % n, (at // n) % n, at // (n * n)], axis=1) + 0.5) * (side / n)
+    q = rng.normal(size=(M, 4))
+    return side, com, q / np.linalg.norm(q, axis=1, keepdims=True), np.argsort(rng.random((M, 3)), axis=1).astype(np.uint8)
+
+
+def sites(com, q, bond):
+    r, h = bond / np.sqrt(3.0), 0.5 * bond
+    body = np.array([[r, 0, 0], [-r / 2, h, 0], [-r / 2, -h, 0]])
+    w, x, y, z = q.T
+    rot = np.stack([1 - 2 * (y * y + z * z), 2 * (x * y - w * z), 2 * (x * z + w * y),
+                    2 * (x * y + w * z), 1 - 2 * (x * x + z * z), 2 * (y * z - w * x),
+                    2 * (x * z - w * y), 2 * (y * z + w * x), 1 - 2 * (x * x + y * y)], axis=1).reshape(-1, 3, 3)
+    return com[:, None, :] + np.einsum("mij,sj->msi", rot, body)
+
+
+def plain(side, com, q, types, dr, nbins):
+    """Energy (Eq. 1) and intermolecular g(r) counts, a block of sites at a time."""
+    s = sites(com, q, 0.9608971989592554).reshape(-1, 3)
+    sg = np.array([0.9, 1.0, 1.1])[types].reshape(-1)
+    mol = np.arange(len(s)) // 3
+    e, counts = 0.0, np.zeros(nbins, dtype=np.int64)
+    for i0 in range(0, len(s), 512):
+        d = s[i0:i0 + 512, None, :] - s[None, :, :]
+        d -= side * np.rint(d / side)
+        r2 = (d * d).sum(axis=2)
+        other = mol[i0:i0 + 512, None] != mol[None, :]
+        b = np.floor(np.sqrt(r2[other]) / dr).astype(np.int64)
+        counts += np.bincount(b[b < nbins], minlength=nbins)[:nbins]
+        s2 = (0.5 * (sg[i0:i0 + 512, None] + sg[None, :])) ** 2
+        x3 = (s2 / np.where(other, r2, 1.0)) ** 3
+        e += 0.5 * np.where(other & (r2 < 2 ** (1 / 3) * s2), 4 * (x3 * x3 - x3) + 1, 0.0).sum()
+    return e, counts
+
+
+@pytest.mark.parametrize("M", [
+    64,    # one unit
+    65,    # a block of one molecule
+    129,   # odd, two ranges of the other half
+    255,   # the largest on one workgroup
+    256,   # even, units over several
+    1001,  # odd, a last block of 41
+    2048,  # whole blocks
+])
+def test_energy_and_gofr_over_units(M):
+    side, com, q, types = start(M, 3)
+    p = flipmc.mc_params_default(n_molecules=M, temperature=1.0, gofr_interval=1, resum_interval=1)
+    s = flipmc.System(p, com=com, quat=q, types=types)
+    e, _, _ = s.energy()
+    o = s.observables()
+    want, _ = plain(side, com, q, types, o["gofr_dr"], len(o["gofr_inter"]))
+    # a site position is off by some eps of the box side, 1e-15 of a distance of
+    # 0.3 or more, and its term (r^-12) by 12 times that
+    assert e == pytest.approx(want, rel=1e-11)
+    s.sweep(1)  # one g(r) frame of the state it leaves
+    st = s.get_state()
+    o = s.observables()
+    want, counts = plain(side, st["com"], st["quat"], types=st["types"], dr=o["gofr_dr"], nbins=len(o["gofr_inter"]))
+    assert o["e_resum"] == pytest.approx(want, rel=1e-11)
+    got = o["gofr_inter"].astype(np.int64)
+    # a pair within rounding of a bin's edge may fall to either side
+    assert np.abs(np.cumsum(got - counts)).max() <= 2
+    s.close()
+
+
+def test_resum_from_cell_lists():
+    # above 8192 molecules a scheduled re-sum takes the pairs from the cell lists
+    # of the sweep before it; over all pairs the energy is the same
+    _, com, q, types = start(8201, 4)
+    for workgroups in (0, 1):
+        p = flipmc.mc_params_default(n_molecules=8201, temperature=1.0, gofr_interval=0, resum_interval=2,
+                                     workgroups=workgroups)
+        s = flipmc.System(p, com=com, quat=q, types=types)
+        s.sweep(2)
+        e = s.observables()["e_resum"]
+        assert s.energy()[0] == pytest.approx(e, rel=1e-12)
+        s.close()
