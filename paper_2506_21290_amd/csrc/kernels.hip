@@ -458,9 +458,16 @@ struct PairQueue {
     }
 };
 
-// The pairs of unit u whose centres are nearer than the root of cut2.
-template <typename Cx, typename Queue>
-__device__ __forceinline__ void unit_pairs(const Cx& C, const EventUnits& U, uint32_t u, double cut2, Queue& Q)
+// The pairs of unit u whose centres are nearer than the root of cut2, and some a
+// little farther: the distance test is in FP32 (half the time of FP64) with a
+// margin far above its rounding (coordinates up to 55: 1e-5).  What is added up
+// for a pair is in FP64 and nothing past the cut-off.
+// window: 3 x (kSpan + 64) words of LDS for the wave, where the centres that the
+// 64 molecules meet next are held as floats.
+constexpr uint32_t kEventSpan = 128, kInlineSpan = 32;
+template <uint32_t kSpan, typename Cx, typename Queue>
+__device__ __forceinline__ void unit_pairs(const Cx& C, const EventUnits& U, uint32_t u, double cut2, float* window,
+                                           Queue& Q)
 {
     const uint32_t M = C.M, half = M / 2;
     const uint32_t blk = u / U.splits, part = u - blk * U.splits;
@@ -468,19 +475,37 @@ __device__ __forceinline__ void unit_pairs(const Cx& C, const EventUnits& U, uin
     const uint32_t d0 = 1u + (uint32_t)((uint64_t)half * part / U.splits),
                    d1 = 1u + (uint32_t)((uint64_t)half * (part + 1u) / U.splits);
     const bool mine = m < M;
-    const double cx = mine ? C.com[m] : 0.0, cy = mine ? C.com[M + m] : 0.0, cz = mine ? C.com[2 * M + m] : 0.0;
-    for (uint32_t dj = d0; dj < d1; ++dj) {
-        // (half way round an even number each pair comes twice)
-        bool keep = mine && !((M & 1u) == 0u && dj == half && m >= half);
-        uint32_t j = m + dj;
-        if (j >= M) j -= M;
-        if (keep) {
-            const double dx = min_image(C.com[j] - cx, C.L, C.invL);
-            const double dy = min_image(C.com[M + j] - cy, C.L, C.invL);
-            const double dz = min_image(C.com[2 * M + j] - cz, C.L, C.invL);
-            keep = dx * dx + dy * dy + dz * dz < cut2;
+    const float cx = mine ? (float)C.com[m] : 0.f, cy = mine ? (float)C.com[M + m] : 0.f,
+                cz = mine ? (float)C.com[2 * M + m] : 0.f;
+    const float L = (float)C.L, invL = (float)C.invL;
+    const float cut = (float)sqrt(cut2) + 1e-3f, lim = cut * cut;
+    constexpr uint32_t kWindow = kSpan + 64u;
+    const uint32_t lane = (uint32_t)__lane_id();
+    for (uint32_t c0 = d0; c0 < d1; c0 += kSpan) {
+        wave_lds_sync();
+#pragma unroll
+        for (uint32_t t = 0; t < (kWindow + 63u) / 64u; ++t) {  // the centres of 64 blk + c0 ...
+            uint32_t j = 64u * blk + c0 + 64u * t + lane;
+            while (j >= M) j -= M;
+            const uint32_t at = 64u * t + lane;
+            if (kWindow % 64u != 0u && at >= kWindow) continue;
+            window[at] = (float)C.com[j];
+            window[kWindow + at] = (float)C.com[M + j];
+            window[2u * kWindow + at] = (float)C.com[2 * M + j];
         }
-        Q.push(keep, m, j);
+        wave_lds_sync();
+        const uint32_t end = min(c0 + kSpan, d1);
+        for (uint32_t dj = c0; dj < end; ++dj) {
+            const uint32_t at = lane + (dj - c0);
+            float dx = window[at] - cx, dy = window[kWindow + at] - cy, dz = window[2u * kWindow + at] - cz;
+            dx = fmaf(-L, rintf(dx * invL), dx);
+            dy = fmaf(-L, rintf(dy * invL), dy);
+            dz = fmaf(-L, rintf(dz * invL), dz);
+            // (half way round an even number each pair comes twice)
+            const bool keep = mine && !((M & 1u) == 0u && dj == half && m >= half) && dx * dx + dy * dy + dz * dz < lim;
+            const uint32_t j = m + dj;
+            Q.push(keep, m, j >= M ? j - M : j);
+        }
     }
 }
 
@@ -513,15 +538,15 @@ __device__ __forceinline__ double pair_energy(const Cx& C, uint32_t m, uint32_t 
 
 // Eq. (1) over all pairs of sites of different molecules in FP64, unit by unit
 // into C.gpart: units wave, wave + nwaves, ...  queue: the wave's words of LDS.
-template <typename Real, int kMem>
+template <uint32_t kSpan, typename Real, int kMem>
 __device__ __forceinline__ void resum_units(const Ctx<Real, kMem>& C, const EventUnits& U, uint32_t wave,
-                                            uint32_t nwaves, uint32_t* queue)
+                                            uint32_t nwaves, uint32_t* queue, float* window)
 {
     for (uint32_t u = wave; u < U.count(); u += nwaves) {
         double e = 0.0;
         auto each = [&](uint32_t m, uint32_t j) __attribute__((always_inline)) { e += pair_energy(C, m, j); };
         PairQueue<decltype(each)> Q{queue, each, 0u};
-        unit_pairs(C, U, u, C.reach2, Q);
+        unit_pairs<kSpan>(C, U, u, C.reach2, window, Q);
         Q.drain(1u);
         e = wave_sum_dpp(e);
         if (__lane_id() == 0) C.gpart[u] = e;
@@ -707,7 +732,7 @@ __device__ void reset_observables(const Ctx<Real, kMem>& C)
 // One g(r) frame (Eq. 3 numerator): every ordered pair of distinct sites.
 template <typename Real, int kMem>
 __device__ void gofr_frame(const Ctx<Real, kMem>& C, const EventUnits& U, uint32_t wave, uint32_t nwaves,
-                           bool shared_out, uint32_t* queue)
+                           bool shared_out, uint32_t* queue, float* window)
 {
     const uint32_t M = C.M, nb = C.gofr_nbins;
     uint32_t* bintra = C.bins;  // intramolecular pairs; all = intra + inter at the end
@@ -766,7 +791,7 @@ __device__ void gofr_frame(const Ctx<Real, kMem>& C, const EventUnits& U, uint32
                     if (b >= 0 && b < (int)nb) atomicAdd(&bintra[b], 2u);
                 }
         }
-        unit_pairs(C, U, u, cut2, Q);
+        unit_pairs<kEventSpan>(C, U, u, cut2, window, Q);
     }
     Q.drain(1u);
     __syncthreads();
@@ -2037,10 +2062,12 @@ __device__ __attribute__((noinline)) void inline_events(const SysDev* __restrict
     Stats* st = E.stats;
     __syncthreads();
     if (resum) {
-        // (the wave's near list is free between sweeps)
-        uint32_t* queue = (uint32_t*)(smem + L.near) + (size_t)wave_index() * Dp->near_cap * 2u;
+        // (the waves' work areas are free between sweeps)
+        constexpr uint32_t kWords = kGofrQueue + 3u * (kInlineSpan + 64u);
+        static_assert(kWaves * kWords * 4u <= kWaves * (kNearMin * 10u + 4u * kMaxSeg), "survivors, segments, near lists");
+        uint32_t* queue = (uint32_t*)(smem + L.surv) + (size_t)wave_index() * kWords;
         const EventUnits U = event_units(E.M);
-        resum_units(E, U, (uint32_t)wave_index(), kWaves, queue);
+        resum_units<kInlineSpan>(E, U, (uint32_t)wave_index(), kWaves, queue, (float*)(queue + kGofrQueue));
         __syncthreads();
         const double e = sum_units(E, U.count());
         if (tid == 0) {
@@ -2187,6 +2214,7 @@ __global__ void __launch_bounds__(kThreads) k_events(const Slot* __restrict__ sl
     __shared__ double misc[16];
     __shared__ uint32_t bins[2 * kGofrBins];
     __shared__ uint32_t gqueue[kWaves * kGofrQueue];
+    __shared__ float windows[kWaves * 3u * (kEventSpan + 64u)];
     extern __shared__ __align__(16) unsigned char ev_stage[];
     const Slot sl = slots ? slots[blockIdx.x] : one;
     if (sl.sys == nullptr || sl.flags == 0) return;
@@ -2204,6 +2232,7 @@ __global__ void __launch_bounds__(kThreads) k_events(const Slot* __restrict__ sl
     C.list = nullptr;
     const int tid = threadIdx.x;
     uint32_t* queue = gqueue + wave_index() * kGofrQueue;
+    float* window = windows + wave_index() * 3u * (kEventSpan + 64u);
     Stats* st = C.stats;
     if (tid == 0) {
         misc[1] = C.sig0;
@@ -2252,7 +2281,7 @@ __global__ void __launch_bounds__(kThreads) k_events(const Slot* __restrict__ sl
         uint32_t n = sl.pad;
         if (!(f & kFlagParts)) {
             const EventUnits U = event_units(M);
-            resum_units(C, U, (uint32_t)wave_index(), kWaves, queue);
+            resum_units<kEventSpan>(C, U, (uint32_t)wave_index(), kWaves, queue, window);
             n = U.count();
             __syncthreads();
         }
@@ -2280,7 +2309,7 @@ __global__ void __launch_bounds__(kThreads) k_events(const Slot* __restrict__ sl
         if (f & kFlagParts) {
             if (tid == 0) st->n_gofr += 1;
         } else {
-            gofr_frame(C, event_units(M), (uint32_t)wave_index(), kWaves, false, queue);
+            gofr_frame(C, event_units(M), (uint32_t)wave_index(), kWaves, false, queue, window);
         }
         __syncthreads();
     }
@@ -2958,6 +2987,7 @@ __global__ void __launch_bounds__(kThreads) k_event_parts(PartList list)
     __shared__ double misc[16];
     __shared__ uint32_t bins[2 * kGofrBins];
     __shared__ uint32_t gqueue[kWaves * kGofrQueue];
+    __shared__ float windows[kWaves * 3u * (kEventSpan + 64u)];
     Ctx<double, kMemAny> C;
     load_ctx(C, one.sys);
     C.com = C.gcom;
@@ -2980,12 +3010,13 @@ __global__ void __launch_bounds__(kThreads) k_event_parts(PartList list)
     const EventUnits U = event_units(C.M);
     const uint32_t wave = bid * kWaves + (uint32_t)wave_index(), nwaves = one.count * kWaves;
     uint32_t* queue = gqueue + wave_index() * kGofrQueue;
+    float* window = windows + wave_index() * 3u * (kEventSpan + 64u);
     if (f & (kFlagResumSet | kFlagResumReport | kFlagResumPeriodic)) {
         const int span = one.span;
         if (span) resum_units_cells(C, wave, nwaves, span, queue);
-        else resum_units(C, U, wave, nwaves, queue);
+        else resum_units<kEventSpan>(C, U, wave, nwaves, queue, window);
     }
-    if (f & kFlagGofr) gofr_frame(C, U, wave, nwaves, true, queue);
+    if (f & kFlagGofr) gofr_frame(C, U, wave, nwaves, true, queue, window);
 }
 
 __global__ void k_init_lattice(SysDev* Dp, uint32_t n)
