@@ -745,6 +745,120 @@ __device__ __forceinline__ void fx_eval_rows(const FxK& K, const FxView<kRes>& V
     }
 }
 
+// dE of the attempt on atom a, summed over the atoms of the 27 cells in stencil
+// order by the whole wave, a lane each, as E_acc has always been summed.  An
+// overlapping start has moves that change its energy by 1e10 and more; the last
+// bits of each stay in E_acc, up to 1e6 in all, until the next re-sum, so for
+// large moves E_acc takes the sum that depends on nothing but the state and not
+// the one over the rows.  (Below kFxLarge the two differ by less than 1e-11.)
+constexpr double kFxLarge = 1e4;
+
+__device__ __forceinline__ bool fx_in_stencil(double x, double h, uint32_t c, const FxDev& D, double m)
+{
+    if (D.nc <= 3u) return true;  // the three cells are the whole axis
+    const double t = fx_mi(fx_wrap(x - h, D.L) - (double)c * D.w, D.L, D.invL);
+    return t >= m - D.w && t <= 2.0 * D.w - m;
+}
+
+constexpr uint32_t kFxListed = 384;  // atoms of a cell's stencil that serve its molecules' other atoms too
+
+template <bool kRes>
+__device__ __attribute__((noinline)) double fx_stencil_sum(const FxDev* Dp, typename FxView<kRes>::template Ptr<FxAtom> atom,
+                                                           typename FxView<kRes>::template Ptr<uint32_t> cell_start,
+                                                           typename FxView<kRes>::template Ptr<uint32_t> cell_list,
+                                                           uint32_t a, uint32_t kind, double tx, double ty, double tz,
+                                                           double hx, double hy, double hz, uint32_t cell)
+{
+    const FxDev& D = *Dp;
+    const FxView<kRes> V{atom, cell_start, cell_list, nullptr};
+    FxK K{};
+    K.nc = D.nc;
+    const int lane = __lane_id();
+    const uint32_t n = D.n, nc = D.nc, base = n * fx_mol(n, a);
+    const bool flip = kind != kFxMove;
+    const double sig[4] = {D.sigma[0], D.sigma[1], D.sigma[2], D.sigma[3]};
+    double ox[4], oy[4], oz[4], nx[4], ny[4], nz[4];
+    uint32_t ot[4], nt[4], changed = 0;
+    for (uint32_t s = 0; s < 4; ++s) {
+        const FxAtom A = V.at(base + (s < n ? s : 0u));
+        ox[s] = nx[s] = A.x; oy[s] = ny[s] = A.y; oz[s] = nz[s] = A.z;
+        ot[s] = nt[s] = A.type;
+    }
+    for (uint32_t s = 0; s < n; ++s) {
+        if (flip) {
+            nt[s] = fx_pick(ot, D.flips[kind][s]);
+            if (nt[s] != ot[s]) changed |= 1u << s;
+        } else if (base + s == a) {
+            nx[s] = fx_wrap(tx, D.L); ny[s] = fx_wrap(ty, D.L); nz[s] = fx_wrap(tz, D.L);
+            changed = 1u << s;
+        }
+    }
+    double de = 0.0;
+    {
+        // intramolecular pairs on lanes 0 .. 5: (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
+        const uint32_t i = lane < 3 ? 0u : (lane < 5 ? 1u : 2u);
+        const uint32_t j = lane < 3 ? (uint32_t)lane + 1u : (lane < 5 ? (uint32_t)lane - 1u : 3u);
+        if (lane < 6 && j < n && (((changed >> i) | (changed >> j)) & 1u)) {
+            const double dxo = fx_mi(fx_pick(ox, i) - fx_pick(ox, j), D.L, D.invL),
+                         dyo = fx_mi(fx_pick(oy, i) - fx_pick(oy, j), D.L, D.invL),
+                         dzo = fx_mi(fx_pick(oz, i) - fx_pick(oz, j), D.L, D.invL);
+            const double dxn = fx_mi(fx_pick(nx, i) - fx_pick(nx, j), D.L, D.invL),
+                         dyn = fx_mi(fx_pick(ny, i) - fx_pick(ny, j), D.L, D.invL),
+                         dzn = fx_mi(fx_pick(nz, i) - fx_pick(nz, j), D.L, D.invL);
+            const double r2o = dxo * dxo + dyo * dyo + dzo * dzo, r2n = dxn * dxn + dyn * dyn + dzn * dzn;
+            const double so = 0.5 * (fx_pick(sig, fx_pick(ot, i)) + fx_pick(sig, fx_pick(ot, j)));
+            const double sn = 0.5 * (fx_pick(sig, fx_pick(nt, i)) + fx_pick(sig, fx_pick(nt, j)));
+            de = fx_wca(sn * sn, r2n, D.rc2f) - fx_wca(so * so, r2o, D.rc2f);
+            if ((D.bonded >> (4 * i + j)) & 1u) {
+                const double lo2 = 2.25 * so * so, ln2 = 2.25 * sn * sn;
+                if (r2o < lo2 && r2n < ln2)
+                    de += -33.75 * log((1.0 - r2n / ln2) / (1.0 - r2o / lo2));
+                else
+                    de += (r2n < ln2 ? 0.0 : __builtin_inf()) - (r2o < lo2 ? 0.0 : __builtin_inf());
+            }
+        }
+    }
+    uint32_t lo, off, total;
+    int nseg = fx_segments(K, V, (int)(cell % nc), (int)((cell / nc) % nc), (int)(cell / (nc * nc)), &lo, &off, &total);
+    const bool list = total <= kFxListed;
+    // an atom of another cell is served by the list of this one when every atom
+    // that can reach it was sorted into the list's 27 cells
+    const double m = sqrt(D.rc2f) * fmax(fmax(sig[0], sig[1]), fmax(sig[2], sig[3])) + 1.7320508075688772 * D.dmax + 1e-9;
+    for (uint32_t s = 0; s < n; ++s) {
+        if (!((changed >> s) & 1u)) continue;  // wave-uniform
+        const uint32_t at = uniform(V.atom[base + s].cell);
+        bool listed = list && at == cell;
+        if (!listed && list && flip)
+            listed = fx_in_stencil(fx_pick(ox, s), hx, cell % nc, D, m) &&
+                     fx_in_stencil(fx_pick(oy, s), hy, (cell / nc) % nc, D, m) &&
+                     fx_in_stencil(fx_pick(oz, s), hz, cell / (nc * nc), D, m);
+        listed = __ballot(listed) != 0ull;  // (the same in every lane)
+        const uint32_t from = listed ? cell : at;
+        nseg = fx_segments(K, V, (int)(from % nc), (int)((from / nc) % nc), (int)(from / (nc * nc)), &lo, &off, &total);
+        const double sos = fx_pick(sig, fx_pick(ot, s)), sns = fx_pick(sig, fx_pick(nt, s));
+        for (uint32_t b = 0; b < total; b += 64u) {
+            const uint32_t idx = b + (uint32_t)lane;
+            uint32_t seg = 0;
+            for (int t = 1; t < nseg; ++t) seg += idx >= rl_u(off, t) ? 1u : 0u;
+            const uint32_t d = (uint32_t)__shfl((int)(lo - off), (int)seg);
+            const uint32_t j = idx < total ? (uint32_t)V.cell_list[idx + d] : base;
+            const bool valid = j - base >= n;  // not an atom of the molecule
+            const FxAtom A = V.at(j);
+            const double sj = fx_pick(sig, valid ? A.type : 0u);
+            const double xj = valid ? A.x : 0.0, yj = valid ? A.y : 0.0, zj = valid ? A.z : 0.0;
+            const double dxo = fx_mi(fx_pick(ox, s) - xj, D.L, D.invL), dyo = fx_mi(fx_pick(oy, s) - yj, D.L, D.invL),
+                         dzo = fx_mi(fx_pick(oz, s) - zj, D.L, D.invL);
+            const double r2o = valid ? dxo * dxo + dyo * dyo + dzo * dzo : 1e30;
+            const double dxn = fx_mi(fx_pick(nx, s) - xj, D.L, D.invL), dyn = fx_mi(fx_pick(ny, s) - yj, D.L, D.invL),
+                         dzn = fx_mi(fx_pick(nz, s) - zj, D.L, D.invL);
+            const double r2n = flip ? r2o : (valid ? dxn * dxn + dyn * dyn + dzn * dzn : 1e30);
+            const double so = 0.5 * (sos + sj), sn = 0.5 * (sns + sj);
+            de += fx_wca(sn * sn, r2n, D.rc2f) - fx_wca(so * so, r2o, D.rc2f);
+        }
+    }
+    return wave_sum_dpp(de);
+}
+
 // The attempts on up to 64 atoms of one cell (lane q holds atom q and its
 // proposal), in order, by one wave.
 //
@@ -762,8 +876,8 @@ __device__ __forceinline__ void fx_eval_rows(const FxK& K, const FxView<kRes>& V
 // 7.4 ms; two rows per 16 lanes against one 0.78 and 1.22 ms).
 template <bool kLog, bool kRes>
 __device__ __forceinline__ void fx_run_rows(const FxDev& Dv, const FxK& K, const FxView<kRes>& V, uint32_t cnt, uint32_t at,
-                                            const FxProp& pr, uint64_t sweep, bool logging, const FxWaveLds& W,
-                                            FxCount& wc)
+                                            const FxProp& pr, uint64_t sweep, const double h[3], uint32_t cell,
+                                            bool logging, const FxWaveLds& W, FxCount& wc)
 {
     const uint32_t lane = (uint32_t)__lane_id();
     const uint32_t n = K.n;
@@ -819,7 +933,11 @@ __device__ __forceinline__ void fx_run_rows(const FxDev& Dv, const FxK& K, const
         live &= ~done;
         if (acc) {
             const int q = (int)__builtin_ctzll(acc);
-            wc.e += rl_d(dE, q);
+            double de = rl_d(dE, q);
+            if (fabs(de) > kFxLarge)
+                de = fx_stencil_sum<kRes>(&Dv, V.atom, V.cell_start, V.cell_list, rl_u(at, q), rl_u(pr.kind, q),
+                                          rl_d(pr.tx, q), rl_d(pr.ty, q), rl_d(pr.tz, q), h[0], h[1], h[2], cell);
+            wc.e += de;
             if (rl_u(pr.kind, q) != kFxMove) wc.acc_f += 1; else wc.acc_t += 1;
             if ((int)lane == q) {
                 if (flip) {
@@ -1027,7 +1145,7 @@ __global__ void __launch_bounds__(kFxThreads) k_fx_sweeps(FxList list, uint64_t 
                 asm volatile("" ::"v"(touched));
                 const bool last = ci + kFxWaves >= nact;
                 if (!last || col + 1u < ncol) touch(last ? cell_of(col + 1u, (uint32_t)wave) : cell_of(col, ci + kFxWaves));
-                fx_run_rows<kLog>(D, K, V, cnt, at, pr, sweep, logging, W, wc);
+                fx_run_rows<kLog>(D, K, V, cnt, at, pr, sweep, h, cell, logging, W, wc);
             }
             if (lane == 0) V.ecell[cell] = wc.e;
         };

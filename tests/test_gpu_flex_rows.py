@@ -42,3 +42,35 @@ def test_system_beyond_16_bit_atom_indices():
     assert e < e0  # the lattice start's overlaps relax
     assert abs(drift) <= 1e-11 * abs(e0)
     assert np.all((st["pos"] >= 0.0) & (st["pos"] < flipmc.mcf_geometry(p)[0]))
+
+
+@pytest.mark.parametrize("body", [flipmc.MC_TRIANGLE, flipmc.MC_SQUARE, flipmc.MC_TETRAHEDRON])
+def test_large_moves_of_an_overlapping_start_add_up(body):
+    # moves that change the energy by more than 1e4 enter E_acc by the sum over
+    # the stencil instead of the one over the rows: the same energy to rounding
+    n = 3 if body == flipmc.MC_TRIANGLE else 4
+    M = 131
+    rng = np.random.default_rng(5)
+    side = (n * M / 1.2) ** (1 / 3)
+    c = int(np.ceil(M ** (1 / 3)))
+    at = np.sort(rng.permutation(c ** 3)[:M])
+    com = (np.stack([at % c, (at // c) % c, at // (c * c)], axis=1) + 0.5) * (side / c)
+    b = 0.9608971989592554
+    shape = {3: np.array([[b / np.sqrt(3), 0, 0], [-b / np.sqrt(12), b / 2, 0], [-b / np.sqrt(12), -b / 2, 0]]),
+             4: np.array([[b / 2, b / 2, 0], [-b / 2, b / 2, 0], [-b / 2, -b / 2, 0], [b / 2, -b / 2, 0]])}[n]
+    if body == flipmc.MC_TETRAHEDRON:
+        shape = b / np.sqrt(8) * np.array([[1, 1, 1], [1, -1, -1], [-1, 1, -1], [-1, -1, 1]])
+    q = np.linalg.qr(rng.normal(size=(M, 3, 3)))[0]
+    pos = com[:, None, :] + np.einsum("mij,sj->msi", q, shape)
+    types = np.argsort(rng.random((M, n)), axis=1).astype(np.uint8)
+    s = flipmc.FlexSystem(flipmc.mcf_params_default(body, n_molecules=M, temperature=1.0, seed=3, resum_interval=0),
+                          pos=pos, types=types)
+    e0 = s.get_state()["e_acc"]
+    s.decision_log(2)
+    s.sweep(2)
+    log, e = s.read_log(), s.get_state()["e_acc"]
+    de = log["delta_e"][log["accepted"] == 1]
+    assert np.abs(de).max() > 1e4
+    # each sum rounds some 40 terms of up to |dE|, and E_acc adds them one by one
+    assert abs(e - (e0 + de.sum())) <= 1e-13 * (abs(e0) + np.abs(de).sum())
+    s.close()
