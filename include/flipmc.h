@@ -511,13 +511,15 @@ int mcf_dynamics(const mc_obs* runs, size_t n_runs, uint32_t n_molecules, uint32
  * the same model, each with its own size, temperature and sweep count, share
  * persistent launches.
  *
- * A batch holds up to max_slots systems of one precision.  Each
- * mc_batch_run gives every system one workgroup; the workgroups left over
+ * A batch holds up to max_slots systems of one precision.  An mc_batch_run of
+ * a time slice gives every system one workgroup; the workgroups left over
  * (up to the batch's workgroup limit, one per compute unit by default) go to
  * the systems that are modelled to finish last and can use several (those
  * beyond one workgroup's LDS, and those within it when that is modelled 25 %
  * faster), which then run on the multi-workgroup engine, each on up to one
- * workgroup per cell of a colour.
+ * workgroup per cell of a colour.  A run of all remaining sweeps divides the
+ * workgroups so that the modelled end of the whole run is earliest; systems
+ * with their state in LDS then follow one another on a workgroup.
  * Systems on one workgroup share one persistent launch per
  * placement class (state in LDS / in HBM; the HBM class beside the LDS
  * class on a third caller stream when mc_batch_set_hbm_stream gives one);
@@ -558,9 +560,10 @@ int mc_batch_add(mc_batch* b, mc_system* s, uint64_t n_sweeps, uint32_t* slot);
  * over its modelled sweep time on its workgroups, scaled per engine by the time
  * per modelled cycle measured on the batch's earlier launches; at least one
  * sweep.  Slices also stop at each system's re-sum / g(r) / C_2 sweeps, whose
- * work follows in a second launch.  *n_launched = number of sweep launches
- * enqueued (one per placement class in use, one for the multi-workgroup
- * engine). */
+ * work follows in a second launch; a run of all remaining sweeps may enqueue
+ * several slices one after another, and systems may stay unfinished at its
+ * end.  *n_launched = number of sweep launches enqueued per slice (one per placement class in use, one for each way in
+ * use of the multi-workgroup engine). */
 int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched);
 
 /* Put the launch of the systems that run on one workgroup with their state in

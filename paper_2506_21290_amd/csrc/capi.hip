@@ -8,6 +8,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <limits>
 #include <string>
 #include <utility>
@@ -177,7 +178,7 @@ double waves_cycles(uint32_t M, uint32_t k, uint32_t nc, uint32_t nb, uint32_t w
 // workgroup with the state in LDS, in HBM; the multi-workgroup engine with a cell
 // per workgroup, with a cell per wave), relative to the LDS class; a batch then
 // measures its own.
-constexpr double kCycleRatio[4] = {1.0, 1.0, 1.1, 1.1};
+constexpr double kCycleRatio[4] = {1.0, 1.0, 1.1, 1.4};
 
 double Geometry::spread_cycles(uint32_t M, uint32_t nb, bool waves) const
 {
@@ -332,6 +333,24 @@ double slice_time(uint64_t max_moves)
 double ms_per_model_cycle()
 {
     return 0.31 / slice_time(1000);
+}
+
+// Times (in falling order) put on n workgroups, each on the one that is done
+// first: the time at which the last is done, and which took each.
+double longest_first(const std::vector<double>& times, uint32_t n, std::vector<uint32_t>* taken)
+{
+    std::vector<std::pair<double, uint32_t>> done;
+    for (uint32_t w = 0; w < n; ++w) done.emplace_back(0.0, w);  // a heap as it is
+    if (taken) taken->clear();
+    double end = 0.0;
+    for (const double t : times) {
+        std::pop_heap(done.begin(), done.end(), std::greater<>());
+        done.back().first += t;
+        end = std::max(end, done.back().first);
+        if (taken) taken->push_back(done.back().second);
+        std::push_heap(done.begin(), done.end(), std::greater<>());
+    }
+    return end;
 }
 
 // Workgroups of the multi-workgroup event kernel for M molecules, 1 =
@@ -1482,16 +1501,113 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
         std::sort(chosen.begin(), chosen.end());
         active.swap(chosen);
     }
-    // The spare compute units go to the systems that would otherwise finish
+    // A run of all remaining sweeps: the earliest end T that the engines' models
+    // allow.  Within T a system takes its own engine's one workgroup, or the
+    // way on several that costs the fewest workgroups times time; the systems
+    // on one workgroup with their state in LDS share as many workgroups as their
+    // times fill, one after another (a system each left the compute units of the
+    // short ones idle: 256 replicas of 216 - 1728 molecules took 24.4 ms, the
+    // longest of them, with 12.6 ms of work per compute unit; 50 sweeps of 24
+    // systems of 125 - 8000 molecules take 13.5 ms, 22 ms with the greedy division
+    // that the time slices below keep, whose lengths come out alike anyway).
+    std::vector<uint32_t> nblk(S, 0);
+    std::vector<char> by_wave(S, 0);
+    uint32_t lds_blocks = S;  // workgroups of the systems on one with the state in LDS
+    const bool whole = max_moves_per_slot == 0 && b->spread_max >= 2 && b->stream2 != b->stream &&
+                       !active.empty() && b->wg_limit >= 2;
+    if (whole) {
+        struct Option {
+            double time;
+            uint32_t nb;
+            char wave;
+        };
+        std::vector<std::vector<Option>> opts(active.size());
+        double hi = 0.0, lo = 0.0;
+        for (size_t x = 0; x < active.size(); ++x) {
+            const mc_system* s = b->sys[active[x]];
+            const double rem = (double)b->remaining[active[x]];
+            const double one = rem * s->g.sweep_cost * b->ms_per_cycle[s->g.resident ? 0 : 1];
+            opts[x].push_back(Option{one, 0u, 0});
+            hi = std::max(hi, one);
+            lo += one;
+            if (!s->g.team_arrays()) continue;
+            const uint32_t na = s->g.nc / s->g.k, nact = na * na * na, M = s->p.n_molecules;
+            for (const char w : {0, 1}) {
+                const uint32_t cells = w ? s->g.wave_fit : 1u;  // of a workgroup at once
+                if (w && cells < 2) continue;
+                uint32_t last = 0;
+                for (uint32_t r = (nact + cells - 1) / cells; r >= 1; r = std::min(r - 1, std::max(r / 2, 8u))) {
+                    const uint32_t nb = std::min(s->g.team_blocks, (nact + cells * r - 1) / (cells * r));
+                    if (nb == last) continue;
+                    last = nb;
+                    const double t = rem * s->g.spread_cycles(M, nb, w) * b->ms_per_cycle[w ? 3 : 2];
+                    if (t < 0.8 * one) opts[x].push_back(Option{t, nb, w});
+                }
+            }
+        }
+        std::vector<uint32_t> pick(active.size(), 0), best;
+        std::vector<double> times;
+        // whether all can end by T, with the options into pick
+        auto fits = [&](double T) {
+            double area = 0.0;
+            uint32_t held = 0, hbm = 0;
+            times.clear();
+            for (size_t x = 0; x < active.size(); ++x) {
+                double least = std::numeric_limits<double>::infinity();
+                for (uint32_t o = 0; o < opts[x].size(); ++o) {
+                    const Option& p = opts[x][o];
+                    const double a = p.time * std::max(p.nb, 1u);
+                    if (p.time <= T && a < least) {
+                        least = a;
+                        pick[x] = o;
+                    }
+                }
+                if (least == std::numeric_limits<double>::infinity()) return false;
+                const Option& p = opts[x][pick[x]];
+                if (p.nb) held += p.nb;
+                else if (b->sys[active[x]]->g.resident) {
+                    area += p.time;
+                    times.push_back(p.time);
+                } else {
+                    ++hbm;
+                }
+            }
+            std::sort(times.begin(), times.end(), std::greater<>());
+            const uint32_t room = held + hbm < b->wg_limit ? b->wg_limit - held - hbm : 0u;
+            if (held > b->spread_max || held + hbm > b->wg_limit || area > T * room) return false;
+            return times.empty() || longest_first(times, std::min(room, (uint32_t)times.size()), nullptr) <= 1.001 * T;
+        };
+        lo /= (double)b->wg_limit * 16.0;
+        if (fits(hi)) {
+            best = pick;
+            for (int step = 0; step < 16; ++step) {
+                const double T = std::sqrt(lo * hi);
+                if (fits(T)) {
+                    hi = T;
+                    best = pick;
+                } else {
+                    lo = T;
+                }
+            }
+            lds_blocks = b->wg_limit;
+            for (size_t x = 0; x < active.size(); ++x) {
+                const Option& p = opts[x][best[x]];
+                nblk[active[x]] = p.nb;
+                by_wave[active[x]] = p.wave;
+                if (p.nb || !b->sys[active[x]]->g.resident) lds_blocks -= std::max(p.nb, 1u);
+            }
+        } else {
+            lds_blocks = S;
+        }
+    }
+    // Time slices: the spare compute units go to the systems that would otherwise finish
     // last: the one with the longest modelled time for its remaining sweeps
     // takes workgroups until one of its rounds of cells per colour is saved, and
     // so on while any are left.  (In proportion to the remaining work, a share
     // that saves no round is lost, and one slow system holds up the run.)  With
     // its workgroups a system has a cell per workgroup or a cell per wave,
     // whichever is modelled faster.
-    std::vector<uint32_t> nblk(S, 0);
-    std::vector<char> by_wave(S, 0);
-    if (b->spread_max >= 2) {
+    if (b->spread_max >= 2 && !whole) {
         struct Cand {
             double time;  // of the remaining sweeps on nb workgroups (0: its own engine's one)
             uint32_t slot, nb;
@@ -1554,6 +1670,11 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
     // the O(M^2) event work of large systems goes to the event kernel over
     // many workgroups, whatever engine ran the sweeps
     std::vector<std::pair<mc_system*, uint32_t>> parts1;
+    std::vector<std::pair<double, Slot>> ones;  // modelled cycles, entry
+    // some system on one workgroup stops at a g(r) frame: those on several then
+    // stop at theirs too, so that the next run has work for all compute units
+    bool ones_left = false;
+    std::vector<char> stopped(S, 0);
     auto event_slot = [&](mc_system* s, uint32_t f, std::vector<std::pair<mc_system*, uint32_t>>& parts) {
         Slot ev{};
         ev.sys = s->dev;
@@ -1582,17 +1703,41 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
             const double cap = t_slice / (b->ms_per_cycle[cls] * s->g.sweep_cost);
             k = std::min<uint64_t>(k, std::max<uint64_t>(1, (uint64_t)cap));
         }
-        pred[cls] = std::max(pred[cls], (double)k * s->g.sweep_cost);
         Slot sl{};
         sl.sys = s->dev;
         sl.n_sweeps = k;
         sl.flags = inl ? kFlagInline : 0u;
-        hs[cls * S + n[cls]++] = sl;
+        if (cls == 0) {
+            ones.emplace_back((double)k * s->g.sweep_cost, sl);
+        } else {
+            pred[cls] = std::max(pred[cls], (double)k * s->g.sweep_cost);
+            hs[cls * S + n[cls]++] = sl;
+        }
         lds[cls] = std::max(lds[cls], s->g.lds);
         b->remaining[i] -= k;
         s->sweep += k;
         const uint32_t f = events_at(s, s->sweep) & (inl ? ~(kFlagResumPeriodic | kFlagC2) : ~0u);
         if (f) hs[2 * S + n[2]++] = event_slot(s, f, parts1);
+        ones_left = ones_left || b->remaining[i] != 0;
+    }
+    // the longest first, each on the workgroup that is done first
+    n[0] = (uint32_t)ones.size();
+    {
+        const uint32_t blocks = std::min(lds_blocks, n[0]);
+        if (blocks < n[0])
+            std::stable_sort(ones.begin(), ones.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
+        std::vector<double> times;
+        for (const auto& x : ones) times.push_back(x.first);
+        std::vector<uint32_t> taken, tail(blocks);
+        if (blocks) pred[0] = longest_first(times, blocks, &taken);
+        uint32_t more = blocks;
+        for (uint32_t x = 0; x < n[0]; ++x) {
+            // the first `blocks` entries start a workgroup each
+            const uint32_t at = x < blocks ? x : more++;
+            hs[at] = ones[x].second;
+            if (x >= blocks) hs[tail[taken[x]]].pad = at + 1u;
+            tail[taken[x]] = at;
+        }
     }
 
     // A slice of every system on the multi-workgroup engine: those with a cell
@@ -1615,7 +1760,7 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
         for (uint32_t i : several) {
             mc_system* s = b->sys[i];
             uint64_t k = std::min<uint64_t>(b->remaining[i], next_event(s) - s->sweep);
-            if (k == 0) continue;
+            if (k == 0 || (ones_left && stopped[i])) continue;
             const int w = by_wave[i];
             const double unit = s->g.spread_cycles(s->p.n_molecules, nblk[i], w);  // modelled cycles of a sweep
             if (max_moves_per_slot) {
@@ -1640,7 +1785,10 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
             }
             b->remaining[i] -= k;
             s->sweep += k;
-            if (const uint32_t f = events_at(s, s->sweep)) hev[ne++] = event_slot(s, f, parts);
+            if (const uint32_t f = events_at(s, s->sweep)) {
+                hev[ne++] = event_slot(s, f, parts);
+                stopped[i] = stopped[i] || (f & kFlagGofr);
+            }
         }
         const uint32_t nt = (uint32_t)by[0].size(), nw = (uint32_t)by[1].size();
         if (nt + nw == 0) return MC_OK;
@@ -1704,8 +1852,8 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
             if (n[cls]) {
                 hipStream_t st = cls == 1 && side ? b->stream3 : b->stream;
                 HIPCHK(hipEventRecord(b->t_beg[cls], st));
-                HIPCHK(launch_sweeps(fp64, cls == 0, b->dev_slots[par] + cls * S, none, n[cls],
-                                     lds[cls], st, true));
+                HIPCHK(launch_sweeps(fp64, cls == 0, b->dev_slots[par] + cls * S, none,
+                                     cls == 0 ? std::min(n[0], lds_blocks) : n[cls], lds[cls], st, true));
                 HIPCHK(hipEventRecord(b->t_end[cls], st));
                 b->pred[cls] = pred[cls];
             }

@@ -149,7 +149,7 @@ struct Slot {
     SysDev* sys;
     uint64_t n_sweeps;
     uint32_t flags;
-    uint32_t pad;
+    uint32_t pad;  // of a sweep: 1 + the entry the workgroup takes next, 0 for none; of events: see kFlagParts
 };
 
 struct MoveRecord {   // mirrors mc_move_record

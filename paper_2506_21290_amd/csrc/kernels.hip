@@ -2097,11 +2097,8 @@ __device__ __attribute__((noinline)) void inline_events(const SysDev* __restrict
 // flagged kFlagInline (a batch's systems); the plain one leaves them to the
 // event kernel.
 template <typename Real, bool kRes, bool kInl>
-__global__ void __launch_bounds__(kThreads) k_sweeps(const Slot* __restrict__ slots, Slot one)
+__device__ __forceinline__ void sweep_system(const Slot& sl, unsigned char* smem)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const Slot sl = slots ? slots[blockIdx.x] : one;
-    if (sl.sys == nullptr || sl.n_sweeps == 0) return;
     const SysDev* __restrict__ Dp = sl.sys;
     constexpr int kMem = kRes ? kMemLds : kMemHbm;
     Ctx<Real, kMem> C;
@@ -2203,6 +2200,22 @@ __global__ void __launch_bounds__(kThreads) k_sweeps(const Slot* __restrict__ sl
     if (tid == 0) {
         st->sweep = sweep;
         st->e_acc = C.misc[0];
+    }
+}
+
+// A workgroup takes the system of table entry blockIdx.x and those that follow it
+// (Slot::pad).
+template <typename Real, bool kRes, bool kInl>
+__global__ void __launch_bounds__(kThreads) k_sweeps(const Slot* __restrict__ slots, Slot one)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    for (uint32_t i = blockIdx.x;;) {
+        const Slot sl = slots ? slots[i] : one;
+        if (sl.sys == nullptr || sl.n_sweeps == 0) return;  // (the same for the whole workgroup)
+        sweep_system<Real, kRes, kInl>(sl, smem);
+        if (sl.pad == 0u) return;
+        i = sl.pad - 1u;
+        __syncthreads();
     }
 }
 
@@ -3066,7 +3079,7 @@ hipError_t launch_res(bool resident, const Slot* dev_slots, const Slot& one, uin
 
 }  // namespace
 
-hipError_t launch_sweeps(bool fp64, bool resident, const Slot* dev_slots, const Slot& one,
+hipError_t launch_sweeps(bool fp64, bool resident, const Slot* dev_slots, const Slot& one, 
                          uint32_t n_blocks, size_t lds_bytes, hipStream_t stream, bool inline_events)
 {
     if (fp64)

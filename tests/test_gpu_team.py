@@ -63,3 +63,44 @@ def test_lists_beyond_lds():
     assert np.array_equal(l0["delta_e"], l1["delta_e"]) and np.array_equal(l0["accepted"], l1["accepted"])
     for f in ("com", "quat", "types", "e_acc"):
         assert np.array_equal(s0[f], s1[f]), f
+
+
+@pytest.mark.parametrize("fp32", [False, True])
+@pytest.mark.parametrize("limit", [12, 0])
+def test_batch_of_short_and_long_systems(fp32, limit):
+    # a run of all remaining sweeps puts short systems one after another on one
+    # workgroup and gives the long ones several (a cell per workgroup or per
+    # wave); each ends as it does alone
+    sizes = [(64, 2, 2)] * 9 + [(1000, 2, 4), (1728, 2, 6), (2197, 2, 6)]
+
+    def system(i, M, k, nc, **kw):
+        p = flipmc.mc_params_default(n_molecules=M, temperature=1.3, colours_per_axis=k, cells_per_side=nc, seed=i,
+                                     precision=flipmc.MC_FP32_DE if fp32 else flipmc.MC_FP64, resum_interval=7,
+                                     gofr_interval=5, workgroups=0)
+        return flipmc.System(p, **kw)
+
+    alone = []
+    for i, (M, k, nc) in enumerate(sizes):
+        s = system(i, M, k, nc)
+        s.sweep(21)
+        alone.append((s.get_state(), s.observables()))
+        s.close()
+    b = flipmc.Batch(len(sizes), flipmc.MC_FP32_DE if fp32 else flipmc.MC_FP64)
+    b.set_workgroups(limit)
+    systems = [system(i, M, k, nc, stream=b.stream) for i, (M, k, nc) in enumerate(sizes)]
+    for s in systems:
+        b.add(s, 21)
+    left = len(systems)
+    for _ in range(100):
+        b.run(0)
+        left -= len(b.poll())
+        if not left:
+            break
+    assert left == 0
+    for s, (ref, obs) in zip(systems, alone):
+        st, o = s.get_state(), s.observables()
+        for f in ("com", "quat", "types", "e_acc", "sweep"):
+            assert np.array_equal(st[f], ref[f]), f
+        for f in ("accepts", "pair_terms", "gofr_all", "c2", "e_resum"):
+            assert np.array_equal(o[f], obs[f]), f
+    b.close()
