@@ -81,6 +81,12 @@ def measured_traffic(name):
     return measured_counters(name).get("bytes_per_launch")
 
 
+def lone_workgroups(torch, k, nc):
+    """Workgroups of a lone system's sweep launch on the multi-workgroup
+    engine: one per cell of a colour, up to the compute units."""
+    return min(torch.cuda.get_device_properties(0).multi_processor_count, (nc // k) ** 3)
+
+
 def run_system(flipmc, torch, precision, steps, warmup, M=1000, T=0.75, k=0, nc=0, seed=1):
     p = flipmc.mc_params_default(
         n_molecules=M, temperature=T, precision=precision, colours_per_axis=k, cells_per_side=nc,
@@ -212,7 +218,7 @@ def bench_c1(args, flipmc, torch):
     flops = f32["pair_terms"] * FLOP_PER_PAIR_TERM
     kern_s = f32["sweep_kernel_ms"] / 1e3
     achieved = flops / kern_s / 1e12
-    traffic = measured_traffic("k_sweeps_c1")
+    traffic = measured_traffic("k_spread_c1")
     out = {
         "metric": METRIC,
         "value": f32["moves_per_s"],
@@ -242,9 +248,9 @@ def bench_c1(args, flipmc, torch):
             "unit": "TFLOP/s",
             "frac": achieved / PEAK_TFLOPS["f32"],
             "traffic": traffic,
-            "kernel": "k_sweeps<float, resident>",
-            "cus_used": 1,
-            "valu_busy_on_its_cu": measured_counters("k_sweeps_c1").get("valu_busy_on_its_cu"),
+            "kernel": "k_spread<float>",
+            "cus_used": lone_workgroups(torch, f32["k"], f32["n_c"]),
+            "valu_busy_on_its_cus": measured_counters("k_spread_c1").get("valu_busy_on_its_cus"),
             "avg_launch_ms": f32["sweep_kernel_ms"] / launches,
             "flops_per_launch": flops / launches,
             "flop_per_pair_term": FLOP_PER_PAIR_TERM,
@@ -319,7 +325,6 @@ def bench_c2(args, flipmc, torch):
     # HBM bytes of one 100-sweep launch from the committed counter summary
     # (null when it was taken on other kernel sources)
     traffic = measured_traffic("k_spread_c2")
-    _, wg = flipmc.mc_engine(p)
     achieved = terms * FLOP_PER_PAIR_TERM / kern_s / 1e12
     return {
         "workload": "c2: 8000 molecules, T=1.1, FP32 dE + FP64 re-sum every 100 sweeps, 1000 timed sweeps",
@@ -330,7 +335,7 @@ def bench_c2(args, flipmc, torch):
         "roofline": {"bound": "alu", "achieved": achieved, "peak": PEAK_TFLOPS["f32"],
                      "unit": "TFLOP/s", "frac": achieved / PEAK_TFLOPS["f32"],
                      "traffic": traffic, "kernel": "k_spread<float>",
-                     "cus_used": wg,
+                     "cus_used": lone_workgroups(torch, k, nc),
                      "valu_busy_on_its_cus": measured_counters("k_spread_c2").get("valu_busy_on_its_cus"),
                      "hbm_gb_per_s": (traffic * n_sweeps / 100 / kern_s / 1e9) if traffic else None,
                      "avg_launch_ms": tm["sweep_ms"] / launches,

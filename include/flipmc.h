@@ -562,8 +562,9 @@ int mc_batch_add(mc_batch* b, mc_system* s, uint64_t n_sweeps, uint32_t* slot);
  * sweep.  Slices also stop at each system's re-sum / g(r) / C_2 sweeps, whose
  * work follows in a second launch; a run of all remaining sweeps may enqueue
  * several slices one after another, and systems may stay unfinished at its
- * end.  *n_launched = number of sweep launches enqueued per slice (one per placement class in use, one for each way in
- * use of the multi-workgroup engine). */
+ * end.  *n_launched = number of sweep launches enqueued per slice (one per
+ * placement class in use, one for each way in use of the multi-workgroup
+ * engine: a cell per workgroup, a cell per wave). */
 int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched);
 
 /* Put the launch of the systems that run on one workgroup with their state in

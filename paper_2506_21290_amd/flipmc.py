@@ -501,7 +501,8 @@ class System:
 
 class Batch:
     """Several systems advanced together, one time slice per run: one workgroup
-    each, spare workgroups to the large systems with the most work left."""
+    each, spare workgroups to the systems that would finish last.  A run of all
+    remaining sweeps divides the workgroups for the earliest end."""
 
     def __init__(self, max_slots, precision=MC_FP32_DE, stream=None, aux_stream=None,
                  hbm_stream=None, device="cuda"):

@@ -8,7 +8,7 @@ advances all admitted jobs by one time slice, so jobs that arrive while others
 run join the next run and their work overlaps on the device.  Every job gets
 one workgroup per run (systems whose working set fits one workgroup's LDS keep
 it there); the workgroups left over go to the jobs that would finish last, which
-then run on the multi-workgroup engine in a launch beside the others.
+then run on the multi-workgroup engine in launches beside the others.
 
 The time slice is given in attempted moves of a 1000-molecule job; the batch
 turns it into a time and gives every job the sweeps it runs in that time on

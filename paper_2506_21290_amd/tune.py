@@ -4,8 +4,8 @@ workgroup.
 For a system size M and a precision, every valid (k, n_c) is a correct
 sampler with its own trajectory; they differ in speed (colour phases, cells per
 wave, neighbour-list length).  For each (k, n_c) the number of workgroups a
-sweep runs on (one, or the multi-workgroup engine on a wave per cell of a
-colour, or on fewer workgroups with several cells per wave) changes only the
+sweep runs on (one, or the multi-workgroup engine on a workgroup per cell of a
+colour, or on fewer workgroups with several cells each) changes only the
 speed: every count gives bitwise the same chain.  The tuner times each
 candidate (k, n_c, workgroups) and records the fastest in ``tuned.json`` next
 to this file.  ``choose`` reads the table (falling back to the engine's own
@@ -58,9 +58,9 @@ def candidates(M, precision, per_k=4):
 
 
 def workgroup_counts(M, precision, k, nc):
-    """Workgroup counts worth timing for one decomposition: the most its cells
-    allow (a wave per cell of a colour), half and a quarter of that, and one
-    workgroup when the state fits its LDS."""
+    """Workgroup counts worth timing for one decomposition: a quarter of the
+    cells of a colour (which stands for a workgroup per cell), half and a quarter
+    of that, and one workgroup when the state fits its LDS."""
     p = flipmc.mc_params_default(n_molecules=M, precision=precision, colours_per_axis=k, cells_per_side=nc,
                                  workgroups=1 << 20)
     _, most = flipmc.mc_engine(p)
