@@ -499,6 +499,23 @@ class System:
         return np.frombuffer(self._log.cpu().numpy().tobytes(), dtype=MOVE_RECORD_DTYPE).copy()
 
 
+# Side streams of the batches on one stream, by device and stream handle.  Those
+# batches run one after another anyway, and a pair of their own for each would
+# in the end put one in the hardware queue of the batch's stream (streams share
+# four), whose launches then follow one another: 50 sweeps of 24 systems of
+# 125 - 8000 molecules took 21 - 24 ms in every second batch, 13.5 otherwise.
+_side_streams = {}
+
+
+def _side_pair(main):
+    import torch
+
+    key = torch.cuda.current_device(), main.value or 0
+    if key not in _side_streams:
+        _side_streams.setdefault(key, (torch.cuda.Stream(), torch.cuda.Stream()))
+    return _side_streams[key]
+
+
 class Batch:
     """Several systems advanced together, one time slice per run: one workgroup
     each, spare workgroups to the systems that would finish last.  A run of all
@@ -512,8 +529,8 @@ class Batch:
         # the multi-workgroup launches overlap the others on a second stream,
         # and the one-workgroup launch of systems with their state in HBM the
         # LDS class's on a third (default priority, like every stream here)
-        self.aux_stream = aux_stream if aux_stream is not None else torch.cuda.Stream()
-        self.hbm_stream = hbm_stream if hbm_stream is not None else torch.cuda.Stream()
+        self.aux_stream = aux_stream if aux_stream is not None else _side_pair(self._stream_handle)[0]
+        self.hbm_stream = hbm_stream if hbm_stream is not None else _side_pair(self._stream_handle)[1]
         self._lib = lib()
         n = C.c_size_t()
         _check(self._lib.mc_batch_required_bytes(int(max_slots), C.byref(n)))

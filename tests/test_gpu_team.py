@@ -3,7 +3,9 @@ the edges of the multi-workgroup engine's layouts."""
 import numpy as np
 import pytest
 
-from paper_2506_21290_amd import flipmc
+torch = pytest.importorskip("torch")
+
+from paper_2506_21290_amd import flipmc  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -104,3 +106,44 @@ def test_batch_of_short_and_long_systems(fp32, limit):
         for f in ("accepts", "pair_terms", "gofr_all", "c2", "e_resum"):
             assert np.array_equal(o[f], obs[f]), f
     b.close()
+
+
+@pytest.mark.parametrize("same", [True, False])
+def test_two_batches_in_turn(same):
+    # batches on one stream share their side streams; batches on two do not
+    sizes = [(64, 2, 2), (216, 3, 6), (1000, 2, 4), (1728, 2, 6)]
+
+    def systems(stream=None):
+        return [flipmc.System(flipmc.mc_params_default(n_molecules=M, temperature=1.3, colours_per_axis=k,
+                                                       cells_per_side=nc, seed=i, resum_interval=7,
+                                                       precision=flipmc.MC_FP32_DE), stream=stream)
+                for i, (M, k, nc) in enumerate(sizes)]
+
+    alone = systems()
+    for s in alone:
+        s.sweep(12)
+    two = [flipmc.Batch(8, flipmc.MC_FP32_DE), flipmc.Batch(8, flipmc.MC_FP32_DE,
+                                                            stream=None if same else torch.cuda.Stream())]
+    assert (two[0].aux_stream == two[1].aux_stream) is same
+    assert len({b.aux_stream for b in two} | {b.hbm_stream for b in two}) == (2 if same else 4)
+    torch.cuda.synchronize()
+    sets = [systems(b.stream) for b in two]
+    for b, own in zip(two, sets):
+        for s in own:
+            b.add(s, 12)
+    left = [len(sizes)] * 2
+    for _ in range(50):
+        for x, b in enumerate(two):
+            b.run(0)
+        for x, b in enumerate(two):
+            left[x] -= len(b.poll())
+        if left == [0, 0]:
+            break
+    assert left == [0, 0]
+    for own in sets:
+        for s, ref in zip(own, alone):
+            st, r = s.get_state(), ref.get_state()
+            for f in ("com", "quat", "types", "e_acc", "sweep"):
+                assert np.array_equal(st[f], r[f]), f
+    for b in two:
+        b.close()
