@@ -871,7 +871,7 @@ __device__ __attribute__((noinline)) double fx_stencil_sum(const FxDev* Dp, type
 // dE does not depend on how the attempts were grouped.  With 7 - 30 % accepted
 // a cell of 6 atoms takes one to three evaluations of 2 us.  The chain of
 // evaluations bounds the kernel (a system runs on one compute unit): a sweep
-// of 1000 triangles at T = 0.75 takes 0.78 ms, of 333 tetrahedra 1.37 ms (by
+// of 1000 triangles at T = 0.75 takes 0.78 ms, of 333 tetrahedra 1.41 ms (by
 // the whole wave, one attempt after another over the 27 cells' atoms, 2.80 and
 // 7.4 ms; two rows per 16 lanes against one 0.78 and 1.22 ms).
 template <bool kLog, bool kRes>
