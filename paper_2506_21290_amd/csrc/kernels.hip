@@ -1847,7 +1847,10 @@ __device__ __forceinline__ void team_trials(const Ctx<Real, kMem>& C, const Vw& 
     for (uint32_t q0 = 0; q0 < ccnt; q0 += 64u) {
         const uint32_t n = min(64u, ccnt - q0);
         const bool mine = lane < n;
-        if (q0) {  // (the last round's barrier freed the records)
+        if (q0) {
+            // every wave has its heads of the last 64 (a round's barriers say
+            // so too, but there is none when all 64 leave the cell)
+            __syncthreads();
             if (wave == 0) load_records(C, props, cbeg, ccnt, q0, bx0, by0, bz0, W.tr);
             __syncthreads();
         }

@@ -10,7 +10,7 @@ from paper_2506_21290_amd import flipmc  # noqa: E402
 pytestmark = pytest.mark.gpu
 
 
-def chain(M, T, k, nc, seed, fp32, sweeps, workgroups):
+def chain(M, T, k, nc, seed, fp32, sweeps, workgroups, **more):
     rng = np.random.default_rng(seed)
     n = int(np.ceil(M ** (1 / 3)))
     side = (3.0 * M / 1.2) ** (1 / 3)
@@ -21,7 +21,7 @@ def chain(M, T, k, nc, seed, fp32, sweeps, workgroups):
     types = np.argsort(rng.random((M, 3)), axis=1).astype(np.uint8)
     p = flipmc.mc_params_default(n_molecules=M, temperature=T, colours_per_axis=k, cells_per_side=nc, seed=seed,
                                  precision=flipmc.MC_FP32_DE if fp32 else flipmc.MC_FP64, workgroups=workgroups,
-                                 gofr_interval=0, resum_interval=2)
+                                 gofr_interval=0, resum_interval=2, **more)
     s = flipmc.System(p, com=com, quat=q, types=types)
     s.decision_log(sweeps)
     s.sweep(sweeps)
@@ -55,6 +55,23 @@ def test_team_equals_one_workgroup(M, k, nc, workgroups, fp32):
     for f in ("attempts", "accepts", "exits", "pair_terms", "pair_tests", "near_overflows"):
         assert np.array_equal(o0[f], o1[f]), f
     assert np.sum(o1["accepts"]) > 0 and (nc > 2 or M < 1000 or o1["near_overflows"] > 0)
+
+
+@pytest.mark.parametrize("fp32", [False, True])
+def test_cells_whose_first_trials_all_exit(fp32):
+    # 125 molecules a cell and steps longer than it: 0.94 of the trials leave
+    # their cell, so in some 2 % of the cells the first 64 all do, and the next
+    # 61 follow with no trial evaluated in between
+    step = dict(p_flip=0.0, p_translate=1.0, max_displacement=8.9)
+    l0, s0, o0 = chain(27000, 1.1, 2, 6, 3, fp32, 2, 1, **step)
+    l1, s1, o1 = chain(27000, 1.1, 2, 6, 3, fp32, 2, 0, **step)
+    assert np.mean(l0["exited"]) > 0.9
+    for f in ("delta_e", "accepted", "exited", "pair_terms"):
+        assert np.array_equal(l0[f], l1[f]), f
+    for f in ("com", "quat", "types", "e_acc"):
+        assert np.array_equal(s0[f], s1[f]), f
+    for f in ("attempts", "accepts", "exits"):
+        assert np.array_equal(o0[f], o1[f]), f
 
 
 def test_lists_beyond_lds():
