@@ -459,9 +459,13 @@ struct PairQueue {
 };
 
 // The pairs of unit u whose centres are nearer than the root of cut2, and some a
-// little farther: the distance test is in FP32 (half the time of FP64) with a
-// margin far above its rounding (coordinates up to 55: 1e-5).  What is added up
-// for a pair is in FP64 and nothing past the cut-off.
+// little farther: the distance test is in FP32 (half the time of FP64).  The
+// centres are folded into the box before they are rounded (a caller's may lie
+// anywhere), which leaves a difference of two within 5 2^-24 L of its value
+// along each axis (two centres, the image's shift, the results); with the
+// rounding of the squares a distance is off by 6e-7 L at most, and the margin is
+// 1e-6 L, or 1e-3 where that is more (boxes up to 1000).  What is added up for a
+// pair is in FP64 and nothing past the cut-off.
 // window: 3 x (kSpan + 64) words of LDS for the wave, where the centres that the
 // 64 molecules meet next are held as floats.
 constexpr uint32_t kEventSpan = 128, kInlineSpan = 32;
@@ -475,10 +479,11 @@ __device__ __forceinline__ void unit_pairs(const Cx& C, const EventUnits& U, uin
     const uint32_t d0 = 1u + (uint32_t)((uint64_t)half * part / U.splits),
                    d1 = 1u + (uint32_t)((uint64_t)half * (part + 1u) / U.splits);
     const bool mine = m < M;
-    const float cx = mine ? (float)C.com[m] : 0.f, cy = mine ? (float)C.com[M + m] : 0.f,
-                cz = mine ? (float)C.com[2 * M + m] : 0.f;
+    auto folded = [&](double x) { return (float)(x - C.L * floor(x * C.invL)); };
+    const float cx = mine ? folded(C.com[m]) : 0.f, cy = mine ? folded(C.com[M + m]) : 0.f,
+                cz = mine ? folded(C.com[2 * M + m]) : 0.f;
     const float L = (float)C.L, invL = (float)C.invL;
-    const float cut = (float)sqrt(cut2) + 1e-3f, lim = cut * cut;
+    const float cut = (float)sqrt(cut2) + fmaxf(1e-3f, 1e-6f * L), lim = cut * cut;
     constexpr uint32_t kWindow = kSpan + 64u;
     const uint32_t lane = (uint32_t)__lane_id();
     for (uint32_t c0 = d0; c0 < d1; c0 += kSpan) {
@@ -489,9 +494,9 @@ __device__ __forceinline__ void unit_pairs(const Cx& C, const EventUnits& U, uin
             while (j >= M) j -= M;
             const uint32_t at = 64u * t + lane;
             if (kWindow % 64u != 0u && at >= kWindow) continue;
-            window[at] = (float)C.com[j];
-            window[kWindow + at] = (float)C.com[M + j];
-            window[2u * kWindow + at] = (float)C.com[2 * M + j];
+            window[at] = folded(C.com[j]);
+            window[kWindow + at] = folded(C.com[M + j]);
+            window[2u * kWindow + at] = folded(C.com[2 * M + j]);
         }
         wave_lds_sync();
         const uint32_t end = min(c0 + kSpan, d1);

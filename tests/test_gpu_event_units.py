@@ -77,6 +77,52 @@ def test_energy_and_gofr_over_units(M):
     s.close()
 
 
+def rounding(side, com, q, centre):
+    """Largest relative change of the energy when centres are off by eps of `centre`: 12 times that of the
+    smallest distance (a term is r^-12)."""
+    s = sites(com, q, 0.9608971989592554).reshape(-1, 3)
+    mol, least = np.arange(len(s)) // 3, np.inf
+    for i0 in range(0, len(s), 512):
+        d = s[i0:i0 + 512, None, :] - s[None, :, :]
+        d -= side * np.rint(d / side)
+        least = min(least, (d * d).sum(axis=2)[mol[i0:i0 + 512, None] != mol[None, :]].min())
+    return 12 * 4 * 2.2e-16 * centre / np.sqrt(least)  # (two centres, each once as given and once folded)
+
+
+@pytest.mark.parametrize("far", [1e4, 1e6])
+def test_energy_and_gofr_of_centres_outside_the_box(far):
+    # the distance test that selects the pairs is in FP32; centres up to `far`
+    # boxes away lose no pair by it
+    M = 513
+    side, com, q, types = start(M, 6)
+    com = com + side * np.random.default_rng(7).integers(-far, far, size=com.shape)
+    p = flipmc.mc_params_default(n_molecules=M, temperature=1.0, gofr_interval=1, resum_interval=1)
+    s = flipmc.System(p, com=com, quat=q, types=types)
+    o = s.observables()
+    want, _ = plain(side, com, q, types, o["gofr_dr"], len(o["gofr_inter"]))
+    assert s.energy()[0] == pytest.approx(want, rel=rounding(side, com, q, side * far))
+    s.sweep(1)
+    st = s.get_state()
+    o = s.observables()
+    want, counts = plain(side, st["com"], st["quat"], types=st["types"], dr=o["gofr_dr"], nbins=len(o["gofr_inter"]))
+    assert o["e_resum"] == pytest.approx(want, rel=rounding(side, st["com"], st["quat"], side * far))
+    assert np.abs(np.cumsum(o["gofr_inter"].astype(np.int64) - counts)).max() <= 2
+    s.close()
+
+
+def test_energy_in_a_dilute_box():
+    # a drop in a box of side 1e7, where a float holds a centre to 0.5
+    M = 343
+    liquid, com, q, types = start(M, 8)
+    p = flipmc.mc_params_default(n_molecules=M, temperature=1.0, density=3.0 * M / 1e21, gofr_interval=0)
+    side = flipmc.mc_geometry(p)[0]
+    com = 1.1 * (com - 0.5 * liquid) + 0.93 * side
+    s = flipmc.System(p, com=com, quat=q, types=types)
+    want, _ = plain(side, com, q, types, 0.02, 1)
+    assert s.energy()[0] == pytest.approx(want, rel=rounding(side, com, q, side))
+    s.close()
+
+
 def test_resum_from_cell_lists():
     # above 8192 molecules a scheduled re-sum takes the pairs from the cell lists
     # of the sweep before it; over all pairs the energy is the same
