@@ -156,9 +156,12 @@ __device__ __forceinline__ FxK fx_const(const FxDev& D)
     K.T = D.T; K.p_flip = D.p_flip; K.dmax = D.dmax; K.rc2f = D.rc2f;
     K.sep = D.sep; K.dyn_base = D.dyn_base; K.together = D.together;
     K.img = (Global<int32_t>*)D.img; K.props = (Global<FxProp>*)D.props; K.nbr = (Global<void>*)D.nbr;
-    // the FP32 distances of the list build are within 1e-5 of the FP64 ones
+    // the FP32 distances of the list build are within 1.2e-6 w of the FP64 ones:
+    // coordinates up to 1.5 w from the cell's centre, rounded to 2^-24 of that,
+    // their difference and its nearest image to 2^-24 of 3 w, along three axes
     const double smax = fmax(fmax(D.sigma[0], D.sigma[1]), fmax(D.sigma[2], D.n > 3u ? D.sigma[3] : 0.0));
-    const float r = (float)(sqrt(D.rc2f) * smax + 2.0 * 1.7320508075688772 * D.dmax) + 1e-3f;
+    const float r = (float)(sqrt(D.rc2f) * smax + 2.0 * 1.7320508075688772 * D.dmax) +
+                    fmaxf(1e-3f, 2e-6f * (float)D.w);
     K.list_r2 = r * r;
     return K;
 }

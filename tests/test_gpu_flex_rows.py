@@ -44,6 +44,33 @@ def test_system_beyond_16_bit_atom_indices():
     assert np.all((st["pos"] >= 0.0) & (st["pos"] < flipmc.mcf_geometry(p)[0]))
 
 
+@pytest.mark.parametrize("k,nc", [(3, 3), (3, 6)])
+def test_lists_in_a_dilute_box(k, nc):
+    # neighbours are selected in FP32: a drop in a box of side 1e8, where a float
+    # holds a coordinate of a cell to 1 or more, keeps every pair all the same
+    M, side = 125, 1e8
+    rng = np.random.default_rng(9)
+    c = np.stack(np.meshgrid(*[np.arange(5)] * 3, indexing="ij"), axis=-1).reshape(-1, 3)
+    b = 0.9608971989592554
+    shape = np.array([[b / np.sqrt(3), 0, 0], [-b / np.sqrt(12), b / 2, 0], [-b / np.sqrt(12), -b / 2, 0]])
+    q = np.linalg.qr(rng.normal(size=(M, 3, 3)))[0]
+    pos = 0.93 * side + 1.5 * c[:, None, :] + np.einsum("mij,sj->msi", q, shape)
+    types = np.argsort(rng.random((M, 3)), axis=1).astype(np.uint8)
+    p = flipmc.mcf_params_default(flipmc.MC_TRIANGLE, n_molecules=M, temperature=1.0, seed=3, resum_interval=0,
+                                  density=3.0 * M / side ** 3, colours_per_axis=k, cells_per_side=nc)
+    s = flipmc.FlexSystem(p, pos=pos, types=types)
+    s.decision_log(5)
+    s.sweep(5)
+    log = s.read_log()
+    assert log["accepted"].sum() > 100 and log["pair_terms"].sum() > 10 * len(log)
+    # differences of coordinates are exact and displacements those of the stored
+    # coordinates, so E_acc is off by the rounding of some 30 terms a move only
+    scale = log["scale"][log["accepted"] == 1].sum()
+    _, _, drift = s.energy()
+    assert abs(drift) <= 32 * 2.2e-16 * scale
+    s.close()
+
+
 @pytest.mark.parametrize("body", [flipmc.MC_TRIANGLE, flipmc.MC_SQUARE, flipmc.MC_TETRAHEDRON])
 def test_large_moves_of_an_overlapping_start_add_up(body):
     # moves that change the energy by more than 1e4 enter E_acc by the sum over
