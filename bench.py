@@ -81,12 +81,6 @@ def measured_traffic(name):
     return measured_counters(name).get("bytes_per_launch")
 
 
-def lone_workgroups(torch, k, nc):
-    """Workgroups of a lone system's sweep launch on the multi-workgroup
-    engine: one per cell of a colour, up to the compute units."""
-    return min(torch.cuda.get_device_properties(0).multi_processor_count, (nc // k) ** 3)
-
-
 def run_system(flipmc, torch, precision, steps, warmup, M=1000, T=0.75, k=0, nc=0, seed=1):
     p = flipmc.mc_params_default(
         n_molecules=M, temperature=T, precision=precision, colours_per_axis=k, cells_per_side=nc,
@@ -120,6 +114,7 @@ def run_system(flipmc, torch, precision, steps, warmup, M=1000, T=0.75, k=0, nc=
     acc = [int(o1["accepts"][i] - o0["accepts"][i]) for i in range(3)]
     return {
         "ms": ms,
+        "workgroups": flipmc.mc_engine(p)[1],
         "moves": moves,
         "moves_per_s": moves / (ms / 1e3),
         "sweep_kernel_ms": tm["sweep_ms"],
@@ -249,7 +244,7 @@ def bench_c1(args, flipmc, torch):
             "frac": achieved / PEAK_TFLOPS["f32"],
             "traffic": traffic,
             "kernel": "k_spread<float>",
-            "cus_used": lone_workgroups(torch, f32["k"], f32["n_c"]),
+            "cus_used": f32["workgroups"],
             "valu_busy_on_its_cus": measured_counters("k_spread_c1").get("valu_busy_on_its_cus"),
             "avg_launch_ms": f32["sweep_kernel_ms"] / launches,
             "flops_per_launch": flops / launches,
@@ -335,7 +330,7 @@ def bench_c2(args, flipmc, torch):
         "roofline": {"bound": "alu", "achieved": achieved, "peak": PEAK_TFLOPS["f32"],
                      "unit": "TFLOP/s", "frac": achieved / PEAK_TFLOPS["f32"],
                      "traffic": traffic, "kernel": "k_spread<float>",
-                     "cus_used": lone_workgroups(torch, k, nc),
+                     "cus_used": flipmc.mc_engine(p)[1],
                      "valu_busy_on_its_cus": measured_counters("k_spread_c2").get("valu_busy_on_its_cus"),
                      "hbm_gb_per_s": (traffic * n_sweeps / 100 / kern_s / 1e9) if traffic else None,
                      "avg_launch_ms": tm["sweep_ms"] / launches,

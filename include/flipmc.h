@@ -214,14 +214,13 @@ int mc_geometry(const mc_params* p, double* box, uint32_t* colours_per_axis,
 int mc_placement(const mc_params* p, int* resident, size_t* lds_bytes);
 
 /* The engine mc_sweep uses for a system with these parameters (MC_ENGINE_*)
- * and, for MC_ENGINE_SPREAD, the number of its workgroups, counted as one for
- * four cells of a colour (*workgroups = 1 otherwise).  A system beyond one
- * workgroup's LDS runs on the multi-workgroup engine, and so does one within it
- * that has more than 16 cells per colour.  A system alone in its launch gets a
- * workgroup per cell of a colour, up to the compute units of the device; one
- * named MC_ENGINE_LDS runs that way too when that is modelled 25 % faster than
- * its one workgroup, without other workgroups to ask for it (flags or
- * workgroups = 1 keep it on one).  Workgroups that find no room beside other
+ * and the number of workgroups of its launches: a workgroup per cell of a
+ * colour, up to the compute units of the device, for MC_ENGINE_SPREAD, and
+ * *workgroups = 1 otherwise.  A system beyond one workgroup's LDS runs on the
+ * multi-workgroup engine, and so does one within it when that is modelled 25 %
+ * faster than its one workgroup (also with a single cell per colour, whose
+ * trials the waves of one workgroup then share), unless flags or
+ * workgroups = 1 keep it on one.  Workgroups that find no room beside other
  * work take no part: any number gives the same results.  Inside a batch the
  * engine is chosen per run (see mc_batch_run).  Either output may be NULL. */
 int mc_engine(const mc_params* p, int* engine, uint32_t* workgroups);

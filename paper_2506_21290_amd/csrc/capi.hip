@@ -105,9 +105,7 @@ struct Geometry {
     uint32_t k, nc, ncell;
     bool resident;
     uint32_t near_cap;    // molecules listed near a cell
-    bool spread;          // standalone sweeps are the multi-workgroup engine's (mc_engine)
-    bool team;            // standalone sweeps run on its workgroups
-    uint32_t spread_blocks;  // its workgroups in units of four cells of a colour (mc_engine)
+    bool team;            // standalone sweeps run on the multi-workgroup engine
     uint32_t team_blocks;    // the workgroups it launches alone, the most it takes in a batch
     bool lists;              // the multi-workgroup engine has the cell lists in LDS
     uint32_t wave_fit;       // cells that its workgroups have room for with one per wave
@@ -277,9 +275,8 @@ int geometry(const mc_params* p, Geometry* g)
            spread_layout(fp64, true, p->n_molecules, g->ncell, g->near_cap, g->wave_fit + 1).total <= limit)
         ++g->wave_fit;
     g->team_waves = 0;
-    g->spread = !g->resident && !one_wg;
     g->team = false;
-    g->spread_blocks = g->team_blocks = 1;
+    g->team_blocks = 1;
     // the model is fitted to the LDS state; with the state in HBM a sweep on
     // one workgroup takes about 1.3 times as long (measured 1.1 - 1.4 over
     // 2197 - 27000 molecules)
@@ -294,23 +291,18 @@ int geometry(const mc_params* p, Geometry* g)
         const hipError_t e = spread_max_blocks(&maxb);
         if (e != hipSuccess || maxb == 0) {
             (void)hipGetLastError();
-            g->spread = false;
         } else {
             constexpr uint32_t kUnit = 4, kMaxUnits = 256;
             const uint32_t na = nc / k, nact = na * na * na;
             const uint32_t units = std::max(1u, std::min({(nact + kUnit - 1) / kUnit, maxb, kMaxUnits}));
-            g->spread_blocks = units;
             g->team_blocks = std::min(nact, maxb);
             if (p->workgroups >= 2 && units >= 2) {
-                if (p->workgroups < units) g->spread_blocks = g->team_blocks = p->workgroups;
-                g->spread = g->team = true;
-            } else if (g->resident) {
-                // many cells per colour are the multi-workgroup engine's by name
-                // as well
-                g->spread = units >= 5;
-                g->team = g->spread || spread_pays(*g, p->n_molecules, g->team_blocks, false, kCycleRatio[0], kCycleRatio[2]);
+                if (p->workgroups < units) g->team_blocks = p->workgroups;
+                g->team = true;
+            } else {
+                g->team = !g->resident ||
+                          spread_pays(*g, p->n_molecules, g->team_blocks, false, kCycleRatio[0], kCycleRatio[2]);
             }
-            if (!g->resident) g->team = true;
             if (g->wave_fit && g->spread_cycles(p->n_molecules, g->team_blocks, true) <
                                    g->spread_cycles(p->n_molecules, g->team_blocks, false))
                 g->team_waves = std::min(g->wave_fit, (nact + g->team_blocks - 1) / g->team_blocks);
@@ -802,8 +794,8 @@ int mc_engine(const mc_params* p, int* engine, uint32_t* workgroups)
     Geometry g;
     const int rc = geometry(p, &g);
     if (rc) return rc;
-    if (engine) *engine = g.spread ? MC_ENGINE_SPREAD : (g.resident ? MC_ENGINE_LDS : MC_ENGINE_HBM);
-    if (workgroups) *workgroups = g.spread ? g.spread_blocks : 1u;
+    if (engine) *engine = g.team ? MC_ENGINE_SPREAD : (g.resident ? MC_ENGINE_LDS : MC_ENGINE_HBM);
+    if (workgroups) *workgroups = g.team ? g.team_blocks : 1u;
     return MC_OK;
 }
 

@@ -75,7 +75,8 @@ def parity_from(gp, op, start, n_sweeps, fp32):
 
 
 @pytest.mark.parametrize("fp32", [False, True])
-@pytest.mark.parametrize("flags,engine", [(0, flipmc.MC_ENGINE_LDS),
+@pytest.mark.parametrize("flags,engine", [(0, flipmc.MC_ENGINE_SPREAD),
+                                          (flipmc.MC_FLAG_SINGLE_WORKGROUP, flipmc.MC_ENGINE_LDS),
                                           (flipmc.MC_FLAG_HBM_STATE, flipmc.MC_ENGINE_SPREAD)])
 def test_liquid_1000_molecules_every_trial(fp32, flags, engine):
     # the timed configuration (k = 2, n_c = 4, T = 0.75) in its timed regime
@@ -99,10 +100,11 @@ def test_liquid_8000_molecules_every_trial():
 
 
 @pytest.mark.parametrize("fp32", [False, True])
-@pytest.mark.parametrize("flags", [0, flipmc.MC_FLAG_HBM_STATE | flipmc.MC_FLAG_SINGLE_WORKGROUP])
+@pytest.mark.parametrize("flags", [0, flipmc.MC_FLAG_SINGLE_WORKGROUP,
+                                   flipmc.MC_FLAG_HBM_STATE | flipmc.MC_FLAG_SINGLE_WORKGROUP])
 def test_near_list_overflow_path(fp32, flags):
     # k = 2, n_c = 2 (cells of side 6.79): every molecule of the box lies
-    # within reach of every cell, far beyond the near list's 192 entries, so
+    # within reach of every cell, far beyond the near list's entries, so
     # every cell takes the overflow path (all stencil molecules evaluated)
     print(f"overflow fp32={fp32} flags={flags}", flush=True)
     gp = gparams(1000, 0.75, 2, 2, fp32=fp32, flags=flags, resum_interval=0, gofr_interval=0)

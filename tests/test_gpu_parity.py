@@ -97,15 +97,25 @@ def run_parity(gp, op, n_sweeps, fp32):
     return g, o, resyncs, trials
 
 
-def test_fp64_small_box_two_colours():
+# One workgroup with the state in LDS, whose waves take a cell each.
+LDS = flipmc.MC_FLAG_SINGLE_WORKGROUP
+
+
+@pytest.mark.parametrize("flags,engine", [(0, flipmc.MC_ENGINE_SPREAD), (LDS, flipmc.MC_ENGINE_LDS)])
+def test_fp64_small_box_two_colours(flags, engine):
     # 64 molecules, k = 2, n_c = 2 (one active cell per colour), T = 3
-    g, o, resyncs, trials = run_parity(gparams(64, 3.0, 2, 2), oparams(64, 3.0, 2, 2), 200, False)
+    gp = gparams(64, 3.0, 2, 2, flags=flags)
+    assert flipmc.mc_engine(gp) == (engine, 1)
+    g, o, resyncs, trials = run_parity(gp, oparams(64, 3.0, 2, 2), 200, False)
     assert trials == 64 * 200 and resyncs == 0
 
 
-def test_fp64_three_colours_many_cells():
-    # 216 molecules, k = 3, n_c = 6: 8 active cells per colour over 8 waves
-    run_parity(gparams(216, 1.0, 3, 6, seed=5), oparams(216, 1.0, 3, 6, seed=5), 25, False)
+@pytest.mark.parametrize("flags", [0, LDS])
+def test_fp64_three_colours_many_cells(flags):
+    # 216 molecules, k = 3, n_c = 6: 8 active cells per colour, over 8 waves with
+    # the state in LDS
+    gp = gparams(216, 1.0, 3, 6, seed=5, flags=flags)
+    run_parity(gp, oparams(216, 1.0, 3, 6, seed=5), 25, False)
 
 
 def test_fp64_hbm_state_path():
@@ -126,10 +136,10 @@ def test_fp64_hbm_single_workgroup_path():
 
 @pytest.mark.parametrize("fp32", [False, True])
 def test_spread_engine_many_workgroups(fp32):
-    # 1728 molecules, k = 2, n_c = 6: 27 cells per colour over 7 workgroups
+    # 1728 molecules, k = 2, n_c = 6: 27 cells per colour, a workgroup each
     gp = gparams(1728, 0.9, 2, 6, fp32=fp32, seed=21, flags=flipmc.MC_FLAG_HBM_STATE)
     engine, wg = flipmc.mc_engine(gp)
-    assert engine == flipmc.MC_ENGINE_SPREAD and wg == 7
+    assert engine == flipmc.MC_ENGINE_SPREAD and wg == 27
     run_parity(gp, oparams(1728, 0.9, 2, 6, seed=21), 4, fp32)
 
 
@@ -140,7 +150,7 @@ def test_engines_make_identical_decisions(fp32):
     # order, so the same dE bits, decisions and states
     n = 12
     runs = []
-    for flags, engine in [(0, flipmc.MC_ENGINE_LDS),
+    for flags, engine in [(LDS, flipmc.MC_ENGINE_LDS),
                           (flipmc.MC_FLAG_HBM_STATE | flipmc.MC_FLAG_SINGLE_WORKGROUP,
                            flipmc.MC_ENGINE_HBM),
                           (flipmc.MC_FLAG_HBM_STATE, flipmc.MC_ENGINE_SPREAD)]:
@@ -167,12 +177,12 @@ def test_engines_make_identical_decisions(fp32):
 def test_workgroup_count_changes_nothing_but_speed(fp32):
     # the tuner's knob: the 1000-molecule system (k = 3, n_c = 9: 27 cells per
     # colour) on one workgroup and on the multi-workgroup engine with 2, 5 and
-    # 7 workgroups (several cells per wave, or one each) gives the same dE
+    # 27 workgroups (several cells per wave, or one per workgroup) gives the same dE
     # bits, decisions and states
     n = 6
     runs = []
     for wg, want in [(1, (flipmc.MC_ENGINE_LDS, 1)), (2, (flipmc.MC_ENGINE_SPREAD, 2)),
-                     (5, (flipmc.MC_ENGINE_SPREAD, 5)), (1000, (flipmc.MC_ENGINE_SPREAD, 7))]:
+                     (5, (flipmc.MC_ENGINE_SPREAD, 5)), (1000, (flipmc.MC_ENGINE_SPREAD, 27))]:
         gp = gparams(1000, 0.9, 3, 9, fp32=fp32, seed=41, workgroups=wg, resum_interval=0,
                      obs_interval=0, gofr_interval=0)
         assert flipmc.mc_engine(gp) == want
@@ -196,7 +206,7 @@ def test_barrier_timeout_marks_the_system_faulted():
     # fault instead of a corrupt state; another system is unaffected.
     gp = gparams(2197, 1.3, 2, 6, fp32=True, seed=9, barrier_polls=1, resum_interval=0,
                  obs_interval=0, gofr_interval=0)
-    assert flipmc.mc_engine(gp) == (flipmc.MC_ENGINE_SPREAD, 7)
+    assert flipmc.mc_engine(gp) == (flipmc.MC_ENGINE_SPREAD, 27)
     g = flipmc.System(gp)
     g.sweep(20)
     with pytest.raises(flipmc.McError, match="barrier"):
@@ -289,18 +299,21 @@ def test_fp32_hbm_state_path():
 
 
 @pytest.mark.parametrize("fp32", [False, True])
-@pytest.mark.parametrize("decomp", ["bench", (3, 9)])
-def test_full_size_1000_molecules_sampled(fp32, decomp):
+@pytest.mark.parametrize("decomp,flags,want", [("bench", 0, (flipmc.MC_ENGINE_SPREAD, 8)),
+                                               ("bench", LDS, (flipmc.MC_ENGINE_LDS, 1)),
+                                               ((3, 9), 0, (flipmc.MC_ENGINE_SPREAD, 27))])
+def test_full_size_1000_molecules_sampled(fp32, decomp, flags, want):
     # the 1000-molecule configuration at T = 0.75 on its first sweeps, every
     # trial checked: with the decomposition the bench runs (the engine's
-    # table, one LDS workgroup) and with k = 3, n_c = 9 (27 cells per colour:
-    # the multi-workgroup engine in FP32)
+    # model: 8 cells per colour, a workgroup each), the same on one workgroup
+    # with the state in LDS, and with k = 3, n_c = 9 (27 cells per colour)
     if decomp == "bench":
         _, k, nc = flipmc.mc_geometry(gparams(1000, 0.75, 0, 0, fp32=fp32))
-        assert flipmc.mc_engine(gparams(1000, 0.75, k, nc, fp32=fp32))[0] == flipmc.MC_ENGINE_LDS
     else:
         k, nc = decomp
-    run_parity(gparams(1000, 0.75, k, nc, fp32=fp32), oparams(1000, 0.75, k, nc), 3, fp32)
+    gp = gparams(1000, 0.75, k, nc, fp32=fp32, flags=flags)
+    assert flipmc.mc_engine(gp) == want
+    run_parity(gp, oparams(1000, 0.75, k, nc), 3, fp32)
 
 
 def test_energy_invariant_and_drift():
@@ -382,7 +395,7 @@ def test_fs_matches_oracle(engine):
     if engine == "lds":
         M, T, k, nc, seed, n = 125, 1e6, 2, 2, 5, 50
         kw = dict(p_flip=0.1, p_translate=0.8, max_displacement=0.35)
-        flags, want_engine = 0, flipmc.MC_ENGINE_LDS
+        flags, want_engine = LDS, flipmc.MC_ENGINE_LDS
     else:
         M, T, k, nc, seed, n = 1000, 0.9, 2, 4, 31, 20
         kw = {}
@@ -484,7 +497,7 @@ def test_batch_equals_alone(fp32, workgroups, third):
 @pytest.mark.parametrize("limit,launches", [(0, 2), (2, 1)])
 def test_batch_moves_lds_system_to_idle_compute_units(limit, launches):
     # FP32: 1728 molecules (k = 2, n_c = 6) fit one workgroup's LDS; with
-    # compute units idle the batch runs them on 7 workgroups of the
+    # compute units idle the batch runs them on several workgroups of the
     # multi-workgroup engine (a second launch beside the LDS launch of the
     # small system), with a limit of 2 workgroups on one; either way bitwise
     # the result of running each system alone
@@ -492,7 +505,7 @@ def test_batch_moves_lds_system_to_idle_compute_units(limit, launches):
     sweeps = [12, 20]
     assert flipmc.mc_placement(gparams(1728, 0.9, 2, 6, fp32=True))[0] == 1
     # alone it takes the multi-workgroup engine too (27 cells per colour)
-    assert flipmc.mc_engine(gparams(1728, 0.9, 2, 6, fp32=True)) == (flipmc.MC_ENGINE_SPREAD, 7)
+    assert flipmc.mc_engine(gparams(1728, 0.9, 2, 6, fp32=True)) == (flipmc.MC_ENGINE_SPREAD, 27)
     alone = []
     for (M, T, k, nc, seed), n in zip(specs, sweeps):
         s = flipmc.System(gparams(M, T, k, nc, fp32=True, seed=seed))

@@ -30,6 +30,18 @@ def chain(M, T, k, nc, seed, fp32, sweeps, workgroups, **more):
     return out
 
 
+@pytest.mark.parametrize("M,k,nc,flags,want", [
+    (64, 2, 2, 0, (flipmc.MC_ENGINE_SPREAD, 1)),      # one cell per colour
+    (1000, 2, 4, 0, (flipmc.MC_ENGINE_SPREAD, 8)),    # fits one workgroup's LDS, faster on a workgroup per cell
+    (1000, 2, 4, flipmc.MC_FLAG_SINGLE_WORKGROUP, (flipmc.MC_ENGINE_LDS, 1)),
+    (2197, 2, 6, 0, (flipmc.MC_ENGINE_SPREAD, 27)),
+    (2197, 2, 6, flipmc.MC_FLAG_SINGLE_WORKGROUP, (flipmc.MC_ENGINE_HBM, 1)),
+])
+def test_engine_names_what_a_sweep_launches(M, k, nc, flags, want):
+    p = flipmc.mc_params_default(n_molecules=M, colours_per_axis=k, cells_per_side=nc, flags=flags)
+    assert flipmc.mc_engine(p) == want
+
+
 @pytest.mark.parametrize("M,k,nc,workgroups", [
     (64, 2, 2, 0),       # one cell per colour: one workgroup's waves share it
     (83, 2, 2, 0),       # no whole groups of eight molecules
