@@ -112,11 +112,10 @@ typedef struct {
     uint32_t workgroups;       /* workgroups of mc_sweep's launches: 0 = the engine's
                                   cost model; 1 = one workgroup (as
                                   MC_FLAG_SINGLE_WORKGROUP); n >= 2 = the
-                                  multi-workgroup engine on n workgroups, also the
-                                  most a batch gives the system, or from a quarter of
-                                  the cells of a colour on (rounded up) on one per
-                                  cell.  Every choice gives bitwise the same chain (an
-                                  autotuner's knob)                                   */
+                                  multi-workgroup engine on min(n, cells of a colour,
+                                  device limit) workgroups, also the most a batch
+                                  gives the system.  Every choice gives bitwise the
+                                  same chain (an autotuner's knob)                    */
     double   fs_q;             /* |q| of F_s(q, t) over the sites (Sec. III.B: 7.4,
                                   the first peak of the structure factor)             */
     double   fs_q_cm;          /* |q| of F_s^cm(q, t) over the centres (5.1)         */

@@ -292,17 +292,11 @@ int geometry(const mc_params* p, Geometry* g)
         if (e != hipSuccess || maxb == 0) {
             (void)hipGetLastError();
         } else {
-            constexpr uint32_t kUnit = 4, kMaxUnits = 256;
             const uint32_t na = nc / k, nact = na * na * na;
-            const uint32_t units = std::max(1u, std::min({(nact + kUnit - 1) / kUnit, maxb, kMaxUnits}));
-            g->team_blocks = std::min(nact, maxb);
-            if (p->workgroups >= 2 && units >= 2) {
-                if (p->workgroups < units) g->team_blocks = p->workgroups;
-                g->team = true;
-            } else {
-                g->team = !g->resident ||
-                          spread_pays(*g, p->n_molecules, g->team_blocks, false, kCycleRatio[0], kCycleRatio[2]);
-            }
+            const uint32_t most = p->workgroups ? std::min(p->workgroups, maxb) : maxb;
+            g->team_blocks = std::min(nact, most);
+            g->team = !g->resident || (p->workgroups >= 2 && g->team_blocks >= 2) ||
+                      spread_pays(*g, p->n_molecules, g->team_blocks, false, kCycleRatio[0], kCycleRatio[2]);
             if (g->wave_fit && g->spread_cycles(p->n_molecules, g->team_blocks, true) <
                                    g->spread_cycles(p->n_molecules, g->team_blocks, false))
                 g->team_waves = std::min(g->wave_fit, (nact + g->team_blocks - 1) / g->team_blocks);

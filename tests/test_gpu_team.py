@@ -42,6 +42,13 @@ def test_engine_names_what_a_sweep_launches(M, k, nc, flags, want):
     assert flipmc.mc_engine(p) == want
 
 
+@pytest.mark.parametrize("M,k,nc,cells", [(1000, 2, 4, 8), (2197, 2, 6, 27)])
+def test_workgroups_is_a_limit(M, k, nc, cells):
+    for n in (2, 3, cells - 1, cells, cells + 1):
+        p = flipmc.mc_params_default(n_molecules=M, colours_per_axis=k, cells_per_side=nc, workgroups=n)
+        assert flipmc.mc_engine(p) == (flipmc.MC_ENGINE_SPREAD, min(n, cells))
+
+
 @pytest.mark.parametrize("M,k,nc,workgroups", [
     (64, 2, 2, 0),       # one cell per colour: one workgroup's waves share it
     (83, 2, 2, 0),       # no whole groups of eight molecules
@@ -50,6 +57,7 @@ def test_engine_names_what_a_sweep_launches(M, k, nc, flags, want):
     (1001, 2, 4, 0),     # 8 workgroups, each ranking all molecules
     (2048, 2, 6, 0),     # the largest that each ranks alone
     (2049, 2, 6, 0),     # the smallest whose ranks are shared out
+    (1000, 2, 4, 3),     # fewer workgroups than the 8 cells of a colour
     (2197, 2, 6, 3),     # fewer workgroups than cells of a colour: a cell per wave
     (8000, 2, 10, 4),    # the same with several cells a wave
     (2747, 2, 8, 0),     # 64 workgroups: barriers in groups
