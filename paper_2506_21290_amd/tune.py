@@ -10,7 +10,9 @@ speed: every count gives bitwise the same chain.  The tuner times each
 candidate (k, n_c, workgroups) and records the fastest in ``tuned.json`` next
 to this file.  ``choose`` reads the table (falling back to the engine's own
 model when a size is missing), so a job's decomposition is a fixed function of
-(M, precision) and can be reproduced by the oracle.
+(M, precision) and can be reproduced by the oracle.  After a change that moves
+the times and not the chains, ``--keep-chains`` times only the workgroup counts
+of the decompositions that are in the table.
 
 Run on the GPU:  python -m paper_2506_21290_amd.tune --out tuned.json
 """
@@ -58,9 +60,10 @@ def candidates(M, precision, per_k=4):
 
 
 def workgroup_counts(M, precision, k, nc):
-    """Workgroup counts worth timing for one decomposition: a quarter of the
-    cells of a colour (which stands for a workgroup per cell), half and a quarter
-    of that, and one workgroup when the state fits its LDS."""
+    """Workgroup counts worth timing for one decomposition: a workgroup per cell
+    of a colour, half and a quarter of that, one workgroup when the state fits its
+    LDS, and with a single cell per colour also 0, the model's choice, where the
+    waves of one workgroup share the cell."""
     p = flipmc.mc_params_default(n_molecules=M, precision=precision, colours_per_axis=k, cells_per_side=nc,
                                  workgroups=1 << 20)
     _, most = flipmc.mc_engine(p)
@@ -68,6 +71,8 @@ def workgroup_counts(M, precision, k, nc):
     p.workgroups = 1
     if flipmc.mc_placement(p)[0] or not counts:
         counts.add(1)
+    if most == 1:
+        counts.add(0)
     return sorted(counts)
 
 
@@ -105,7 +110,7 @@ def time_candidate(M, precision, k, nc, sweeps, T=1.0, workgroups=0):
     return (time.perf_counter() - t0) / sweeps
 
 
-def tune(sizes, precisions, budget_moves=600_000):
+def tune(sizes, precisions, budget_moves=600_000, keep_chains=False):
     result = {}
     for prec in precisions:
         name = PREC_NAME[prec]
@@ -113,7 +118,8 @@ def tune(sizes, precisions, budget_moves=600_000):
         for M in sizes:
             sweeps = max(10, min(200, budget_moves // M))
             timed = []
-            for k, nc in candidates(M, prec):
+            kept = table().get(name, {}).get(str(M)) if keep_chains else None
+            for k, nc in [(kept["k"], kept["n_c"])] if kept else candidates(M, prec):
                 for wg in workgroup_counts(M, prec, k, nc):
                     dt = time_candidate(M, prec, k, nc, sweeps, workgroups=wg)
                     timed.append((dt, k, nc, wg))
@@ -133,10 +139,11 @@ def main():
     ap.add_argument("--sizes", default=",".join(str(n ** 3) for n in range(4, 31)))
     ap.add_argument("--precisions", default="fp32")
     ap.add_argument("--out", default=TABLE)
+    ap.add_argument("--keep-chains", action="store_true", help="time only the workgroup counts of the table's (k, n_c)")
     args = ap.parse_args()
     sizes = [int(x) for x in args.sizes.split(",")]
     precs = [{"fp32": flipmc.MC_FP32_DE, "fp64": flipmc.MC_FP64}[x] for x in args.precisions.split(",")]
-    res = tune(sizes, precs)
+    res = tune(sizes, precs, keep_chains=args.keep_chains)
     old = {}
     if os.path.exists(args.out):
         with open(args.out) as f:

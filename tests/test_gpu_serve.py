@@ -10,7 +10,7 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
-from paper_2506_21290_amd import flipmc, serve, workloads  # noqa: E402
+from paper_2506_21290_amd import flipmc, serve, tune, workloads  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -66,3 +66,18 @@ def test_cancel_then_readmit_on_device():
     assert srv.cancel(0, 0).index == 0
     assert srv.used == 0
     assert srv.try_admit(jobs[1], 0.0)
+
+
+@pytest.mark.parametrize("M", [64, 343, 1000, 2197, 8000])
+def test_tuned_workgroup_count_is_about_the_fastest(M):
+    # the table's counts are the engine's of today: no other count for the same
+    # (k, n_c) is a quarter faster (two runs of one count differ by some percent)
+    prec = flipmc.MC_FP32_DE
+    k, nc, wg = tune.choose(M, prec)
+    assert k and nc
+
+    def fastest(n):
+        return min(tune.time_candidate(M, prec, k, nc, 50, workgroups=n) for _ in range(3))
+
+    times = {n: fastest(n) for n in {wg, *tune.workgroup_counts(M, prec, k, nc)}}
+    assert times[wg] <= 1.25 * min(times.values()), times
