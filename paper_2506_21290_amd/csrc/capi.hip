@@ -1650,6 +1650,30 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
             heap.push_back(c);
             std::push_heap(heap.begin(), heap.end(), later);
         }
+        // The two ways are two launches, the second beside the first on the third
+        // stream.  Where that is taken (systems on one workgroup with their state
+        // in HBM) or missing, a second one would start when the first has ended
+        // and double the slice: one job of 125 molecules with a cell per
+        // workgroup made slices of 54 ms out of 31 (a stream of 200 jobs:
+        // 2.74e8 moves/s, 3.1 - 3.2e8 with one way).  Then all that have several workgroups have a
+        // cell per wave, and the others stay on their one.  (A system whose cell
+        // lists do not fit LDS has no other way; with one of those both stay.)
+        bool busy3 = !b->stream3 || b->stream2 == b->stream, movable = true;
+        uint32_t by[2] = {0, 0};
+        for (uint32_t i : active) {
+            const mc_system* s = b->sys[i];
+            if (nblk[i]) ++by[(int)by_wave[i]];
+            else busy3 = busy3 || !s->g.resident;
+            movable = movable && (!nblk[i] || s->g.resident || s->g.wave_fit >= 2);
+        }
+        if (busy3 && by[0] && by[1] && movable)
+            for (uint32_t i : active) {
+                const mc_system* s = b->sys[i];
+                if (!nblk[i] || by_wave[i]) continue;
+                by_wave[i] = s->g.wave_fit >= 2 &&
+                             spread_pays(s->g, s->p.n_molecules, nblk[i], true, b->ms_per_cycle[0], b->ms_per_cycle[3]);
+                if (!by_wave[i]) nblk[i] = 0;
+            }
     }
     uint32_t n[3] = {0, 0, 0};
     size_t lds[2] = {0, 0};

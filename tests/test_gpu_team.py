@@ -145,6 +145,38 @@ def test_batch_of_short_and_long_systems(fp32, limit):
     b.close()
 
 
+def test_time_slices_of_every_engine_run_beside_each_other():
+    # a time slice has at most three launches, one per stream: with systems on
+    # one HBM workgroup, those with several workgroups take one way, and each
+    # ends as it does alone
+    sizes = [(8000, 2, 10, 60), (125, 2, 2, 400), (125, 2, 2, 300), (343, 2, 4, 200)] + [(2197, 2, 6, 40)] * 4
+
+    def system(i, M, k, nc, **kw):
+        p = flipmc.mc_params_default(n_molecules=M, temperature=1.3, colours_per_axis=k, cells_per_side=nc, seed=i,
+                                     precision=flipmc.MC_FP32_DE, resum_interval=0, gofr_interval=0)
+        return flipmc.System(p, **kw)
+
+    b = flipmc.Batch(len(sizes), flipmc.MC_FP32_DE)
+    b.set_workgroups(16)
+    systems = [system(i, M, k, nc, stream=b.stream) for i, (M, k, nc, _) in enumerate(sizes)]
+    for s, (_, _, _, n) in zip(systems, sizes):
+        b.add(s, n)
+    launched, left = [], len(systems)
+    for _ in range(500):
+        launched.append(b.run(10000))
+        left -= len(b.poll())
+        if not left:
+            break
+    assert left == 0 and max(launched) == 3
+    for i, (s, (M, k, nc, n)) in enumerate(zip(systems, sizes)):
+        alone = system(i, M, k, nc)
+        alone.sweep(n)
+        st, ref = s.get_state(), alone.get_state()
+        for f in ("com", "quat", "types", "e_acc", "sweep"):
+            assert np.array_equal(st[f], ref[f]), f
+    b.close()
+
+
 @pytest.mark.parametrize("same", [True, False])
 def test_two_batches_in_turn(same):
     # batches on one stream share their side streams; batches on two do not
