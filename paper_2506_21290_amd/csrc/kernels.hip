@@ -1642,39 +1642,45 @@ __device__ __forceinline__ TrialSum eval_trial(const Ctx<Real, kMem>& C, const V
     // 2. prune and compact the survivors (the prune needs only the molecule's
     // relative centre, taken from the lane that holds it while that lane's
     // record is still being written); after a list overflow every stencil
-    // molecule, 64 at a time
-    const uint32_t nrun = overflow ? (g.total + 63u) / 64u : 1u;
-    for (uint32_t run = 0; run < nrun; ++run) {
+    // molecule, 64 at a time.  (The two apart: with one loop for both the moved
+    // sites were carried through it, which FP64 paid with spills: 1000 molecules
+    // on one workgroup 447 us a sweep, 417 so, FP32 317 and 312.)
+    if (!overflow) {
         uint32_t nsurv = 0;
-        if (!overflow) {
-            const float tmx = rl_f(T.mrx, i), tmy = rl_f(T.mry, i), tmz = rl_f(T.mrz, i);
-            const float r_far = P.pr_base + (move == 0u ? P.pr_step : 0.f);
-            auto prune = [&](const NearOne& e) __attribute__((always_inline)) {
-                const float px = e.x - tmx, py = e.y - tmy, pz = e.z - tmz;
-                const float rr = r_far + e.more;
-                const float lim = P.prune_on ? rr * rr : P.prune2;
-                const bool keep = e.j != kNoMolecule && e.j != mloc && px * px + py * py + pz * pz < lim;
-                const uint64_t bm = __ballot(keep);
-                if (keep) W.surv[nsurv + rank_below(bm)] = (uint16_t)e.j;
-                nsurv += (uint32_t)__popcll(bm);
-            };
+        const float tmx = rl_f(T.mrx, i), tmy = rl_f(T.mry, i), tmz = rl_f(T.mrz, i);
+        const float r_far = P.pr_base + (move == 0u ? P.pr_step : 0.f);
+        auto prune = [&](const NearOne& e) __attribute__((always_inline)) {
+            const float px = e.x - tmx, py = e.y - tmy, pz = e.z - tmz;
+            const float rr = r_far + e.more;
+            const float lim = P.prune_on ? rr * rr : P.prune2;
+            const bool keep = e.j != kNoMolecule && e.j != mloc && px * px + py * py + pz * pz < lim;
+            const uint64_t bm = __ballot(keep);
+            if (keep) W.surv[nsurv + rank_below(bm)] = (uint16_t)e.j;
+            nsurv += (uint32_t)__popcll(bm);
+        };
 #pragma unroll
-            for (int c = 0; c < kNearSlots; ++c) prune(nr.e[c]);
-            for (uint32_t b = 64u * kNearSlots; b < nr.n; b += 64u)
-                prune(near_one(P, nr.near, b + (uint32_t)lane, nr.n));
-        } else {
-            const uint32_t m = rl_u(T.mi, i), idx = 64u * run + (uint32_t)lane;
+        for (int c = 0; c < kNearSlots; ++c) prune(nr.e[c]);
+        for (uint32_t b = 64u * kNearSlots; b < nr.n; b += 64u)
+            prune(near_one(P, nr.near, b + (uint32_t)lane, nr.n));
+        wave_lds_sync();  // the record and the survivors
+        load_moved();
+        if (nsurv) eval_items(3u * nsurv);
+    } else {
+        wave_lds_sync();  // the record
+        load_moved();
+        const uint32_t m = rl_u(T.mi, i);
+        for (uint32_t base = 0; base < g.total; base += 64u) {
+            const uint32_t idx = base + (uint32_t)lane;
             uint32_t j = kNoMolecule;
             if (idx < g.total) j = stencil_molecule(C, W.seglo, W.segoff, g.n, idx);
             const bool keep = j != kNoMolecule && j != m;
             const uint64_t bm = __ballot(keep);
             wave_lds_sync();
             if (keep) W.surv[rank_below(bm)] = (uint16_t)j;
-            nsurv = (uint32_t)__popcll(bm);
+            wave_lds_sync();
+            const uint32_t nsurv = (uint32_t)__popcll(bm);
+            if (nsurv) eval_items(3u * nsurv);
         }
-        wave_lds_sync();  // the record and the survivors
-        if (run == 0) load_moved();
-        if (nsurv) eval_items(3u * nsurv);
     }
     r.de = wave_sum_dpp((double)acc);
     if (P.logging) r.scale = wave_sum_dpp((double)accs);
