@@ -816,6 +816,11 @@ int fx_init(mcf_system* s, const mcf_params* p, const FxGeom& g, const FxLayout&
     D.dyn_base = g.rc + 4.0 * std::sqrt(3.0) * p->max_displacement + 1e-9;
     D.together = (p->flags & MC_FLAG_SERIAL_CELLS) ? 2u : (D.sep >= g.reach ? 1u : 0u);
     for (int t = 0; t < 4; ++t) D.sigma[t] = t < (int)g.n ? p->sigma[t] : 1.0;
+    {
+        const double smax = *std::max_element(p->sigma, p->sigma + g.n);
+        const float r = (float)(std::sqrt(D.rc2f) * smax + 2.0 * std::sqrt(3.0) * D.dmax) + 2e-6f * (float)D.w;
+        D.wide_r2 = r * r;
+    }
     const double rmax = std::min(0.5 * g.L, 5.0);
     D.gofr_nbins = std::min((uint32_t)kGofrBins, (uint32_t)std::floor(rmax / p->gofr_dr + 1e-6));
     D.gofr_dr = p->gofr_dr;

@@ -81,7 +81,7 @@ struct FxDev {
     uint32_t seed_lo, seed_hi, pad2, pad3;
     uint32_t bonded;  // bit 4 i + j: atoms i, j of a molecule are bonded
     uint32_t resum_interval, obs_interval, gofr_interval, obs_start, max_samples, gofr_nbins;
-    uint32_t pad;
+    float wide_r2;  // FxK::list_r2 of cells wider than 500
     double L, invL, w, T, p_flip, dmax, rc2f;
     double sigma[4];
     double gofr_dr, gofr_rmax, fs_q, fs_q_cm;
@@ -158,11 +158,12 @@ __device__ __forceinline__ FxK fx_const(const FxDev& D)
     K.img = (Global<int32_t>*)D.img; K.props = (Global<FxProp>*)D.props; K.nbr = (Global<void>*)D.nbr;
     // the FP32 distances of the list build are within 1.2e-6 w of the FP64 ones:
     // coordinates up to 1.5 w from the cell's centre, rounded to 2^-24 of that,
-    // their difference and its nearest image to 2^-24 of 3 w, along three axes
+    // their difference and its nearest image to 2^-24 of 3 w, along three axes;
+    // cells wider than 500 have a margin of their own (FxDev::wide_r2, which for
+    // all cells, as a scalar, makes the sweep 1 % slower)
     const double smax = fmax(fmax(D.sigma[0], D.sigma[1]), fmax(D.sigma[2], D.n > 3u ? D.sigma[3] : 0.0));
-    const float r = (float)(sqrt(D.rc2f) * smax + 2.0 * 1.7320508075688772 * D.dmax) +
-                    fmaxf(1e-3f, 2e-6f * (float)D.w);
-    K.list_r2 = r * r;
+    const float r = (float)(sqrt(D.rc2f) * smax + 2.0 * 1.7320508075688772 * D.dmax) + 1e-3f;
+    K.list_r2 = D.w > 500.0 ? D.wide_r2 : r * r;
     return K;
 }
 
