@@ -271,8 +271,8 @@ int geometry(const mc_params* p, Geometry* g)
     const bool one_wg = (p->flags & MC_FLAG_SINGLE_WORKGROUP) || p->workgroups == 1;
     g->lists = spread_layout(fp64, true, p->n_molecules, g->ncell, g->near_cap, 0).total <= limit;
     g->wave_fit = 0;
-    while (g->lists && g->wave_fit < (uint32_t)kWaves &&
-           spread_layout(fp64, true, p->n_molecules, g->ncell, g->near_cap, g->wave_fit + 1).total <= limit)
+    while (g->wave_fit < (uint32_t)cell_threads(fp64, g->lists) / 64u &&
+           spread_layout(fp64, g->lists, p->n_molecules, g->ncell, g->near_cap, g->wave_fit + 1).total <= limit)
         ++g->wave_fit;
     g->team_waves = 0;
     g->team = false;
@@ -610,6 +610,13 @@ __global__ void k_zero_counter(uint32_t* c)
     for (int i = threadIdx.x; i < kBarWords; i += blockDim.x) c[i] = 0u;
 }
 
+// The kernel of systems with a cell per wave (waves) or per workgroup, whose cell
+// lists all fit its LDS or not.
+SpreadMode spread_mode(bool waves, bool lists)
+{
+    return waves ? (lists ? kSpreadWaves : kSpreadCrewWaves) : (lists ? kSpreadTeam : kSpreadCrew);
+}
+
 // Enqueue n sweeps of one system, split at event sweeps.
 int advance(mc_system* s, uint64_t n)
 {
@@ -635,8 +642,7 @@ int advance(mc_system* s, uint64_t n)
             sl.waves = s->g.team_waves;
             const size_t lds = spread_layout(s->p.precision == MC_FP64, s->g.lists, s->p.n_molecules, s->g.ncell,
                                              s->g.near_cap, sl.waves).total;
-            HIPCHK(launch_spread(s->p.precision == MC_FP64,
-                                 sl.waves ? kSpreadWaves : (s->g.lists ? kSpreadTeam : kSpreadCrew), nullptr, 1, sl,
+            HIPCHK(launch_spread(s->p.precision == MC_FP64, spread_mode(sl.waves, s->g.lists), nullptr, 1, sl,
                                  s->g.team_blocks, lds, s->stream));
         }
         else
@@ -1385,7 +1391,7 @@ int mc_batch_create(uint32_t max_slots, uint32_t precision, void* device_buf, si
         SpreadSlot snone{};
         hipError_t e = launch_sweeps(fp64, true, nullptr, none, 1, 0, b->stream, true);
         if (e == hipSuccess) e = launch_sweeps(fp64, false, nullptr, none, 1, 0, b->stream, true);
-        for (const SpreadMode m : {kSpreadTeam, kSpreadWaves, kSpreadCrew})
+        for (const SpreadMode m : {kSpreadTeam, kSpreadWaves, kSpreadCrew, kSpreadCrewWaves})
             if (e == hipSuccess && b->spread_max >= 2) e = launch_spread(fp64, m, nullptr, 0, snone, 1, 0, b->stream);
         if (e != hipSuccess) {
             mc_batch_destroy(b);
@@ -1764,9 +1770,9 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
         std::vector<std::pair<mc_system*, uint32_t>> parts;
         std::vector<SpreadSlot> by[2];
         uint32_t blocks[2] = {0, 0}, ne = 0;
-        size_t need[2] = {0, 0}, crew_need = 0;
+        size_t need[2] = {0, 0}, crew_need[2] = {0, 0};
         double cycles[2] = {0.0, 0.0};
-        bool lists = true;  // the cell lists of all systems with a cell per workgroup fit its LDS
+        bool lists[2] = {true, true};  // the cell lists of all systems fit the LDS
         for (uint32_t i : several) {
             mc_system* s = b->sys[i];
             uint64_t k = std::min<uint64_t>(b->remaining[i], next_event(s) - s->sweep);
@@ -1788,11 +1794,9 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
             blocks[w] += nblk[i];
             need[w] = std::max(need[w], spread_layout(fp64, s->g.lists, s->p.n_molecules, s->g.ncell, s->g.near_cap,
                                                       sl.waves).total);
-            if (!w) {
-                lists = lists && s->g.lists;
-                crew_need = std::max(crew_need, spread_layout(fp64, false, s->p.n_molecules, s->g.ncell,
-                                                              s->g.near_cap, 0).total);
-            }
+            lists[w] = lists[w] && s->g.lists;
+            crew_need[w] = std::max(crew_need[w], spread_layout(fp64, false, s->p.n_molecules, s->g.ncell,
+                                                                s->g.near_cap, sl.waves).total);
             b->remaining[i] -= k;
             s->sweep += k;
             if (const uint32_t f = events_at(s, s->sweep)) {
@@ -1821,11 +1825,11 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
         }
         for (int w = 1; w >= 0; --w) {
             if (by[w].empty()) continue;
-            const SpreadMode mode = w ? kSpreadWaves : (lists ? kSpreadTeam : kSpreadCrew);
+            const SpreadMode mode = spread_mode(w, lists[w]);
             const bool sample = cycles[w] > pred[2 + w];  // the longest slice is the run's sample
             if (sample) HIPCHK(hipEventRecord(b->t_beg[2 + w], st_of[w]));
             HIPCHK(launch_spread(fp64, mode, b->dev_spread[par] + (w ? nt : 0u), (uint32_t)by[w].size(), none, blocks[w],
-                                 mode == kSpreadCrew ? crew_need : need[w], st_of[w]));
+                                 lists[w] ? need[w] : crew_need[w], st_of[w]));
             if (sample) {
                 HIPCHK(hipEventRecord(b->t_end[2 + w], st_of[w]));
                 b->pred[2 + w] = pred[2 + w] = cycles[w];

@@ -208,6 +208,13 @@ __host__ __device__ inline LdsLayout lds_layout(bool fp64, bool resident, uint32
 // colour, stages the cell's neighbourhood (up to near_cap molecules) in its LDS
 // and its waves share the cell's trials; or each of the first `waves` waves of a
 // workgroup takes and stages a cell of its own.
+// Threads of a workgroup whose waves have a cell each.  A wave of 512 threads has
+// 256 registers, of which FP64 trials spill 280 values and FP32 160: 20 sweeps of
+// 20 systems of 8000 molecules take 23.3 ms in FP64 so, 12.3 with half the waves
+// and twice the registers.  FP32 gains more by the second wave of a SIMD (64
+// workgroups, 8000 molecules), but not with the lists in the buffer (50000
+// molecules 365 us a sweep, 312 with 256 threads).
+__host__ __device__ constexpr int cell_threads(bool fp64, bool lists) { return fp64 || !lists ? kThreads / 2 : kThreads; }
 constexpr int kBarWords = 272;   // words of SysDev::g_bar
 
 // LDS of one of its workgroups: the lists of the system's cells too where they
@@ -265,12 +272,11 @@ struct SpreadSlot {
 
 // Launch of the multi-workgroup engine over n_blocks workgroups: the systems of
 // dev_slots[0 .. n_slots) (device array), or `one` when dev_slots is null, with
-// a cell per workgroup and the cell lists in LDS or in the systems' buffers, or
-// with a cell per wave (SpreadSlot::waves, lists in LDS), and the LDS that the
-// largest needs (spread_layout).  The workgroups of each system synchronise
+// a cell per workgroup or a cell per wave (SpreadSlot::waves) and the cell lists
+// in LDS or in the systems' buffers (crew), and the LDS that the largest needs (spread_layout).  The workgroups of each system synchronise
 // among themselves only (each system's g_bar must be zero at launch; one
 // workgroup alone does not use it).
-enum SpreadMode { kSpreadTeam, kSpreadWaves, kSpreadCrew };
+enum SpreadMode { kSpreadTeam, kSpreadWaves, kSpreadCrew, kSpreadCrewWaves };
 hipError_t launch_spread(bool fp64, SpreadMode mode, const SpreadSlot* dev_slots, uint32_t n_slots,
                          const SpreadSlot& one, uint32_t n_blocks, size_t lds, hipStream_t stream);
 // Zero the barrier words of the systems of dev_slots[0 .. n_slots).

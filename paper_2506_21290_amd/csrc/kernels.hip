@@ -2397,8 +2397,8 @@ struct SysBarrier {
     uint32_t epoch;
     uint32_t polls;
 };
-// kFenced: the exchanged data lies in the caches (write back, invalidate);
-// otherwise it went past them, and every wave waits for its own stores.
+// Every wave waits for its own stores; kFenced: some of the exchanged data lies
+// in the caches (write back, invalidate), otherwise all went past them.
 
 __device__ __forceinline__ SysBarrier crew_barrier(uint32_t* bar, uint32_t nblk, uint32_t bid, uint32_t polls)
 {
@@ -2455,7 +2455,7 @@ __device__ uint32_t join_crew(uint32_t* bar, uint32_t n, uint32_t polls, uint32_
 template <bool kFenced>
 __device__ __forceinline__ void sys_arrive(SysBarrier& B)
 {
-    if (!kFenced) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (B.nblk == 1) return;
     ++B.epoch;
@@ -2511,7 +2511,7 @@ __device__ __forceinline__ bool sys_sync(SysBarrier& B, uint32_t* fault, uint32_
 // The molecules of every cell, in no order, in this workgroup's LDS from the
 // cell of every molecule: count, scan, fill.  base is C.cellb (ncell + 1
 // words), tmp M words of LDS, both this workgroup's.
-template <typename Real>
+template <int kThr, typename Real>
 __device__ __forceinline__ void team_fill(const Ctx<Real, kMemTeam>& C, Lds<uint16_t>* tmp, uint32_t* scratch)
 {
     const uint32_t tid = threadIdx.x, M = C.M, ncell = C.ncell;
@@ -2526,15 +2526,15 @@ __device__ __forceinline__ void team_fill(const Ctx<Real, kMemTeam>& C, Lds<uint
     auto ids_at = [&](uint32_t i) { return __builtin_bit_cast(C8, agent_words(ids, 16u * i)); };
     C8 held[kHeld];
 #pragma unroll
-    for (uint32_t u = 0; u < kHeld; ++u) held[u] = ids_at(tid + u * kThreads);  // (none past the end)
+    for (uint32_t u = 0; u < kHeld; ++u) held[u] = ids_at(tid + u * kThr);  // (none past the end)
     auto turns = [&](auto&& f) __attribute__((always_inline)) {
 #pragma unroll
         for (uint32_t u = 0; u < kHeld; ++u)
-            if (tid + u * kThreads < M8) f(tid + u * kThreads, held[u]);
-        for (uint32_t i = tid + kHeld * kThreads; i < M8; i += kThreads) f(i, ids_at(i));
+            if (tid + u * kThr < M8) f(tid + u * kThr, held[u]);
+        for (uint32_t i = tid + kHeld * kThr; i < M8; i += kThr) f(i, ids_at(i));
     };
     if (tid == 0) base[0] = 0u;
-    for (uint32_t c = tid; c < ncell; c += kThreads) cur[c] = 0u;
+    for (uint32_t c = tid; c < ncell; c += kThr) cur[c] = 0u;
     const uint32_t mr = 8u * M8 + tid, cr = mr < M ? (uint32_t)agent_load(&C.cellid[mr]) : 0u;  // the last M mod 8
     __syncthreads();
     turns([&](uint32_t, C8 c) __attribute__((always_inline)) {
@@ -2543,7 +2543,7 @@ __device__ __forceinline__ void team_fill(const Ctx<Real, kMemTeam>& C, Lds<uint
     });
     if (mr < M) atomicAdd((uint32_t*)&cur[cr], 1u);
     __syncthreads();
-    block_excl_scan_t<kThreads>((uint32_t*)cur, ncell, scratch);
+    block_excl_scan_t<kThr>((uint32_t*)cur, ncell, scratch);
     // a cell's cursor moves from its start to its end, which is the next start
     turns([&](uint32_t i, C8 c) __attribute__((always_inline)) {
         uint32_t at[8];
@@ -2558,22 +2558,22 @@ __device__ __forceinline__ void team_fill(const Ctx<Real, kMemTeam>& C, Lds<uint
 
 // Each of the molecules at places [p0, p1) of tmp (whole cells) to its rank
 // among its cell's (ascending index), four places per thread at a time.
-template <typename Real, typename Put>
+template <int kThr, typename Real, typename Put>
 __device__ __forceinline__ void team_rank(const Ctx<Real, kMemTeam>& C, const Lds<uint16_t>* tmp, uint32_t p0,
                                           uint32_t p1, Put put)
 {
     const Lds<uint32_t>* base = C.cellb;
-    for (uint32_t q0 = p0 + threadIdx.x; q0 < p1; q0 += 4u * kThreads) {
+    for (uint32_t q0 = p0 + threadIdx.x; q0 < p1; q0 += 4u * kThr) {
         uint32_t m[4], lo[4], n[4], rank[4], most = 0;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) m[t] = tmp[min(q0 + t * kThreads, p1 - 1u)];
+        for (int t = 0; t < 4; ++t) m[t] = tmp[min(q0 + t * kThr, p1 - 1u)];
 #pragma unroll
         for (int t = 0; t < 4; ++t) lo[t] = agent_load(&C.cellid[m[t]]);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const uint32_t c = lo[t];
             lo[t] = base[c];
-            n[t] = q0 + t * kThreads < p1 ? base[c + 1] - lo[t] : 0u;
+            n[t] = q0 + t * kThr < p1 ? base[c + 1] - lo[t] : 0u;
             rank[t] = 0;
             most = max(most, n[t]);
         }
@@ -2668,13 +2668,13 @@ constexpr uint32_t kRankAlone = 2048;
 // with the cell's neighbourhood staged in LDS and the state in HBM; kMem says
 // where the cell lists are (kMemTeam: in LDS, where they fit; kMemCrew: in the
 // buffer).  With kCellWaves each of some of its waves takes a cell instead (two
-// kernels: one with both has 10 % slower trials, from spilled registers).  One launch
-// can advance several systems: slot i owns workgroups
-// [first_block, first_block + n_blocks) and runs n_sweeps sweeps; the
-// workgroups of a system synchronise among themselves (sys_sync), so systems
-// of one launch run at their own pace.
-template <typename Real, int kMem, bool kCellWaves>
-__global__ void __launch_bounds__(kThreads) k_spread(const SpreadSlot* __restrict__ slots,
+// kernels: one with both has 10 % slower trials, from spilled registers), in
+// workgroups of kThr threads (see cell_threads).  One launch can advance several
+// systems: slot i owns workgroups [first_block, first_block + n_blocks) and runs
+// n_sweeps sweeps; the workgroups of a system synchronise among themselves
+// (sys_sync), so systems of one launch run at their own pace.
+template <typename Real, int kMem, bool kCellWaves, int kThr>
+__global__ void __launch_bounds__(kThr) k_spread(const SpreadSlot* __restrict__ slots,
                                                      uint32_t n_slots, SpreadSlot one)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -2732,8 +2732,8 @@ __global__ void __launch_bounds__(kThreads) k_spread(const SpreadSlot* __restric
     }
     // this workgroup's molecules: an equal share
     const uint32_t m0 = (uint32_t)((uint64_t)M * bid / nblk), m1 = (uint32_t)((uint64_t)M * (bid + 1u) / nblk);
-    const uint32_t gtid = bid * kThreads + tid, GT = nblk * kThreads;
-    const uint32_t gw = bid * kWaves + wave, NW = nblk * kWaves;
+    const uint32_t gtid = bid * kThr + tid, GT = nblk * kThr;
+    const uint32_t gw = bid * (kThr / 64) + wave, NW = nblk * (kThr / 64);
     const int k = (int)C.k, nc = (int)C.nc, na = nc / k;
     const uint32_t nact = (uint32_t)(na * na * na);
     const int ncol = k * k * k;
@@ -2747,7 +2747,7 @@ __global__ void __launch_bounds__(kThreads) k_spread(const SpreadSlot* __restric
         *bflag = 0u;
     }
     __syncthreads();
-    for (uint32_t m = m0 + tid; m < m1; m += kThreads) store_sites_from_quat(C, m);
+    for (uint32_t m = m0 + tid; m < m1; m += kThr) store_sites_from_quat(C, m);
     for (uint32_t c = gtid; c < 2 * ncell; c += GT) agent_store(&cnt[c], 0u);
     Global<uint32_t>* done = cnt;  // (kMemTeam) the last sweep of the launch each cell has had, from 1
     const CellDeps deps = cell_deps(C);
@@ -2768,8 +2768,8 @@ __global__ void __launch_bounds__(kThreads) k_spread(const SpreadSlot* __restric
         // cell of every molecule, counts, proposals
         // (the proposals through LDS, so that they leave in whole lines: as
         // single words past the caches they took 20 us at 27000 molecules)
-        for (uint32_t b0 = m0; b0 < m1; b0 += kThreads) {
-            const uint32_t m = b0 + tid, n = min((uint32_t)kThreads, m1 - b0);
+        for (uint32_t b0 = m0; b0 < m1; b0 += kThr) {
+            const uint32_t m = b0 + tid, n = min((uint32_t)kThr, m1 - b0);
             Lds<PropRec>* out = (Lds<PropRec>*)smem;
             if (m < m1) {
                 const int ix = cell_axis(agent_load(&C.rec[m].c[0]), hx, C.L, C.w, nc);
@@ -2785,50 +2785,50 @@ __global__ void __launch_bounds__(kThreads) k_spread(const SpreadSlot* __restric
             __syncthreads();
             const __amdgpu_buffer_rsrc_t pb = agent_buffer((const void*)props, M * sizeof(PropRec));
             constexpr uint32_t kW = sizeof(PropRec) / sizeof(Words);
-            for (uint32_t i = tid; i < kW * n; i += kThreads)
+            for (uint32_t i = tid; i < kW * n; i += kThr)
                 agent_put_words(pb, b0 * (uint32_t)sizeof(PropRec) + 16u * i, ((Lds<Words>*)smem)[i]);
             __syncthreads();
         }
         if (!sys_sync<kFenced>(B, &st->fault, bflag)) return;
         if constexpr (kMem == kMemTeam) {
             Lds<uint16_t>* tmp = (Lds<uint16_t>*)smem;
-            team_fill(C, tmp, (uint32_t*)(C.misc + 8));
+            team_fill<kThr>(C, tmp, (uint32_t*)(C.misc + 8));
             Global<uint16_t>* gl = (Global<uint16_t>*)Dp->g_list;
             const bool shared = nblk > 1 && M > kRankAlone;
             if (shared) {
                 // each workgroup ranks the molecules of its share of the cells
                 const uint32_t c0 = (uint32_t)((uint64_t)ncell * bid / nblk),
                                c1 = (uint32_t)((uint64_t)ncell * (bid + 1u) / nblk);
-                team_rank(C, tmp, uniform(C.cellb[c0]), uniform(C.cellb[c1]),
+                team_rank<kThr>(C, tmp, uniform(C.cellb[c0]), uniform(C.cellb[c1]),
                           [&](uint32_t at, uint16_t m) { agent_store(gl + at, m); });
                 if (!sys_sync<kFenced>(B, &st->fault, bflag)) return;
                 using C8 = uint16_t __attribute__((ext_vector_type(8)));
                 const __amdgpu_buffer_rsrc_t gb = agent_buffer((const void*)gl, M * sizeof(uint16_t));
-                for (uint32_t i = tid; i < M / 8u; i += kThreads) {
+                for (uint32_t i = tid; i < M / 8u; i += kThr) {
                     const C8 v = __builtin_bit_cast(C8, agent_words(gb, 16u * i));
 #pragma unroll
                     for (int t = 0; t < 8; ++t) C.list[8u * i + t] = v[t];
                 }
-                for (uint32_t i = M / 8u * 8u + tid; i < M; i += kThreads) C.list[i] = agent_load(gl + i);
+                for (uint32_t i = M / 8u * 8u + tid; i < M; i += kThr) C.list[i] = agent_load(gl + i);
             } else {
-                team_rank(C, tmp, 0u, M, [&](uint32_t at, uint16_t m) { C.list[at] = m; });
+                team_rank<kThr>(C, tmp, 0u, M, [&](uint32_t at, uint16_t m) { C.list[at] = m; });
             }
             __syncthreads();
             if (it + 1 == sl.n_sweeps) {  // for a scheduled re-sum after the launch
                 Global<uint32_t>* gc = (Global<uint32_t>*)Dp->g_cell;
-                for (uint32_t c = bid * kThreads + tid; c <= ncell; c += nblk * kThreads) gc[c] = C.cellb[c];
+                for (uint32_t c = bid * kThr + tid; c <= ncell; c += nblk * kThr) gc[c] = C.cellb[c];
                 if (!shared)
-                    for (uint32_t i = bid * kThreads + tid; i < M; i += nblk * kThreads) gl[i] = C.list[i];
+                    for (uint32_t i = bid * kThr + tid; i < M; i += nblk * kThr) gl[i] = C.list[i];
             }
         } else {
             // cell starts (exclusive scan of the counts); counts cleared for the
             // next sweep
             if (bid == 0) {
-                for (uint32_t c = tid; c < ncell; c += kThreads) C.cellb[c] = cnt[c];
+                for (uint32_t c = tid; c < ncell; c += kThr) C.cellb[c] = cnt[c];
                 __syncthreads();
-                block_excl_scan_t<kThreads>((uint32_t*)C.cellb, ncell, (uint32_t*)(C.misc + 8));
+                block_excl_scan_t<kThr>((uint32_t*)C.cellb, ncell, (uint32_t*)(C.misc + 8));
                 if (tid == 0) C.cellb[ncell] = M;
-                for (uint32_t c = tid; c < ncell; c += kThreads) cnt[c] = 0;
+                for (uint32_t c = tid; c < ncell; c += kThr) cnt[c] = 0;
             }
             if (!sys_sync<kFenced>(B, &st->fault, bflag)) return;
             for (uint32_t m = gtid; m < M; m += GT) {
@@ -2872,13 +2872,16 @@ __global__ void __launch_bounds__(kThreads) k_spread(const SpreadSlot* __restric
             return e;
         };
         if constexpr (kCellWaves) {
-            // a cell per wave, each wave at its own pace (see CellDeps)
-            const uint32_t worker = bid + nblk * (uint32_t)wave, workers = nblk * cell_waves;
+            // a cell per wave, each wave at its own pace (see CellDeps); colour by
+            // colour where the cell lists, and with them the words that say which
+            // cells are done, have their place taken (kMemCrew)
+            const uint32_t workers = nblk * cell_waves;
+            const uint32_t first = (uint32_t)wave < cell_waves ? bid + nblk * (uint32_t)wave : nact;
             bool ok = true;
-            for (int col = 0; col < ncol && ok && (uint32_t)wave < cell_waves; ++col) {
+            for (int col = 0; col < ncol && ok; ++col) {
                 int kx, ky, kz;
                 split3((uint32_t)col, k, invk, kx, ky, kz);
-                for (uint32_t a = worker; a < nact; a += workers) {
+                for (uint32_t a = first; a < nact; a += workers) {
                     int cx, cy, cz;
                     split3(a, na, inva, cx, cy, cz);
                     cx = kx + k * cx; cy = ky + k * cy; cz = kz + k * cz;
@@ -2890,10 +2893,12 @@ __global__ void __launch_bounds__(kThreads) k_spread(const SpreadSlot* __restric
                         const double by0 = hy + ((double)cy + 0.5) * C.w;
                         const double bz0 = hz + ((double)cz + 0.5) * C.w;
                         const Segments sg = stencil_segments(C, rows, cx, cy, cz, W.seglo, W.segoff);
-                        uint32_t dep0, dep1;
-                        cell_waits(C, deps, col, cx, cy, cz, kx, ky, kz, dep0, dep1);
-                        ok = wave_cells_done(done, dep0, dep1, (uint32_t)it + 1u, B.polls, &st->fault);
-                        if (!ok) break;
+                        if constexpr (kMem == kMemTeam) {
+                            uint32_t dep0, dep1;
+                            cell_waits(C, deps, col, cx, cy, cz, kx, ky, kz, dep0, dep1);
+                            ok = wave_cells_done(done, dep0, dep1, (uint32_t)it + 1u, B.polls, &st->fault);
+                            if (!ok) break;
+                        }
                         bool overflow;
                         const uint32_t ns = gather_wave(C, P, sg, bx0, by0, bz0, cbeg, ccnt, recs, W, S, overflow);
                         const NearRegs nr = near_regs(P, W.near, ns, overflow);
@@ -2906,16 +2911,22 @@ __global__ void __launch_bounds__(kThreads) k_spread(const SpreadSlot* __restric
                                         S.own);
                     }
                     if (lane == 0) agent_store(&C.ecell[cell], wc.e);
-                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // its moves are out before it is done
-                    if (lane == 0) agent_store(&done[cell], (uint32_t)it + 1u);
+                    if constexpr (kMem == kMemTeam) {
+                        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // its moves are out before it is done
+                        if (lane == 0) agent_store(&done[cell], (uint32_t)it + 1u);
+                    }
                 }
+                if constexpr (kMem == kMemCrew)
+                    if (!sys_sync<kFenced>(B, &st->fault, bflag)) return;
             }
-            if (!ok && lane == 0) *bflag = 2u;
             ++sweep;
-            sys_arrive<kFenced>(B);
-            const bool all = *bflag != 2u;
-            __syncthreads();  // (the wait writes the flag)
-            if (!sys_wait<kFenced>(B, &st->fault, bflag) || !all) return;
+            if constexpr (kMem == kMemTeam) {
+                if (!ok && lane == 0) *bflag = 2u;
+                sys_arrive<kFenced>(B);
+                const bool all = *bflag != 2u;
+                __syncthreads();  // (the wait writes the flag)
+                if (!sys_wait<kFenced>(B, &st->fault, bflag) || !all) return;
+            }
         } else {
         Cell e{};
         if (bid < nact) e = take_cell(0, bid);
@@ -2971,7 +2982,7 @@ __global__ void __launch_bounds__(kThreads) k_spread(const SpreadSlot* __restric
     }
 
     // centres and types from the records
-    for (uint32_t m = m0 + tid; m < m1; m += kThreads) {
+    for (uint32_t m = m0 + tid; m < m1; m += kThr) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) C.com[a * M + m] = agent_load(&C.rec[m].c[a]);
         C.types[m] = agent_load(&C.rec[m].types);
@@ -3122,14 +3133,15 @@ template <typename Real, int kMem, bool kCellWaves>
 hipError_t launch_spread_t(const SpreadSlot* dev_slots, uint32_t n_slots, const SpreadSlot& one,
                            uint32_t n_blocks, size_t lds, hipStream_t stream)
 {
+    constexpr int kThr = kCellWaves ? cell_threads(sizeof(Real) == 8, kMem == kMemTeam) : kThreads;
     static size_t configured = 0;
     if (lds > configured) {
-        const hipError_t e = hipFuncSetAttribute((const void*)&k_spread<Real, kMem, kCellWaves>,
+        const hipError_t e = hipFuncSetAttribute((const void*)&k_spread<Real, kMem, kCellWaves, kThr>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         configured = lds;
     }
-    hipLaunchKernelGGL((k_spread<Real, kMem, kCellWaves>), dim3(n_blocks), dim3(kThreads), lds, stream, dev_slots,
+    hipLaunchKernelGGL((k_spread<Real, kMem, kCellWaves, kThr>), dim3(n_blocks), dim3(kThr), lds, stream, dev_slots,
                        n_slots, one);
     return hipGetLastError();
 }
@@ -3140,6 +3152,7 @@ hipError_t launch_spread_m(SpreadMode mode, const SpreadSlot* dev_slots, uint32_
 {
     switch (mode) {
     case kSpreadWaves: return launch_spread_t<Real, kMemTeam, true>(dev_slots, n_slots, one, n_blocks, lds, stream);
+    case kSpreadCrewWaves: return launch_spread_t<Real, kMemCrew, true>(dev_slots, n_slots, one, n_blocks, lds, stream);
     case kSpreadTeam: return launch_spread_t<Real, kMemTeam, false>(dev_slots, n_slots, one, n_blocks, lds, stream);
     default: return launch_spread_t<Real, kMemCrew, false>(dev_slots, n_slots, one, n_blocks, lds, stream);
     }

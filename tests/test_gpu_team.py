@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 def chain(M, T, k, nc, seed, fp32, sweeps, workgroups, **more):
     rng = np.random.default_rng(seed)
     n = int(np.ceil(M ** (1 / 3)))
-    side = (3.0 * M / 1.2) ** (1 / 3)
+    side = (3.0 * M / more.get("density", 1.2)) ** (1 / 3)
     at = np.sort(rng.permutation(n ** 3)[:M])
     com = (np.stack([at % n, (at // n) % n, at // (n * n)], axis=1) + 0.5) * (side / n)
     q = rng.normal(size=(M, 4))
@@ -94,11 +94,18 @@ def test_cells_whose_first_trials_all_exit(fp32):
         assert np.array_equal(o0[f], o1[f]), f
 
 
-def test_lists_beyond_lds():
-    # 40000 molecules: the cell lists do not fit a workgroup's LDS, and the
-    # workgroups build them together in the system's buffer
-    l0, s0, _ = chain(40000, 1.1, 2, 18, 5, True, 2, 1)
-    l1, s1, _ = chain(40000, 1.1, 2, 18, 5, True, 2, 0)
+@pytest.mark.parametrize("M,nc,workgroups,fp32,more", [
+    (40000, 18, 0, True, {}),        # more cells of a colour than workgroups: a cell per wave
+    (40000, 18, 0, False, {}),
+    (40000, 18, 3, True, {}),        # several cells a wave
+    (40000, 12, 0, True, {}),        # 216 cells of a colour: a cell per workgroup
+    (9000, 34, 0, True, dict(density=0.05)),  # it is the cells that are too many, most of them empty
+])
+def test_lists_beyond_lds(M, nc, workgroups, fp32, more):
+    # the cell lists do not fit a workgroup's LDS, and the workgroups build them
+    # together in the system's buffer
+    l0, s0, _ = chain(M, 1.1, 2, nc, 5, fp32, 2, 1, **more)
+    l1, s1, _ = chain(M, 1.1, 2, nc, 5, fp32, 2, workgroups, **more)
     assert np.array_equal(l0["delta_e"], l1["delta_e"]) and np.array_equal(l0["accepted"], l1["accepted"])
     for f in ("com", "quat", "types", "e_acc"):
         assert np.array_equal(s0[f], s1[f]), f
