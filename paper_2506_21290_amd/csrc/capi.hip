@@ -174,9 +174,14 @@ double waves_cycles(uint32_t M, uint32_t k, uint32_t nc, uint32_t nb, uint32_t w
 
 // Initial milliseconds per modelled cycle of the engine classes (one
 // workgroup with the state in LDS, in HBM; the multi-workgroup engine with a cell
-// per workgroup, with a cell per wave), relative to the LDS class; a batch then
-// measures its own.
-constexpr double kCycleRatio[4] = {1.0, 1.0, 1.1, 1.4};
+// per workgroup, with a cell per wave) in FP32 and in FP64, relative to the FP32
+// LDS class; a batch then measures its own.  Measured alone at T = 1.5, 216 - 27000
+// molecules: FP32 LDS 0.84 - 1.05, HBM 0.74 - 0.91, a cell per workgroup 0.7 - 1.1,
+// per wave 0.85 - 1.3; FP64 1.1 - 1.5, 1.1 - 1.4, 1.0 - 1.5, 0.85 - 1.2.  (With one
+// set for both, 1.0, 1.0, 1.1, 1.4, a batch never tried what it took for slow: 100
+// FP64 systems of 2197 molecules stayed on one workgroup each, 29 ms for 20 sweeps,
+// 20 on two.)
+constexpr double kCycleRatio[2][4] = {{1.0, 0.85, 1.0, 1.1}, {1.4, 1.25, 1.35, 1.1}};
 
 double Geometry::spread_cycles(uint32_t M, uint32_t nb, bool waves) const
 {
@@ -294,11 +299,19 @@ int geometry(const mc_params* p, Geometry* g)
         } else {
             const uint32_t na = nc / k, nact = na * na * na;
             const uint32_t most = p->workgroups ? std::min(p->workgroups, maxb) : maxb;
+            const double* ratio = kCycleRatio[fp64];
             g->team_blocks = std::min(nact, most);
             g->team = !g->resident || (p->workgroups >= 2 && g->team_blocks >= 2) ||
-                      spread_pays(*g, p->n_molecules, g->team_blocks, false, kCycleRatio[0], kCycleRatio[2]);
-            if (g->wave_fit && g->spread_cycles(p->n_molecules, g->team_blocks, true) <
-                                   g->spread_cycles(p->n_molecules, g->team_blocks, false))
+                      spread_pays(*g, p->n_molecules, g->team_blocks, false, ratio[0], ratio[2]);
+            // With several cells for each workgroup of a colour, a cell per wave
+            // where that is modelled less than 15 % slower: its time hardly
+            // depends on how many trials are accepted, that of a cell per
+            // workgroup does (27000 molecules on 256, FP32: T = 0.75 214 and 217 us
+            // a sweep, T = 3 235 and 217, steps a tenth as long 296 and 225; FP64
+            // 306 - 398 and 239 - 245).
+            const double margin = nact > g->team_blocks ? 0.85 : 1.0;
+            if (g->wave_fit && margin * ratio[3] * g->spread_cycles(p->n_molecules, g->team_blocks, true) <
+                                   ratio[2] * g->spread_cycles(p->n_molecules, g->team_blocks, false))
                 g->team_waves = std::min(g->wave_fit, (nact + g->team_blocks - 1) / g->team_blocks);
         }
     }
@@ -1324,7 +1337,7 @@ int mc_batch_create(uint32_t max_slots, uint32_t precision, void* device_buf, si
     b->wg_limit = 0;
     b->turn = 0;
     for (int c = 0; c < 4; ++c) {
-        b->ms_per_cycle[c] = ms_per_model_cycle() * kCycleRatio[c];
+        b->ms_per_cycle[c] = ms_per_model_cycle() * kCycleRatio[precision == MC_FP64][c];
         b->pred[c] = 0.0;
         b->t_beg[c] = b->t_end[c] = nullptr;
     }
