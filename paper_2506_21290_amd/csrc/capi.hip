@@ -1550,59 +1550,85 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
                 }
             }
         }
-        std::vector<uint32_t> pick(active.size(), 0), best;
+        std::vector<uint32_t> pick(active.size(), 0), narrow(active.size(), 0), best, order;
         std::vector<double> times;
+        uint32_t room = 0, best_room = 0;  // for the systems on one workgroup with their state in LDS
         // whether all can end by T, with the options into pick
         auto fits = [&](double T) {
+            // each system's option of the least workgroups times time, and where
+            // those are too many for the device, the narrowest for those that give
+            // back most
+            uint32_t count[3] = {0, 0, 0};  // a cell per workgroup, per wave, one with the state in HBM
             double area = 0.0;
-            uint32_t held = 0, hbm = 0;
-            times.clear();
+            auto add = [&](size_t x, uint32_t o, int sign) {
+                const Option& p = opts[x][o];
+                if (p.nb) count[(int)p.wave] += (uint32_t)(sign * (int)p.nb);
+                else if (b->sys[active[x]]->g.resident) area += sign * p.time;
+                else count[2] += (uint32_t)sign;
+            };
+            order.clear();
             for (size_t x = 0; x < active.size(); ++x) {
                 double least = std::numeric_limits<double>::infinity();
+                uint32_t fewest = 0;
                 for (uint32_t o = 0; o < opts[x].size(); ++o) {
                     const Option& p = opts[x][o];
-                    const double a = p.time * std::max(p.nb, 1u);
-                    if (p.time <= T && a < least) {
+                    if (p.time > T) continue;
+                    const uint32_t n = std::max(p.nb, 1u);
+                    const double a = p.time * n;
+                    if (a < least) {
                         least = a;
                         pick[x] = o;
                     }
+                    if (!fewest || n < fewest) {
+                        fewest = n;
+                        narrow[x] = o;
+                    }
                 }
-                if (least == std::numeric_limits<double>::infinity()) return false;
-                const Option& p = opts[x][pick[x]];
-                if (p.nb) held += p.nb;
-                else if (b->sys[active[x]]->g.resident) {
-                    area += p.time;
-                    times.push_back(p.time);
-                } else {
-                    ++hbm;
-                }
+                if (!fewest) return false;
+                add(x, pick[x], 1);
+                if (narrow[x] != pick[x]) order.push_back((uint32_t)x);
             }
-            std::sort(times.begin(), times.end(), std::greater<>());
-            const uint32_t room = held + hbm < b->wg_limit ? b->wg_limit - held - hbm : 0u;
-            if (held > b->spread_max || held + hbm > b->wg_limit || area > T * room) return false;
-            return times.empty() || longest_first(times, std::min(room, (uint32_t)times.size()), nullptr) <= 1.001 * T;
+            auto gain = [&](uint32_t x) { return opts[x][pick[x]].nb - std::max(opts[x][narrow[x]].nb, 1u); };
+            std::sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return gain(x) > gain(y); });
+            for (size_t next = 0;;) {
+                const uint32_t held = count[0] + count[1] + count[2];
+                room = held < b->wg_limit ? b->wg_limit - held : 0u;
+                if (held <= b->wg_limit && count[0] + count[1] <= b->spread_max && area <= T * room) {
+                    times.clear();
+                    for (size_t x = 0; x < active.size(); ++x)
+                        if (!opts[x][pick[x]].nb && b->sys[active[x]]->g.resident) times.push_back(opts[x][pick[x]].time);
+                    std::sort(times.begin(), times.end(), std::greater<>());
+                    if (times.empty() ||
+                        longest_first(times, std::min(room, (uint32_t)times.size()), nullptr) <= 1.001 * T)
+                        return true;
+                }
+                if (next == order.size()) return false;
+                const uint32_t x = order[next++];
+                add(x, pick[x], -1);
+                add(x, narrow[x], 1);
+                pick[x] = narrow[x];
+            }
         };
         lo /= (double)b->wg_limit * 16.0;
         if (fits(hi)) {
             best = pick;
+            best_room = room;
             for (int step = 0; step < 16; ++step) {
                 const double T = std::sqrt(lo * hi);
                 if (fits(T)) {
                     hi = T;
                     best = pick;
+                    best_room = room;
                 } else {
                     lo = T;
                 }
             }
-            lds_blocks = b->wg_limit;
+            lds_blocks = best_room;
             for (size_t x = 0; x < active.size(); ++x) {
                 const Option& p = opts[x][best[x]];
                 nblk[active[x]] = p.nb;
                 by_wave[active[x]] = p.wave;
-                if (p.nb || !b->sys[active[x]]->g.resident) lds_blocks -= std::max(p.nb, 1u);
             }
-        } else {
-            lds_blocks = S;
         }
     }
     // Time slices: the spare compute units go to the systems that would otherwise finish

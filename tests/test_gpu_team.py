@@ -152,6 +152,43 @@ def test_batch_of_short_and_long_systems(fp32, limit):
     b.close()
 
 
+@pytest.mark.parametrize("fp32", [False, True])
+@pytest.mark.parametrize("limit", [24, 40, 0])
+def test_batch_too_wide_for_its_least_work(fp32, limit):
+    # each of these systems takes the least work on several workgroups, and all
+    # of them more than the limit: some keep fewer, and each ends as it does alone
+    sizes = [(2197, 2, 6), (1728, 2, 6), (1000, 2, 4)] * 8
+
+    def system(i, M, k, nc, **kw):
+        p = flipmc.mc_params_default(n_molecules=M, temperature=1.3, colours_per_axis=k, cells_per_side=nc, seed=i % 3,
+                                     precision=flipmc.MC_FP32_DE if fp32 else flipmc.MC_FP64, gofr_interval=0)
+        return flipmc.System(p, **kw)
+
+    alone = []
+    for i, (M, k, nc) in enumerate(sizes[:3]):
+        s = system(i, M, k, nc)
+        s.sweep(6)
+        alone.append(s.get_state())
+        s.close()
+    b = flipmc.Batch(len(sizes), flipmc.MC_FP32_DE if fp32 else flipmc.MC_FP64)
+    b.set_workgroups(limit)
+    systems = [system(i, M, k, nc, stream=b.stream) for i, (M, k, nc) in enumerate(sizes)]
+    for s in systems:
+        b.add(s, 6)
+    left = len(systems)
+    for _ in range(100):
+        b.run(0)
+        left -= len(b.poll())
+        if not left:
+            break
+    assert left == 0
+    for i, s in enumerate(systems):
+        st = s.get_state()
+        for f in ("com", "quat", "types", "e_acc", "sweep"):
+            assert np.array_equal(st[f], alone[i % 3][f]), f
+    b.close()
+
+
 def test_time_slices_of_every_engine_run_beside_each_other():
     # a time slice has at most three launches, one per stream: with systems on
     # one HBM workgroup, those with several workgroups take one way, and each
