@@ -164,12 +164,15 @@ double team_cycles(uint32_t M, uint32_t k, uint32_t nc, uint32_t nb)
 }
 
 // With a cell per wave on nb workgroups of `waves` such waves: longer, but at a
-// quarter of the work, so a full device moves more molecules.
+// quarter of the work, so a full device moves more molecules.  With at most a
+// wave on each SIMD a round is 7 % shorter (2197 molecules, 27 cells of a colour:
+// 290 us a sweep on 4 workgroups, 271 on 7).
 double waves_cycles(uint32_t M, uint32_t k, uint32_t nc, uint32_t nb, uint32_t waves)
 {
     const double per_cell = std::max(1.0, (double)M / ((double)nc * nc * nc));
-    const double rounds = std::ceil(std::pow((double)(nc / k), 3.0) / (nb * waves)), colours = (double)k * k * k;
-    return colours * (rounds * (9000.0 + 4800.0 * per_cell) + 8000.0) + 45000.0;
+    const double cells = std::pow((double)(nc / k), 3.0) / nb;  // of a workgroup
+    const double rounds = std::ceil(cells / waves), colours = (double)k * k * k, pace = cells <= 4.0 ? 0.93 : 1.0;
+    return colours * (rounds * (9000.0 + 4800.0 * per_cell) * pace + 8000.0) + 45000.0;
 }
 
 // Initial milliseconds per modelled cycle of the engine classes (one
@@ -181,7 +184,7 @@ double waves_cycles(uint32_t M, uint32_t k, uint32_t nc, uint32_t nb, uint32_t w
 // set for both, 1.0, 1.0, 1.1, 1.4, a batch never tried what it took for slow: 100
 // FP64 systems of 2197 molecules stayed on one workgroup each, 29 ms for 20 sweeps,
 // 20 on two.)
-constexpr double kCycleRatio[2][4] = {{1.0, 0.85, 1.0, 1.1}, {1.4, 1.25, 1.35, 1.1}};
+constexpr double kCycleRatio[2][4] = {{1.0, 0.85, 1.0, 1.1}, {1.4, 1.25, 1.35, 1.0}};
 
 double Geometry::spread_cycles(uint32_t M, uint32_t nb, bool waves) const
 {
@@ -1541,13 +1544,17 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
                 const uint32_t cells = w ? s->g.wave_fit : 1u;  // of a workgroup at once
                 if (w && cells < 2) continue;
                 uint32_t last = 0;
-                for (uint32_t r = (nact + cells - 1) / cells; r >= 1; r = std::min(r - 1, std::max(r / 2, 8u))) {
-                    const uint32_t nb = std::min(s->g.team_blocks, (nact + cells * r - 1) / (cells * r));
-                    if (nb == last) continue;
+                auto offer = [&](uint32_t n) {
+                    const uint32_t nb = std::min(s->g.team_blocks, n);
+                    if (nb == last) return;
                     last = nb;
                     const double t = rem * s->g.spread_cycles(M, nb, w) * b->ms_per_cycle[w ? 3 : 2];
-                    if (t < 0.8 * one) opts[x].push_back(Option{t, nb, w});
-                }
+                    // (the model is off by about that much, see kCycleRatio)
+                    if (t < 0.9 * one) opts[x].push_back(Option{t, nb, w});
+                };
+                for (uint32_t r = (nact + cells - 1) / cells; r >= 1; r = std::min(r - 1, std::max(r / 2, 8u)))
+                    offer((nact + cells * r - 1) / (cells * r));
+                if (cells > 4u) offer((nact + 3u) / 4u);  // a wave for each SIMD
             }
         }
         // The workgroups of a launch go to the XCDs in turn, whether a compute unit
