@@ -618,6 +618,10 @@ uint64_t next_event(const mc_system* s, bool gofr_only = false)
 }
 
 constexpr uint64_t kMaxSweepsPerLaunch = 1u << 16;
+// Workgroups that share a system are those that find room when the launch starts
+// (join_crew), for the whole launch, so a launch beside other work is kept short:
+// 0.1 s and more of sweeps, against some 20 us for the next launch.
+constexpr uint64_t kCrewSweeps = 1024;
 
 // Zero a system's barrier words with a kernel, not a memset: mc_sweep stays
 // free of memset nodes for callers that capture it into a graph.
@@ -640,7 +644,8 @@ int advance(mc_system* s, uint64_t n)
     one.sys = s->dev;
     while (n > 0) {
         // at most kMaxSweepsPerLaunch sweeps per launch (a bounded kernel time)
-        const uint64_t chunk = std::min<uint64_t>({n, next_event(s) - s->sweep, kMaxSweepsPerLaunch});
+        const uint64_t chunk = std::min<uint64_t>({n, next_event(s) - s->sweep,
+                                                   s->g.team && s->g.team_blocks >= 2 ? kCrewSweeps : kMaxSweepsPerLaunch});
         one.n_sweeps = chunk;
         one.flags = 0;
         TraceRange tr(s->g.team ? "flipmc sweeps: multi-workgroup launch" : "flipmc sweeps: one-workgroup launch");
@@ -1829,7 +1834,7 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
         bool lists[2] = {true, true};  // the cell lists of all systems fit the LDS
         for (uint32_t i : several) {
             mc_system* s = b->sys[i];
-            uint64_t k = std::min<uint64_t>(b->remaining[i], next_event(s) - s->sweep);
+            uint64_t k = std::min<uint64_t>({b->remaining[i], next_event(s) - s->sweep, kCrewSweeps});
             if (k == 0 || (ones_left && stopped[i])) continue;
             const int w = by_wave[i];
             const double unit = s->g.spread_cycles(s->p.n_molecules, nblk[i], w);  // modelled cycles of a sweep

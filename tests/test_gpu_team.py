@@ -42,6 +42,24 @@ def test_engine_names_what_a_sweep_launches(M, k, nc, flags, want):
     assert flipmc.mc_engine(p) == want
 
 
+def test_long_runs_take_several_launches():
+    # the workgroups that share a system are chosen at a launch, which is
+    # therefore bounded; the chain goes on as in one launch
+    p = flipmc.mc_params_default(n_molecules=343, temperature=1.5, colours_per_axis=2, cells_per_side=4, workgroups=8,
+                                 precision=flipmc.MC_FP32_DE, resum_interval=0, gofr_interval=0)
+    a, b = flipmc.System(p), flipmc.System(p)
+    a.sweep(2000)
+    b.sweep(2000)
+    a.timing_enable(True)
+    a.sweep(2990)  # no event before sweep 5000
+    assert a.timing_read()["sweep_launches"] == 3
+    for _ in range(13):
+        b.sweep(230)
+    sa, sb = a.get_state(), b.get_state()
+    for f in ("com", "quat", "types", "e_acc", "sweep"):
+        assert np.array_equal(sa[f], sb[f]), f
+
+
 @pytest.mark.parametrize("M,k,nc,cells", [(1000, 2, 4, 8), (2197, 2, 6, 27)])
 def test_workgroups_is_a_limit(M, k, nc, cells):
     for n in (2, 3, cells - 1, cells, cells + 1):
