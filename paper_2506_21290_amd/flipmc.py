@@ -11,6 +11,7 @@ import atexit
 import ctypes as C
 import math
 import os
+import threading
 import weakref
 
 import numpy as np
@@ -504,16 +505,23 @@ class System:
 # in the end put one in the hardware queue of the batch's stream (streams share
 # four), whose launches then follow one another: 50 sweeps of 24 systems of
 # 125 - 8000 molecules took 21 - 24 ms in every second batch, 13.5 otherwise.
+# A program with more main streams than MAX_SIDE_PAIRS gives the oldest pair back
+# (the batches that have it keep it).
+MAX_SIDE_PAIRS = 16
 _side_streams = {}
+_side_lock = threading.Lock()
 
 
 def _side_pair(main):
     import torch
 
     key = torch.cuda.current_device(), main.value or 0
-    if key not in _side_streams:
-        _side_streams.setdefault(key, (torch.cuda.Stream(), torch.cuda.Stream()))
-    return _side_streams[key]
+    with _side_lock:
+        if key not in _side_streams:
+            while len(_side_streams) >= MAX_SIDE_PAIRS:
+                del _side_streams[next(iter(_side_streams))]
+            _side_streams[key] = torch.cuda.Stream(), torch.cuda.Stream()
+        return _side_streams[key]
 
 
 class Batch:
@@ -529,8 +537,10 @@ class Batch:
         # the multi-workgroup launches overlap the others on a second stream,
         # and the one-workgroup launch of systems with their state in HBM the
         # LDS class's on a third (default priority, like every stream here)
-        self.aux_stream = aux_stream if aux_stream is not None else _side_pair(self._stream_handle)[0]
-        self.hbm_stream = hbm_stream if hbm_stream is not None else _side_pair(self._stream_handle)[1]
+        if aux_stream is None or hbm_stream is None:
+            pair = _side_pair(self._stream_handle)
+        self.aux_stream = aux_stream if aux_stream is not None else pair[0]
+        self.hbm_stream = hbm_stream if hbm_stream is not None else pair[1]
         self._lib = lib()
         n = C.c_size_t()
         _check(self._lib.mc_batch_required_bytes(int(max_slots), C.byref(n)))

@@ -147,3 +147,19 @@ def test_batch_setters_reject_a_null_batch_without_a_device():
     assert L.mc_batch_set_workgroups(None, 8) == flipmc.MC_EINVAL
     assert L.mc_batch_set_hbm_stream(None, None) == flipmc.MC_EINVAL
     assert b"null batch" in L.mc_last_error()
+
+
+def test_side_streams_of_batches_are_bounded(monkeypatch):
+    # a pair per main stream, shared by the batches on it, the oldest given back
+    torch = pytest.importorskip("torch")
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "Stream", object)
+    monkeypatch.setattr(flipmc, "_side_streams", {})
+    first = flipmc._side_pair(C.c_void_p(1))
+    assert flipmc._side_pair(C.c_void_p(1)) is first
+    pairs = [flipmc._side_pair(C.c_void_p(1 + i)) for i in range(flipmc.MAX_SIDE_PAIRS)]
+    assert pairs[0] is first and len({x for p in pairs for x in p}) == 2 * flipmc.MAX_SIDE_PAIRS
+    for i in range(100):
+        flipmc._side_pair(C.c_void_p(1000 + i))
+    assert len(flipmc._side_streams) == flipmc.MAX_SIDE_PAIRS
+    assert flipmc._side_pair(C.c_void_p(1)) is not first
