@@ -1754,9 +1754,13 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
         Slot ev{};
         ev.sys = s->dev;
         ev.flags = f;
-        // (many small systems fill the device with a workgroup each)
+        // (many small systems fill the device with a workgroup each: 20 sweeps with
+        // five g(r) frames of 128 systems of 300, 1000 and 1900 molecules take 6.1,
+        // 12.4 and 24.5 ms so, 6.0, 10.5 and 19.0 on many workgroups; of 160, 6.3,
+        // 12.5 and 30.5, and 6.8, 11.7 and 27.6; of 224, 6.4, 12.7 and 31.5, and
+        // 7.4, 13.5 and 32.2)
         const uint32_t M = s->p.n_molecules;
-        if ((M >= kInlineBelow || active.size() <= 32) && event_blocks(M) > 1 && (f & kOverPairs)) {
+        if ((M >= kInlineBelow || active.size() <= 128) && event_blocks(M) > 1 && (f & kOverPairs)) {
             parts.emplace_back(s, f);
             (void)part_slot(s, f, 0u, &ev.pad);
             ev.flags = f | kFlagParts;

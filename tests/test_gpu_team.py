@@ -207,6 +207,40 @@ def test_batch_too_wide_for_its_least_work(fp32, limit):
     b.close()
 
 
+@pytest.mark.parametrize("count", [40, 129])
+def test_frames_of_many_systems(count):
+    # up to 128 systems take their g(r) frames on many workgroups each, more on
+    # one: the same counts as alone
+    def system(i, **kw):
+        p = flipmc.mc_params_default(n_molecules=343, temperature=1.3, colours_per_axis=2, cells_per_side=4, seed=i % 3,
+                                     precision=flipmc.MC_FP32_DE, gofr_interval=3, resum_interval=0)
+        return flipmc.System(p, **kw)
+
+    alone = []
+    for i in range(3):
+        s = system(i)
+        s.sweep(7)
+        alone.append(s.observables())
+        s.close()
+    b = flipmc.Batch(count, flipmc.MC_FP32_DE)
+    systems = [system(i, stream=b.stream) for i in range(count)]
+    for s in systems:
+        b.add(s, 7)
+    left = count
+    for _ in range(20):
+        b.run(0)
+        left -= len(b.poll())
+        if not left:
+            break
+    assert left == 0
+    for i, s in enumerate(systems):
+        o = s.observables()
+        assert o["n_gofr_frames"] == 2
+        for f in ("gofr_all", "gofr_inter", "e_acc", "accepts"):
+            assert np.array_equal(o[f], alone[i % 3][f]), f
+    b.close()
+
+
 def test_time_slices_of_every_engine_run_beside_each_other():
     # a time slice has at most three launches, one per stream: with systems on
     # one HBM workgroup, those with several workgroups take one way, and each
