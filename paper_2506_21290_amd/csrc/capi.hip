@@ -356,8 +356,9 @@ double longest_first(const std::vector<double>& times, uint32_t n, std::vector<u
 }
 
 // Workgroups of the multi-workgroup event kernel for M molecules, 1 =
-// single-workgroup events.  256 molecules are 20 units: below that the extra
-// launch takes longer than it saves.
+// single-workgroup events.  256 molecules are 16 units; a total energy of 200
+// takes 44 us on one workgroup and 43 on several, of 255 49 and 45, of 300 61 and
+// 45, of 1000 207 and 39.
 uint32_t event_blocks(uint32_t M)
 {
     if (M < 256) return 1;

@@ -32,9 +32,9 @@ constexpr uint32_t kEventStage = 2047;
 constexpr size_t kEventStageBytes = size_t(kEventStage) * (7 * sizeof(double) + sizeof(uint32_t));
 
 // The units of the event work over all pairs of M molecules (a wave's each):
-// blocks of 64 molecules, each against `splits` ranges of the other half.  About
-// 2048 in all, a wave for every two SIMDs of the device, and ranges of 32 pairs
-// or more.
+// blocks of 64 molecules, each against `splits` ranges of the other half, of 32
+// molecules or more.  That allows (M / 64)^2 units: 16 of 256 molecules, 225 of
+// 1000; from 2900 on there are about 2048, two waves for each of the 1024 SIMDs.
 struct EventUnits {
     uint32_t blocks, splits;
     __host__ __device__ uint32_t count() const { return blocks * splits; }

@@ -750,11 +750,14 @@ __device__ __forceinline__ void fx_eval_rows(const FxK& K, const FxView<kRes>& V
 }
 
 // dE of the attempt on atom a, summed over the atoms of the 27 cells in stencil
-// order by the whole wave, a lane each, as E_acc has always been summed.  An
-// overlapping start has moves that change its energy by 1e10 and more; the last
-// bits of each stay in E_acc, up to 1e6 in all, until the next re-sum, so for
-// large moves E_acc takes the sum that depends on nothing but the state and not
-// the one over the rows.  (Below kFxLarge the two differ by less than 1e-11.)
+// order by the whole wave, a lane each: the order in which E_acc was summed
+// before attempts had rows.  An overlapping start has moves that change its
+// energy by 1e10 and more; the last bits of their terms, up to 1e6 in all, stay in
+// E_acc until the next re-sum, and with this order E_acc of such a start keeps the
+// values it had.  Neither order is the more exact one, and this second evaluation
+// makes the sweeps of an overlapping start 3 % longer.  Only the net change is
+// tested: terms of 1e10 that cancel to less than kFxLarge enter by the sum over
+// the rows, and the two sums then differ by some 1e-6.
 constexpr double kFxLarge = 1e4;
 
 __device__ __forceinline__ bool fx_in_stencil(double x, double h, uint32_t c, const FxDev& D, double m)
@@ -875,9 +878,9 @@ __device__ __attribute__((noinline)) double fx_stencil_sum(const FxDev* Dp, type
 // dE does not depend on how the attempts were grouped.  With 7 - 30 % accepted
 // a cell of 6 atoms takes one to three evaluations of 2 us.  The chain of
 // evaluations bounds the kernel (a system runs on one compute unit): a sweep
-// of 1000 triangles at T = 0.75 takes 0.78 ms, of 333 tetrahedra 1.41 ms (by
+// of 1000 triangles at T = 0.75 takes 0.78 ms, of 333 tetrahedra 1.38 ms (by
 // the whole wave, one attempt after another over the 27 cells' atoms, 2.80 and
-// 7.4 ms; two rows per 16 lanes against one 0.78 and 1.22 ms).
+// 7.4 ms; with one row per 16 lanes instead of two 0.78 and 1.61 ms).
 template <bool kLog, bool kRes>
 __device__ __forceinline__ void fx_run_rows(const FxDev& Dv, const FxK& K, const FxView<kRes>& V, uint32_t cnt, uint32_t at,
                                             const FxProp& pr, uint64_t sweep, const double h[3], uint32_t cell,

@@ -160,7 +160,7 @@ __device__ __forceinline__ uint32_t dpp_move_u(uint32_t v)
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, kRowMask, 0xf, true);
 }
 
-// Wave-wide OR and maximum in the same steps; every lane gets them.
+// Wave-wide OR in the same steps; every lane gets it.
 __device__ __forceinline__ uint32_t wave_or_dpp(uint32_t v)
 {
     v |= dpp_move_u<0x111, 0xf>(v);
@@ -169,17 +169,6 @@ __device__ __forceinline__ uint32_t wave_or_dpp(uint32_t v)
     v |= dpp_move_u<0x118, 0xf>(v);
     v |= dpp_move_u<0x142, 0xa>(v);
     v |= dpp_move_u<0x143, 0xc>(v);
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
-
-__device__ __forceinline__ uint32_t wave_max_dpp(uint32_t v)
-{
-    v = max(v, dpp_move_u<0x111, 0xf>(v));
-    v = max(v, dpp_move_u<0x112, 0xf>(v));
-    v = max(v, dpp_move_u<0x114, 0xf>(v));
-    v = max(v, dpp_move_u<0x118, 0xf>(v));
-    v = max(v, dpp_move_u<0x142, 0xa>(v));
-    v = max(v, dpp_move_u<0x143, 0xc>(v));
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
