@@ -633,13 +633,15 @@ def bench_c3(args, flipmc, torch):
         "launches": launches,
         "pair_interactions_per_s": terms / (ms / 1e3),
         "near_overflows": overflows,
-        # the batch's run is one launch of the one-workgroup sweep kernel (all
-        # 256 replicas, re-sums and C_2 samples inside it): its time is the
-        # timed region, measured with events on the batch's stream
+        # the batch's run puts most replicas one after another on workgroups of
+        # the one-workgroup sweep kernel (one launch, re-sums and C_2 samples
+        # inside it) and the larger ones beside them on two workgroups each, a
+        # cell per wave; the launch of the former lasts the whole run, whose time
+        # is measured with events on the batch's stream
         "roofline": {"bound": "alu", "achieved": achieved, "peak": PEAK_TFLOPS["f32"],
                      "unit": "TFLOP/s", "frac": achieved / PEAK_TFLOPS["f32"],
                      "traffic": measured_traffic("k_sweeps_c3"),
-                     "kernel": "k_sweeps<float, resident, inline events>",
+                     "kernel": "k_sweeps<float, resident, inline events> beside k_spread<float>, a cell per wave",
                      "cus_used": min(ncu, len(jobs)),
                      "valu_busy": measured_counters("k_sweeps_c3").get("valu_busy"),
                      "avg_launch_ms": ms / max(1, launches),
