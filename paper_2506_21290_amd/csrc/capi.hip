@@ -142,7 +142,8 @@ double cost_estimate(uint32_t M, double L, double reach, uint32_t k, uint32_t nc
 
 // Cycles of a sweep on one workgroup, for the sizes of time slices and the
 // choice of the engine.  Fitted to 216 (k = 3, n_c = 6), 512 and 1000 (k = 2,
-// n_c = 4) and 1728 (n_c = 6) molecules in LDS: 195, 180, 313 and 565 us.
+// n_c = 4) and 1728 (n_c = 6) molecules in LDS: 195, 180, 313 and 565 us (by now
+// 185, 171, 302 and 549).
 double sweep_cycles(uint32_t M, uint32_t k, uint32_t nc)
 {
     const double per_cell = std::max(1.0, (double)M / ((double)nc * nc * nc));
@@ -330,7 +331,7 @@ double slice_time(uint64_t max_moves)
 }
 
 // Milliseconds per modelled cycle on an idle device: a sweep of the
-// 1000-molecule reference (k = 2, n_c = 4) takes about 0.31 ms on one
+// 1000-molecule reference (k = 2, n_c = 4) takes about 0.3 ms on one
 // workgroup with the state in LDS.
 double ms_per_model_cycle()
 {
@@ -682,8 +683,9 @@ int advance(mc_system* s, uint64_t n)
     return MC_OK;
 }
 
-// A copy of the system's buffer from its statistics up to byte `to` (a system of 1000 molecules took 70 us for its configuration in
-// four copies, each with a wait of its own).
+// A copy of the system's buffer from its statistics up to byte `to` (a system of
+// 1000 molecules took 70 us for its configuration in four copies, each with a wait
+// of its own).
 int read_block(mc_system* s, size_t to, std::vector<uint8_t>* out, Stats* st)
 {
     if (int rc = sync_owner(s)) return rc;
@@ -1493,7 +1495,7 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
     }
     // every launch of a run is sized to the time the reference system takes
     // for max_moves_per_slot moves
-    const double t_slice = slice_time(max_moves_per_slot) * ms_per_model_cycle();
+    double t_slice = slice_time(max_moves_per_slot) * ms_per_model_cycle();
     double pred[4] = {0.0, 0.0, 0.0, 0.0};
 
     // Engine of every system for this run.  Each system needs one workgroup;
@@ -1520,9 +1522,9 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
     // way on several that costs the fewest workgroups times time; the systems
     // on one workgroup with their state in LDS share as many workgroups as their
     // times fill, one after another (a system each left the compute units of the
-    // short ones idle: 256 replicas of 216 - 1728 molecules took 24.4 ms, the
-    // longest of them, with 12.6 ms of work per compute unit; 50 sweeps of 24
-    // systems of 125 - 8000 molecules take 13.5 ms, 22 ms with the greedy division
+    // short ones idle: 40 sweeps of 256 replicas of 216 - 1728 molecules took 24.4 ms,
+    // the longest of them, with 12.6 ms of work per compute unit; 50 sweeps of 24
+    // systems of 125 - 8000 molecules 22 ms instead of 13, with the greedy division
     // that the time slices below keep, whose lengths come out alike anyway).
     std::vector<uint32_t> nblk(S, 0);
     std::vector<char> by_wave(S, 0);
@@ -1721,9 +1723,10 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
         // in HBM) or missing, a second one would start when the first has ended
         // and double the slice: one job of 125 molecules with a cell per
         // workgroup made slices of 54 ms out of 31 (a stream of 200 jobs:
-        // 2.74e8 moves/s, 3.1 - 3.2e8 with one way).  Then all that have several workgroups have a
-        // cell per wave, and the others stay on their one.  (A system whose cell
-        // lists do not fit LDS has no other way; with one of those both stay.)
+        // 2.74e8 moves/s, 3.1 - 3.2e8 with one way).  Then all that have several
+        // workgroups have a cell per wave, and the others stay on their one.  (A
+        // system whose cell lists do not fit LDS has no other way; with one of
+        // those both stay.)
         bool busy3 = !b->stream3 || b->stream2 == b->stream, movable = true;
         uint32_t by[2] = {0, 0};
         for (uint32_t i : active) {
@@ -1741,6 +1744,17 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
                 if (!by_wave[i]) nblk[i] = 0;
             }
     }
+    // More workgroups than compute units (the device's, not the batch's limit):
+    // they take turns within the run, so each gets its part of the slice, and
+    // what a launch then takes is mostly the others' time and no sample of its
+    // own.  Taken as one, the class whose workgroups started first kept its 31 ms,
+    // and the others' slices shrank to what was left: of 1024 jobs with 256 on the
+    // multi-workgroup engine those in LDS had 3 ms of 46 (a stream of 2000 jobs: the
+    // median job done after 16.6 s).
+    uint32_t wanted = 0;
+    for (uint32_t i : active) wanted += std::max(nblk[i], 1u);
+    const bool crowded = max_moves_per_slot && wanted > b->ncu;
+    if (crowded) t_slice *= (double)b->ncu / (double)wanted;
     uint32_t n[3] = {0, 0, 0};
     size_t lds[2] = {0, 0};
     // the O(M^2) event work of large systems goes to the event kernel over
@@ -1890,7 +1904,7 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
         for (int w = 1; w >= 0; --w) {
             if (by[w].empty()) continue;
             const SpreadMode mode = spread_mode(w, lists[w]);
-            const bool sample = cycles[w] > pred[2 + w];  // the longest slice is the run's sample
+            const bool sample = !crowded && cycles[w] > pred[2 + w];  // the longest slice is the run's sample
             if (sample) HIPCHK(hipEventRecord(b->t_beg[2 + w], st_of[w]));
             HIPCHK(launch_spread(fp64, mode, b->dev_spread[par] + (w ? nt : 0u), (uint32_t)by[w].size(), none, blocks[w],
                                  lists[w] ? need[w] : crew_need[w], st_of[w]));
@@ -1933,7 +1947,7 @@ int mc_batch_run(mc_batch* b, uint64_t max_moves_per_slot, uint32_t* n_launched)
                 HIPCHK(launch_sweeps(fp64, cls == 0, b->dev_slots[par] + cls * S, none,
                                      cls == 0 ? std::min(n[0], lds_blocks) : n[cls], lds[cls], st, true));
                 HIPCHK(hipEventRecord(b->t_end[cls], st));
-                b->pred[cls] = pred[cls];
+                b->pred[cls] = crowded ? 0.0 : pred[cls];
             }
         if (side) {
             HIPCHK(hipEventRecord(b->done3, b->stream3));

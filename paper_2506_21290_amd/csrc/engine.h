@@ -208,6 +208,7 @@ __host__ __device__ inline LdsLayout lds_layout(bool fp64, bool resident, uint32
 // colour, stages the cell's neighbourhood (up to near_cap molecules) in its LDS
 // and its waves share the cell's trials; or each of the first `waves` waves of a
 // workgroup takes and stages a cell of its own.
+
 // Threads of a workgroup whose waves have a cell each.  A wave of 512 threads has
 // 256 registers, of which FP64 trials spill 280 values and FP32 160: 20 sweeps of
 // 20 systems of 8000 molecules take 23.3 ms in FP64 so, 12.3 with half the waves

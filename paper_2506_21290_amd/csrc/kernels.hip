@@ -24,9 +24,9 @@
 //     8 trials of the cell at once; one system, or few, on the whole device.
 // What bounds both is the chain of dependent trials in a cell; a wave issues an
 // instruction about every eighth cycle, a trial has some 550, two waves fill a
-// SIMD.  1000 molecules (T = 0.75, FP32): 313 us a sweep with k_sweeps, 142 with
-// k_spread on 8 compute units; 8000: 121 on 125, 27000: 211 on 256 (212 and 266
-// with a wave per cell on 32 and 128).
+// SIMD.  FP32: 1000 molecules (T = 0.75) 302 us a sweep with k_sweeps, 134 - 140
+// with k_spread on 8 compute units; 8000 (T = 1.1) 2650 on one, 203 with a cell per
+// wave on 32, 123 - 127 on 125; 27000 (T = 2) 225 with a cell per wave on 256.
 //
 // The random numbers are Philox4x32-10 (Salmon, Moraes, Dror & Shaw, SC'11)
 // keyed by the seed and counted by (molecule, sweep low, sweep high, tag), so a

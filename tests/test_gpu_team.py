@@ -1,5 +1,7 @@
 """Workgroups that share a system's sweeps: bitwise what one workgroup does, at
 the edges of the multi-workgroup engine's layouts."""
+import time
+
 import numpy as np
 import pytest
 
@@ -270,6 +272,46 @@ def test_time_slices_of_every_engine_run_beside_each_other():
         st, ref = s.get_state(), alone.get_state()
         for f in ("com", "quat", "types", "e_acc", "sweep"):
             assert np.array_equal(st[f], ref[f]), f
+    b.close()
+
+
+def test_time_slices_of_more_systems_than_compute_units_are_fair():
+    # small systems in LDS and as many large ones, some of which take the
+    # multi-workgroup engine on one workgroup: each gets about the same time,
+    # in sweeps of it alone on one workgroup (the engines differ by 1.5 there and
+    # the cost model by 1.3 either way, so a third counts as the same; where the
+    # launch that started first kept the device it was a tenth)
+    kinds = [(343, 2, 4), (2744, 2, 8)]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+
+    def params(kind, seed):
+        M, k, nc = kinds[kind]
+        return flipmc.mc_params_default(n_molecules=M, temperature=1.5, colours_per_axis=k, cells_per_side=nc, seed=seed,
+                                        precision=flipmc.MC_FP32_DE, resum_interval=0, obs_interval=0,
+                                        gofr_interval=0, workgroups=1)
+
+    alone = []
+    for kind in (0, 1):
+        s = flipmc.System(params(kind, 1))
+        s.sweep(20)
+        s.energy()
+        t0 = time.perf_counter()
+        s.sweep(50)
+        s.energy()
+        alone.append((time.perf_counter() - t0) / 50)
+        s.close()
+    b = flipmc.Batch(2 * cus, flipmc.MC_FP32_DE)
+    systems = []
+    for i in range(2 * cus):
+        p = params(i % 2, i + 1)
+        p.workgroups = 0
+        systems.append(flipmc.System(p, stream=b.stream))
+        b.add(systems[-1], 10**6)
+    for _ in range(24):
+        b.run(100000)
+        b.poll()
+    done = [np.mean([s.get_state()["sweep"] for s in systems[kind::2]]) * alone[kind] for kind in (0, 1)]
+    assert 1 / 3 < done[0] / done[1] < 3, (done, alone)
     b.close()
 
 
