@@ -521,8 +521,10 @@ int mcf_dynamics(const mc_obs* runs, size_t n_runs, uint32_t n_molecules, uint32
  * Systems on one workgroup share one persistent launch per
  * placement class (state in LDS / in HBM; the HBM class beside the LDS
  * class on a third caller stream when mc_batch_set_hbm_stream gives one);
- * systems on the multi-workgroup engine share one launch on the caller's
- * second stream (hip_stream_aux of mc_batch_create).
+ * systems on the multi-workgroup engine share one launch for each way in use (a
+ * cell per workgroup, a cell per wave) on the caller's second stream
+ * (hip_stream_aux of mc_batch_create; the second way beside the first on the
+ * third, where that is free).
  * All engines make the same decisions and sum the energy in the same order,
  * so a system gives bitwise the same results in a batch as alone, whichever
  * engines its runs used. */
@@ -557,7 +559,8 @@ int mc_batch_add(mc_batch* b, mc_system* s, uint64_t n_sweeps, uint32_t* slot);
  * max_moves_per_slot moves on one workgroup: each system's slice is that time
  * over its modelled sweep time on its workgroups, scaled per engine by the time
  * per modelled cycle measured on the batch's earlier launches; at least one
- * sweep.  Slices also stop at each system's re-sum / g(r) / C_2 sweeps, whose
+ * sweep.  With more workgroups than compute units, which then take turns, the
+ * time is divided by the turns.  Slices also stop at each system's re-sum / g(r) / C_2 sweeps, whose
  * work follows in a second launch; a run of all remaining sweeps may enqueue
  * several slices one after another, and systems may stay unfinished at its
  * end.  *n_launched = number of sweep launches enqueued per slice (one per

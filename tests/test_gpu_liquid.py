@@ -155,10 +155,11 @@ def test_batched_systems_match_the_oracle(fp32):
 
 
 def test_replica_batch_launch_sampled_against_the_oracle():
-    # the 256-replica set in the launch the bench times (one batch, FP32 dE,
-    # every replica on its workgroup, re-sums and C_2 samples inside the
-    # sweep kernel), a few sweeps: 8 replicas sampled 2 per size, trial by
-    # trial against the oracle run alone on the same seeds and decomposition
+    # the 256-replica set in the run the bench times (one batch, FP32 dE, all
+    # remaining sweeps: systems in LDS one after another on a workgroup, re-sums
+    # and C_2 samples inside the sweep kernel, beside systems with a cell per
+    # wave), a few sweeps: 8 replicas sampled 2 per size, trial by trial against
+    # the oracle run alone on the same seeds and decomposition
     from paper_2506_21290_amd import workloads
 
     n = 3
