@@ -1262,21 +1262,33 @@ __device__ __forceinline__ NearOne near_one(const PhaseConst& P, const NearEntry
     return r;
 }
 
-// The first entries of the near list in registers (entries lane, lane + 64,
-// ...); longer lists are read again from LDS at each trial.
+// The first entries of the near list (entries lane, lane + 64, ...) are held in
+// registers; longer lists are read again from LDS at each trial.  FP64 trials of
+// k_sweeps with the state in HBM have no registers left: ten of the twelve values
+// came back from scratch memory at each trial, with three waits.  They read the
+// entries from LDS, all at once (2197 molecules on one workgroup 1165 us a sweep
+// held, 1050 so, 1400 803 and 705; with the state in LDS, or on the engine of
+// several workgroups, held is 2 - 6 % faster).
+template <typename Real, int kMem>
+constexpr bool near_held() { return !(sizeof(Real) == 8 && kMem == kMemHbm); }
+
+template <bool kHeld>
 struct NearRegs {
-    NearOne e[kNearSlots];
+    NearOne e[kHeld ? kNearSlots : 1];
     const NearEntry* near;
     uint32_t n;  // entries (0 after an overflow)
 };
 
-__device__ __forceinline__ NearRegs near_regs(const PhaseConst& P, const NearEntry* near, uint32_t nnear, bool overflow)
+template <bool kHeld>
+__device__ __forceinline__ NearRegs<kHeld> near_regs(const PhaseConst& P, const NearEntry* near, uint32_t nnear, bool overflow)
 {
-    NearRegs r;
+    NearRegs<kHeld> r;
     r.n = overflow ? 0u : nnear;
     r.near = near;
+    if constexpr (kHeld) {
 #pragma unroll
-    for (int c = 0; c < kNearSlots; ++c) r.e[c] = near_one(P, near, (uint32_t)__lane_id() + 64u * c, r.n);
+        for (int c = 0; c < kNearSlots; ++c) r.e[c] = near_one(P, near, (uint32_t)__lane_id() + 64u * c, r.n);
+    }
     return r;
 }
 
@@ -1591,7 +1603,7 @@ static_assert(sizeof(TrialSum) == kSumBytes, "evaluated trial");
 // After a near-list overflow every stencil molecule is a candidate.
 template <typename Real, int kMem, typename Vw>
 __device__ __forceinline__ TrialSum eval_trial(const Ctx<Real, kMem>& C, const Vw& V, const PhaseConst& P,
-                                               const TrialHead& T, int i, const NearRegs& nr, bool overflow,
+                                               const TrialHead& T, int i, const NearRegs<near_held<Real, kMem>()>& nr, bool overflow,
                                                const Segments& g, const TrialLds<Real>* tr, const WaveLds<Real>& W)
 {
     const int lane = __lane_id();
@@ -1658,8 +1670,14 @@ __device__ __forceinline__ TrialSum eval_trial(const Ctx<Real, kMem>& C, const V
             if (keep) W.surv[nsurv + rank_below(bm)] = (uint16_t)e.j;
             nsurv += (uint32_t)__popcll(bm);
         };
+        NearOne e[kNearSlots];
 #pragma unroll
-        for (int c = 0; c < kNearSlots; ++c) prune(nr.e[c]);
+        for (int c = 0; c < kNearSlots; ++c) {
+            if constexpr (near_held<Real, kMem>()) e[c] = nr.e[c];
+            else e[c] = near_one(P, nr.near, (uint32_t)lane + 64u * c, nr.n);
+        }
+#pragma unroll
+        for (int c = 0; c < kNearSlots; ++c) prune(e[c]);
         for (uint32_t b = 64u * kNearSlots; b < nr.n; b += 64u)
             prune(near_one(P, nr.near, b + (uint32_t)lane, nr.n));
         wave_lds_sync();  // the record and the survivors
@@ -1764,7 +1782,7 @@ __device__ __forceinline__ void log_trial(const Ctx<Real, kMem>& C, const TrialH
 template <typename Real, int kMem, typename Vw>
 __device__ void cell_trials(const Ctx<Real, kMem>& C, const Vw& V, const Global<PropRec>* props,
                             uint64_t sweep, const PhaseConst& P, uint32_t cbeg, uint32_t ccnt,
-                            double bx0, double by0, double bz0, const NearRegs& nr, bool overflow,
+                            double bx0, double by0, double bz0, const NearRegs<near_held<Real, kMem>()>& nr, bool overflow,
                             const Segments& g, const WaveLds<Real>& W, WaveCount& wc,
                             const Lds<uint16_t>* own_slot = nullptr)
 {
@@ -1849,7 +1867,7 @@ template <bool kStaged, typename Real, int kMem, typename Vw>
 __device__ __forceinline__ void team_trials(const Ctx<Real, kMem>& C, const Vw& V,
                                             const Global<PropRec>* props, uint64_t sweep, const PhaseConst& P,
                                             uint32_t cbeg, uint32_t ccnt, double bx0, double by0, double bz0,
-                                            const NearRegs& nr, bool overflow, const Segments& g, int wave,
+                                            const NearRegs<near_held<Real, kMem>()>& nr, bool overflow, const Segments& g, int wave,
                                             const Lds<uint16_t>* own_slot, const WaveLds<Real>& W, TrialSum* sums,
                                             WaveCount& wc)
 {
@@ -2003,7 +2021,7 @@ __device__ void run_phase(const Ctx<Real, kMem>& C, const Global<PropRec>* props
         const Segments g = stencil_segments(C, rows, cx, cy, cz, W.seglo, W.segoff);
         bool overflow;
         const uint32_t nnear = gather_near(C, P, g, bx0, by0, bz0, cbeg, W, overflow);
-        const NearRegs nr = near_regs(P, W.near, nnear, overflow);
+        const auto nr = near_regs<near_held<Real, kMem>()>(P, W.near, nnear, overflow);
         wc.overflows += overflow ? 1u : 0u;
         wc.e = 0.0;
         cell_trials(C, V, props, sweep, P, cbeg, ccnt, bx0, by0, bz0, nr, overflow, g, W, wc);
@@ -2901,7 +2919,7 @@ __global__ void __launch_bounds__(kThr) k_spread(const SpreadSlot* __restrict__ 
                         }
                         bool overflow;
                         const uint32_t ns = gather_wave(C, P, sg, bx0, by0, bz0, cbeg, ccnt, recs, W, S, overflow);
-                        const NearRegs nr = near_regs(P, W.near, ns, overflow);
+                        const auto nr = near_regs<near_held<Real, kMem>()>(P, W.near, ns, overflow);
                         wc.overflows += overflow ? 1u : 0u;
                         if (overflow)
                             cell_trials(C, RecView<Real>{C.rec, C.misc + 1}, props, sweep, P, cbeg, ccnt, bx0, by0, bz0,
@@ -2940,7 +2958,7 @@ __global__ void __launch_bounds__(kThr) k_spread(const SpreadSlot* __restrict__ 
                     bool overflow;
                     const uint32_t ns = gather_team(C, P, e.sg, e.bx0, e.by0, e.bz0, e.beg, e.cnt, e.place, recs, wave, W, S,
                                                     overflow);
-                    const NearRegs nr = near_regs(P, W.near, ns, overflow);
+                    const auto nr = near_regs<near_held<Real, kMem>()>(P, W.near, ns, overflow);
                     if (wave == 0) wc.overflows += overflow ? 1u : 0u;
                     if (overflow)  // not staged: straight from the system's arrays
                         team_trials<false>(C, RecView<Real>{C.rec, C.misc + 1}, props, sweep, P, e.beg, e.cnt, e.bx0,

@@ -97,6 +97,27 @@ def test_team_equals_one_workgroup(M, k, nc, workgroups, fp32):
     assert np.sum(o1["accepts"]) > 0 and (nc > 2 or M < 1000 or o1["near_overflows"] > 0)
 
 
+@pytest.mark.parametrize("M,k,nc,density", [
+    (60, 2, 2, 1.2),     # less than one entry a lane
+    (500, 2, 4, 0.6),    # one to two
+    (1000, 2, 4, 1.2),   # up to three
+    (1000, 2, 4, 2.0),   # the last of the list beyond three a lane
+])
+@pytest.mark.parametrize("fp32", [False, True])
+def test_near_entries_of_either_state(M, k, nc, density, fp32):
+    # in LDS a lane holds its near entries, FP64 in HBM reads them at each trial
+    one = flipmc.MC_FLAG_SINGLE_WORKGROUP
+    l0, s0, o0 = chain(M, 3.0, k, nc, 11, fp32, 3, 1, density=density, flags=one)
+    l1, s1, o1 = chain(M, 3.0, k, nc, 11, fp32, 3, 1, density=density, flags=one | flipmc.MC_FLAG_HBM_STATE)
+    for f in ("delta_e", "scale", "accepted", "exited", "move", "pair_terms"):
+        assert np.array_equal(l0[f], l1[f]), f
+    for f in ("com", "quat", "types", "e_acc", "sweep"):
+        assert np.array_equal(s0[f], s1[f]), f
+    for f in ("attempts", "accepts", "exits", "pair_terms", "pair_tests", "near_overflows"):
+        assert np.array_equal(o0[f], o1[f]), f
+    assert np.sum(o1["accepts"]) > 0
+
+
 @pytest.mark.parametrize("fp32", [False, True])
 def test_cells_whose_first_trials_all_exit(fp32):
     # 125 molecules a cell and steps longer than it: 0.94 of the trials leave
